@@ -40,23 +40,24 @@ int launch_dequantize(const srft_plan* p, const uint8_t* codes, const float* sca
     return SRFT_OK;
 }
 
-// One batched launch: the segment table is complete except for first_block, which is laid out here.
+// One batched launch: the segment table is complete except for the workgroups, which are laid out here.
 // Every segment gets at least one workgroup and at most one per tile; when the tiles of all segments
 // exceed the persistent grid, workgroups are shared out in proportion to the tiles.
 int launch_batched(const srft_plan* p, srft_batch_args& a, bool write_path, hipStream_t st) {
     long long budget = p->max_wgs > 0 ? p->max_wgs : (write_path ? p->grid_q : p->grid_dq);
     long long total_tiles = 0;
-    for (int i = 0; i < a.count; ++i) total_tiles += (a.n_vec[i] + kTileVecs - 1) / kTileVecs;
+    for (int i = 0; i < a.count; ++i) total_tiles += (a.seg[i].n_vec + kTileVecs - 1) / kTileVecs;
     int next = 0;
     for (int i = 0; i < a.count; ++i) {
-        const long long tiles = (a.n_vec[i] + kTileVecs - 1) / kTileVecs;
+        const long long tiles = (a.seg[i].n_vec + kTileVecs - 1) / kTileVecs;
         long long blocks = total_tiles <= budget ? tiles : tiles * budget / total_tiles;
         if (blocks < 1) blocks = 1;
         if (blocks > tiles) blocks = tiles;
         a.first_block[i] = next;
+        a.seg[i].blocks = (int)blocks;
         next += (int)blocks;
     }
-    a.first_block[a.count] = next;
+    for (int i = a.count; i < kMaxBatch; ++i) a.first_block[i] = INT32_MAX;
     batched_kernel_t kernel = nullptr;
     int threads = 0;
     if (write_path) {
@@ -108,15 +109,15 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
     a.count = 0;
     for (int i = 0; i <= count; ++i) {
         if (i < count && n_vec[i] > 0) {
-            const int k = a.count++;
-            a.frag[k] = write_path ? (plans[i]->fold4_q ? plans[i]->wfold4 : plans[i]->fold_q ? plans[i]->wfold : plans[i]->wfrag)
-                                   : srft_plan_read_table(plans[i]);
-            a.in0[k] = in0[i];
-            a.in1[k] = write_path ? nullptr : in1[i];
-            a.out0[k] = out0[i];
-            a.out1[k] = write_path ? out1[i] : nullptr;
-            a.n_vec[k] = n_vec[i];
-            a.unscale[k] = write_path ? plans[i]->unscale_w : srft_plan_read_unscale(plans[i]);
+            srft_segment& s = a.seg[a.count++];
+            s.frag = write_path ? (plans[i]->fold4_q ? plans[i]->wfold4 : plans[i]->fold_q ? plans[i]->wfold : plans[i]->wfrag)
+                                : srft_plan_read_table(plans[i]);
+            s.in0 = in0[i];
+            s.in1 = write_path ? nullptr : in1[i];
+            s.out0 = out0[i];
+            s.out1 = write_path ? out1[i] : nullptr;
+            s.n_vec = n_vec[i];
+            s.unscale = write_path ? plans[i]->unscale_w : srft_plan_read_unscale(plans[i]);
         }
         if (a.count == kMaxBatch || (i == count && a.count > 0)) {
             const int rc = launch_batched(plans[0], a, write_path, st);

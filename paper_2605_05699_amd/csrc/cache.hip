@@ -9,7 +9,7 @@ namespace {
 
 // Cache append: the new tokens of every plan, [n_seq][t][units] 16-byte units each, go to their place in the paged
 // fp16 view [block][n_seq][R][units]: token pos0 + j of sequence q lands in block (pos0 + j) / R, slot (pos0 + j) % R.
-// a.in0[p] / a.out0[p] are plan p's new tokens and view.  A few kilobytes per step: one thread per unit.
+// a.seg[p].in0 / .out0 are plan p's new tokens and view.  A few kilobytes per step: one thread per unit.
 __global__ void __launch_bounds__(256)
 srft_cache_scatter_kernel(const srft_batch_args a, int n_seq, int t, int units, int R, long long pos0) {
     const long long per_plan = (long long)n_seq * t * units, total = per_plan * a.count;
@@ -21,8 +21,8 @@ srft_cache_scatter_kernel(const srft_batch_args a, int n_seq, int t, int units, 
         const int tok = (int)(st % t), seq = (int)(st / t);
         const long long token = pos0 + tok, block = token / R;
         const int slot = (int)(token % R);
-        reinterpret_cast<uint4*>(a.out0[p])[((block * n_seq + seq) * R + slot) * units + u] =
-            reinterpret_cast<const uint4*>(a.in0[p])[r];
+        reinterpret_cast<uint4*>(a.seg[p].out0)[((block * n_seq + seq) * R + slot) * units + u] =
+            reinterpret_cast<const uint4*>(a.seg[p].in0)[r];
     }
 }
 
@@ -108,8 +108,8 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
         srft_batch_args a;
         a.count = (int)std::min<size_t>(kMaxBatch, np - p0);
         for (int k = 0; k < a.count; ++k) {
-            a.in0[k] = new_f16_dev[p0 + k];
-            a.out0[k] = cache->view[p0 + k];
+            a.seg[k].in0 = new_f16_dev[p0 + k];
+            a.seg[k].out0 = cache->view[p0 + k];
         }
         const long long total = (long long)a.count * cache->n_seq * t * units;
         const unsigned grid = (unsigned)std::min<long long>((total + 255) / 256, 4096);

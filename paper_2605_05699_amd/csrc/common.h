@@ -83,19 +83,24 @@ enum { kOutCodes = 0, kOutRaw = 1, kOutAmax = 2, kOutQFrag32 = 3, kOutQFrag16 = 
 
 // Several plans in one launch (a decode step appends a few hundred vectors to each of many (layer, K|V)
 // caches: one launch per plan would be all launch latency).  Segment i = plan i's constants and buffers; it
-// is served by workgroups first_block[i] .. first_block[i+1]-1, each walking that segment's tiles with
-// that many as stride.  The table travels as a kernel argument.
-constexpr int kMaxBatch = 64;       // the table is about 3.5 KiB of the 4 KiB a kernel may take as arguments
+// is served by workgroups first_block[i] .. first_block[i] + seg[i].blocks - 1, each walking that segment's tiles with
+// that many as stride.  Entries of first_block past the last segment hold INT32_MAX.  The table travels as a kernel
+// argument.
+constexpr int kMaxBatch = 64;       // the table is about 3.8 KiB of the 4 KiB a kernel may take as arguments
+struct srft_segment {
+    const uint4* frag;
+    const void* in0;                // write path: x      read path: codes
+    const void* in1;                //                    read path: scales
+    void* out0;                     // write path: codes  read path: out
+    void* out1;                     // write path: scales
+    long long n_vec;
+    float unscale;
+    int blocks;
+};
 struct srft_batch_args {
+    int first_block[kMaxBatch];
+    srft_segment seg[kMaxBatch];
     int count;
-    int first_block[kMaxBatch + 1];
-    const uint4* frag[kMaxBatch];
-    const void* in0[kMaxBatch];      // write path: x      read path: codes
-    const void* in1[kMaxBatch];      //                    read path: scales
-    void* out0[kMaxBatch];           // write path: codes  read path: out
-    void* out1[kMaxBatch];           // write path: scales
-    long long n_vec[kMaxBatch];
-    float unscale[kMaxBatch];
 };
 static_assert(sizeof(srft_batch_args) + sizeof(int) <= 4096, "kernel arguments are limited to 4 KiB");
 

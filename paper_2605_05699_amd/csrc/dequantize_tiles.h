@@ -424,11 +424,10 @@ srft_dequantize_kernel(const uint4* __restrict__ rfrag, const uint2* __restrict_
 template <int D, int S, int KS, bool FOLD, int BITS>
 __global__ void __launch_bounds__(2 * D / S, 1)
 srft_dequantize_batched_kernel(const srft_batch_args a, int gw) {
-    const int i = srft_segment_of_block(a, blockIdx.x);
-    srft_dequantize_tiles<D, S, KS, FOLD, BITS>(a.frag[i], (const uint2*)a.in0[i], (const float*)a.in1[i], a.n_vec[i],
-                                    (uint4*)a.out0[i], a.unscale[i], gw, blockIdx.x - a.first_block[i],
-                                    a.first_block[i + 1] - a.first_block[i],
-                                    (int)((a.n_vec[i] + kTileVecs - 1) / kTileVecs));
+    int t0;
+    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    srft_dequantize_tiles<D, S, KS, FOLD, BITS>(s.frag, (const uint2*)s.in0, (const float*)s.in1, s.n_vec, (uint4*)s.out0,
+                                    s.unscale, gw, t0, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 
 #endif  // SRFT_DEQUANTIZE_TILES_H

@@ -347,11 +347,11 @@ srft_quantize_fold4_kernel(const uint4* __restrict__ wf4, const uint4* __restric
 template <int BITS>
 __global__ void __launch_bounds__(256, 2)
 srft_quantize_fold4_batched_kernel(const srft_batch_args a, int) {
-    const int i = srft_segment_of_block(a, blockIdx.x);
-    srft_quantize_fold4_tiles<BITS>(a.frag[i], (const uint4*)a.in0[i], a.n_vec[i], (uint2*)a.out0[i],
-                                    (float*)a.out1[i], 1.0f / (BITS == 8 ? 127.0f : 7.0f),
-                                    blockIdx.x - a.first_block[i], a.first_block[i + 1] - a.first_block[i],
-                                    (int)((a.n_vec[i] + kTileVecs - 1) / kTileVecs));
+    int t0;
+    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    srft_quantize_fold4_tiles<BITS>(s.frag, (const uint4*)s.in0, s.n_vec, (uint2*)s.out0, (float*)s.out1,
+                                    1.0f / (BITS == 8 ? 127.0f : 7.0f), t0, s.blocks,
+                                    (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 
 #endif  // SRFT_QUANTIZE_FOLD4_TILES_H

@@ -500,11 +500,11 @@ srft_quantize_fold_amax_kernel(const uint4* __restrict__ wfold, const uint4* __r
 template <int D, int BITS, bool WIDE>
 __global__ void __launch_bounds__(D, (D >= 256 ? SRFT_QF_WG_PER_CU_256 : 2))
 srft_quantize_fold_batched_kernel(const srft_batch_args a, int gw) {
-    const int i = srft_segment_of_block(a, blockIdx.x);
-    srft_quantize_fold_tiles<D, BITS, WIDE>(a.frag[i], (const uint4*)a.in0[i], a.n_vec[i], (uint2*)a.out0[i],
-                                            (float*)a.out1[i], a.unscale[i], a.unscale[i] / (BITS == 8 ? 127.0f : 7.0f),
-                                            gw, blockIdx.x - a.first_block[i], a.first_block[i + 1] - a.first_block[i],
-                                            (int)((a.n_vec[i] + kTileVecs - 1) / kTileVecs));
+    int t0;
+    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    srft_quantize_fold_tiles<D, BITS, WIDE>(s.frag, (const uint4*)s.in0, s.n_vec, (uint2*)s.out0, (float*)s.out1,
+                                            s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, t0, s.blocks,
+                                            (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 
 #endif  // SRFT_QUANTIZE_FOLD_TILES_H

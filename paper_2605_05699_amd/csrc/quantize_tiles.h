@@ -272,15 +272,14 @@ srft_quantize_kernel(const uint4* __restrict__ wfrag, const uint4* __restrict__ 
                                        gridDim.x);       // the grid never exceeds the number of tiles
 }
 
-// Several plans in one launch: segment i of the table is served by workgroups first_block[i] .. first_block[i+1]-1.
+// Several plans in one launch (see srft_batch_args).
 template <int D, int S, int GM, int BITS>
 __global__ void __launch_bounds__(2 * D / S)
 srft_quantize_batched_kernel(const srft_batch_args a, int gw) {
-    const int i = srft_segment_of_block(a, blockIdx.x);
-    srft_quantize_tiles<D, S, kOutCodes, GM, BITS>(a.frag[i], (const uint4*)a.in0[i], a.n_vec[i], (uint2*)a.out0[i],
-                                         (float*)a.out1[i], nullptr, a.unscale[i],
-                                         a.unscale[i] / (BITS == 8 ? 127.0f : 7.0f), gw,
-                                         blockIdx.x - a.first_block[i], a.first_block[i + 1] - a.first_block[i]);
+    int t0;
+    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    srft_quantize_tiles<D, S, kOutCodes, GM, BITS>(s.frag, (const uint4*)s.in0, s.n_vec, (uint2*)s.out0, (float*)s.out1,
+                                         nullptr, s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, t0, s.blocks);
 }
 
 #endif  // SRFT_QUANTIZE_TILES_H

@@ -195,3 +195,14 @@ def test_full_size_plans_in_the_launch_shape_the_benchmark_times(B):
         P.check_dequantize(c, s, p.signs, lam, w.g, o)
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("entries", [1, 2, 7, 8, 9, 63, 64, 65])
+def test_workgroup_to_entry_map(B, entries):
+    """Every entry is served whatever the number of entries and workgroups (grids below, at and past a multiple of 8)."""
+    d, g = 128, 32
+    counts = [1 + (53 * i) % 97 for i in range(entries)]
+    plans, xs, ref = _make(B, d, g, counts, seed0=9000 + entries)
+    _assert_same(ref, _batched(B, plans, xs, d, g))
+    for p in plans:
+        p.close()
