@@ -103,8 +103,15 @@ def _check(status: int, where: str) -> None:
         raise SrftError(status, where)
 
 
+# The handle of the current stream without building a torch.cuda.Stream object around it: 0.3 us against 2.8 us a call,
+# as much as the launch of a small kernel.  (Where torch has no such function the public way is taken.)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream) -> int:
     if stream is None:
+        if _current_raw_stream is not None:
+            return _current_raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
