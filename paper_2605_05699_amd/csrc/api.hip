@@ -8,10 +8,24 @@
 
 namespace {
 
+// Workgroups of the abs-max statistic.  Each ends with one request per 32 channels to the same few cache lines, served one
+// after the other (about 11 ns a workgroup at d = 128, all at once at the end), so more workgroups shorten the streaming
+// and lengthen the end: the sum is smallest near sqrt(tiles) times a constant.  At most what reaches the read rate: one
+// workgroup per compute unit with five and more wavefronts each (d >= 160), two below; at d = 128, where a workgroup has
+// two wavefronts, more still help.  Measured, us for 20,000 / 100,000 / 600,000 vectors, against the write path's grid:
+// d = 96: 15.7 / 27.4 / 51.6 -> 11 / 14 / 33;  d = 128: 16.5 / 26.2 / 48.7 -> 11 / 17 / 44;  d = 256: 16.5 / 29.7 / 104 ->
+// 13 / 25 / 98.
+long long amax_grid(const srft_plan* p, long long n_tiles) {
+    long long g = (long long)(5.0 * std::sqrt((double)n_tiles)) + 1;
+    const long long most = p->d >= 160 ? p->compute_units : p->d == 128 ? p->grid_q : 2LL * p->compute_units;
+    if (g > most) g = most;
+    return g < p->grid_q ? g : p->grid_q;
+}
+
 int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* codes, float* scales, float* wout,
                     int out, hipStream_t st) {
     const long long n_tiles = (n + kTileVecs - 1) / kTileVecs;
-    long long grid = p->max_wgs > 0 ? p->max_wgs : p->grid_q;
+    long long grid = p->max_wgs > 0 ? p->max_wgs : out == kOutAmax ? amax_grid(p, n_tiles) : p->grid_q;
     if (grid > n_tiles) grid = n_tiles;
     int threads = 0;
     const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads);

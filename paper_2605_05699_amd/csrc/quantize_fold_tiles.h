@@ -338,23 +338,19 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
         }
     };
 
-    // AMAX: lanes of one half hold the same 32 indices for 32 different vectors: butterfly over the 32, then one atomic
-    // per channel (non-negative floats order like their bit patterns)
+    // AMAX: lanes of one half hold the same 32 indices for 32 different vectors: they meet in LDS (the tile buffers,
+    // which no wavefront reads any more), then one atomic per channel
     auto emit_amax = [&]() __attribute__((always_inline)) {
         if constexpr (AMAX) {
+            static_assert(sizeof(lds) >= sizeof(float) * kTileVecs * kAmaxRow<D>, "the tile buffers hold 32 rows of maxima");
+            __syncthreads();
+            float* part = reinterpret_cast<float*>(&lds[0][0]) + col * kAmaxRow<D>;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                float md = amd[v], mm = amm[v];
-#pragma unroll
-                for (int step = 1; step < 32; step *= 2) {
-                    md = fmaxf(md, __shfl_xor(md, step, 64));
-                    mm = fmaxf(mm, __shfl_xor(mm, step, 64));
-                }
-                if (col == 0) {
-                    atomic_max_nonneg(&amax[base_d + 16 * half + v], md * unscale);
-                    atomic_max_nonneg(&amax[p_top - 16 * half - (v == 0 ? 16 : v)], mm * unscale);
-                }
+                part[base_d + 16 * half + v] = amd[v];
+                part[p_top - 16 * half - (v == 0 ? 16 : v)] = amm[v];
             }
+            publish_amax<D>(reinterpret_cast<float*>(&lds[0][0]), amax, unscale);
         }
     };
     const int m = (t_end - 1 - t0) / stride + 1;            // tiles of this workgroup: t0, t0 + stride, ... < t_end

@@ -248,18 +248,16 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
         finish(acc_a, t0 + (k - 1) * stride);
     }
     if constexpr (OUT == kOutAmax) {
-        // lanes of one half hold the same 16 channels for 32 different vectors: butterfly over the 32, then one
-        // atomic per channel (non-negative floats order like their bit patterns)
-        unsigned int* amax = reinterpret_cast<unsigned int*>(wout);
+        // lanes of one half hold the same 16 channels for 32 different vectors: they meet in LDS (the tile buffers, which
+        // no wavefront reads any more), then one atomic per channel
+        static_assert(sizeof(lds) >= sizeof(float) * kTileVecs * kAmaxRow<D> && NT >= D, "room and a thread per channel");
+        __syncthreads();
+        float* part = reinterpret_cast<float*>(&lds[0][0]);
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float mx = cmax[s][v];
-#pragma unroll
-                for (int step = 1; step < 32; step *= 2) mx = fmaxf(mx, __shfl_xor(mx, step, 64));
-                if (col == 0) atomic_max_nonneg(&amax[32 * (wave * S + s) + 16 * half + v], mx * unscale);
-            }
+            for (int v = 0; v < 16; ++v) part[col * kAmaxRow<D> + 32 * (wave * S + s) + 16 * half + v] = cmax[s][v];
+        publish_amax<D>(part, reinterpret_cast<unsigned int*>(wout), unscale);
     }
 }
 

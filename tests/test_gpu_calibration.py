@@ -73,6 +73,21 @@ def test_result_does_not_depend_on_the_grid(B):
     plan.close()
 
 
+@pytest.mark.parametrize("d", [32, 64, 128, 192, 256])
+def test_many_workgroups_meet_on_one_statistic(B, d):
+    """Enough tiles for every workgroup of the grid, a ragged last tile, a statistic that starts at zero; the largest
+    value of each channel sits in another workgroup's tiles."""
+    n = 70001
+    x = W.gaussian_with_outliers(n, d, seed=d, outliers=1, gain=4.0)
+    plan = B.Plan(d, 32, 300 + d)
+    xg = torch.from_numpy(x).cuda()
+    a = plan.channel_absmax(xg)
+    _check(a.cpu().numpy(), x, plan.signs, None)
+    B.srft_plan_set_max_workgroups(plan.handle, 5)
+    assert torch.equal(a, plan.channel_absmax(xg))
+    plan.close()
+
+
 def test_closed_form_and_calibrated_plan_round_trip(B):
     """Constant vectors move only the DC channel; lambda from the statistic makes every channel of the
     calibration batch peak at 1, and the plan built from it quantizes to the oracle's codes."""
