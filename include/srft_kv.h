@@ -195,12 +195,11 @@ int srft_kv_attend(const srft_plan_t* plan, const float* weights_f32_dev, int n_
 /*
  * One decode step of attention over a stored cache: out = softmax(softmax_scale * q K^T) V with K and V read from
  * their records (plan_k, plan_v: same d, own signs and lambda each).    (Sec. 1; Sec. 7.2)
- * On one stream: srft_kv_scores, whose scan also keeps the maximum of softmax_scale * score per row; then the weighted
- * sums of srft_kv_attend, whose kernel forms the weights exp(softmax_scale * score - maximum) from the raw scores as it
- * loads them, carries their sums along and divides by them at the end (the scores are written once and read once; the
- * row softmax has no pass of its own).  q_f16_dev [n_q, d] fp16 (16-byte aligned),
+ * On one stream, two kernels: one pass over both records that carries scores, a running softmax and the weighted sums of
+ * the values in registers, then the addition of the workgroups' sums (in a fixed order), the division and the inverse
+ * transform.  q_f16_dev [n_q, d] fp16 (16-byte aligned),
  * out_f32_dev [n_q, d] fp32; workspace_dev: srft_decode_attention_workspace_bytes(plan_k, plan_v, n_q, n_keys) bytes,
- * 256-byte aligned (it holds the n_q x n_keys scores).  Shapes and limits as for the two calls it is made of.
+ * 256-byte aligned, overwritten.  Shapes and limits as for srft_kv_scores and srft_kv_attend.
  */
 int64_t srft_decode_attention_workspace_bytes(const srft_plan_t* plan_k, const srft_plan_t* plan_v, int n_q,
                                               int64_t n_keys);

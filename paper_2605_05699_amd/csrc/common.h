@@ -45,7 +45,7 @@
 //
 // Source layout: the kernel templates live in quantize_tiles.h (write path, plain form), quantize_fold_tiles.h and
 // quantize_fold4_tiles.h (write path, folded forms), dequantize_tiles.h and dequantize_fold4_tiles.h (read path),
-// kernels/scores.hip and kernels/attend.hip; every file under kernels/
+// kernels/scores.hip, kernels/attend.hip and kernels/decode_attention.hip; every file under kernels/
 // instantiates one family of them and exports a function that picks the instance for a plan; plan.hip builds
 // the constant tables, api.hip holds the C entry points, cache.hip the cache manager.
 #ifndef SRFT_COMMON_H
@@ -70,7 +70,6 @@ constexpr int kMaxScoreWorkgroups = 4096;   // scores kernel: largest grid (each
 constexpr int kMaxD = 256;
 constexpr int kMaxAttendStripes = 2048;      // value-side kernel: most workgroups per channel slab (each owns 32 x d floats of workspace)
 constexpr int kAttendFan = 64;                // value-side kernel: first-level sums the partial results are added into
-constexpr int kRowMaxCopies = 64;            // copies of the per-query score maxima (a cache line each), so that the scan's atomics spread
 constexpr float kMinScale = 7.888609052210118e-31f;   // 2^-100: below this a group is stored as zero
 // The kernels index tiles of 32 vectors with 32-bit integers and look a few grid strides ahead.
 constexpr int64_t kMaxVectors = (int64_t)1 << 33;
@@ -176,24 +175,22 @@ int srft_rfold4_table_units(int d);
 int srft_launch_quantize_butterfly(int d, const float* table_dev, const void* x, long long n_vec, uint8_t* codes,
                                    float* scales, int max_workgroups, hipStream_t st);
 // scores in the rotated domain: launch of the scan (kernels/scores.hip) and its resident workgroups per unit
-// row_max: nullptr, or kRowMaxCopies x 32 cleared words: copy (workgroup mod kRowMaxCopies) receives, per query, the
-// ordered code (srft_ordered_code) of the maximum of sign * score over that workgroup's keys
 int srft_launch_scores(const srft_plan* p, uint4* qfrag, float* dump, int n_q, const uint8_t* codes,
-                       const float* scales, long long n_keys, float* out, unsigned int* row_max, float sign,
-                       hipStream_t st);
+                       const float* scales, long long n_keys, float* out, hipStream_t st);
 int srft_scores_occupancy(int d, bool r16, int* blocks_per_cu);
 
 // weighted sums of the stored values in the rotated domain (kernels/attend.hip): workgroups per channel slab for
 // n_q queries over n_keys values, and the three launches (partial sums per workgroup into `part`, their fixed-order
-// reduction, the inverse transform).  row_max: nullptr (w holds the weights), or the kRowMaxCopies x 32 ordered codes of
-// the maxima of sign(softmax_scale) * w over the keys, as srft_launch_scores leaves them: w then holds raw scores, the
-// weights exp(softmax_scale * w - maximum) are formed as the scores are loaded, their sums are carried along and the
-// result is divided by them (a row softmax without a pass of its own).
+// reduction, the inverse transform)
 int srft_attend_stripes(const srft_plan* p, int n_q, long long n_keys);
 size_t srft_attend_workspace_floats(int d);
 int srft_launch_attend(const srft_plan* p, const float* w, int n_q, const uint8_t* codes, const float* scales,
-                       long long n_keys, float* out, float* part, const unsigned int* row_max, float softmax_scale,
-                       hipStream_t st);
+                       long long n_keys, float* out, float* part, hipStream_t st);
+
+// one decode step of attention in one pass over both records (kernels/decode_attention.hip)
+int srft_launch_decode_attention(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, const uint8_t* k_codes,
+                                 const float* k_scales, const uint8_t* v_codes, const float* v_scales, long long n_keys,
+                                 float softmax_scale, float* out, void* workspace, hipStream_t st);
 
 // ---- host side (plan.hip, api.hip) ----
 int srft_hip_fail(hipError_t e);         // records the error for srft_last_hip_error, returns SRFT_ERR_HIP

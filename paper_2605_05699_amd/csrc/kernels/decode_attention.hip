@@ -1,0 +1,578 @@
+// One decode step of attention over the stored records: out_i = sum_t softmax_t(softmax_scale <q_i, k_t>) v_t.
+//
+// Both products are taken in the rotated domain on the codes (kernels/scores.hip, kernels/attend.hip): a score is
+// <q'_i, code_t * scale_t> with q' = Q (s * q) / max(lambda_k, 1e-6), the output is one inverse transform per query of
+// sum_t w_t code_t * scale_t.  Two launches:
+//
+// 1. srft_attention_scan_kernel: ONE pass over K and V.  A workgroup forms q' (every workgroup for itself); a wavefront takes
+//    tiles of 64 or 32 keys: scores, a softmax running over its own tiles (its maximum, the sum of its weights; sums taken
+//    under an older maximum are scaled down when the maximum grows), weighted sums of the V codes.  The wavefronts of a
+//    workgroup meet in LDS at the end, and a workgroup leaves n_q x D sums, a maximum and a sum of weights per query.
+// 2. srft_attention_finish_kernel: the workgroups' sums are brought under one maximum, added in a fixed order (the result does
+//    not depend on timing), divided by the sum of the weights and taken through the inverse transform.
+//
+// What bounds it: at 131,072 keys and d = 128 the record is 21 MB (4 us at the rate of a copy) and every wavefront of the chip
+// has one tile, so the time is the latency of the launches and of one tile's chain (about 18,000 clocks in the scan: 3,000
+// until q' and the tile are there, 3,700 for q' to reach every wavefront, 4,000 scores, 700 softmax, 2,300 values, 4,900 to
+// meet).  Scores and weights therefore never leave the registers: with keys on the rows and queries on the columns of the
+// score product, a lane holds, for ITS query (lane % 16), the keys of its quarter of the wavefront (lane / 16), which is what
+// the second product takes as its B operand and what a running maximum and its correction need; with channels on the rows and
+// queries on the columns of the second product the sums belong to the same query.
+// Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
+// d = 128, 8 queries, 131,072 keys 36.6 -> 15.4, 400,000 keys 51 -> 26; 32 queries, 400,000 keys 111 -> 39; d = 256, 4 queries,
+// 4096 keys 27.7 -> 15.3; d = 64, 1 query, 500 keys 21.9 -> 11.2.
+#include "../device_util.h"
+
+namespace {
+
+constexpr int kWaves = 8;                                    // wavefronts per workgroup of the scan: two per SIMD
+constexpr int kScanGridMax = 1024;                           // most workgroups of the scan (a cap on the grid may ask for more than one per unit)
+constexpr float kLowest = -3.0e38f;                          // "no key yet": finite, so that differences of two are
+
+typedef int v2i __attribute__((ext_vector_type(2)));
+
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));     // scales are 4-byte aligned
+
+__device__ __forceinline__ uint2 swap16(uint32_t a, uint32_t b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    return make_uint2(r[0], r[1]);
+}
+__device__ __forceinline__ uint2 swap32(uint32_t a, uint32_t b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    return make_uint2(r[0], r[1]);
+}
+// maximum / sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (one query's quarters), in all of them
+__device__ __forceinline__ float quarters_max(float m) {
+    const uint2 a = swap16(__float_as_uint(m), __float_as_uint(m));
+    m = fmaxf(__uint_as_float(a.x), __uint_as_float(a.y));
+    return other_half_max(m);
+}
+__device__ __forceinline__ float quarters_sum(float s) {
+    const uint2 a = swap16(__float_as_uint(s), __float_as_uint(s));
+    s = __uint_as_float(a.x) + __uint_as_float(a.y);
+    const uint2 b = swap32(__float_as_uint(s), __float_as_uint(s));
+    return __uint_as_float(b.x) + __uint_as_float(b.y);
+}
+
+// D: head dimension.  KEYS: keys per tile, 64 or 32.  WIDE: groups of gw > 1 runs of 32 channels share a scale.
+// blockIdx.y: block of 16 queries.  (Both blocks of 32 queries in one wavefront -- the codes decoded once -- needs more
+// registers than two wavefronts per SIMD leave: 250 spilled at d = 128.)
+template <int D, int KEYS, bool WIDE>
+__global__ void __launch_bounds__(64 * kWaves, 2)
+srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ wfrag,
+                           const float* __restrict__ q_scale, float unscale, const uint8_t* __restrict__ k_codes,
+                           const float* __restrict__ k_scales, int k_gw, const uint8_t* __restrict__ v_codes,
+                           const float* __restrict__ v_scales, int v_gw, long long n_keys, float softmax_scale,
+                           float* __restrict__ part, float* __restrict__ part_max, float* __restrict__ part_sum) {
+    constexpr int G = D / 32, QUADS = G / 4, REST = G % 4;   // a row of codes: QUADS x 64 bytes, then REST x 16 bytes
+    constexpr int W = kWaves;
+    constexpr int ROW = D / 2;                               // bytes
+    constexpr int BK = KEYS / 16;                            // blocks of 16 keys
+    constexpr int KQ = KEYS / 4;                             // keys per quarter of the wavefront
+    constexpr int VROW = ROW + 16;                           // padded: the 16 rows of a transposed read hit different banks
+    constexpr int VTILE = KEYS * VROW + 4 * 8;               // and 8 bytes more per quarter's rows keep the quarters apart
+    constexpr int NV = KEYS * G / 64;                        // 16-byte pieces of a V tile per lane
+    constexpr int NB = D / 16;                               // blocks of 16 channels
+    constexpr int WAVE_BYTES = VTILE + 2 * G * KEYS * 4;
+    constexpr int LDS_BYTES = W * WAVE_BYTES;
+    static_assert(D % 64 == 0 && VTILE % 16 == 0 && (KEYS == 32 || KEYS == 64), "layout");
+    __shared__ __align__(16) unsigned char lds[LDS_BYTES];
+    __shared__ uint4 qs[G * 2 * 64];
+    __shared__ float meet[2][W][16];
+
+    // all arguments in one go: loaded where they are used, each is a round trip of its own in the chain of one tile
+    asm volatile("" :: "s"(unscale), "s"(softmax_scale), "s"(part), "s"(part_max), "s"(part_sum), "s"(q_scale));
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // (uniform: tile addresses in scalar registers)
+    const int l16 = lane & 15, a = lane >> 4;                // query (or key / channel of a block of 16), quarter
+    unsigned char* const vt = lds + wave * WAVE_BYTES;       // this wavefront's V tile and scales: no other one touches them
+    float* const ks = reinterpret_cast<float*>(vt + VTILE);  // [group][key]
+    float* const vs = ks + G * KEYS;
+    const int q0 = 16 * blockIdx.y, nq = min(16, n_q - q0);  // the queries of this workgroup
+
+    const long long n_tiles = (n_keys + KEYS - 1) / KEYS;
+    const long long stride = (long long)gridDim.x * W;
+    // tiles wave * grid + workgroup + k * stride: a short prefix is spread over as many compute units as it has tiles
+    const long long first = (long long)wave * gridDim.x + blockIdx.x;
+
+    // Which key a lane loads as row m = l16 of block b of the K tile: KQ (m / 4) + 4 b + m % 4.  The score product's result
+    // register i of quarter a is row 4 a + i, so a quarter ends up with the keys KQ a .. KQ a + KQ - 1 (register [b][i]:
+    // key KQ a + 4 b + i), and the transposed reads of V take whole rows of keys per quarter.
+    uint4 pk[BK][QUADS ? QUADS : 1], pv[NV];
+    uint32_t pr[BK][REST ? REST : 1];
+    floatx4 pks[(G + 3) / 4], pvs[(G + 3) / 4];
+    auto fetch_scales = [&](floatx4 (&dst)[(G + 3) / 4], const float* src, int gw, long long t0, int rl) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+            const int ns = G / gw;
+#pragma unroll
+            for (int j = 0; j < G; ++j) dst[j / 4][j % 4] = (src + t0 * ns)[(unsigned)(rl * ns + j / gw)];
+        } else {
+            const float* row = src + t0 * G + (unsigned)(rl * G);
+#pragma unroll
+            for (int j = 0; j + 4 <= G; j += 4) dst[j / 4] = *reinterpret_cast<const floatx4u*>(row + j);
+#pragma unroll
+            for (int j = G / 4 * 4; j < G; ++j) dst[j / 4][j % 4] = row[j];
+        }
+    };
+    // keys past the end alias to the last one
+    auto lim_of = [&](long long t0) __attribute__((always_inline)) { return (int)min((long long)(KEYS - 1), n_keys - 1 - t0); };
+    auto fetch_k = [&](long long tile, bool all) __attribute__((always_inline)) {
+        const long long t0 = tile * KEYS;
+        const int lim = all ? lim_of(t0) : 0;
+        const uint8_t* kb = k_codes + t0 * ROW;
+#pragma unroll
+        for (int b = 0; b < BK; ++b) {
+            const unsigned row = (unsigned)min(KQ * (l16 >> 2) + 4 * b + (l16 & 3), lim) * ROW;
+#pragma unroll
+            for (int s = 0; s < QUADS; ++s) pk[b][s] = *reinterpret_cast<const uint4*>(kb + (row + 64 * s + 16 * a));
+#pragma unroll
+            for (int s = 0; s < REST; ++s) pr[b][s] = *reinterpret_cast<const uint32_t*>(kb + (row + 64 * QUADS + 16 * s + 4 * a));
+        }
+        fetch_scales(pks, k_scales, k_gw, t0, min(lane & (KEYS - 1), lim));
+    };
+    auto fetch_v = [&](long long tile, bool all) __attribute__((always_inline)) {
+        const long long t0 = tile * KEYS;
+        const int lim = all ? lim_of(t0) : 0;
+        const uint8_t* vb = v_codes + t0 * ROW;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int u = lane + 64 * i;
+            pv[i] = *reinterpret_cast<const uint4*>(vb + ((unsigned)min(u / G, lim) * ROW + 16 * (u % G)));
+        }
+        fetch_scales(pvs, v_scales, v_gw, t0, min(lane & (KEYS - 1), lim));
+    };
+    auto v_at = [&](int row) __attribute__((always_inline)) { return vt + row * VROW + (row / KQ) * 8; };
+
+    // ---- The operands of the queries, while the first tile is on its way: q' = w / (lambda max(lambda, 1e-6)) with w the
+    // write path's transform (its dense matrix, fp16 hi + lo, one slab of 32 channels per wavefront or PARTS wavefronts),
+    // split into fp16 hi + lo.  qs: [group][hi, lo][64 lanes]: lane l holds query l % 16 and the 8 codes of unit l / 16 of
+    // the group, in the order decode8 lays them out.  Every workgroup does this for itself (64 KB of matrix from L2 at
+    // d = 128); a launch of its own took 3.0 us at d = 128, 4.6 us at d = 256.
+    constexpr int PARTS = W / G > 0 ? W / G : 1, T = D / 16 / PARTS;     // MFMA k-steps per wavefront
+    static_assert(PARTS * G <= W && PARTS * T * 16 == D, "every slab has its wavefronts");
+    const int slab = min(wave / PARTS, G - 1), piece = wave % PARTS, half = lane >> 5;
+    const bool spare = wave / PARTS >= G;                    // (D = 192: the last wavefronts repeat a slab and keep it to themselves)
+    floatx16 qacc = floatx16{0};
+    floatx4 q_mul[4];                                        // 1 / (lambda max(lambda, 1e-6)) of this lane's 16 channels
+    {
+        // the queries meet the matrix through LDS: every wavefront needs all of them
+        constexpr int XROW = D * 2 + 16;
+        if (tid < 16 * (D / 8))
+            *reinterpret_cast<uint4*>(lds + (tid / (D / 8)) * XROW + 16 * (tid % (D / 8))) =
+                q[(size_t)min(q0 + tid / (D / 8), n_q - 1) * (D / 8) + tid % (D / 8)];
+        const unsigned char* xr = lds + l16 * XROW + 16 * (2 * piece * T + half);
+        const uint4* wr = wfrag + ((size_t)(slab * (D / 16) + piece * T) * 2) * 64 + lane;
+        constexpr int TB = T % 8 == 0 && KEYS == 32 ? 8 : T < 4 ? T : 4;   // k-steps in flight
+#pragma unroll
+        for (int t0 = 0; t0 < T; t0 += TB) {
+            uint4 h[TB], l[TB];
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                h[t] = wr[(2 * (t0 + t)) * 64];
+                l[t] = wr[(2 * (t0 + t) + 1) * 64];
+            }
+            if (t0 + TB >= T) {                              // behind the last of the operands: their wait does not include it
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q_mul[i] = reinterpret_cast<const floatx4*>(q_scale)[8 * slab + 4 * half + i];
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_k(min(first, n_tiles - 1), first < n_tiles);
+                fetch_v(min(first, n_tiles - 1), first < n_tiles);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (t0 == 0) __syncthreads();
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                const half8 b = *reinterpret_cast<const half8*>(xr + 32 * (t0 + t));
+                qacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, h[t]), b, qacc, 0, 0, 0);
+                qacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, l[t]), b, qacc, 0, 0, 0);
+            }
+        }
+    }
+    // (used under a branch only: without this the loads move there, behind the tile's)
+    asm volatile("" : "+v"(q_mul[0]), "+v"(q_mul[1]), "+v"(q_mul[2]), "+v"(q_mul[3]));
+    if constexpr (PARTS > 1) {
+        // columns 16 .. 31 of the product repeat 0 .. 15: lanes without bit 4
+        static_assert(16 * (D * 2 + 16) + G * (PARTS - 1) * 32 * 16 * 4 <= LDS_BYTES, "partial sums fit");
+        float* sums = reinterpret_cast<float*>(lds + 16 * (D * 2 + 16)) + (slab * (PARTS - 1) + piece - 1) * (32 * 16) + 16 * half + l16;
+        if (piece > 0 && (lane & 16) == 0)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sums[v * 32] = qacc[v];
+        __syncthreads();
+        if (piece == 0)
+#pragma unroll
+            for (int k = 1; k < PARTS; ++k)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) qacc[v] += sums[k * (32 * 16) + v * 32];
+    }
+    if (!spare && piece == 0 && (lane & 16) == 0) {
+        // lane (query l16, half) holds the 16 channels 32 slab + 16 half + v: two whole units
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            half8 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int v = 8 * i + (e / 2) + 4 * (e % 2);
+                const float x = l16 < nq ? (qacc[v] * unscale) * q_mul[v / 4][v % 4] : 0.0f;
+                hi[e] = (_Float16)x;
+                lo[e] = (_Float16)(x - (float)hi[e]);
+            }
+            qs[(slab * 2 + 0) * 64 + 16 * (2 * half + i) + l16] = __builtin_bit_cast(uint4, hi);
+            qs[(slab * 2 + 1) * 64 + 16 * (2 * half + i) + l16] = __builtin_bit_cast(uint4, lo);
+        }
+    }
+    __syncthreads();
+
+    floatx4 acc[NB];                                         // [block of 16 channels]: channels 16 b + 4 a + i, query l16
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = floatx4{0, 0, 0, 0};
+    float top = kLowest, den = 0.0f;                         // maximum of |softmax_scale| * (signed score), sum of weights
+    // weights are 2^(c * score - top)
+    const float c = softmax_scale * 1.44269504088896340736f, sign = c < 0.0f ? -1.0f : 1.0f, c_abs = fabsf(c);
+
+    // The LDS operands of a step are read one step ahead of their use.
+    struct KStep { uint4 h, l; float4 sc[BK]; };
+    auto load_k = [&](KStep& f, int j) __attribute__((always_inline)) {
+        f.h = qs[(j * 2 + 0) * 64 + lane];
+        f.l = qs[(j * 2 + 1) * 64 + lane];
+#pragma unroll
+        for (int b = 0; b < BK; ++b) f.sc[b] = *reinterpret_cast<const float4*>(&ks[j * KEYS + KQ * a + 4 * b]);
+    };
+    struct VStep { v2i r[2]; float4 sc[BK]; };
+    auto load_v = [&](VStep& f, int j) __attribute__((always_inline)) {
+        // transposed reads of the group's two 16-channel units: lane l gives the address of key row KQ a + l16 (mod KQ) and
+        // receives, as nibbles, the 16 rows' codes of channel l16
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            f.r[h] = __builtin_amdgcn_ds_read_tr4_b64_v2i32(
+                (__attribute__((address_space(3))) v2i*)(v_at(KQ * a + (l16 & (KQ - 1))) + 8 * (2 * j + h)));
+#pragma unroll
+        for (int b = 0; b < BK; ++b) f.sc[b] = *reinterpret_cast<const float4*>(&vs[j * KEYS + KQ * a + 4 * b]);
+    };
+    for (long long tile = first; tile < n_tiles; tile += stride) {
+        const bool more = tile + stride < n_tiles;
+        // LDS of one wavefront: its accesses complete in program order
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            ks[j * KEYS + (lane & (KEYS - 1))] = pks[j / 4][j % 4];
+            vs[j * KEYS + (lane & (KEYS - 1))] = pvs[j / 4][j % 4];
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int u = lane + 64 * i;
+            unsigned char* dst = v_at(u / G) + 16 * (u % G);
+            reinterpret_cast<uint2*>(dst)[0] = make_uint2(pv[i].x, pv[i].y);         // (8-byte aligned)
+            reinterpret_cast<uint2*>(dst)[1] = make_uint2(pv[i].z, pv[i].w);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // The next tile goes into the registers that have just been read.  Not under a branch (the compiler then keeps both
+        // sets: 100 registers more at d = 128): past the end every lane reads the first row of this tile again.
+        fetch_v(more ? tile + stride : tile, more);
+        // ---- scores: keys on the rows, queries on the columns
+        float w[BK][4];
+#pragma unroll
+        for (int b = 0; b < BK; ++b)
+#pragma unroll
+            for (int s = 0; s < QUADS; ++s) {
+                // quarter k loaded group 4 s + k whole; a 4 x 4 transpose over the quarters gives every quarter its unit of
+                // each of the four groups
+                const uint4 r = pk[b][s];
+                const uint2 x01 = swap16(r.x, r.y), x23 = swap16(r.z, r.w);
+                const uint2 y02 = swap32(x01.x, x23.x), y13 = swap32(x01.y, x23.y);
+                pk[b][s] = make_uint4(y02.x, y13.x, y02.y, y13.y);
+            }
+        KStep kc, kn;
+        load_k(kc, 0);
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (j + 1 < G) load_k(kn, j + 1);
+            const half8 qh = __builtin_bit_cast(half8, kc.h), ql = __builtin_bit_cast(half8, kc.l);
+#pragma unroll
+            for (int b = 0; b < BK; ++b) {
+                const uint4& four = pk[b][j / 4 < QUADS ? j / 4 : 0];
+                const uint32_t kd = j >= 4 * QUADS ? pr[b][j >= 4 * QUADS ? j - 4 * QUADS : 0]
+                                  : j % 4 == 0 ? four.x : j % 4 == 1 ? four.y : j % 4 == 2 ? four.z : four.w;
+                const half8 kf = __builtin_bit_cast(half8, decode8(kd));
+                const float scv[4] = {kc.sc[b].x, kc.sc[b].y, kc.sc[b].z, kc.sc[b].w};
+                floatx4 s = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qh, floatx4{0, 0, 0, 0}, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, ql, s, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[b][i] = j == 0 ? s[i] * scv[i] : fmaf(s[i], scv[i], w[b][i]);
+            }
+            kc = kn;
+            __builtin_amdgcn_sched_barrier(0);               // one group's operands at a time (registers)
+        }
+        fetch_k(more ? tile + stride : tile, more);
+        VStep vc, vn;
+        load_v(vc, 0);
+        // ---- running softmax, per query (column)
+        {
+            float m = sign * w[0][0];
+#pragma unroll
+            for (int v = 1; v < KQ; ++v) m = fmaxf(m, sign * w[v / 4][v % 4]);
+            m = fmaxf(quarters_max(m) * c_abs, kLowest);
+            if (__ballot(m > top)) {                         // uniform
+                const float t = fmaxf(m, top), down = __builtin_amdgcn_exp2f(top - t);
+                top = t;
+                den *= down;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b] *= down;
+            }
+#pragma unroll
+            for (int v = 0; v < KQ; ++v) w[v / 4][v % 4] = __builtin_amdgcn_exp2f(fmaf(c, w[v / 4][v % 4], -top));
+            if (tile == n_tiles - 1) {                       // uniform: keys past the end weigh nothing
+                int lim = lim_of(tile * KEYS);
+                asm volatile("" : "+s"(lim));                 // (the comparisons stay here, out of the way of the first tile)
+#pragma unroll
+                for (int v = 0; v < KQ; ++v) w[v / 4][v % 4] = KQ * a + v <= lim ? w[v / 4][v % 4] : 0.0f;
+            }
+#pragma unroll
+            for (int v = 0; v < KQ; ++v) den += w[v / 4][v % 4];
+        }
+        // ---- sums of the values: channels on the rows, queries on the columns; k-step s takes the keys 8 s .. 8 s + 7 of
+        // every quarter, in the order 0 4 1 5 2 6 3 7 of decode8
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (j + 1 < G) load_v(vn, j + 1);
+            half8 wh[BK / 2], wl[BK / 2];
+#pragma unroll
+            for (int s = 0; s < BK / 2; ++s) {
+                // w * scale as fp16 hi (truncated) + fp16 lo of the exact remainder: about 21 bits
+                const float4 f0 = vc.sc[2 * s], f1 = vc.sc[2 * s + 1];
+                const float sc0[4] = {f0.x, f0.y, f0.z, f0.w}, sc1[4] = {f1.x, f1.y, f1.z, f1.w};
+                uint32_t hh[4], ll[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float x0 = w[2 * s][i] * sc0[i], x1 = w[2 * s + 1][i] * sc1[i];
+                    const auto h2 = __builtin_amdgcn_cvt_pkrtz(x0, x1);
+                    const auto l2 = __builtin_amdgcn_cvt_pkrtz(fmaf((float)h2[0], -1.0f, x0), fmaf((float)h2[1], -1.0f, x1));
+                    hh[i] = __builtin_bit_cast(uint32_t, h2);
+                    ll[i] = __builtin_bit_cast(uint32_t, l2);
+                }
+                wh[s] = __builtin_bit_cast(half8, make_uint4(hh[0], hh[1], hh[2], hh[3]));
+                wl[s] = __builtin_bit_cast(half8, make_uint4(ll[0], ll[1], ll[2], ll[3]));
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                floatx4& sum = acc[2 * j + h];
+#pragma unroll
+                for (int s = 0; s < BK / 2; ++s) {
+                    const half8 f = __builtin_bit_cast(half8, decode8((uint32_t)(s == 0 ? vc.r[h].x : vc.r[h].y)));
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(f, wh[s], sum, 0, 0, 0);
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(f, wl[s], sum, 0, 0, 0);
+                }
+            }
+            vc = vn;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    // ---- the wavefronts of the workgroup that had a tile meet
+    const int active = (int)min((long long)W, (n_tiles - 1 - blockIdx.x) / gridDim.x + 1);
+    den = quarters_sum(den);
+    if (a == 0) {
+        meet[0][wave][l16] = top;
+        meet[1][wave][l16] = den;
+    }
+    __syncthreads();
+    float t = meet[0][0][l16];
+    for (int k = 1; k < active; ++k) t = fmaxf(t, meet[0][k][l16]);
+    const float f = __builtin_amdgcn_exp2f(top - t);
+    if (tid < nq) {
+        float s = 0.0f;
+        for (int k = 0; k < active; ++k) s = fmaf(meet[1][k][l16], __builtin_amdgcn_exp2f(meet[0][k][l16] - t), s);
+        part_max[(q0 + l16) * kScanGridMax + blockIdx.x] = t;
+        part_sum[(q0 + l16) * kScanGridMax + blockIdx.x] = s;
+    }
+    // sums: [wavefront][query][channel], as many channels at a time as fit
+    float* const merge = reinterpret_cast<float*>(lds);
+    static_assert(W * 16 * (16 + 4) * 4 <= LDS_BYTES, "at least one block at a time");
+    int nb = NB;
+    while (active * nq * (16 * nb + 4) * 4 > LDS_BYTES) nb = (nb + 1) / 2;
+    const int mrow = 16 * nb + 4;                            // padded
+    float* const dst = part + ((size_t)blockIdx.x * n_q + q0) * D;
+    for (int b0 = 0; b0 < NB; b0 += nb) {
+        const int b1 = min(NB, b0 + nb);
+        if (b0) __syncthreads();
+        if (wave < active && l16 < nq)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                if (b >= b0 && b < b1)                       // uniform
+                    *reinterpret_cast<floatx4*>(&merge[(wave * nq + l16) * mrow + 16 * (b - b0) + 4 * a]) = acc[b] * f;
+        __syncthreads();
+        const int per = 4 * (b1 - b0);                       // 16-byte pieces per query
+        for (int e = tid; e < nq * per; e += 64 * W) {
+            const int r = e / per, p = e % per;
+            floatx4 s = *reinterpret_cast<const floatx4*>(&merge[r * mrow + 4 * p]);
+            for (int k = 1; k < active; ++k) s += *reinterpret_cast<const floatx4*>(&merge[(k * nq + r) * mrow + 4 * p]);
+            *reinterpret_cast<floatx4*>(&dst[r * D + 16 * b0 + 4 * p]) = s;
+        }
+    }
+}
+
+// over the 64 lanes, in all of them; the order of the sum is fixed
+template <int CTRL> __device__ __forceinline__ float row_rotated(float x) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, row_rotated<0x128>(x));                     // row_ror: 8, 4, 2, 1 within 16 lanes
+    x = fmaxf(x, row_rotated<0x124>(x));
+    x = fmaxf(x, row_rotated<0x122>(x));
+    x = fmaxf(x, row_rotated<0x121>(x));
+    return quarters_max(x);
+}
+__device__ __forceinline__ float wave_sum(float x) {
+    x += row_rotated<0x128>(x);
+    x += row_rotated<0x124>(x);
+    x += row_rotated<0x122>(x);
+    x += row_rotated<0x121>(x);
+    return quarters_sum(x);
+}
+
+// Workgroup (query, block of 64 outputs), 1024 threads.  It adds the scan's workgroups over all D channels (thread: channels
+// 4 (t % (D / 4)) .. + 3 of the workgroups t / (D / 4), + SLICES, ...), then takes its 64 columns of the inverse transform
+// (thread: outputs 4 (t % 16) .. + 3, terms KS (t / 16) ...).  Every load is on its way before the first is waited for, the
+// maxima ahead of the sums ahead of the matrix.  Bound by what one compute unit can pull in: 64 columns instead of all D
+// leave a quarter of the matrix at d = 256 (64 of 256 KB) for the same sums (128 KB).  Against a workgroup per query that
+// reduced the maxima through LDS: 5.6 -> 4.0 us at d = 128, 256 workgroups to add; 6.7 -> 5.8 us at d = 256, 128 of them.
+template <int D>
+__global__ void __launch_bounds__(1024)
+srft_attention_finish_kernel(const float* __restrict__ part, const float* __restrict__ part_max,
+                             const float* __restrict__ part_sum, int parts, int n_q, const float4* __restrict__ rmat,
+                             float* __restrict__ out) {
+    constexpr int C4 = D / 4, SLICES = 1024 / C4, AHEAD = D / 16, KS = D / 64;
+    constexpr int ROWS = D == 192 ? SLICES : 16;             // partial sums that meet in LDS (else one per wavefront)
+    __shared__ __align__(16) float red[ROWS * D];
+    __shared__ __align__(16) float accs[D];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, query = blockIdx.x;
+    const int c4 = tid % C4, slice = tid / C4;
+    // every wavefront finds the maximum and the sum of the weights for itself
+    float pm[4], ps[4];
+    auto load_max = [&](int p0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int p = min(p0 + 64 * i + lane, parts - 1);
+            pm[i] = part_max[query * kScanGridMax + p];
+            ps[i] = p0 + 64 * i + lane < parts ? part_sum[query * kScanGridMax + p] : 0.0f;
+        }
+    };
+    floatx4 x[AHEAD];
+    float xm[AHEAD];
+    auto load = [&](int p0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            const int p = min(p0 + i * SLICES, parts - 1);
+            xm[i] = part_max[query * kScanGridMax + p];
+            x[i] = *reinterpret_cast<const floatx4*>(part + ((size_t)p * n_q + query) * D + 4 * c4);
+        }
+    };
+    load_max(0);
+    load(slice);
+    float4 m[KS];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) m[i] = rmat[(KS * (tid / 16) + i) * C4 + 16 * blockIdx.y + tid % 16];
+    float top = kLowest;
+    for (int p0 = 0; p0 < parts; p0 += 256) {                // (one pass up to 256 workgroups)
+        if (p0) load_max(p0);
+        top = fmaxf(top, fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])));
+    }
+    top = wave_max(top);
+    float den = 0.0f;
+    for (int p0 = 0; p0 < parts; p0 += 256) {
+        if (parts > 256) load_max(p0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) den = fmaf(ps[i], __builtin_amdgcn_exp2f(pm[i] - top), den);
+    }
+    den = wave_sum(den);
+    floatx4 sum = {0, 0, 0, 0};
+    for (int p0 = slice; p0 < parts; p0 += AHEAD * SLICES) {
+        if (p0 != slice) load(p0);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            const float f = p0 + i * SLICES < parts ? __builtin_amdgcn_exp2f(xm[i] - top) : 0.0f;
+            sum = f != 0.0f ? sum + x[i] * f : sum;          // (a workgroup that counts for nothing may hold anything)
+        }
+    }
+    if constexpr (D == 128) {                                // two slices in a wavefront
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint2 h = swap32(__float_as_uint(sum[e]), __float_as_uint(sum[e]));
+            sum[e] = __uint_as_float(h.x) + __uint_as_float(h.y);
+        }
+    } else if constexpr (D == 64) {                          // four
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] = quarters_sum(sum[e]);
+    }
+    if (D != 192 || slice < SLICES)
+        *reinterpret_cast<floatx4*>(&red[(D == 192 ? slice : wave) * D + 4 * c4]) = sum;     // (lanes with the same sum: the same value)
+    __syncthreads();
+    if (tid < D) {
+        float v = red[tid];
+#pragma unroll
+        for (int k = 1; k < ROWS; ++k) v += red[k * D + tid];
+        accs[tid] = v;
+    }
+    __syncthreads();
+    floatx4 o = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+        const float v = accs[KS * (tid / 16) + i];
+        o[0] = fmaf(m[i].x, v, o[0]);
+        o[1] = fmaf(m[i].y, v, o[1]);
+        o[2] = fmaf(m[i].z, v, o[2]);
+        o[3] = fmaf(m[i].w, v, o[3]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = quarters_sum(o[e]);   // the wavefront's four sets of terms
+    if (lane < 16) *reinterpret_cast<floatx4*>(&red[wave * 64 + 4 * lane]) = o;      // (red has been read: the barrier above)
+    __syncthreads();
+    if (tid < 64) {
+        float v = red[tid];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) v += red[k * 64 + tid];
+        out[(size_t)query * D + 64 * blockIdx.y + tid] = v / den;
+    }
+}
+
+template <int D>
+int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, const uint8_t* k_codes, const float* k_scales,
+           const uint8_t* v_codes, const float* v_scales, long long n_keys, float softmax_scale, float* out, void* workspace,
+           hipStream_t st) {
+    // Tiles of 64 keys, or of 32 where that still leaves every wavefront of the chip at most one: the chain of one tile is then
+    // half as long.  Workgroups: one per tile, up to one per compute unit (its eight wavefronts fill the register file); with
+    // two blocks of queries half of that each, so that both read a tile at about the same time.
+    const int blocks = n_q <= 16 ? 1 : 2;
+    long long grid = pv->compute_units / blocks;
+    if (pk->max_wgs > 0) grid = pk->max_wgs;
+    if (pv->max_wgs > 0 && (pk->max_wgs == 0 || pv->max_wgs < grid)) grid = pv->max_wgs;
+    if (grid > kScanGridMax) grid = kScanGridMax;
+    const bool narrow = n_keys <= 32 * kWaves * grid;
+    const long long n_tiles = narrow ? (n_keys + 31) / 32 : (n_keys + 63) / 64;
+    if (grid > n_tiles) grid = n_tiles;
+    float* part_max = (float*)workspace;                     // [32][kScanGridMax] each
+    float* part_sum = part_max + kScanGridMax * 32;
+    float* part = part_sum + kScanGridMax * 32;              // [workgroup][n_q][D]
+    const bool wide = pk->gw > 1 || pv->gw > 1;
+    auto kernel = narrow ? (wide ? srft_attention_scan_kernel<D, 32, true> : srft_attention_scan_kernel<D, 32, false>)
+                         : (wide ? srft_attention_scan_kernel<D, 64, true> : srft_attention_scan_kernel<D, 64, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid, blocks), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q,
+                       (const uint4*)pk->wfrag, (const float*)pk->inv_lam2, pk->unscale_w, k_codes, k_scales, pk->gw, v_codes,
+                       v_scales, pv->gw, n_keys, softmax_scale, part, part_max, part_sum);
+    SRFT_HIP(hipGetLastError());
+    hipLaunchKernelGGL(srft_attention_finish_kernel<D>, dim3((unsigned)n_q, D / 64), dim3(1024), 0, st, (const float*)part,
+                       (const float*)part_max, (const float*)part_sum, (int)grid, n_q, (const float4*)pv->rmat_f32, out);
+    SRFT_HIP(hipGetLastError());
+    return SRFT_OK;
+}
+
+}  // namespace
+
+int srft_launch_decode_attention(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, const uint8_t* k_codes,
+                                 const float* k_scales, const uint8_t* v_codes, const float* v_scales, long long n_keys,
+                                 float softmax_scale, float* out, void* workspace, hipStream_t st) {
+    switch (pv->d) {
+        case 64: return launch<64>(pk, pv, q, n_q, k_codes, k_scales, v_codes, v_scales, n_keys, softmax_scale, out, workspace, st);
+        case 128: return launch<128>(pk, pv, q, n_q, k_codes, k_scales, v_codes, v_scales, n_keys, softmax_scale, out, workspace, st);
+        case 192: return launch<192>(pk, pv, q, n_q, k_codes, k_scales, v_codes, v_scales, n_keys, softmax_scale, out, workspace, st);
+        case 256: return launch<256>(pk, pv, q, n_q, k_codes, k_scales, v_codes, v_scales, n_keys, softmax_scale, out, workspace, st);
+        default: return SRFT_ERR_BAD_D;
+    }
+}

@@ -166,3 +166,39 @@ def test_decode_attention_replayed_from_a_hip_graph_equals_the_eager_calls(B):
         assert torch.isfinite(got).all() and got.abs().max() > 0
     pk.close()
     pv.close()
+
+
+@pytest.mark.parametrize("d,g,n_q,n_keys,cap,scale", [
+    (128, 32, 1, 1, 0, 0.1), (128, 32, 16, 31, 0, 0.1), (64, 32, 17, 33, 0, 0.1),          # less than one tile, one key more
+    (256, 32, 32, 768, 3, 0.1), (256, 32, 5, 769, 3, 0.1),                                 # last of the 32-key tiles, first of 64
+    (192, 32, 16, 1537, 3, 0.1), (128, 64, 9, 3 * 512 + 65, 3, 0.1), (64, 64, 8, 5000, 1, 0.1),     # second and later tiles of a wavefront
+    (256, 256, 4, 1000, 0, 0.1), (192, 96, 3, 200, 2, 0.1),                                # wide groups
+    (128, 32, 8, 2000, 0, -0.1), (128, 32, 8, 300, 0, 0.0), (128, 32, 3, 16500, 300, 0.1),  # sign of the scale; more than 256 workgroups
+])
+def test_decode_attention_at_the_edges_of_its_tiles_and_grid(B, d, g, n_q, n_keys, cap, scale):
+    k = W.gaussian_with_outliers(n_keys, d, seed=d + n_keys, outliers=1, gain=15.0)
+    v = W.gaussian_with_outliers(n_keys, d, seed=d + n_keys + 1, outliers=0)
+    q = W.gaussian_with_outliers(n_q, d, seed=d + n_keys + 2, outliers=1, gain=4.0)
+    k[n_keys // 2] *= 8.0                              # a key that outweighs what came before it
+    lam_k, lam_v = W.lognormal_lambda(d, seed=1), W.lognormal_lambda(d, seed=2)
+    pk, pv = B.Plan(d, g, 23, lam_k), B.Plan(d, g, 24, lam_v)
+    kc, ks = pk.quantize(torch.from_numpy(k).cuda())
+    vc, vs = pv.quantize(torch.from_numpy(v).cuda())
+    B.srft_plan_set_max_workgroups(pv.handle, cap)
+    ws = torch.empty(B.lib().srft_decode_attention_workspace_bytes(pk.handle, pv.handle, n_q, n_keys), dtype=torch.uint8,
+                     device="cuda")
+    ws.fill_(0xFF)                                     # (NaN as floats: nothing is read that was not written)
+    out = torch.full((n_q, d), float("nan"), dtype=torch.float32, device="cuda")
+    B.srft_kv_decode_attention(pk.handle, pv.handle, torch.from_numpy(q).cuda(), kc, ks, vc, vs, scale, out, ws)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float64)
+    kc, ks, vc, vs = (t.cpu().numpy() for t in (kc, ks, vc, vs))
+    ref = O.decode_attention(q, kc, ks, pk.signs, lam_k, vc, vs, pv.signs, lam_v, g, scale)
+    kb, vb = O.dequantize_f64(kc, ks, pk.signs, lam_k, g), O.dequantize_f64(vc, vs, pv.signs, lam_v, g)
+    # the bound of test_decode_attention_matches_the_definition
+    ds = 4e-6 * abs(scale) * np.linalg.norm(q.astype(np.float64), axis=1).max() * np.linalg.norm(kb, axis=1).max() + 2e-7
+    tol = (2 * ds + 6e-6) * np.abs(vb).max() + 1e-30
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= tol, float(np.abs(got - ref).max() / tol)
+    pk.close()
+    pv.close()
