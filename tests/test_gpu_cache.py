@@ -151,3 +151,28 @@ def test_decode_workload_shape_and_capacity_errors(B):
     cache.close()
     for pl in plans:
         pl.close()
+
+
+@pytest.mark.parametrize("d,n_plans,n_seq,R,schedule", [
+    (96, 65, 70, 64, [1, 37, 2]),            # more plans than one launch takes, more sequences than the grid's depth
+    (32, 1, 1, 20000, [1, 1, 12345]),        # many tokens of one sequence
+    (256, 2, 3, 7, [5, 1]),                  # a page that is no power of two
+])
+def test_new_tokens_are_copied_to_their_place(B, d, n_plans, n_seq, R, schedule):
+    """Nothing is flushed (the window is longer than what is appended): the view holds the tokens, bit for bit, and
+    nothing else is written."""
+    T = sum(schedule)
+    plan = B.Plan(d, 32, 5)
+    cache = B.Cache([plan] * n_plans, n_seq, 2 * R, R)
+    for p in range(n_plans):
+        cache.view[p].fill_(3.0)
+    x = torch.randn(n_plans, n_seq, T, d, device="cuda").to(torch.float16)
+    pos = 0
+    for t in schedule:
+        cache.append([x[p, :, pos:pos + t].contiguous() for p in range(n_plans)])
+        pos += t
+    torch.cuda.synchronize()
+    for p in range(n_plans):
+        view = _tokens(cache.view[p], 2 * R)
+        assert torch.equal(view[:, :T], x[p])
+        assert bool((view[:, T:] == 3.0).all())
