@@ -55,9 +55,13 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     constexpr int SROW = NSMAX + 1;      // padded row of the scale tile (floats)
     constexpr int PS = (32 * NSMAX + NT - 1) / NT;      // scale floats a thread may have to carry (1 or 2)
     static_assert((D / 32) % S == 0 && (S == 1 || S == 2), "one or two slabs per wavefront");
-    // Two slabs of a large matrix leave no room for alternating accumulators: one accumulator set, each group
-    // folded in as soon as it is done, the tile staged in the stage that computes it.
-    constexpr bool LEAN = (S == 2 && (D / 32 > 4 || FOLD));
+    // Where registers are short there is no room for alternating accumulators: one accumulator set, each group folded in as
+    // soon as it is done, the tile staged in the stage that computes it.  That is the folded form, g = 16 (two accumulator
+    // sets, and the compiler reads the many groups' operands ahead: 192 to 256 registers and up to 400 of them in scratch
+    // against 110 to 190) and d >= 224.  Measured, us over 400 MB of record and result at 4 bits, alternating -> one set:
+    // g = 16: d = 96 110 -> 82, 128 108 -> 96, 160 282 -> 166, 192 682 -> 173, 224 1061 -> 181; d = 224, g = 32: 195 -> 155.
+    // At d = 160, g = 32, the two are equal.  (d = 32 and 64 fit.)
+    constexpr bool LEAN = FOLD || (S == 1 && D >= (kPerStep ? 96 : 224));
     __shared__ uint4 dec[2][kTileVecs * ROW];    // decoded codes of T_k in dec[k % 2]
     __shared__ uint4 stg[2][kTileVecs * ROW];    // finished fp16 rows of T_k in stg[k % 2]
     __shared__ float scl[2][kTileVecs * SROW];   // scales (times 2^-e) of T_k in scl[k % 2]

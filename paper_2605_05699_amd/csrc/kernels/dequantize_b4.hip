@@ -4,26 +4,19 @@
 namespace {
 template <int D>
 dequantize_kernel_t pick(int slabs, int gm, bool fold) {
-    if constexpr ((D / 32) % 2 == 0) {
-        if constexpr (D != 128 && D != 256)      // d = 128 and 256 run the twice-folded kernel instead
-            if (fold && gm != kGroup16) return srft_dequantize_kernel<D, 2, 1, true, 4>;
-        if (slabs == 2)
-            return gm == kGroup16 ? srft_dequantize_kernel<D, 2, 1, false, 4>
-                                  : srft_dequantize_kernel<D, 2, 2, false, 4>;
-    }
+    if constexpr (D == 192)                      // (d = 128 and 256 run the twice-folded kernel)
+        if (fold && gm != kGroup16) return srft_dequantize_kernel<D, 2, 1, true, 4>;
+    if constexpr (D == 64)
+        if (slabs == 2) return gm == kGroup16 ? srft_dequantize_kernel<D, 2, 1, false, 4> : srft_dequantize_kernel<D, 2, 2, false, 4>;
     return gm == kGroup16 ? srft_dequantize_kernel<D, 1, 1, false, 4> : srft_dequantize_kernel<D, 1, 2, false, 4>;
 }
 template <int D>
 batched_kernel_t pick_batched(int slabs, int gm, bool fold) {
-    if constexpr ((D / 32) % 2 == 0) {
-        if constexpr (D != 128 && D != 256)      // d = 128 and 256 run the twice-folded kernel instead
-            if (fold && gm != kGroup16) return srft_dequantize_batched_kernel<D, 2, 1, true, 4>;
-        if (slabs == 2)
-            return gm == kGroup16 ? srft_dequantize_batched_kernel<D, 2, 1, false, 4>
-                                  : srft_dequantize_batched_kernel<D, 2, 2, false, 4>;
-    }
-    return gm == kGroup16 ? srft_dequantize_batched_kernel<D, 1, 1, false, 4>
-                          : srft_dequantize_batched_kernel<D, 1, 2, false, 4>;
+    if constexpr (D == 192)                      // (d = 128 and 256 run the twice-folded kernel)
+        if (fold && gm != kGroup16) return srft_dequantize_batched_kernel<D, 2, 1, true, 4>;
+    if constexpr (D == 64)
+        if (slabs == 2) return gm == kGroup16 ? srft_dequantize_batched_kernel<D, 2, 1, false, 4> : srft_dequantize_batched_kernel<D, 2, 2, false, 4>;
+    return gm == kGroup16 ? srft_dequantize_batched_kernel<D, 1, 1, false, 4> : srft_dequantize_batched_kernel<D, 1, 2, false, 4>;
 }
 }  // namespace
 

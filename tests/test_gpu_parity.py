@@ -480,3 +480,26 @@ def test_plan_form_reports_the_factorisation_each_plan_runs(B):
         assert L.srft_plan_form(plan.handle, 2) == -7
         plan.close()
     assert L.srft_plan_form(None, 0) == -1
+
+
+@pytest.mark.parametrize("d,g,bits,transform", [(96, 16, 4, "dft"), (128, 16, 8, "dft"), (160, 16, 4, "dft"), (192, 16, 4, "dft"),
+                                                (192, 16, 8, "dft"), (224, 16, 4, "dft"), (224, 32, 8, "dft"), (224, 224, 4, "dft"),
+                                                (256, 16, 4, "dft"), (256, 32, 4, "hadamard")])
+def test_read_path_with_one_accumulator_set_through_its_stages(B, d, g, bits, transform):
+    """One to six tiles per workgroup (every way the two-stage loop can end), ragged last tiles: the same results as one
+    workgroup per tile, bit for bit, and the oracle's."""
+    lam = W.lognormal_lambda(d, seed=d + g)
+    plan = B.Plan(d, g, 80 + d, lam, bits=bits, transform=transform)
+    x = torch.from_numpy(W.gaussian_with_outliers(12 * 32, d, seed=d + 1, outliers=1)).cuda()
+    codes, scales = plan.quantize(x)
+    whole = plan.dequantize(codes, scales)
+    if transform == "dft" and bits == 4:
+        P.check_dequantize(codes.cpu().numpy(), scales.cpu().numpy(), plan.signs, lam, g, whole.cpu().numpy())
+    else:
+        # 4 or 8 bits move a value by at most half a step: the round trip is bounded by the largest scale of its vector
+        step = scales.abs().amax(dim=1, keepdim=True) / float(lam.min()) * d ** 0.5
+        assert bool(((whole.float() - x.float()).abs() <= step + 1e-2 * x.float().abs()).all())
+    B.srft_plan_set_max_workgroups(plan.handle, 2)
+    for n in (1, 32, 33, 64, 65, 100, 160, 192, 200, 255, 256, 320, 383, 384):
+        assert torch.equal(plan.dequantize(codes[:n].contiguous(), scales[:n].contiguous()), whole[:n]), n
+    plan.close()
