@@ -72,7 +72,7 @@ int launch_batched(const srft_plan* p, srft_batch_args& a, bool write_path, hipS
         next += (int)blocks;
     }
     for (int i = a.count; i < kMaxBatch; ++i) a.first_block[i] = INT32_MAX;
-    batched_kernel_t kernel = nullptr;
+    batched_kernels_t kernel;
     int threads = 0;
     if (write_path) {
         if (p->fold4_q) {
@@ -94,8 +94,16 @@ int launch_batched(const srft_plan* p, srft_batch_args& a, bool write_path, hipS
                               : srft_pick_dequantize_batched_b4(p->d, p->slabs_dq, p->gm, p->fold_dq);
         threads = 2 * p->d / p->slabs_dq;
     }
-    if (!kernel) return SRFT_ERR_BAD_D;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)next), dim3(threads), 0, st, a, p->gw);
+    if (!kernel.many) return SRFT_ERR_BAD_D;
+    if (a.count <= kFewBatch) {
+        srft_batch_few few;
+        std::copy_n(a.first_block, kFewBatch, few.first_block);
+        std::copy_n(a.seg, a.count, few.seg);
+        few.count = a.count;
+        hipLaunchKernelGGL(kernel.few, dim3((unsigned)next), dim3(threads), 0, st, few, p->gw);
+    } else {
+        hipLaunchKernelGGL(kernel.many, dim3((unsigned)next), dim3(threads), 0, st, a, p->gw);
+    }
     SRFT_HIP(hipGetLastError());
     return SRFT_OK;
 }

@@ -53,6 +53,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -86,6 +87,9 @@ enum { kOutCodes = 0, kOutRaw = 1, kOutAmax = 2, kOutQFrag32 = 3, kOutQFrag16 = 
 // that many as stride.  Entries of first_block past the last segment hold INT32_MAX.  The table travels as a kernel
 // argument.
 constexpr int kMaxBatch = 64;       // the table is about 3.8 KiB of the 4 KiB a kernel may take as arguments
+// Up to kFewBatch segments travel in a table of their own: the runtime writes the arguments of a launch out one by one, 0.8 us
+// of a launch's 4 us for 3.8 KiB (append of 2 x 256 vectors at d = 128: 5.9 -> 5.4 us a call).
+constexpr int kFewBatch = 8;
 struct srft_segment {
     const uint4* frag;
     const void* in0;                // write path: x      read path: codes
@@ -96,16 +100,25 @@ struct srft_segment {
     float unscale;
     int blocks;
 };
-struct srft_batch_args {
-    int first_block[kMaxBatch];
-    srft_segment seg[kMaxBatch];
+template <int N>
+struct srft_batch {
+    int first_block[N];
+    srft_segment seg[N];
     int count;
 };
+using srft_batch_args = srft_batch<kMaxBatch>;
+using srft_batch_few = srft_batch<kFewBatch>;
 static_assert(sizeof(srft_batch_args) + sizeof(int) <= 4096, "kernel arguments are limited to 4 KiB");
 
 typedef void (*quantize_kernel_t)(const uint4*, const uint4*, long long, uint2*, float*, float4*, float, float, int);
 typedef void (*dequantize_kernel_t)(const uint4*, const uint2*, const float*, long long, uint4*, float, int);
-typedef void (*batched_kernel_t)(const srft_batch_args, int);
+struct batched_kernels_t {
+    void (*many)(const srft_batch_args, int);
+    void (*few)(const srft_batch_few, int);
+    batched_kernels_t(std::nullptr_t = nullptr) : many(nullptr), few(nullptr) {}
+    batched_kernels_t(void (*m)(const srft_batch_args, int), void (*f)(const srft_batch_few, int)) : many(m), few(f) {}
+};
+#define SRFT_BATCHED(kernel, ...) batched_kernels_t(kernel<__VA_ARGS__, kMaxBatch>, kernel<__VA_ARGS__, kFewBatch>)
 
 struct srft_plan {
     int d = 0, g = 0, bits = 4, transform = 0, device = 0;
@@ -150,26 +163,26 @@ struct srft_cache {
 // write path, plain form, codes out: d, slabs per wavefront (1 or 2), group mode; 4- and 8-bit codes
 quantize_kernel_t srft_pick_quantize_plain_b4(int d, int slabs, int gm);
 quantize_kernel_t srft_pick_quantize_plain_b8(int d, int slabs, int gm);
-batched_kernel_t srft_pick_quantize_plain_batched_b4(int d, int slabs, int gm);
-batched_kernel_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
+batched_kernels_t srft_pick_quantize_plain_batched_b4(int d, int slabs, int gm);
+batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
 // write path, plain form, other outputs (kOutRaw, kOutAmax with `slabs`; kOutQFrag32 / kOutQFrag16 with one slab)
 quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out);
 // write path, folded form (d = 128, 256)
 quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide);
 quantize_kernel_t srft_pick_quantize_fold_amax(int d);      // the abs-max statistic through the once-folded contraction
-batched_kernel_t srft_pick_quantize_fold_batched(int d, int bits, bool wide);
+batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide);
 // write path, folded twice (d = 256, g = 32); the size of its table in 16-byte units
 quantize_kernel_t srft_pick_quantize_fold4(int bits);
-batched_kernel_t srft_pick_quantize_fold4_batched(int bits);
+batched_kernels_t srft_pick_quantize_fold4_batched(int bits);
 int srft_fold4_table_units(void);
 // read path
 dequantize_kernel_t srft_pick_dequantize_b4(int d, int slabs, int gm, bool fold);
 dequantize_kernel_t srft_pick_dequantize_b8(int d, int slabs, int gm, bool fold);
-batched_kernel_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm, bool fold);
-batched_kernel_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm, bool fold);
+batched_kernels_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm, bool fold);
+batched_kernels_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm, bool fold);
 // read path, folded twice (d = 128 and 256, g >= 32); the size of its table in 16-byte units
 dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits);
-batched_kernel_t srft_pick_dequantize_fold4_batched(int d, int bits);
+batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits);
 int srft_rfold4_table_units(int d);
 // write path with the transform as FFT butterflies on the vector ALU (d = 128 or 256, g = 32, 4-bit; the comparison form)
 int srft_launch_quantize_butterfly(int d, const float* table_dev, const void* x, long long n_vec, uint8_t* codes,

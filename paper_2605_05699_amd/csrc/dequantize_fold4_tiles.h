@@ -324,9 +324,9 @@ srft_dequantize_fold4_kernel(const uint4* __restrict__ tab, const uint2* __restr
     srft_dequantize_fold4_tiles<D, BITS>(tab, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
 }
 
-template <int D, int BITS>
+template <int D, int BITS, int N>
 __global__ void __launch_bounds__(D / 64 * 64, 2)
-srft_dequantize_fold4_batched_kernel(const srft_batch_args a, int gw) {
+srft_dequantize_fold4_batched_kernel(const srft_batch<N> a, int gw) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
     srft_dequantize_fold4_tiles<D, BITS>(s.frag, (const uint2*)s.in0, (const float*)s.in1, s.n_vec, (uint4*)s.out0,

@@ -425,9 +425,9 @@ srft_dequantize_kernel(const uint4* __restrict__ rfrag, const uint2* __restrict_
     srft_dequantize_tiles<D, S, KS, FOLD, BITS>(rfrag, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
 }
 
-template <int D, int S, int KS, bool FOLD, int BITS>
+template <int D, int S, int KS, bool FOLD, int BITS, int N>
 __global__ void __launch_bounds__(2 * D / S, 1)
-srft_dequantize_batched_kernel(const srft_batch_args a, int gw) {
+srft_dequantize_batched_kernel(const srft_batch<N> a, int gw) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
     srft_dequantize_tiles<D, S, KS, FOLD, BITS>(s.frag, (const uint2*)s.in0, (const float*)s.in1, s.n_vec, (uint4*)s.out0,

@@ -105,11 +105,12 @@ __device__ __forceinline__ uint32_t pack4_bytes(const floatx16& acc, int base, f
 // contiguous eighth of the list, so that the workgroups of one plan share one copy of its matrix table instead of pulling
 // it into every L2.  Measured against workgroup b = place b: 64 plans x 512 vectors at d = 96, write 6.7 -> 5.6 us;
 // 52 x 4096 at d = 256, read 40.6 -> 37.0 us; 56 x 8192 at d = 128, write 38.3 -> 37.1 us; 4 x 1,048,576 within 0.5 %.
-__device__ __forceinline__ int srft_segment_of_block(const srft_batch_args& a, int& place) {
-    static_assert(kMaxBatch == 64, "a lane per boundary");
+template <int N>
+__device__ __forceinline__ int srft_segment_of_block(const srft_batch<N>& a, int& place) {
+    static_assert(N <= 64 && (N & (N - 1)) == 0, "a lane per boundary");
     const int q = gridDim.x >> 3, r = gridDim.x & 7, die = blockIdx.x & 7;
     const int block = die * q + min(die, r) + (int)(blockIdx.x >> 3);        // a permutation of 0 .. gridDim.x - 1
-    const int first = a.first_block[threadIdx.x & 63];
+    const int lane = threadIdx.x & 63, first = lane < N ? a.first_block[lane & (N - 1)] : INT32_MAX;
     const int i = (int)__popcll(__ballot(first <= block)) - 1;
     place = block - __builtin_amdgcn_readlane(first, i);
     return i;

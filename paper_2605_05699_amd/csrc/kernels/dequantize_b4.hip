@@ -11,18 +11,18 @@ dequantize_kernel_t pick(int slabs, int gm, bool fold) {
     return gm == kGroup16 ? srft_dequantize_kernel<D, 1, 1, false, 4> : srft_dequantize_kernel<D, 1, 2, false, 4>;
 }
 template <int D>
-batched_kernel_t pick_batched(int slabs, int gm, bool fold) {
+batched_kernels_t pick_batched(int slabs, int gm, bool fold) {
     if constexpr (D == 192)                      // (d = 128 and 256 run the twice-folded kernel)
-        if (fold && gm != kGroup16) return srft_dequantize_batched_kernel<D, 2, 1, true, 4>;
+        if (fold && gm != kGroup16) return SRFT_BATCHED(srft_dequantize_batched_kernel, D, 2, 1, true, 4);
     if constexpr (D == 64)
-        if (slabs == 2) return gm == kGroup16 ? srft_dequantize_batched_kernel<D, 2, 1, false, 4> : srft_dequantize_batched_kernel<D, 2, 2, false, 4>;
-    return gm == kGroup16 ? srft_dequantize_batched_kernel<D, 1, 1, false, 4> : srft_dequantize_batched_kernel<D, 1, 2, false, 4>;
+        if (slabs == 2) return gm == kGroup16 ? SRFT_BATCHED(srft_dequantize_batched_kernel, D, 2, 1, false, 4) : SRFT_BATCHED(srft_dequantize_batched_kernel, D, 2, 2, false, 4);
+    return gm == kGroup16 ? SRFT_BATCHED(srft_dequantize_batched_kernel, D, 1, 1, false, 4) : SRFT_BATCHED(srft_dequantize_batched_kernel, D, 1, 2, false, 4);
 }
 }  // namespace
 
 dequantize_kernel_t srft_pick_dequantize_b4(int d, int slabs, int gm, bool fold) {
     SRFT_DISPATCH_D(d, pick, slabs, gm, fold)
 }
-batched_kernel_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm, bool fold) {
+batched_kernels_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm, bool fold) {
     SRFT_DISPATCH_D(d, pick_batched, slabs, gm, fold)
 }

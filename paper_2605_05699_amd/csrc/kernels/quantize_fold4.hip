@@ -4,8 +4,8 @@
 quantize_kernel_t srft_pick_quantize_fold4(int bits) {
     return bits == 8 ? srft_quantize_fold4_kernel<8> : srft_quantize_fold4_kernel<4>;
 }
-batched_kernel_t srft_pick_quantize_fold4_batched(int bits) {
-    return bits == 8 ? srft_quantize_fold4_batched_kernel<8> : srft_quantize_fold4_batched_kernel<4>;
+batched_kernels_t srft_pick_quantize_fold4_batched(int bits) {
+    return bits == 8 ? SRFT_BATCHED(srft_quantize_fold4_batched_kernel, 8) : SRFT_BATCHED(srft_quantize_fold4_batched_kernel, 4);
 }
 int srft_fold4_table_units(void) { return kFold4Units; }
 

@@ -344,9 +344,9 @@ srft_quantize_fold4_kernel(const uint4* __restrict__ wf4, const uint4* __restric
     srft_quantize_fold4_tiles<BITS>(wf4, x, n_vec, codes, scales, scale_mul, t0, stride, t_end);
 }
 
-template <int BITS>
+template <int BITS, int N>
 __global__ void __launch_bounds__(256, 2)
-srft_quantize_fold4_batched_kernel(const srft_batch_args a, int) {
+srft_quantize_fold4_batched_kernel(const srft_batch<N> a, int) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
     srft_quantize_fold4_tiles<BITS>(s.frag, (const uint4*)s.in0, s.n_vec, (uint2*)s.out0, (float*)s.out1,

@@ -493,9 +493,9 @@ srft_quantize_fold_amax_kernel(const uint4* __restrict__ wfold, const uint4* __r
                                                 reinterpret_cast<unsigned int*>(amax));
 }
 
-template <int D, int BITS, bool WIDE>
+template <int D, int BITS, bool WIDE, int N>
 __global__ void __launch_bounds__(D, (D >= 256 ? SRFT_QF_WG_PER_CU_256 : 2))
-srft_quantize_fold_batched_kernel(const srft_batch_args a, int gw) {
+srft_quantize_fold_batched_kernel(const srft_batch<N> a, int gw) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
     srft_quantize_fold_tiles<D, BITS, WIDE>(s.frag, (const uint4*)s.in0, s.n_vec, (uint2*)s.out0, (float*)s.out1,
