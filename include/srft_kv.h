@@ -163,10 +163,10 @@ int srft_kv_forward_f32(const srft_plan_t* plan, const void* x_f16_dev, int64_t 
  *   q_f16_dev      [n_q, d] fp16, 16-byte aligned, 1 <= n_q <= 32 (e.g. the query heads sharing one KV head).
  *   codes_dev      [n_keys, d/2] bytes, 16-byte aligned;  scales_dev [n_keys, d/g] fp32: the plan's record.
  *   scores_dev     [n_q, n_keys] fp32, row-major, written.
- *   workspace_dev  srft_scores_workspace_bytes(plan) bytes of device memory (about 1 MiB), 16-byte aligned,
- *                  overwritten; two calls that may run at the same time need a workspace each.
+ *   workspace_dev  srft_scores_workspace_bytes(plan) bytes of device memory (about 1 MiB), 16-byte aligned;
+ *                  the present kernel leaves it alone.
  * For plans with d a multiple of 64, 4-bit codes and g >= 32 (else SRFT_ERR_BAD_D / _BAD_BITS / _BAD_GROUP).
- * Enqueues two kernels on the stream: transform of the queries into the scan's operand layout, then the scan.
+ * Enqueues one kernel on the stream.
  */
 int64_t srft_scores_workspace_bytes(const srft_plan_t* plan);
 int srft_kv_scores(const srft_plan_t* plan, const void* q_f16_dev, int n_q, const uint8_t* codes_dev,
@@ -211,11 +211,7 @@ int srft_kv_decode_attention(const srft_plan_t* plan_k, const srft_plan_t* plan_
 /*
  * srft_kv_scores for callers that cannot allocate device memory or pass a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, checks and results as
- * srft_kv_scores without workspace_dev: the workspace is a static device array inside the library (1 MiB + 32 KiB
- * per GPU, held until the process ends; its address is looked up when the plan is created).  Calls no hipMalloc,
- * hipFree or other allocating routine.  A plan whose srft_scores_workspace_bytes exceeds that array is refused with
- * SRFT_ERR_BAD_N (no plan this library creates does).  Every call on one GPU uses the same array: calls that may
- * overlap on one GPU (different streams, or threads) race -- order them, or use srft_kv_scores with a workspace each.
+ * srft_kv_scores without workspace_dev.  Calls no hipMalloc, hipFree or other allocating routine.
  */
 int srft_kv_scores_static(const srft_plan_t* plan, const void* q_f16_dev, int n_q, const uint8_t* codes_dev,
                           const float* scales_dev, int64_t n_keys, float* scores_dev, void* hip_stream);

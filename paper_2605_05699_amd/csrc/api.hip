@@ -1,7 +1,6 @@
 // api.hip -- the C entry points of the write path, the read path and what sits around them: argument checks
 // (all before the first HIP call), grid sizing, launches.
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 
 #include "common.h"
@@ -150,31 +149,6 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
     return SRFT_OK;
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// Workspace of srft_kv_scores_static: a file-scope device array, so that the entry point allocates nothing.
-// Every GPU the library runs on holds its own copy of the array at its own address until the process ends.
-// In host code the array's name is only a stand-in for the symbol: the device address comes from
-// hipGetSymbolAddress, once per device with that device current, and only that address is ever handed to a
-// kernel.
-// ---------------------------------------------------------------------------------------------------------
-constexpr size_t kScoresQfragBytesMax = (size_t)(kMaxD / 16) * 2 * 64 * 16;                    // 32 KiB at d = 256
-constexpr size_t kScoresScratchBytes = kScoresQfragBytesMax + (size_t)kMaxScoreWorkgroups * 64 * 4;   // + 1 MiB
-static __device__ __align__(256) unsigned char scratch[kScoresScratchBytes];
-
-constexpr int kMaxDevices = 64;
-static std::atomic<void*> g_scratch_ptr[kMaxDevices];
-
-// The address of `scratch` on `device`, which must be the current device; resolved on the first call per device.
-int srft_scores_scratch_prepare(int device) {
-    if (device < 0 || device >= kMaxDevices) return SRFT_ERR_HIP;
-    if (g_scratch_ptr[device].load(std::memory_order_acquire)) return SRFT_OK;
-    void* ptr = nullptr;
-    SRFT_HIP(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)));
-    if (!ptr) return srft_hip_fail(hipErrorInvalidSymbol);
-    g_scratch_ptr[device].store(ptr, std::memory_order_release);
-    return SRFT_OK;
-}
-
 extern "C" {
 
 int srft_kv_quantize(const srft_plan_t* plan, const void* x_f16_dev, int64_t n_vec, uint8_t* codes_dev,
@@ -224,42 +198,41 @@ int srft_kv_channel_absmax(const srft_plan_t* plan, const void* x_f16_dev, int64
 
 int64_t srft_scores_workspace_bytes(const srft_plan_t* plan) {
     if (!plan) return SRFT_ERR_NULL;
-    // the A fragments of up to 32 queries: d/16 k-steps x (hi, lo) x 64 lanes x 16 bytes, then 64 floats per
-    // workgroup that absorb the stores of lanes without a valid (query, key)
-    return (int64_t)(plan->d / 16) * 2 * 64 * 16 + (int64_t)kMaxScoreWorkgroups * 64 * 4;
+    // (the kernel needs none; callers keep buffers of this size)
+    return (int64_t)(plan->d / 16) * 2 * 64 * 16 + (int64_t)4096 * 64 * 4;
 }
 
-int srft_kv_scores(const srft_plan_t* plan, const void* q_f16_dev, int n_q, const uint8_t* codes_dev,
-                   const float* scales_dev, int64_t n_keys, float* scores_dev, void* workspace_dev, void* hip_stream) {
+static int scores_check(const srft_plan_t* plan, const void* q_f16_dev, int n_q, const uint8_t* codes_dev,
+                        const float* scales_dev, int64_t n_keys, const float* scores_dev) {
     if (!plan) return SRFT_ERR_NULL;
     if (plan->d % 64 != 0) return SRFT_ERR_BAD_D;
     if (plan->bits != 4) return SRFT_ERR_BAD_BITS;
     if (plan->gm == kGroup16) return SRFT_ERR_BAD_GROUP;
     if (n_q < 1 || n_q > 32 || n_keys < 0 || n_keys > kMaxVectors) return SRFT_ERR_BAD_N;
     if (n_keys == 0) return SRFT_OK;
-    if (!q_f16_dev || !codes_dev || !scales_dev || !scores_dev || !workspace_dev) return SRFT_ERR_NULL;
-    if (!srft_aligned(q_f16_dev, 16) || !srft_aligned(codes_dev, 16) || !srft_aligned(scales_dev, 4) || !srft_aligned(scores_dev, 4) ||
-        !srft_aligned(workspace_dev, 16))
+    if (!q_f16_dev || !codes_dev || !scales_dev || !scores_dev) return SRFT_ERR_NULL;
+    if (!srft_aligned(q_f16_dev, 16) || !srft_aligned(codes_dev, 16) || !srft_aligned(scales_dev, 4) || !srft_aligned(scores_dev, 4))
         return SRFT_ERR_ALIGN;
-    hipStream_t st = (hipStream_t)hip_stream;
-    uint4* qfrag = (uint4*)workspace_dev;
-    float* dump = (float*)((char*)qfrag + (size_t)(plan->d / 16) * 2 * 64 * 16);
-    // the write path's plain kernel transforms the queries and stores them as the scan's MFMA operands
-    const int rc = launch_quantize(plan, q_f16_dev, n_q, nullptr, plan->inv_lam2, (float*)qfrag, n_q <= 16 ? kOutQFrag16 : kOutQFrag32, st);
+    return SRFT_OK;
+}
+
+int srft_kv_scores(const srft_plan_t* plan, const void* q_f16_dev, int n_q, const uint8_t* codes_dev,
+                   const float* scales_dev, int64_t n_keys, float* scores_dev, void* workspace_dev, void* hip_stream) {
+    const int rc = scores_check(plan, q_f16_dev, n_q, codes_dev, scales_dev, n_keys, scores_dev);
+    if (n_keys == 0 && rc == SRFT_OK) return SRFT_OK;
+    // (the workspace is not used; what was refused without a proper one still is)
+    if ((rc == SRFT_OK || rc == SRFT_ERR_ALIGN) && !workspace_dev) return SRFT_ERR_NULL;
+    if (rc == SRFT_OK && !srft_aligned(workspace_dev, 16)) return SRFT_ERR_ALIGN;
     if (rc != SRFT_OK) return rc;
-    return srft_launch_scores(plan, qfrag, dump, n_q, codes_dev, scales_dev, n_keys, scores_dev, st);
+    return srft_launch_scores(plan, q_f16_dev, n_q, codes_dev, scales_dev, n_keys, scores_dev, (hipStream_t)hip_stream);
 }
 
 int srft_kv_scores_static(const srft_plan_t* plan, const void* q_f16_dev, int n_q, const uint8_t* codes_dev,
                           const float* scales_dev, int64_t n_keys, float* scores_dev, void* hip_stream) {
     if (!plan) return SRFT_ERR_NULL;
-    // the static workspace holds the operands of up to 32 queries at d <= 256 and the dump slots of the largest
-    // grid: anything a plan can ask for; a larger request is refused, never served from elsewhere
-    if (srft_scores_workspace_bytes(plan) > (int64_t)kScoresScratchBytes) return SRFT_ERR_BAD_N;
-    if (plan->device < 0 || plan->device >= kMaxDevices) return SRFT_ERR_HIP;
-    void* ws = g_scratch_ptr[plan->device].load(std::memory_order_acquire);   // resolved when the plan was created
-    if (!ws) return SRFT_ERR_NULL;
-    return srft_kv_scores(plan, q_f16_dev, n_q, codes_dev, scales_dev, n_keys, scores_dev, ws, hip_stream);
+    const int rc = scores_check(plan, q_f16_dev, n_q, codes_dev, scales_dev, n_keys, scores_dev);
+    if (rc != SRFT_OK || n_keys == 0) return rc;
+    return srft_launch_scores(plan, q_f16_dev, n_q, codes_dev, scales_dev, n_keys, scores_dev, (hipStream_t)hip_stream);
 }
 
 static int attend_supported(const srft_plan_t* plan) {

@@ -67,7 +67,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kTileVecs = 32;          // vectors per tile = N of the 32x32x16 MFMA
-constexpr int kMaxScoreWorkgroups = 4096;   // scores kernel: largest grid (each workgroup owns 256 bytes of workspace)
 constexpr int kMaxD = 256;
 constexpr int kMaxAttendStripes = 2048;      // value-side kernel: most workgroups per channel slab (each owns 32 x d floats of workspace)
 constexpr int kAttendFan = 64;                // value-side kernel: first-level sums the partial results are added into
@@ -79,7 +78,7 @@ constexpr int64_t kMaxVectors = (int64_t)1 << 33;
 // lane (g = 16).  kGroupWide: g = 32 * gw with gw >= 2 slabs per group, up to the per-token case g = d.
 enum { kGroup16 = 0, kGroup32 = 1, kGroupWide = 2 };
 // what the write-path kernel produces (see quantize_tiles.h)
-enum { kOutCodes = 0, kOutRaw = 1, kOutAmax = 2, kOutQFrag32 = 3, kOutQFrag16 = 4 };
+enum { kOutCodes = 0, kOutRaw = 1, kOutAmax = 2 };
 
 // Several plans in one launch (a decode step appends a few hundred vectors to each of many (layer, K|V)
 // caches: one launch per plan would be all launch latency).  Segment i = plan i's constants and buffers; it
@@ -135,8 +134,6 @@ struct srft_plan {
     int compute_units = 0;
     float* bfly = nullptr;      // table of the butterfly form of the write path (device), d = 128 or 256 / g = 32 / 4-bit only
     float* inv_lam2 = nullptr;  // 1 / (lambda * max(lambda, 1e-6)) per channel (device): scores in the rotated domain
-    int grid_scores = 0;        // persistent grid of the scores kernel (32 rows of queries)
-    int grid_scores16 = 0;      // the same with 16 rows
     bool fold_dq = false;       // read path contracts even and odd codes separately (half the matrix work)
     bool fold_q = false;        // write path contracts even and odd inputs separately (half the matrix work)
     bool fold4_q = false;       // write path contracts the inputs in four classes n mod 4 (a quarter of the work)
@@ -165,7 +162,7 @@ quantize_kernel_t srft_pick_quantize_plain_b4(int d, int slabs, int gm);
 quantize_kernel_t srft_pick_quantize_plain_b8(int d, int slabs, int gm);
 batched_kernels_t srft_pick_quantize_plain_batched_b4(int d, int slabs, int gm);
 batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
-// write path, plain form, other outputs (kOutRaw, kOutAmax with `slabs`; kOutQFrag32 / kOutQFrag16 with one slab)
+// write path, plain form, other outputs (kOutRaw, kOutAmax)
 quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out);
 // write path, folded form (d = 128, 256)
 quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide);
@@ -187,10 +184,9 @@ int srft_rfold4_table_units(int d);
 // write path with the transform as FFT butterflies on the vector ALU (d = 128 or 256, g = 32, 4-bit; the comparison form)
 int srft_launch_quantize_butterfly(int d, const float* table_dev, const void* x, long long n_vec, uint8_t* codes,
                                    float* scales, int max_workgroups, hipStream_t st);
-// scores in the rotated domain: launch of the scan (kernels/scores.hip) and its resident workgroups per unit
-int srft_launch_scores(const srft_plan* p, uint4* qfrag, float* dump, int n_q, const uint8_t* codes,
-                       const float* scales, long long n_keys, float* out, hipStream_t st);
-int srft_scores_occupancy(int d, bool r16, int* blocks_per_cu);
+// scores in the rotated domain (kernels/scores.hip)
+int srft_launch_scores(const srft_plan* p, const void* q, int n_q, const uint8_t* codes, const float* scales,
+                       long long n_keys, float* out, hipStream_t st);
 
 // weighted sums of the stored values in the rotated domain (kernels/attend.hip): workgroups per channel slab for
 // n_q queries over n_keys values, and the three launches (partial sums per workgroup into `part`, their fixed-order
@@ -225,10 +221,6 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
                      hipStream_t st);
 // true when two plans can share one batched launch or one cache (shape, code width, transform, device, kernel forms)
 bool srft_plans_compatible(const srft_plan* a, const srft_plan* b);
-
-// resolves, once per device, the device address of the static workspace of srft_kv_scores_static (api.hip);
-// called with `device` current when a plan is created
-int srft_scores_scratch_prepare(int device);
 
 inline bool srft_aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 

@@ -21,7 +21,7 @@
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
 // d = 128, 8 queries, 131,072 keys 36.6 -> 15.4, 400,000 keys 51 -> 26; 32 queries, 400,000 keys 111 -> 39; d = 256, 4 queries,
 // 4096 keys 27.7 -> 15.3; d = 64, 1 query, 500 keys 21.9 -> 11.2.
-#include "../device_util.h"
+#include "../rotated_queries.h"
 
 namespace {
 
@@ -31,16 +31,7 @@ constexpr float kLowest = -3.0e38f;                          // "no key yet": fi
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 
-typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));     // scales are 4-byte aligned
 
-__device__ __forceinline__ uint2 swap16(uint32_t a, uint32_t b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-    return make_uint2(r[0], r[1]);
-}
-__device__ __forceinline__ uint2 swap32(uint32_t a, uint32_t b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    return make_uint2(r[0], r[1]);
-}
 // maximum / sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (one query's quarters), in all of them
 __device__ __forceinline__ float quarters_max(float m) {
     const uint2 a = swap16(__float_as_uint(m), __float_as_uint(m));
@@ -98,7 +89,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     // register i of quarter a is row 4 a + i, so a quarter ends up with the keys KQ a .. KQ a + KQ - 1 (register [b][i]:
     // key KQ a + 4 b + i), and the transposed reads of V take whole rows of keys per quarter.
     uint4 pk[BK][QUADS ? QUADS : 1], pv[NV];
-    uint32_t pr[BK][REST ? REST : 1];
+    static_assert(REST == 0 || REST == 2, "d is a multiple of 64");
+    uint2 pr[BK];
     floatx4 pks[(G + 3) / 4], pvs[(G + 3) / 4];
     auto fetch_scales = [&](floatx4 (&dst)[(G + 3) / 4], const float* src, int gw, long long t0, int rl) __attribute__((always_inline)) {
         if constexpr (WIDE) {
@@ -124,8 +116,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             const unsigned row = (unsigned)min(KQ * (l16 >> 2) + 4 * b + (l16 & 3), lim) * ROW;
 #pragma unroll
             for (int s = 0; s < QUADS; ++s) pk[b][s] = *reinterpret_cast<const uint4*>(kb + (row + 64 * s + 16 * a));
-#pragma unroll
-            for (int s = 0; s < REST; ++s) pr[b][s] = *reinterpret_cast<const uint32_t*>(kb + (row + 64 * QUADS + 16 * s + 4 * a));
+            if constexpr (REST > 0) pr[b] = *reinterpret_cast<const uint2*>(kb + (row + 64 * QUADS + 8 * a));
         }
         fetch_scales(pks, k_scales, k_gw, t0, min(lane & (KEYS - 1), lim));
     };
@@ -142,84 +133,12 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     };
     auto v_at = [&](int row) __attribute__((always_inline)) { return vt + row * VROW + (row / KQ) * 8; };
 
-    // ---- The operands of the queries, while the first tile is on its way: q' = w / (lambda max(lambda, 1e-6)) with w the
-    // write path's transform (its dense matrix, fp16 hi + lo, one slab of 32 channels per wavefront or PARTS wavefronts),
-    // split into fp16 hi + lo.  qs: [group][hi, lo][64 lanes]: lane l holds query l % 16 and the 8 codes of unit l / 16 of
-    // the group, in the order decode8 lays them out.  Every workgroup does this for itself (64 KB of matrix from L2 at
-    // d = 128); a launch of its own took 3.0 us at d = 128, 4.6 us at d = 256.
-    constexpr int PARTS = W / G > 0 ? W / G : 1, T = D / 16 / PARTS;     // MFMA k-steps per wavefront
-    static_assert(PARTS * G <= W && PARTS * T * 16 == D, "every slab has its wavefronts");
-    const int slab = min(wave / PARTS, G - 1), piece = wave % PARTS, half = lane >> 5;
-    const bool spare = wave / PARTS >= G;                    // (D = 192: the last wavefronts repeat a slab and keep it to themselves)
-    floatx16 qacc = floatx16{0};
-    floatx4 q_mul[4];                                        // 1 / (lambda max(lambda, 1e-6)) of this lane's 16 channels
-    {
-        // the queries meet the matrix through LDS: every wavefront needs all of them
-        constexpr int XROW = D * 2 + 16;
-        if (tid < 16 * (D / 8))
-            *reinterpret_cast<uint4*>(lds + (tid / (D / 8)) * XROW + 16 * (tid % (D / 8))) =
-                q[(size_t)min(q0 + tid / (D / 8), n_q - 1) * (D / 8) + tid % (D / 8)];
-        const unsigned char* xr = lds + l16 * XROW + 16 * (2 * piece * T + half);
-        const uint4* wr = wfrag + ((size_t)(slab * (D / 16) + piece * T) * 2) * 64 + lane;
-        constexpr int TB = T % 8 == 0 && KEYS == 32 ? 8 : T < 4 ? T : 4;   // k-steps in flight
-#pragma unroll
-        for (int t0 = 0; t0 < T; t0 += TB) {
-            uint4 h[TB], l[TB];
-#pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                h[t] = wr[(2 * (t0 + t)) * 64];
-                l[t] = wr[(2 * (t0 + t) + 1) * 64];
-            }
-            if (t0 + TB >= T) {                              // behind the last of the operands: their wait does not include it
-#pragma unroll
-                for (int i = 0; i < 4; ++i) q_mul[i] = reinterpret_cast<const floatx4*>(q_scale)[8 * slab + 4 * half + i];
-                __builtin_amdgcn_sched_barrier(0);
-                fetch_k(min(first, n_tiles - 1), first < n_tiles);
-                fetch_v(min(first, n_tiles - 1), first < n_tiles);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (t0 == 0) __syncthreads();
-#pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                const half8 b = *reinterpret_cast<const half8*>(xr + 32 * (t0 + t));
-                qacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, h[t]), b, qacc, 0, 0, 0);
-                qacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, l[t]), b, qacc, 0, 0, 0);
-            }
-        }
-    }
-    // (used under a branch only: without this the loads move there, behind the tile's)
-    asm volatile("" : "+v"(q_mul[0]), "+v"(q_mul[1]), "+v"(q_mul[2]), "+v"(q_mul[3]));
-    if constexpr (PARTS > 1) {
-        // columns 16 .. 31 of the product repeat 0 .. 15: lanes without bit 4
-        static_assert(16 * (D * 2 + 16) + G * (PARTS - 1) * 32 * 16 * 4 <= LDS_BYTES, "partial sums fit");
-        float* sums = reinterpret_cast<float*>(lds + 16 * (D * 2 + 16)) + (slab * (PARTS - 1) + piece - 1) * (32 * 16) + 16 * half + l16;
-        if (piece > 0 && (lane & 16) == 0)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sums[v * 32] = qacc[v];
-        __syncthreads();
-        if (piece == 0)
-#pragma unroll
-            for (int k = 1; k < PARTS; ++k)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) qacc[v] += sums[k * (32 * 16) + v * 32];
-    }
-    if (!spare && piece == 0 && (lane & 16) == 0) {
-        // lane (query l16, half) holds the 16 channels 32 slab + 16 half + v: two whole units
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            half8 hi, lo;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int v = 8 * i + (e / 2) + 4 * (e % 2);
-                const float x = l16 < nq ? (qacc[v] * unscale) * q_mul[v / 4][v % 4] : 0.0f;
-                hi[e] = (_Float16)x;
-                lo[e] = (_Float16)(x - (float)hi[e]);
-            }
-            qs[(slab * 2 + 0) * 64 + 16 * (2 * half + i) + l16] = __builtin_bit_cast(uint4, hi);
-            qs[(slab * 2 + 1) * 64 + 16 * (2 * half + i) + l16] = __builtin_bit_cast(uint4, lo);
-        }
-    }
-    __syncthreads();
+    // ---- the operands of the queries, while the first tile is on its way
+    static_assert(srft_query_scratch_bytes<D, W, 1>() <= LDS_BYTES, "the tiles' LDS serves it first");
+    srft_query_operands<D, W, 1>(q, n_q, q0, wfrag, q_scale, unscale, lds, qs, [&]() __attribute__((always_inline)) {
+        fetch_k(min(first, n_tiles - 1), first < n_tiles);
+        fetch_v(min(first, n_tiles - 1), first < n_tiles);
+    });
 
     floatx4 acc[NB];                                         // [block of 16 channels]: channels 16 b + 4 a + i, query l16
 #pragma unroll
@@ -269,16 +188,11 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
         // ---- scores: keys on the rows, queries on the columns
         float w[BK][4];
 #pragma unroll
-        for (int b = 0; b < BK; ++b)
+        for (int b = 0; b < BK; ++b) {
 #pragma unroll
-            for (int s = 0; s < QUADS; ++s) {
-                // quarter k loaded group 4 s + k whole; a 4 x 4 transpose over the quarters gives every quarter its unit of
-                // each of the four groups
-                const uint4 r = pk[b][s];
-                const uint2 x01 = swap16(r.x, r.y), x23 = swap16(r.z, r.w);
-                const uint2 y02 = swap32(x01.x, x23.x), y13 = swap32(x01.y, x23.y);
-                pk[b][s] = make_uint4(y02.x, y13.x, y02.y, y13.y);
-            }
+            for (int s = 0; s < QUADS; ++s) pk[b][s] = srft_quad_transpose(pk[b][s]);
+            if constexpr (REST > 0) pr[b] = srft_pair_transpose(pr[b]);
+        }
         KStep kc, kn;
         load_k(kc, 0);
 #pragma unroll
@@ -288,7 +202,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 #pragma unroll
             for (int b = 0; b < BK; ++b) {
                 const uint4& four = pk[b][j / 4 < QUADS ? j / 4 : 0];
-                const uint32_t kd = j >= 4 * QUADS ? pr[b][j >= 4 * QUADS ? j - 4 * QUADS : 0]
+                const uint32_t kd = j >= 4 * QUADS ? (j == 4 * QUADS ? pr[b].x : pr[b].y)
                                   : j % 4 == 0 ? four.x : j % 4 == 1 ? four.y : j % 4 == 2 ? four.z : four.w;
                 const half8 kf = __builtin_bit_cast(half8, decode8(kd));
                 const float scv[4] = {kc.sc[b].x, kc.sc[b].y, kc.sc[b].z, kc.sc[b].w};

@@ -1,5 +1,5 @@
-// Write path, plain form, outputs other than codes: the raw coefficients (srft_kv_forward_f32), the per-channel
-// abs-max statistic (srft_kv_channel_absmax) and the query operands of the scores kernel.
+// Write path, plain form, outputs other than codes: the raw coefficients (srft_kv_forward_f32) and the
+// per-channel abs-max statistic (srft_kv_channel_absmax).
 #include "../quantize_tiles.h"
 
 namespace {
@@ -7,10 +7,6 @@ template <int D, int S>
 quantize_kernel_t by_output(int out) {
     if (out == kOutRaw) return srft_quantize_kernel<D, S, kOutRaw, kGroup32, 4>;
     if (out == kOutAmax) return srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4>;
-    if constexpr (S == 1 && D % 64 == 0) {       // the scores set-up always runs one slab per wavefront
-        if (out == kOutQFrag32) return srft_quantize_kernel<D, 1, kOutQFrag32, kGroup32, 4>;
-        if (out == kOutQFrag16) return srft_quantize_kernel<D, 1, kOutQFrag16, kGroup32, 4>;
-    }
     return nullptr;
 }
 template <int D>

@@ -241,12 +241,6 @@ int occupancy_grids(srft_plan* p, int cus) {
     rc = resident_blocks((const void*)dk, threads, &blocks);
     if (rc != SRFT_OK) return rc;
     p->grid_dq = cus * blocks;
-    rc = srft_scores_occupancy(p->d, false, &blocks);
-    if (rc != SRFT_OK) return rc;
-    p->grid_scores = cus * (blocks > 0 ? blocks : 1);
-    rc = srft_scores_occupancy(p->d, true, &blocks);
-    if (rc != SRFT_OK) return rc;
-    p->grid_scores16 = cus * (blocks > 0 ? blocks : 1);
     return SRFT_OK;
 }
 
@@ -258,10 +252,6 @@ int srft_hip_fail(hipError_t e) {
 }
 
 quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads) {
-    if (out == kOutQFrag32 || out == kOutQFrag16) {      // the scores set-up always runs one slab per wavefront
-        *threads = 2 * p->d;
-        return srft_pick_quantize_aux(p->d, 1, out);
-    }
     if (out == kOutAmax && p->fold_q) {                  // the statistic does not depend on the groups: folded wherever the table exists
         *threads = p->d;
         return srft_pick_quantize_fold_amax(p->d);
@@ -519,7 +509,6 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
     if (e == hipSuccess && p->fold_dq) e = hipMalloc((void**)&p->rfold, rfold.size() * 2);
     if (e == hipSuccess && p->fold_dq) e = hipMemcpy(p->rfold, rfold.data(), rfold.size() * 2, hipMemcpyHostToDevice);
     int rc = (e == hipSuccess) ? occupancy_grids(p, cus) : srft_hip_fail(e);
-    if (rc == SRFT_OK) rc = srft_scores_scratch_prepare(p->device);
     if (rc != SRFT_OK) {
         srft_plan_destroy(p);
         return rc;

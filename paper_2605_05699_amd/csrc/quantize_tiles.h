@@ -16,9 +16,6 @@
 //         kOutAmax: no per-vector output; every lane keeps the running maximum of |w| of its 16 channels over the
 //         tiles it sees, lanes are reduced once at the end and one atomic max per channel and workgroup goes
 //         to wout, read as float[d] (srft_kv_channel_absmax: the statistic lambda is calibrated from, Sec. 7.1).
-//         kOutQFrag32 / kOutQFrag16: the vectors are queries of srft_kv_scores (one tile at most): w times
-//         scales[p] (there: 1 / (lambda max(lambda, 1e-6))), split into fp16 hi + lo and stored to wout as the
-//         A fragments of the scores kernel with 32 or 16 rows of queries (layouts described there).
 // GM    : group mode.  kGroup32: one scale per slab (g = 32, the deployed format).  kGroup16: one scale per
 //         lane (g = 16; a lane's 16 outputs are one group, no cross-lane step).  kGroupWide: g = 32 * gw with
 //         gw >= 2 slabs per group, up to the per-token case g = d; the slab maxima meet in LDS, which costs
@@ -112,40 +109,6 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
             each_acc(accs, [&](floatx16& acc, int s) __attribute__((always_inline)) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) cmax[s][v] = fmaxf(cmax[s][v], fabsf(acc[v]));
-            });
-        } else if constexpr (OUT == kOutQFrag32 || OUT == kOutQFrag16) {
-            // lane (query col, half) holds the packed indices p0 .. p0 + 15 of its query: code units p0 / 8 and
-            // p0 / 8 + 1, whole.  Fragment element e of a unit is packed index 8 unit + e / 2 + 4 (e % 2) (the
-            // 4-bit decode order of the read path).  Rows of queries that do not exist are zero.
-            uint4* frag = reinterpret_cast<uint4*>(wout);
-            const int q = col;
-            each_acc(accs, [&](floatx16& acc, int s) __attribute__((always_inline)) {
-                const int p0 = 32 * (wave * S + s) + 16 * half;
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    half8 hi, lo;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int pp = 8 * i + (e / 2) + 4 * (e % 2);
-                        const float v = q <= lim ? (acc[pp] * unscale) * scales[p0 + pp] : 0.0f;
-                        hi[e] = (_Float16)v;
-                        lo[e] = (_Float16)(v - (float)hi[e]);
-                    }
-                    const int u = p0 / 8 + i;
-                    if constexpr (OUT == kOutQFrag16) {
-                        // MFMA row 4 a + i' carries query 2 i' + a (a < 2) or 8 + 2 i' + (a - 2); lane = 16 (u % 4) + row
-                        const int row = q < 8 ? 4 * (q % 2) + q / 2 : 4 * (2 + q % 2) + (q - 8) / 2;
-                        if (q < 16) {
-                            frag[((u / 4) * 2 + 0) * 64 + 16 * (u % 4) + row] = __builtin_bit_cast(uint4, hi);
-                            frag[((u / 4) * 2 + 1) * 64 + 16 * (u % 4) + row] = __builtin_bit_cast(uint4, lo);
-                        }
-                    } else {
-                        // MFMA row 8 (v / 4) + 4 h + v % 4 carries query 2 v + h; lane = 32 (u % 2) + row
-                        const int row = 8 * ((q / 2) / 4) + 4 * (q % 2) + (q / 2) % 4;
-                        frag[((u / 2) * 2 + 0) * 64 + 32 * (u % 2) + row] = __builtin_bit_cast(uint4, hi);
-                        frag[((u / 2) * 2 + 1) * 64 + 32 * (u % 2) + row] = __builtin_bit_cast(uint4, lo);
-                    }
-                }
             });
         } else if constexpr (OUT == kOutRaw) {
             each_acc(accs, [&](floatx16& acc, int s) __attribute__((always_inline)) {

@@ -113,3 +113,30 @@ def test_scores_argument_errors(B):
         bad.close()
     torch.cuda.synchronize()
     plan.close()
+
+
+@pytest.mark.parametrize("d,g,n_q,cap", [(64, 32, 16, 2), (64, 64, 17, 1), (128, 32, 17, 2), (128, 128, 3, 1), (192, 32, 32, 1),
+                                         (192, 96, 16, 2), (256, 32, 8, 1), (256, 64, 32, 2)])
+def test_scores_at_the_edges_of_tiles_and_of_a_wavefronts_share(B, d, g, n_q, cap):
+    """Key counts around one tile and around one, two and three rounds of a capped grid; rows of scores at every alignment
+    (odd counts), nothing written past the last one."""
+    lam = W.lognormal_lambda(d, seed=d + g)
+    plan = B.Plan(d, g, 900 + d, lam)
+    n_max = 3200
+    keys = W.gaussian_with_outliers(n_max, d, seed=d + 9, outliers=1, gain=15.0)
+    q = W.gaussian_with_outliers(n_q, d, seed=d + 10, outliers=1, gain=4.0)
+    codes, scales = plan.quantize(torch.from_numpy(keys).cuda())
+    c, sc = codes.cpu().numpy(), scales.cpu().numpy()
+    ref = O.attention_scores(q, c, sc, plan.signs, lam, g)
+    tol = _tolerance(q, O.dequantize_f64(c, sc, plan.signs, lam, g))
+    B.srft_plan_set_max_workgroups(plan.handle, cap)
+    ws = torch.empty(B.lib().srft_scores_workspace_bytes(plan.handle), dtype=torch.uint8, device="cuda")
+    qd = torch.from_numpy(q).cuda()
+    for n in (1, 31, 32, 33, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1023, 1025, 1537, 3199, 3200):
+        flat = torch.full((n_q * n + 64,), -7.0, dtype=torch.float32, device="cuda")
+        B.srft_kv_scores(plan.handle, qd, codes[:n].contiguous(), scales[:n].contiguous(), flat[:n_q * n].view(n_q, n), ws)
+        torch.cuda.synchronize()
+        got = flat.cpu().numpy().astype(np.float64)
+        assert np.all(got[n_q * n:] == -7.0), n
+        assert np.all(np.abs(got[:n_q * n].reshape(n_q, n) - ref[:, :n]) <= tol[:, :n]), n
+    plan.close()
