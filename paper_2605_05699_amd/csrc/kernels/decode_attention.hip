@@ -19,8 +19,8 @@
 // the second product takes as its B operand and what a running maximum and its correction need; with channels on the rows and
 // queries on the columns of the second product the sums belong to the same query.
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
-// d = 128, 8 queries, 131,072 keys 36.6 -> 15.4, 400,000 keys 51 -> 26; 32 queries, 400,000 keys 111 -> 39; d = 256, 4 queries,
-// 4096 keys 27.7 -> 15.3; d = 64, 1 query, 500 keys 21.9 -> 11.2.
+// d = 128, 8 queries, 131,072 keys 36.6 -> 15.6, 400,000 keys 51 -> 26; 32 queries, 400,000 keys 111 -> 39; d = 256, 4 queries,
+// 4096 keys 27.7 -> 15.6; d = 64, 1 query, 500 keys 21.9 -> 11.2.  Error against 64 bits 6e-6 -> 4e-7.
 #include "../rotated_queries.h"
 
 namespace {
@@ -43,6 +43,25 @@ __device__ __forceinline__ float quarters_sum(float s) {
     s = __uint_as_float(a.x) + __uint_as_float(a.y);
     const uint2 b = swap32(__float_as_uint(s), __float_as_uint(s));
     return __uint_as_float(b.x) + __uint_as_float(b.y);
+}
+
+// over the 64 lanes, in all of them; the order of the sum is fixed
+template <int CTRL> __device__ __forceinline__ float row_rotated(float x) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_max(float x) {
+    x = fmaxf(x, row_rotated<0x128>(x));                     // row_ror: 8, 4, 2, 1 within 16 lanes
+    x = fmaxf(x, row_rotated<0x124>(x));
+    x = fmaxf(x, row_rotated<0x122>(x));
+    x = fmaxf(x, row_rotated<0x121>(x));
+    return quarters_max(x);
+}
+__device__ __forceinline__ float wave_sum(float x) {
+    x += row_rotated<0x128>(x);
+    x += row_rotated<0x124>(x);
+    x += row_rotated<0x122>(x);
+    x += row_rotated<0x121>(x);
+    return quarters_sum(x);
 }
 
 // D: head dimension.  KEYS: keys per tile, 64 or 32.  WIDE: groups of gw > 1 runs of 32 channels share a scale.
@@ -144,6 +163,10 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = floatx4{0, 0, 0, 0};
     float top = kLowest, den = 0.0f;                         // maximum of |softmax_scale| * (signed score), sum of weights
+    // The products weight * scale go to the matrix cores as fp16 hi + lo, and a weight far below the largest must not fall under
+    // fp16's range: V's scales are taken times a power of two (fit) that brings the largest of a tile to 2^13 .. 2^14; it
+    // only ever gets smaller, the sums with it, and is divided out at the end.
+    float fit = 0x1p73f;
     // weights are 2^(c * score - top)
     const float c = softmax_scale * 1.44269504088896340736f, sign = c < 0.0f ? -1.0f : 1.0f, c_abs = fabsf(c);
 
@@ -168,11 +191,18 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     };
     for (long long tile = first; tile < n_tiles; tile += stride) {
         const bool more = tile + stride < n_tiles;
+        float most = 0.0f;
+#pragma unroll
+        for (int j = 0; j < G; ++j) most = fmaxf(most, fabsf(pvs[j / 4][j % 4]));
+        const uint32_t exponent = __float_as_uint(wave_max(most)) & 0x7F800000u;
+        const float fit_here = __uint_as_float((267u << 23) - max(exponent, 67u << 23));      // 2^(13 - exponent), at most 2^73
+        const float fit_down = fminf(fit_here, fit) / fit;   // a power of two, 1 as long as the scales do not grow
+        fit = fminf(fit_here, fit);
         // LDS of one wavefront: its accesses complete in program order
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             ks[j * KEYS + (lane & (KEYS - 1))] = pks[j / 4][j % 4];
-            vs[j * KEYS + (lane & (KEYS - 1))] = pvs[j / 4][j % 4];
+            vs[j * KEYS + (lane & (KEYS - 1))] = pvs[j / 4][j % 4] * fit;
         }
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -230,6 +260,9 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b] *= down;
             }
+            if (fit_down != 1.0f)                            // uniform
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b] *= fit_down;
 #pragma unroll
             for (int v = 0; v < KQ; ++v) w[v / 4][v % 4] = __builtin_amdgcn_exp2f(fmaf(c, w[v / 4][v % 4], -top));
             if (tile == n_tiles - 1) {                       // uniform: keys past the end weigh nothing
@@ -310,7 +343,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 if (b >= b0 && b < b1)                       // uniform
-                    *reinterpret_cast<floatx4*>(&merge[(wave * nq + l16) * mrow + 16 * (b - b0) + 4 * a]) = acc[b] * f;
+                    *reinterpret_cast<floatx4*>(&merge[(wave * nq + l16) * mrow + 16 * (b - b0) + 4 * a]) = acc[b] * (f / fit);
         __syncthreads();
         const int per = 4 * (b1 - b0);                       // 16-byte pieces per query
         for (int e = tid; e < nq * per; e += 64 * W) {
@@ -320,25 +353,6 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             *reinterpret_cast<floatx4*>(&dst[r * D + 16 * b0 + 4 * p]) = s;
         }
     }
-}
-
-// over the 64 lanes, in all of them; the order of the sum is fixed
-template <int CTRL> __device__ __forceinline__ float row_rotated(float x) {
-    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_max(float x) {
-    x = fmaxf(x, row_rotated<0x128>(x));                     // row_ror: 8, 4, 2, 1 within 16 lanes
-    x = fmaxf(x, row_rotated<0x124>(x));
-    x = fmaxf(x, row_rotated<0x122>(x));
-    x = fmaxf(x, row_rotated<0x121>(x));
-    return quarters_max(x);
-}
-__device__ __forceinline__ float wave_sum(float x) {
-    x += row_rotated<0x128>(x);
-    x += row_rotated<0x124>(x);
-    x += row_rotated<0x122>(x);
-    x += row_rotated<0x121>(x);
-    return quarters_sum(x);
 }
 
 // Workgroup (query, block of 64 outputs), 1024 threads.  It adds the scan's workgroups over all D channels (thread: channels

@@ -202,3 +202,30 @@ def test_decode_attention_at_the_edges_of_its_tiles_and_grid(B, d, g, n_q, n_key
     assert np.abs(got - ref).max() <= tol, float(np.abs(got - ref).max() / tol)
     pk.close()
     pv.close()
+
+
+def test_decode_attention_keeps_weights_far_below_the_largest(B):
+    """One key outweighs each of the others by about e^17, and there are enough of them that together they still matter:
+    a weight below the smallest fp16 number (relative to the row's maximum) must not vanish."""
+    d, g, n_keys = 64, 32, 200_000
+    rng = np.random.RandomState(3)
+    k = (0.02 * rng.standard_normal((n_keys, d))).astype(np.float16)
+    q = np.ones((1, d), dtype=np.float16)
+    k[12345] = np.float16(17.0 / 64 / 0.125)          # softmax_scale q.k = 17 for this key, about 0 for the others
+    v = (1.0 + 0.1 * rng.standard_normal((n_keys, d))).astype(np.float16)
+    v[12345] = 0.0                                    # so the output is what the others carry: about n e^-17 / (1 + n e^-17)
+    pk, pv = B.Plan(d, g, 31), B.Plan(d, g, 32)
+    kc, ks = pk.quantize(torch.from_numpy(k).cuda())
+    vc, vs = pv.quantize(torch.from_numpy(v).cuda())
+    out = torch.empty(1, d, dtype=torch.float32, device="cuda")
+    ws = torch.empty(B.lib().srft_decode_attention_workspace_bytes(pk.handle, pv.handle, 1, n_keys), dtype=torch.uint8, device="cuda")
+    B.srft_kv_decode_attention(pk.handle, pv.handle, torch.from_numpy(q).cuda(), kc, ks, vc, vs, 0.125, out, ws)
+    torch.cuda.synchronize()
+    ones = np.ones(d, dtype=np.float32)
+    ref = O.decode_attention(q, kc.cpu().numpy(), ks.cpu().numpy(), pk.signs, ones, vc.cpu().numpy(), vs.cpu().numpy(),
+                             pv.signs, ones, g, 0.125)
+    # scores of size 17 in fp32 (2e-6 absolute), weights and sums as in the other tests
+    assert np.abs(out.cpu().numpy() - ref).max() <= 3e-5 * np.abs(ref).max(), (np.abs(out.cpu().numpy() - ref).max(), np.abs(ref).max())
+    assert 0.003 < np.abs(ref).max() < 0.1
+    pk.close()
+    pv.close()
