@@ -4,6 +4,7 @@
 #include <cmath>
 
 #include "common.h"
+#include "launch_shape.h"
 
 namespace {
 
@@ -53,24 +54,33 @@ int launch_dequantize(const srft_plan* p, const uint8_t* codes, const float* sca
     return SRFT_OK;
 }
 
-// One batched launch: the segment table is complete except for the workgroups, which are laid out here.
-// Every segment gets at least one workgroup and at most one per tile; when the tiles of all segments
-// exceed the persistent grid, workgroups are shared out in proportion to the tiles.
-int launch_batched(const srft_plan* p, srft_batch_args& a, bool write_path, hipStream_t st) {
-    long long budget = p->max_wgs > 0 ? p->max_wgs : (write_path ? p->grid_q : p->grid_dq);
-    long long total_tiles = 0;
-    for (int i = 0; i < a.count; ++i) total_tiles += (a.seg[i].n_vec + kTileVecs - 1) / kTileVecs;
-    int next = 0;
-    for (int i = 0; i < a.count; ++i) {
-        const long long tiles = (a.seg[i].n_vec + kTileVecs - 1) / kTileVecs;
-        long long blocks = total_tiles <= budget ? tiles : tiles * budget / total_tiles;
-        if (blocks < 1) blocks = 1;
-        if (blocks > tiles) blocks = tiles;
-        a.first_block[i] = next;
-        a.seg[i].blocks = (int)blocks;
-        next += (int)blocks;
+// What a launch of `Batch` takes: the shares' tiles of the segments' buffers.
+template <class Batch>
+Batch batch_table(const srft_plan* p, bool write_path, const srft_segment* segments, const srft_share* shares, int n) {
+    Batch a;
+    const long long code_bytes = (long long)p->d * p->bits / 8, row_bytes = 2LL * p->d;
+    for (int i = 0; i < Batch::kSegments; ++i) a.first_block[i] = i < n ? shares[i].first_block : INT32_MAX;
+    for (int i = 0; i < n; ++i) {
+        const srft_share& sh = shares[i];
+        srft_segment& s = a.seg[i] = segments[sh.segment];
+        const long long v0 = sh.tile * kTileVecs;
+        s.in = (const char*)s.in + v0 * (write_path ? row_bytes : code_bytes);
+        s.out = (char*)s.out + v0 * (write_path ? code_bytes : row_bytes);
+        s.scales += v0 * (p->d / p->g);
+        s.n_vec = std::min(s.n_vec - v0, sh.tiles * kTileVecs);
+        s.blocks = sh.blocks;
     }
-    for (int i = a.count; i < kMaxBatch; ++i) a.first_block[i] = INT32_MAX;
+    return a;
+}
+
+// One batched launch over up to kMaxBatch segments.
+int launch_batched(const srft_plan* p, const srft_segment* segments, int count, bool write_path, hipStream_t st) {
+    long long tiles[kMaxBatch];
+    for (int i = 0; i < count; ++i) tiles[i] = (segments[i].n_vec + kTileVecs - 1) / kTileVecs;
+    srft_share shares[kMaxBatch];
+    int next = 0;
+    const int n = srft_share_out(tiles, count, p->max_wgs > 0 ? p->max_wgs : write_path ? p->grid_q : p->grid_dq, shares,
+                                 kMaxBatch, &next);
     batched_kernels_t kernel;
     int threads = 0;
     if (write_path) {
@@ -94,15 +104,11 @@ int launch_batched(const srft_plan* p, srft_batch_args& a, bool write_path, hipS
         threads = 2 * p->d / p->slabs_dq;
     }
     if (!kernel.many) return SRFT_ERR_BAD_D;
-    if (a.count <= kFewBatch) {
-        srft_batch_few few;
-        std::copy_n(a.first_block, kFewBatch, few.first_block);
-        std::copy_n(a.seg, a.count, few.seg);
-        few.count = a.count;
-        hipLaunchKernelGGL(kernel.few, dim3((unsigned)next), dim3(threads), 0, st, few, p->gw);
-    } else {
-        hipLaunchKernelGGL(kernel.many, dim3((unsigned)next), dim3(threads), 0, st, a, p->gw);
-    }
+    const dim3 grid((unsigned)next), block(threads);
+    if (n <= kFewBatch)
+        hipLaunchKernelGGL(kernel.few, grid, block, 0, st, batch_table<srft_batch_few>(p, write_path, segments, shares, n), p->gw);
+    else
+        hipLaunchKernelGGL(kernel.many, grid, block, 0, st, batch_table<srft_batch_many>(p, write_path, segments, shares, n), p->gw);
     SRFT_HIP(hipGetLastError());
     return SRFT_OK;
 }
@@ -126,24 +132,23 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
         if (!in0[i] || !out0[i] || !small) return SRFT_ERR_NULL;
         if (!srft_aligned(in0[i], 16) || !srft_aligned(out0[i], 16) || !srft_aligned(small, 4)) return SRFT_ERR_ALIGN;
     }
-    srft_batch_args a;
-    a.count = 0;
+    srft_segment segments[kMaxBatch];
+    int k = 0;
     for (int i = 0; i <= count; ++i) {
         if (i < count && n_vec[i] > 0) {
-            srft_segment& s = a.seg[a.count++];
+            srft_segment& s = segments[k++];
             s.frag = write_path ? (plans[i]->fold4_q ? plans[i]->wfold4 : plans[i]->fold_q ? plans[i]->wfold : plans[i]->wfrag)
                                 : srft_plan_read_table(plans[i]);
-            s.in0 = in0[i];
-            s.in1 = write_path ? nullptr : in1[i];
-            s.out0 = out0[i];
-            s.out1 = write_path ? out1[i] : nullptr;
+            s.in = in0[i];
+            s.out = out0[i];
+            s.scales = (float*)(write_path ? out1[i] : in1[i]);
             s.n_vec = n_vec[i];
             s.unscale = write_path ? plans[i]->unscale_w : srft_plan_read_unscale(plans[i]);
         }
-        if (a.count == kMaxBatch || (i == count && a.count > 0)) {
-            const int rc = launch_batched(plans[0], a, write_path, st);
+        if (k == kMaxBatch || (i == count && k > 0)) {
+            const int rc = launch_batched(plans[0], segments, k, write_path, st);
             if (rc != SRFT_OK) return rc;
-            a.count = 0;
+            k = 0;
         }
     }
     return SRFT_OK;

@@ -81,41 +81,40 @@ enum { kGroup16 = 0, kGroup32 = 1, kGroupWide = 2 };
 enum { kOutCodes = 0, kOutRaw = 1, kOutAmax = 2 };
 
 // Several plans in one launch (a decode step appends a few hundred vectors to each of many (layer, K|V)
-// caches: one launch per plan would be all launch latency).  Segment i = plan i's constants and buffers; it
-// is served by workgroups first_block[i] .. first_block[i] + seg[i].blocks - 1, each walking that segment's tiles with
-// that many as stride.  Entries of first_block past the last segment hold INT32_MAX.  The table travels as a kernel
-// argument.
+// caches: one launch per plan would be all launch latency).  A segment = a plan's constants and buffers, or a part of them
+// (launch_shape.h); it is served by workgroups first_block[i] .. first_block[i] + seg[i].blocks - 1, each walking that
+// segment's tiles with that many as stride.  Entries of first_block past the last segment hold INT32_MAX.  The table travels
+// as a kernel argument.
 constexpr int kMaxBatch = 64;       // the table is about 3.8 KiB of the 4 KiB a kernel may take as arguments
 // Up to kFewBatch segments travel in a table of their own: the runtime writes the arguments of a launch out one by one, 0.8 us
 // of a launch's 4 us for 3.8 KiB (append of 2 x 256 vectors at d = 128: 5.9 -> 5.4 us a call).
 constexpr int kFewBatch = 8;
 struct srft_segment {
     const uint4* frag;
-    const void* in0;                // write path: x      read path: codes
-    const void* in1;                //                    read path: scales
-    void* out0;                     // write path: codes  read path: out
-    void* out1;                     // write path: scales
+    const void* in;                 // write path: x      read path: codes
+    void* out;                      // write path: codes  read path: out
+    float* scales;                  // written / read
     long long n_vec;
     float unscale;
     int blocks;
 };
 template <int N>
 struct srft_batch {
+    static constexpr int kSegments = N;
     int first_block[N];
     srft_segment seg[N];
-    int count;
 };
-using srft_batch_args = srft_batch<kMaxBatch>;
+using srft_batch_many = srft_batch<kMaxBatch>;
 using srft_batch_few = srft_batch<kFewBatch>;
-static_assert(sizeof(srft_batch_args) + sizeof(int) <= 4096, "kernel arguments are limited to 4 KiB");
+static_assert(sizeof(srft_batch_many) + sizeof(int) <= 4096, "kernel arguments are limited to 4 KiB");
 
 typedef void (*quantize_kernel_t)(const uint4*, const uint4*, long long, uint2*, float*, float4*, float, float, int);
 typedef void (*dequantize_kernel_t)(const uint4*, const uint2*, const float*, long long, uint4*, float, int);
 struct batched_kernels_t {
-    void (*many)(const srft_batch_args, int);
+    void (*many)(const srft_batch_many, int);
     void (*few)(const srft_batch_few, int);
     batched_kernels_t(std::nullptr_t = nullptr) : many(nullptr), few(nullptr) {}
-    batched_kernels_t(void (*m)(const srft_batch_args, int), void (*f)(const srft_batch_few, int)) : many(m), few(f) {}
+    batched_kernels_t(void (*m)(const srft_batch_many, int), void (*f)(const srft_batch_few, int)) : many(m), few(f) {}
 };
 #define SRFT_BATCHED(kernel, ...) batched_kernels_t(kernel<__VA_ARGS__, kMaxBatch>, kernel<__VA_ARGS__, kFewBatch>)
 

@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(D / 64 * 64, 2)
 srft_dequantize_fold4_batched_kernel(const srft_batch<N> a, int gw) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
-    srft_dequantize_fold4_tiles<D, BITS>(s.frag, (const uint2*)s.in0, (const float*)s.in1, s.n_vec, (uint4*)s.out0,
+    srft_dequantize_fold4_tiles<D, BITS>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
                                          s.unscale, gw, t0, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 

@@ -1,0 +1,60 @@
+// launch_shape.h -- how a batched launch shares its workgroups out; plain C++ for the host, no HIP.
+#ifndef SRFT_LAUNCH_SHAPE_H
+#define SRFT_LAUNCH_SHAPE_H
+#include <algorithm>
+
+constexpr int kDies = 8;                     // accelerator dies; a launch's workgroups run die by die (srft_segment_of_block)
+
+// Workgroups first_block .. first_block + blocks - 1 walk the tiles tile .. tile + tiles - 1 of a segment, each with stride
+// `blocks`.
+struct srft_share {
+    int segment, first_block, blocks;
+    long long tile, tiles;
+};
+
+// Shares of a launch over segments of tiles[i] >= 1 tiles; returns how many were written to `out` (room for `most` >= count)
+// and sets *grid.  Every segment gets at least one workgroup and at most one per tile; when the tiles of all segments exceed
+// `budget`, workgroups are shared out in proportion to the tiles.
+// Where a share's tiles do not divide evenly, its first workgroups walk one tile more than the others.  A segment that lies on
+// several dies would give all of these tiles to the first of them (2 plans x 698 tiles on 1024 workgroups: 256 tiles on one
+// die, 128 on another), so it is cut where the dies meet, and each part gets its part of the tiles.  Whole segments against
+// cut ones, us: d = 128, 2 plans x 18,836 vectors, write 7.0 -> 5.8, read 6.5 -> 5.9; d = 256, 2 x 9415, write 7.2 -> 6.0; 2 x
+// 18,017 10.4 -> 9.0.  Only where it pays: segments of two dies and more (5 to 7 plans even out by themselves, and lose 2 % when
+// cut), up to 4 tiles per workgroup (from there on within 1 %).
+inline int srft_share_out(const long long* tiles, int count, long long budget, srft_share* out, int most, int* grid) {
+    long long total = 0;
+    for (int i = 0; i < count; ++i) total += tiles[i];
+    int next = 0;
+    for (int i = 0; i < count; ++i) {
+        const long long blocks = total <= budget ? tiles[i] : std::min(std::max(tiles[i] * budget / total, 1LL), tiles[i]);
+        out[i] = {i, next, (int)blocks, 0, tiles[i]};
+        next += (int)blocks;
+    }
+    *grid = next;
+    if (total <= budget) return count;
+    const int q = next / kDies, r = next % kDies;
+    int last[kDies], cuts = 0;               // places up to the end of each die
+    for (int die = 0, end = 0; die < kDies; ++die) last[die] = end += q + (die < r);
+    const auto cut_at = [&](const srft_share& s, int place) {
+        return place > s.first_block && place < s.first_block + s.blocks && s.blocks >= 2 * q && s.tiles > s.blocks && s.tiles < 4LL * s.blocks;
+    };
+    for (int i = 0, die = 0; i < count; ++i)
+        for (; die < kDies && last[die] < out[i].first_block + out[i].blocks; ++die) cuts += cut_at(out[i], last[die]);
+    if (cuts == 0 || count + cuts > most) return count;
+    // from the last segment to the first: the parts are written behind the segments that are still to be read
+    for (int i = count - 1, at = count + cuts, die = kDies - 1; i >= 0; --i) {
+        const srft_share s = out[i];
+        int end = s.first_block + s.blocks;
+        const auto part = [&](int from) {
+            const long long t0 = s.tiles * (from - s.first_block) / s.blocks, t1 = s.tiles * (end - s.first_block) / s.blocks;
+            out[--at] = {i, from, end - from, t0, t1 - t0};
+            end = from;
+        };
+        for (; die >= 0 && last[die] > s.first_block; --die)
+            if (cut_at(s, last[die])) part(last[die]);
+        part(s.first_block);
+    }
+    return count + cuts;
+}
+
+#endif  // SRFT_LAUNCH_SHAPE_H

@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(256, 2)
 srft_quantize_fold4_batched_kernel(const srft_batch<N> a, int) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
-    srft_quantize_fold4_tiles<BITS>(s.frag, (const uint4*)s.in0, s.n_vec, (uint2*)s.out0, (float*)s.out1,
+    srft_quantize_fold4_tiles<BITS>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
                                     1.0f / (BITS == 8 ? 127.0f : 7.0f), t0, s.blocks,
                                     (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }

@@ -498,7 +498,7 @@ __global__ void __launch_bounds__(D, (D >= 256 ? SRFT_QF_WG_PER_CU_256 : 2))
 srft_quantize_fold_batched_kernel(const srft_batch<N> a, int gw) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
-    srft_quantize_fold_tiles<D, BITS, WIDE>(s.frag, (const uint4*)s.in0, s.n_vec, (uint2*)s.out0, (float*)s.out1,
+    srft_quantize_fold_tiles<D, BITS, WIDE>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
                                             s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, t0, s.blocks,
                                             (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }

@@ -20,12 +20,12 @@ def B():
     return binding
 
 
-def _make(B, d, g, counts, seed0, cap=None):
+def _make(B, d, g, counts, seed0, cap=None, bits=4):
     """Plans with distinct signs and lambda, inputs of the given lengths, and the per-plan results."""
     plans, xs, ref = [], [], []
     for i, n in enumerate(counts):
         lam = W.lognormal_lambda(d, seed=seed0 + 7 * i)
-        plan = B.Plan(d, g, seed0 + i, lam)
+        plan = B.Plan(d, g, seed0 + i, lam, bits=bits)
         plan.lam = lam
         x = torch.from_numpy(W.gaussian_with_outliers(max(n, 1), d, seed=seed0 + 13 * i, outliers=1))[:n].cuda()
         if n:
@@ -43,8 +43,8 @@ def _make(B, d, g, counts, seed0, cap=None):
     return plans, xs, ref
 
 
-def _batched(B, plans, xs, d, g):
-    codes = [torch.full((x.shape[0], d // 2), 0xAB, dtype=torch.uint8, device="cuda") for x in xs]
+def _batched(B, plans, xs, d, g, bits=4):
+    codes = [torch.full((x.shape[0], d * bits // 8), 0xAB, dtype=torch.uint8, device="cuda") for x in xs]
     scales = [torch.full((x.shape[0], d // g), -1.0, dtype=torch.float32, device="cuda") for x in xs]
     outs = [torch.full((x.shape[0], d), 77.0, dtype=torch.float16, device="cuda") for x in xs]
     h = [p.handle for p in plans]
@@ -204,5 +204,18 @@ def test_workgroup_to_entry_map(B, entries):
     counts = [1 + (53 * i) % 97 for i in range(entries)]
     plans, xs, ref = _make(B, d, g, counts, seed0=9000 + entries)
     _assert_same(ref, _batched(B, plans, xs, d, g))
+    for p in plans:
+        p.close()
+
+
+@pytest.mark.parametrize("d,g,bits,counts,cap", [
+    (128, 32, 4, (1000, 999), 24), (128, 32, 4, (1300,), 37), (96, 32, 4, (700, 1000, 33), 16), (256, 32, 4, (2017, 2017), 40),
+    (64, 64, 4, (1500, 1400, 1300, 1211), 48), (256, 16, 4, (1111, 1000), 20), (192, 96, 4, (1000, 37), 5), (32, 32, 4, (2000,), 8),
+    (128, 32, 8, (1000, 999), 24), (192, 16, 8, (1000,), 16), (256, 256, 8, (700, 700), 16),
+])
+def test_segments_cut_where_the_dies_meet(B, d, g, bits, counts, cap):
+    """Few plans and one to four tiles per workgroup: a segment goes out in parts, and nothing but the launch changes."""
+    plans, xs, ref = _make(B, d, g, list(counts), seed0=700 + d + g, cap=cap, bits=bits)
+    _assert_same(ref, _batched(B, plans, xs, d, g, bits))
     for p in plans:
         p.close()

@@ -1,0 +1,93 @@
+"""How a batched launch shares its workgroups out (csrc/launch_shape.h, host code, built here with g++)."""
+import ctypes as C
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_05699_amd", "csrc")
+SOURCE = """
+#include "launch_shape.h"
+extern "C" int share_out(const long long* tiles, int count, long long budget, srft_share* out, int most, int* grid) {
+    return srft_share_out(tiles, count, budget, out, most, grid);
+}
+"""
+
+
+class Share(C.Structure):
+    _fields_ = [("segment", C.c_int), ("first_block", C.c_int), ("blocks", C.c_int), ("tile", C.c_longlong), ("tiles", C.c_longlong)]
+
+
+@pytest.fixture(scope="module")
+def share_out(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no g++")
+    at = tmp_path_factory.mktemp("launch_shape")
+    (at / "s.cpp").write_text(SOURCE)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(at / "s.cpp"), "-o", str(at / "s.so")], check=True)
+    fn = C.CDLL(str(at / "s.so")).share_out
+
+    def call(tiles, budget, most=64):
+        out, grid = (Share * (most + 1))(), C.c_int()
+        out[most].segment = -77
+        n = fn((C.c_longlong * len(tiles))(*tiles), len(tiles), C.c_longlong(budget), out, most, C.byref(grid))
+        assert out[most].segment == -77 and n <= most
+        return list(out[:n]), grid.value
+    return call
+
+
+def _check(shares, grid, tiles):
+    """Every tile of every segment once, every workgroup with a tile, places in order."""
+    place, done = 0, [0] * len(tiles)
+    for s in shares:
+        assert s.first_block == place and 1 <= s.blocks <= s.tiles and s.tile == done[s.segment]
+        place += s.blocks
+        done[s.segment] += s.tiles
+    assert place == grid and done == list(tiles)
+    assert [s.segment for s in shares] == sorted(s.segment for s in shares)
+
+
+def _tiles_per_die(shares, grid):
+    load, q, r = [], grid // 8, grid % 8
+    walked = [s.tiles // s.blocks + (k < s.tiles % s.blocks) for s in shares for k in range(s.blocks)]
+    for die in range(8):
+        first = die * q + min(die, r)
+        load.append(sum(walked[first:first + q + (die < r)]))
+    return load
+
+
+@pytest.mark.parametrize("plans", [1, 2, 4])
+@pytest.mark.parametrize("budget", [512, 1024, 1280])
+@pytest.mark.parametrize("ratio", [1.02, 1.36, 1.5, 1.99, 2.3, 3.7])
+def test_few_plans_load_the_dies_alike(share_out, plans, budget, ratio):
+    tiles = [int(budget * ratio / plans)] * plans
+    shares, grid = share_out(tiles, budget)
+    _check(shares, grid, tiles)
+    load = _tiles_per_die(shares, grid)
+    assert max(load) - min(load) <= 2, load              # (uncut: 256 against 128 at 2 plans x 698 tiles on 1024 workgroups)
+
+
+def test_shares_of_random_launches(share_out):
+    rng = random.Random(5)
+    for _ in range(3000):
+        count = rng.choice([1, 2, 3, 4, 5, 9, 33, 57, 58, 63, 64])
+        tiles = [rng.choice([1, 2, rng.randint(1, 40), rng.randint(1, 3000)]) for _ in range(count)]
+        budget = rng.choice([1, 3, 7, 8, 9, 20, 512, 1023, 1024, 10 ** 9])
+        shares, grid = share_out(tiles, budget)
+        _check(shares, grid, tiles)
+        assert len(shares) <= count + 7
+        assert grid <= max(budget, count) + count
+
+
+def test_the_largest_launch_and_a_full_table(share_out):
+    tiles = [2 ** 28] * 64                               # 2^33 vectors each
+    shares, grid = share_out(tiles, 1024)
+    _check(shares, grid, tiles)
+    assert len(shares) == 64
+    tiles = [1] * 62 + [700] * 2                         # the cuts would not fit the table: none is made
+    shares, grid = share_out(tiles, 1024)
+    _check(shares, grid, tiles)
+    assert len(shares) == 64
