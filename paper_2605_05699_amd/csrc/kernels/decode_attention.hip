@@ -83,7 +83,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     constexpr int VTILE = KEYS * VROW + 4 * 8;               // and 8 bytes more per quarter's rows keep the quarters apart
     constexpr int NV = KEYS * G / 64;                        // 16-byte pieces of a V tile per lane
     constexpr int NB = D / 16;                               // blocks of 16 channels
-    constexpr int WAVE_BYTES = VTILE + 2 * G * KEYS * 4;
+    constexpr int WAVE_BYTES = VTILE + (2 * G + 1) * KEYS * 4;
     constexpr int LDS_BYTES = W * WAVE_BYTES;
     static_assert(D % 64 == 0 && VTILE % 16 == 0 && (KEYS == 32 || KEYS == 64), "layout");
     __shared__ __align__(16) unsigned char lds[LDS_BYTES];
@@ -97,6 +97,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     unsigned char* const vt = lds + wave * WAVE_BYTES;       // this wavefront's V tile and scales: no other one touches them
     float* const ks = reinterpret_cast<float*>(vt + VTILE);  // [group][key]
     float* const vs = ks + G * KEYS;
+    float* const vtop = vs + G * KEYS;                       // [key]: largest of V's scales
     const int q0 = 16 * blockIdx.y, nq = min(16, n_q - q0);  // the queries of this workgroup
 
     const long long n_tiles = (n_keys + KEYS - 1) / KEYS;
@@ -162,13 +163,17 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     floatx4 acc[NB];                                         // [block of 16 channels]: channels 16 b + 4 a + i, query l16
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = floatx4{0, 0, 0, 0};
-    float top = kLowest, den = 0.0f;                         // maximum of |softmax_scale| * (signed score), sum of weights
-    // The products weight * scale go to the matrix cores as fp16 hi + lo, and a weight far below the largest must not fall under
-    // fp16's range: V's scales are taken times a power of two (fit) that brings the largest of a tile to 2^13 .. 2^14; it
-    // only ever gets smaller, the sums with it, and is divided out at the end.
-    float fit = 0x1p73f;
+    float top = kLowest, den = 0.0f;                         // maximum of the exponents, sum of weights
+    // The products weight * scale go to the matrix cores as fp16 hi + lo, and neither may leave fp16's range: a query's weights
+    // are taken times 2^fit, which brings the largest product that its sums hold (big, under the present maximum; a key's
+    // largest scale stands for all of them) to 2^13 .. 2^14.  What a product below it loses is then under 2^-37 of the largest,
+    // whatever the scales and weights of other keys, before or after.  The sums carry the same power, divided out at the end.
+    // (A power from the largest scale alone, that only fell, cost up to 1 % less at 400,000 keys and more, and left a key beside
+    // or after one of 2^28 times its scale and no weight with 1e-3 of error.)
+    float big = 0.0f;
+    int fit = 113;
     // weights are 2^(c * score - top)
-    const float c = softmax_scale * 1.44269504088896340736f, sign = c < 0.0f ? -1.0f : 1.0f, c_abs = fabsf(c);
+    const float c = softmax_scale * 1.44269504088896340736f;
 
     // The LDS operands of a step are read one step ahead of their use.
     struct KStep { uint4 h, l; float4 sc[BK]; };
@@ -191,19 +196,16 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     };
     for (long long tile = first; tile < n_tiles; tile += stride) {
         const bool more = tile + stride < n_tiles;
-        float most = 0.0f;
-#pragma unroll
-        for (int j = 0; j < G; ++j) most = fmaxf(most, fabsf(pvs[j / 4][j % 4]));
-        const uint32_t exponent = __float_as_uint(wave_max(most)) & 0x7F800000u;
-        const float fit_here = __uint_as_float((267u << 23) - max(exponent, 67u << 23));      // 2^(13 - exponent), at most 2^73
-        const float fit_down = fminf(fit_here, fit) / fit;   // a power of two, 1 as long as the scales do not grow
-        fit = fminf(fit_here, fit);
         // LDS of one wavefront: its accesses complete in program order
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             ks[j * KEYS + (lane & (KEYS - 1))] = pks[j / 4][j % 4];
-            vs[j * KEYS + (lane & (KEYS - 1))] = pvs[j / 4][j % 4] * fit;
+            vs[j * KEYS + (lane & (KEYS - 1))] = pvs[j / 4][j % 4];
         }
+        float most = fabsf(pvs[0][0]);
+#pragma unroll
+        for (int j = 1; j < G; ++j) most = fmaxf(most, fabsf(pvs[j / 4][j % 4]));
+        vtop[lane & (KEYS - 1)] = most;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int u = lane + 64 * i;
@@ -249,20 +251,13 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
         load_v(vc, 0);
         // ---- running softmax, per query (column)
         {
-            float m = sign * w[0][0];
+            float m = w[0][0];
 #pragma unroll
-            for (int v = 1; v < KQ; ++v) m = fmaxf(m, sign * w[v / 4][v % 4]);
-            m = fmaxf(quarters_max(m) * c_abs, kLowest);
-            if (__ballot(m > top)) {                         // uniform
-                const float t = fmaxf(m, top), down = __builtin_amdgcn_exp2f(top - t);
-                top = t;
-                den *= down;
-#pragma unroll
-                for (int b = 0; b < NB; ++b) acc[b] *= down;
-            }
-            if (fit_down != 1.0f)                            // uniform
-#pragma unroll
-                for (int b = 0; b < NB; ++b) acc[b] *= fit_down;
+            for (int v = 1; v < KQ; ++v) m = fmaxf(m, w[v / 4][v % 4]);
+            m = fmaxf(quarters_max(m) * c, kLowest);
+            const float t = fmaxf(m, top), down = __builtin_amdgcn_exp2f(top - t);
+            top = t;
+            den *= down;
 #pragma unroll
             for (int v = 0; v < KQ; ++v) w[v / 4][v % 4] = __builtin_amdgcn_exp2f(fmaf(c, w[v / 4][v % 4], -top));
             if (tile == n_tiles - 1) {                       // uniform: keys past the end weigh nothing
@@ -273,6 +268,21 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             }
 #pragma unroll
             for (int v = 0; v < KQ; ++v) den += w[v / 4][v % 4];
+            float product = 0.0f;
+#pragma unroll
+            for (int b = 0; b < BK; ++b) {
+                const float4 f = *reinterpret_cast<const float4*>(&vtop[KQ * a + 4 * b]);
+                product = fmaxf(product, fmaxf(fmaxf(w[b][0] * f.x, w[b][1] * f.y), fmaxf(w[b][2] * f.z, w[b][3] * f.w)));
+            }
+            big = fmaxf(big * down, quarters_max(product));
+            const int fit_now = 140 - max((int)((__float_as_uint(big) >> 23) & 0xFF), 27);    // 13 - exponent, at most 113
+            const float change = __builtin_ldexpf(down, fit_now - fit);
+            fit = fit_now;
+            if (__ballot(change != 1.0f))                    // uniform
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b] *= change;
+#pragma unroll
+            for (int v = 0; v < KQ; ++v) w[v / 4][v % 4] = __builtin_ldexpf(w[v / 4][v % 4], fit);
         }
         // ---- sums of the values: channels on the rows, queries on the columns; k-step s takes the keys 8 s .. 8 s + 7 of
         // every quarter, in the order 0 4 1 5 2 6 3 7 of decode8
@@ -322,7 +332,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     __syncthreads();
     float t = meet[0][0][l16];
     for (int k = 1; k < active; ++k) t = fmaxf(t, meet[0][k][l16]);
-    const float f = __builtin_amdgcn_exp2f(top - t);
+    const float f = __builtin_ldexpf(__builtin_amdgcn_exp2f(top - t), -fit);
     if (tid < nq) {
         float s = 0.0f;
         for (int k = 0; k < active; ++k) s = fmaf(meet[1][k][l16], __builtin_amdgcn_exp2f(meet[0][k][l16] - t), s);
@@ -343,7 +353,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 if (b >= b0 && b < b1)                       // uniform
-                    *reinterpret_cast<floatx4*>(&merge[(wave * nq + l16) * mrow + 16 * (b - b0) + 4 * a]) = acc[b] * (f / fit);
+                    *reinterpret_cast<floatx4*>(&merge[(wave * nq + l16) * mrow + 16 * (b - b0) + 4 * a]) = acc[b] * f;
         __syncthreads();
         const int per = 4 * (b1 - b0);                       // 16-byte pieces per query
         for (int e = tid; e < nq * per; e += 64 * W) {
@@ -479,11 +489,12 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     float* part_sum = part_max + kScanGridMax * 32;
     float* part = part_sum + kScanGridMax * 32;              // [workgroup][n_q][D]
     const bool wide = pk->gw > 1 || pv->gw > 1;
+    const float sign = softmax_scale < 0.0f ? -1.0f : 1.0f;  // goes into the queries: the kernel's scale is not negative
     auto kernel = narrow ? (wide ? srft_attention_scan_kernel<D, 32, true> : srft_attention_scan_kernel<D, 32, false>)
                          : (wide ? srft_attention_scan_kernel<D, 64, true> : srft_attention_scan_kernel<D, 64, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid, blocks), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q,
-                       (const uint4*)pk->wfrag, (const float*)pk->inv_lam2, pk->unscale_w, k_codes, k_scales, pk->gw, v_codes,
-                       v_scales, pv->gw, n_keys, softmax_scale, part, part_max, part_sum);
+                       (const uint4*)pk->wfrag, (const float*)pk->inv_lam2, sign * pk->unscale_w, k_codes, k_scales, pk->gw, v_codes,
+                       v_scales, pv->gw, n_keys, sign * softmax_scale, part, part_max, part_sum);
     SRFT_HIP(hipGetLastError());
     hipLaunchKernelGGL(srft_attention_finish_kernel<D>, dim3((unsigned)n_q, D / 64), dim3(1024), 0, st, (const float*)part,
                        (const float*)part_max, (const float*)part_sum, (int)grid, n_q, (const float4*)pv->rmat_f32, out);

@@ -229,3 +229,49 @@ def test_decode_attention_keeps_weights_far_below_the_largest(B):
     assert 0.003 < np.abs(ref).max() < 0.1
     pk.close()
     pv.close()
+
+
+def _decode_attention(B, pk, pv, q, kc, ks, vc, vs, scale):
+    ws = torch.full((B.lib().srft_decode_attention_workspace_bytes(pk.handle, pv.handle, q.shape[0], kc.shape[0]),), 0xFF,
+                    dtype=torch.uint8, device="cuda")                # (NaN as floats: nothing is read that was not written)
+    out = torch.full((q.shape[0], pk.d), float("nan"), dtype=torch.float32, device="cuda")
+    B.srft_kv_decode_attention(pk.handle, pv.handle, q, kc, ks, vc, vs, scale, out, ws)
+    torch.cuda.synchronize()
+    return out
+
+
+# where the large scales are (keys of no weight), the power of two of the others
+SPANS = {"before": (lambda t, n: t < n // 4, 0), "beside": (lambda t, n: t % 2 == 1, 0), "after": (lambda t, n: t >= n - n // 4, 0),
+         "none, tiny scales": (lambda t, n: t < 0, -80), "none, large scales": (lambda t, n: t < 0, 40)}
+
+
+@pytest.mark.parametrize("where", SPANS)
+@pytest.mark.parametrize("d,n_q,n_keys,cap", [(64, 3, 4096, 1), (128, 8, 4096, 2), (256, 4, 4096, 2), (128, 5, 500, 2), (192, 17, 2048, 1)])
+def test_decode_attention_of_values_whose_scales_span_many_powers(B, d, n_q, n_keys, cap, where):
+    """Keys of no weight (e^-40 and less) with values 2^28 times the others', before, beside and after those that weigh: what
+    the others carry must keep its 20 bits.  Tiles of 64 and of 32 keys, several tiles per wavefront."""
+    rng = np.random.RandomState(d + n_keys)
+    direction = rng.standard_normal(d)
+    q = (np.outer(1.0 + 0.1 * np.arange(n_q), direction)).astype(np.float16)
+    large, power = SPANS[where]
+    loud = torch.from_numpy(large(np.arange(n_keys), n_keys)).cuda()
+    # all keys that weigh are the same key: their scores are equal to the last bit, 40 above those of the others
+    k = torch.from_numpy(np.tile(direction * 40.0 / (direction @ direction) / 0.125, (n_keys, 1)).astype(np.float16)).cuda()
+    v = torch.from_numpy(W.gaussian_with_outliers(n_keys, d, seed=d, outliers=0)).cuda()
+    pk, pv = B.Plan(d, 32, 41), B.Plan(d, 32, 42)
+    kc, ks = pk.quantize(k)
+    vc, vs = pv.quantize(v)
+    ks[loud] = 0.0
+    vs *= 2.0 ** power
+    vs[loud] *= 2.0 ** 28
+    B.srft_plan_set_max_workgroups(pv.handle, cap)
+    got = _decode_attention(B, pk, pv, torch.from_numpy(q).cuda(), kc, ks, vc, vs, 0.125).double().cpu().numpy()
+    ones = np.ones(d, dtype=np.float32)
+    kc, ks, vc, vs = (t.cpu().numpy() for t in (kc, ks, vc, vs))
+    weights = O.softmax_rows(O.attention_scores(q, kc, ks, pk.signs, ones, 32), 0.125)
+    vb = O.dequantize_f64(vc, vs, pv.signs, ones, 32)
+    tol = 6e-6 * (weights @ np.abs(vb)).max(axis=1, keepdims=True)       # of the weighted sums, see _tolerance
+    err = np.abs(got - weights @ vb)
+    assert np.all(err <= tol), float((err / tol).max())
+    pk.close()
+    pv.close()
