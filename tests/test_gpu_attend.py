@@ -275,3 +275,88 @@ def test_decode_attention_of_values_whose_scales_span_many_powers(B, d, n_q, n_k
     assert np.all(err <= tol), float((err / tol).max())
     pk.close()
     pv.close()
+
+
+# shapes at the edges of the decode attention's tiles (32 and 64 keys), of a wavefront's share and of its grid: d, g, n_q, n_keys, cap
+EDGES = [(128, 32, 1, 1, 0), (128, 32, 16, 31, 0), (64, 32, 17, 33, 0), (256, 32, 32, 768, 3), (256, 32, 5, 769, 3), (192, 32, 16, 1537, 3),
+         (128, 64, 9, 1601, 3), (64, 64, 8, 5000, 1), (256, 256, 4, 1000, 0), (192, 96, 3, 200, 2), (128, 32, 3, 16500, 300)]
+
+
+def _plans_and_record(B, d, g, k, v, cap):
+    lam_k, lam_v = W.lognormal_lambda(d, seed=1), W.lognormal_lambda(d, seed=2)
+    pk, pv = B.Plan(d, g, 51, lam_k), B.Plan(d, g, 52, lam_v)
+    record = (*pk.quantize(torch.from_numpy(k).cuda()), *pv.quantize(torch.from_numpy(v).cuda()))
+    B.srft_plan_set_max_workgroups(pv.handle, cap)
+    host = [t.cpu().numpy() for t in record]
+    return pk, pv, record, O.dequantize_f64(*host[:2], pk.signs, lam_k, g), O.dequantize_f64(*host[2:], pv.signs, lam_v, g)
+
+
+@pytest.mark.parametrize("d,g,n_q,n_keys,cap", EDGES)
+def test_decode_attention_with_equal_weights_counts_every_key_once(B, d, g, n_q, n_keys, cap):
+    """softmax_scale 0: the mean of the values, to the error of the weighted sum alone.  The last key and the first of the
+    last tile are 100 times the others: one that is lost, or taken twice, shows at any length."""
+    k = W.gaussian_with_outliers(n_keys, d, seed=d + n_keys, outliers=1, gain=15.0)
+    v = W.gaussian_with_outliers(n_keys, d, seed=d + n_keys + 1, outliers=0)
+    for t in {n_keys - 1, (n_keys - 1) // 32 * 32, (n_keys - 1) // 64 * 64}:
+        v[t] *= 100.0
+    q = W.gaussian_with_outliers(n_q, d, seed=d + n_keys + 2, outliers=1, gain=4.0)
+    pk, pv, record, _, vb = _plans_and_record(B, d, g, k, v, cap)
+    got = _decode_attention(B, pk, pv, torch.from_numpy(q).cuda(), *record, 0.0).double().cpu().numpy()
+    tol = 6e-6 * np.abs(vb).mean(axis=0).max()               # of the weighted sums, see _tolerance
+    assert np.abs(got - vb.mean(axis=0)).max() <= tol, float(np.abs(got - vb.mean(axis=0)).max() / tol)
+    assert tol < 0.01 * np.abs(vb[-1]).max() / n_keys        # one key of the large ones is far above it
+    pk.close()
+    pv.close()
+
+
+@pytest.mark.parametrize("d,g,n_q,n_keys,cap", [e for e in EDGES if e[3] > 500])
+def test_decode_attention_where_the_maximum_keeps_growing(B, d, g, n_q, n_keys, cap):
+    """Scores that rise by 1/2 from one stretch of keys to the next (and fall, in the second half of the queries), magnitudes of
+    the values that go up and down by 2^10: every tile brings a new maximum, and what was summed before still counts."""
+    direction = np.random.RandomState(d).standard_normal(d)
+    level = 8.0 * np.arange(n_keys) // n_keys                # 0 .. 7
+    k = (np.outer(0.5 * level, direction) / (direction @ direction)).astype(np.float16)
+    v = (W.gaussian_with_outliers(n_keys, d, seed=d + n_keys, outliers=0).astype(np.float32) * 2.0 ** (5 * (level % 3))[:, None]).astype(np.float16)
+    q = np.outer(np.where(2 * np.arange(n_q) >= n_q, -1.0, 1.0), direction).astype(np.float16)
+    pk, pv, record, kb, vb = _plans_and_record(B, d, g, k, v, cap)
+    got = _decode_attention(B, pk, pv, torch.from_numpy(q).cuda(), *record, 1.0).double().cpu().numpy()
+    scores = q.astype(np.float64) @ kb.T
+    weights = O.softmax_rows(scores, 1.0)
+    # scores of up to 4 are off by 4e-6 |q| |k| (test_gpu_scores.py), per row; the weighted sums as in _tolerance
+    ds = 4e-6 * np.linalg.norm(q.astype(np.float64), axis=1) * np.linalg.norm(kb, axis=1).max()
+    tol = (2 * ds + 6e-6)[:, None] * (weights @ np.abs(vb)).max(axis=1, keepdims=True)
+    err = np.abs(got - weights @ vb)
+    assert np.all(err <= tol), float((err / tol).max())
+    pk.close()
+    pv.close()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_what_is_not_finite_stays_with_its_query_or_its_key(B, bad):
+    d, n_q, n_keys = 128, 20, 700
+    k, v = (W.gaussian_with_outliers(n_keys, d, seed=s, outliers=0) for s in (1, 2))
+    q = torch.from_numpy(W.gaussian_with_outliers(n_q, d, seed=3, outliers=0)).cuda()
+    pk, pv, (kc, ks, vc, vs), _, _ = _plans_and_record(B, d, 32, k, v, 0)
+    ws = torch.empty(B.lib().srft_scores_workspace_bytes(pk.handle), dtype=torch.uint8, device="cuda")
+
+    def both(q, ks, vs):
+        scores = torch.empty(n_q, n_keys, device="cuda")
+        B.srft_kv_scores(pk.handle, q, kc, ks, scores, ws)
+        return scores, _decode_attention(B, pk, pv, q, kc, ks, vc, vs, 0.09)
+
+    scores, out = both(q, ks, vs)
+    assert bool(torch.isfinite(scores).all()) and bool(torch.isfinite(out).all())
+    qb, ksb, vsb = q.clone(), ks.clone(), vs.clone()
+    qb[17, 5] = bad
+    ksb[300, 2] = bad
+    vsb[600, 1] = bad
+    rest = torch.arange(n_q, device="cuda") != 17
+    for got, good in zip(both(qb, ks, vs), (scores, out)):   # a query: its row and no other
+        assert torch.equal(got[rest], good[rest]) and not bool(torch.isfinite(got[17]).any())
+    got, attended = both(q, ksb, vs)                         # a key's scale: its score, and every softmax over it
+    others = torch.arange(n_keys, device="cuda") != 300
+    assert torch.equal(got[:, others], scores[:, others]) and not bool(torch.isfinite(got[:, 300]).any())
+    assert not bool(torch.isfinite(attended[got[:, 300] != -bad]).any())
+    assert not bool(torch.isfinite(both(q, ks, vsb)[1]).any())           # a value's scale: every sum over it
+    pk.close()
+    pv.close()
