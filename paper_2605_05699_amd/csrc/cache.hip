@@ -4,6 +4,7 @@
 #include <new>
 
 #include "common.h"
+#include "launch_shape.h"
 
 namespace {
 
@@ -106,10 +107,10 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
     hipStream_t st = (hipStream_t)hip_stream;
     const int units = cache->plans[0]->d / 8;
     // 1. the new tokens join the window: an exact fp16 copy into the view
-    constexpr int kMaxScatterTokens = 1 << 24;               // a launch's units are counted with 32 bits
-    for (int t0 = 0; t0 < t; t0 += kMaxScatterTokens)
+    for (int part = 0; part < srft_copy_launches(t); ++part)
         for (size_t p0 = 0; p0 < np; p0 += kMaxBatch) {
-            const unsigned n = (unsigned)std::min(kMaxScatterTokens, t - t0);
+            const int64_t t0 = srft_copy_first(part);
+            const unsigned n = srft_copy_tokens(part, t);
             const int plans = (int)std::min<size_t>(kMaxBatch, np - p0);
             scatter_args a;
             for (int k = 0; k < plans; ++k) {

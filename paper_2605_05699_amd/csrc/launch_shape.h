@@ -1,4 +1,4 @@
-// launch_shape.h -- how a batched launch shares its workgroups out; plain C++ for the host, no HIP.
+// launch_shape.h -- how launches are laid out; plain C++ for the host, no HIP.
 #ifndef SRFT_LAUNCH_SHAPE_H
 #define SRFT_LAUNCH_SHAPE_H
 #include <algorithm>
@@ -56,5 +56,12 @@ inline int srft_share_out(const long long* tiles, int count, long long budget, s
     }
     return count + cuts;
 }
+
+// The cache's copy of t new tokens: launch i of srft_copy_launches(t) copies srft_copy_tokens(i, t) tokens from
+// srft_copy_first(i) on.  A launch counts its 16-byte units with 32 bits; t may be anything an int holds.
+constexpr long long kCopyTokens = 1 << 24;
+constexpr int srft_copy_launches(int t) { return (int)((t + kCopyTokens - 1) / kCopyTokens); }
+constexpr long long srft_copy_first(int i) { return i * kCopyTokens; }
+constexpr unsigned srft_copy_tokens(int i, int t) { return (unsigned)std::min(kCopyTokens, t - srft_copy_first(i)); }
 
 #endif  // SRFT_LAUNCH_SHAPE_H

@@ -13,6 +13,9 @@ SOURCE = """
 extern "C" int share_out(const long long* tiles, int count, long long budget, srft_share* out, int most, int* grid) {
     return srft_share_out(tiles, count, budget, out, most, grid);
 }
+extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
+extern "C" long long copy_first(int i) { return srft_copy_first(i); }
+extern "C" unsigned copy_tokens(int i, int t) { return srft_copy_tokens(i, t); }
 """
 
 
@@ -21,19 +24,22 @@ class Share(C.Structure):
 
 
 @pytest.fixture(scope="module")
-def share_out(tmp_path_factory):
+def lib(tmp_path_factory):
     gxx = shutil.which("g++")
     if not gxx:
         pytest.skip("no g++")
     at = tmp_path_factory.mktemp("launch_shape")
     (at / "s.cpp").write_text(SOURCE)
     subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(at / "s.cpp"), "-o", str(at / "s.so")], check=True)
-    fn = C.CDLL(str(at / "s.so")).share_out
+    return C.CDLL(str(at / "s.so"))
 
+
+@pytest.fixture(scope="module")
+def share_out(lib):
     def call(tiles, budget, most=64):
         out, grid = (Share * (most + 1))(), C.c_int()
         out[most].segment = -77
-        n = fn((C.c_longlong * len(tiles))(*tiles), len(tiles), C.c_longlong(budget), out, most, C.byref(grid))
+        n = lib.share_out((C.c_longlong * len(tiles))(*tiles), len(tiles), C.c_longlong(budget), out, most, C.byref(grid))
         assert out[most].segment == -77 and n <= most
         return list(out[:n]), grid.value
     return call
@@ -91,3 +97,13 @@ def test_the_largest_launch_and_a_full_table(share_out):
     shares, grid = share_out(tiles, 1024)
     _check(shares, grid, tiles)
     assert len(shares) == 64
+
+
+@pytest.mark.parametrize("t", [1, 2 ** 24 - 1, 2 ** 24, 2 ** 24 + 1, 3 * 2 ** 24, 127 * 2 ** 24, 127 * 2 ** 24 + 1, 2 ** 31 - 1])
+def test_the_copy_of_new_tokens_takes_every_one_of_them_once(lib, t):
+    lib.copy_first.restype, lib.copy_tokens.restype = C.c_longlong, C.c_uint
+    done = 0
+    for i in range(lib.copy_launches(t)):
+        assert lib.copy_first(i) == done and 0 < lib.copy_tokens(i, t) <= 2 ** 24
+        done += lib.copy_tokens(i, t)
+    assert done == t                                     # (a 32-bit count of tokens never got past 127 x 2^24)
