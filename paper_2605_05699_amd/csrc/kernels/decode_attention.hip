@@ -21,6 +21,8 @@
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
 // d = 128, 8 queries, 131,072 keys 36.6 -> 15.6, 400,000 keys 51 -> 26; 32 queries, 400,000 keys 111 -> 39; d = 256, 4 queries,
 // 4096 keys 27.7 -> 15.6; d = 64, 1 query, 500 keys 21.9 -> 11.2.  Error against 64 bits 6e-6 -> 4e-7.
+#include <algorithm>
+
 #include "../rotated_queries.h"
 
 namespace {
@@ -478,9 +480,10 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     // half as long.  Workgroups: one per tile, up to one per compute unit (its eight wavefronts fill the register file); with
     // two blocks of queries half of that each, so that both read a tile at about the same time.
     const int blocks = n_q <= 16 ? 1 : 2;
-    long long grid = pv->compute_units / blocks;
-    if (pk->max_wgs > 0) grid = pk->max_wgs;
-    if (pv->max_wgs > 0 && (pk->max_wgs == 0 || pv->max_wgs < grid)) grid = pv->max_wgs;
+    long long most = pv->compute_units;
+    if (pk->max_wgs > 0) most = pk->max_wgs;
+    if (pv->max_wgs > 0 && (pk->max_wgs == 0 || pv->max_wgs < most)) most = pv->max_wgs;
+    long long grid = std::max(most / blocks, 1LL);           // (a cap is on all of them; one for each block of queries is the least)
     if (grid > kScanGridMax) grid = kScanGridMax;
     const bool narrow = n_keys <= 32 * kWaves * grid;
     const long long n_tiles = narrow ? (n_keys + 31) / 32 : (n_keys + 63) / 64;

@@ -360,3 +360,23 @@ def test_what_is_not_finite_stays_with_its_query_or_its_key(B, bad):
     assert not bool(torch.isfinite(both(q, ks, vsb)[1]).any())           # a value's scale: every sum over it
     pk.close()
     pv.close()
+
+
+@pytest.mark.parametrize("n_q,cap", [(16, 6), (17, 6), (32, 7), (32, 1)])
+def test_decode_attention_keeps_to_the_cap_on_workgroups(B, n_q, cap):
+    """The scan leaves a maximum per query and workgroup, 1024 floats apart per query, at the start of the workspace; every
+    16 queries have workgroups of their own."""
+    d, n_keys = 128, 6000
+    k, v, q = (W.gaussian_with_outliers(n, d, seed=n + s, outliers=0) for n, s in ((n_keys, 1), (n_keys, 2), (n_q, 3)))
+    pk, pv, (kc, ks, vc, vs), kb, vb = _plans_and_record(B, d, 32, k, v, cap)
+    ws = torch.full((B.lib().srft_decode_attention_workspace_bytes(pk.handle, pv.handle, n_q, n_keys),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = torch.empty(n_q, d, device="cuda")
+    B.srft_kv_decode_attention(pk.handle, pv.handle, torch.from_numpy(q).cuda(), kc, ks, vc, vs, 0.09, out, ws)
+    torch.cuda.synchronize()
+    written = ~torch.isnan(ws[:32 * 1024 * 4].view(torch.float32).view(32, 1024))
+    workgroups = sum(int(written[i].sum()) for i in range(0, n_q, 16))
+    assert 1 <= workgroups <= max(cap, (n_q + 15) // 16)
+    ref = O.softmax_rows(q.astype(np.float64) @ kb.T, 0.09) @ vb
+    assert np.abs(out.cpu().numpy() - ref).max() <= 1e-4 * np.abs(vb).max()
+    pk.close()
+    pv.close()
