@@ -7,7 +7,7 @@
 // One launch.  Every workgroup forms q' (rotated_queries.h); a wavefront walks over tiles of 64 or 32 keys.  Keys are the rows and
 // queries the columns of v_mfma_f32_16x16x32_f16: the codes of a key go from global memory into the A operand with a
 // transpose over the wavefront's quarters and never through LDS, and a lane ends up with 4 consecutive keys of ITS query per block
-// of 16 -- one 16-byte store, 64 bytes next to each other per query.  With more than 16 queries both blocks of 16 take the same
+// of 16 -- one 16-byte store, 64 bytes next to each other per query (with more than 8 queries whole lines, by way of LDS).  With more than 16 queries both blocks of 16 take the same
 // decoded keys.  At many keys it is bound by memory, at few by the chain of one launch.  Measured, us, against a launch for q'
 // and a scan by one-wavefront workgroups that decoded the codes into LDS (and wrote a query's keys with 4-byte stores):
 // d = 128, 8 queries: 20,000 keys 13.1 -> 7.9, 1,000,000 keys 30.0 -> 21.6 (112 MB: 5.2 TB/s); 32 queries, 300,000 keys
@@ -21,8 +21,12 @@ constexpr int kWaves = 8;                        // wavefronts per workgroup
 template <int D, int RB> constexpr int kTileKeys = D * RB > 256 || D == 256 ? 32 : 64;
 
 // D: head dimension.  RB: blocks of 16 queries.  WIDE: groups of gw > 1 runs of 32 channels share a scale.
+// STAGE: scores go out by way of LDS (more than 8 queries).  Many queries are mostly stores, and one from the registers writes
+// 64 bytes each of 16 queries; from LDS it writes whole lines of a few.  us, d = 64, 32 queries, 2,000,000 keys 86 -> 74,
+// 16 queries, 1,000,000 keys 27.0 -> 21.5; d = 128, 32 queries 49 -> 45.  With half-empty blocks it is slower at 300,000 keys
+// (8 queries, d = 64 7.4 -> 7.6) and with one query everywhere (1,000,000 keys 10.4 -> 11.0).
 // codes [n_keys][D / 2] bytes, scales [n_keys][D / 32 / gw], out [n_q][n_keys]
-template <int D, int RB, bool WIDE>
+template <int D, int RB, bool WIDE, bool STAGE>
 __global__ void __launch_bounds__(64 * kWaves, 2)
 srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ wfrag, const float* __restrict__ q_scale,
                    float unscale, const uint8_t* __restrict__ codes, const float* __restrict__ scales, int gw,
@@ -32,6 +36,8 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
     constexpr int SCRATCH = srft_query_scratch_bytes<D, W, RB>(), TILES = W * G * KEYS * 4;
     __shared__ __align__(16) unsigned char lds[SCRATCH > TILES ? SCRATCH : TILES];
     __shared__ uint4 qs[RB * G * 2 * 64];
+    constexpr int SROW = KEYS + 4;                           // padded
+    __shared__ __align__(16) float staged[STAGE ? W * 16 * SROW : 4];        // [wavefront][query of a block][key]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, a = lane >> 4;                // query (or key of a block of 16), quarter
     float* const ks = reinterpret_cast<float*>(lds) + wave * G * KEYS;      // this wavefront's scales, [group][key]
@@ -128,7 +134,20 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
         for (int rb = 0; rb < RB; ++rb) {
             const int query = 16 * rb + l16;
             float* const row = out + (long long)min(query, n_q - 1) * n_keys + t0 + 4 * a;
-            if (query < n_q) {
+            if (STAGE && t0 + KEYS <= n_keys) {              // uniform
+                float* const st = staged + wave * 16 * SROW;
+#pragma unroll
+                for (int b = 0; b < BK; ++b) *reinterpret_cast<floatx4*>(&st[l16 * SROW + 16 * b + 4 * a]) = w[rb][b];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                constexpr int L = KEYS / 4, R = 64 / L;      // lanes per query, queries per store
+#pragma unroll
+                for (int i = 0; i < 16; i += R) {
+                    const int mine = i + lane / L, c = 4 * (lane % L);
+                    const floatx4 v = *reinterpret_cast<const floatx4*>(&st[mine * SROW + c]);
+                    if (16 * rb + mine < n_q) *reinterpret_cast<floatx4u*>(out + (16 * rb + mine) * n_keys + t0 + c) = v;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            } else if (query < n_q) {
                 if (t0 + KEYS <= n_keys) {                  // uniform
 #pragma unroll
                     for (int b = 0; b < BK; ++b) *reinterpret_cast<floatx4u*>(row + 16 * b) = w[rb][b];
@@ -147,15 +166,17 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
 template <int D>
 int launch(const srft_plan* p, const void* q, int n_q, const uint8_t* codes, const float* scales, long long n_keys, float* out,
            hipStream_t st) {
-    // a workgroup per tile, up to one per compute unit, two at d = 64 (what the registers hold at once; at d = 128 a second
-    // workgroup that waits for the first only adds its own start: 1,000,000 keys, 8 queries 21.5 us against 25.5)
+    // a workgroup per tile, up to one per compute unit, two at d = 64 with up to 16 queries (what the registers hold at once; at
+    // d = 128 a second workgroup that waits for the first only adds its own start: 1,000,000 keys, 8 queries 21.5 us against
+    // 25.5; d = 64, 32 queries, 300,000 keys 11 against 14)
     const int keys = n_q <= 16 ? kTileKeys<D, 1> : kTileKeys<D, 2>;
     const long long n_tiles = (n_keys + keys - 1) / keys;
-    long long grid = p->max_wgs > 0 ? p->max_wgs : (D == 64 ? 2 : 1) * p->compute_units;
+    long long grid = p->max_wgs > 0 ? p->max_wgs : (D == 64 && n_q <= 16 ? 2 : 1) * p->compute_units;
     if (grid > n_tiles) grid = n_tiles;
     const bool wide = p->gw > 1;
-    auto kernel = n_q <= 16 ? (wide ? srft_scores_kernel<D, 1, true> : srft_scores_kernel<D, 1, false>)
-                            : (wide ? srft_scores_kernel<D, 2, true> : srft_scores_kernel<D, 2, false>);
+    auto kernel = n_q <= 8    ? (wide ? srft_scores_kernel<D, 1, true, false> : srft_scores_kernel<D, 1, false, false>)
+                  : n_q <= 16 ? (wide ? srft_scores_kernel<D, 1, true, true> : srft_scores_kernel<D, 1, false, true>)
+                              : (wide ? srft_scores_kernel<D, 2, true, true> : srft_scores_kernel<D, 2, false, true>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q, (const uint4*)p->wfrag,
                        (const float*)p->inv_lam2, p->unscale_w, codes, scales, p->gw, n_keys, out);
     SRFT_HIP(hipGetLastError());

@@ -116,7 +116,8 @@ def test_scores_argument_errors(B):
 
 
 @pytest.mark.parametrize("d,g,n_q,cap", [(64, 32, 16, 2), (64, 64, 17, 1), (128, 32, 17, 2), (128, 128, 3, 1), (192, 32, 32, 1),
-                                         (192, 96, 16, 2), (256, 32, 8, 1), (256, 64, 32, 2)])
+                                         (192, 96, 16, 2), (256, 32, 8, 1), (256, 64, 32, 2),
+                                         (64, 32, 9, 1), (128, 32, 13, 2), (192, 32, 9, 1), (256, 256, 10, 2), (64, 32, 29, 2)])
 def test_scores_at_the_edges_of_tiles_and_of_a_wavefronts_share(B, d, g, n_q, cap):
     """Key counts around one tile and around one, two and three rounds of a capped grid; rows of scores at every alignment
     (odd counts), nothing written past the last one."""
