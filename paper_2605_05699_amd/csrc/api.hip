@@ -272,7 +272,8 @@ int64_t srft_decode_attention_workspace_bytes(const srft_plan_t* plan_k, const s
                                               int64_t n_keys) {
     if (!plan_k || !plan_v) return SRFT_ERR_NULL;
     if (n_q < 1 || n_q > 32 || n_keys < 1 || n_keys > kMaxVectors) return SRFT_ERR_BAD_N;
-    // (more than the one-pass kernels use: callers keep a workspace of this size for all their calls)
+    // (More than the one-pass kernels use, which is checked against the last term where they are launched.  The size stays what
+    // it was: programs take it as large as their longest context once and keep it for all their calls.)
     const int64_t scores = ((int64_t)n_q * n_keys * 4 + 255) / 256 * 256;
     return scores + 8192 + std::max(srft_scores_workspace_bytes(plan_k), srft_attend_workspace_bytes(plan_v));
 }

@@ -191,7 +191,9 @@ int srft_launch_scores(const srft_plan* p, const void* q, int n_q, const uint8_t
 // n_q queries over n_keys values, and the three launches (partial sums per workgroup into `part`, their fixed-order
 // reduction, the inverse transform)
 int srft_attend_stripes(const srft_plan* p, int n_q, long long n_keys);
-size_t srft_attend_workspace_floats(int d);
+// workspace: part [kMaxAttendStripes][32][d], part2 [kAttendFan][32][d] (and room of another 32 floats each, which callers'
+// buffers have always had)
+constexpr size_t srft_attend_workspace_floats(int d) { return (size_t)(kMaxAttendStripes + kAttendFan) * 32 * (d + 1); }
 int srft_launch_attend(const srft_plan* p, const float* w, int n_q, const uint8_t* codes, const float* scales,
                        long long n_keys, float* out, float* part, hipStream_t st);
 

@@ -332,10 +332,6 @@ int srft_attend_stripes(const srft_plan* p, int n_q, long long n_keys) {
     return (int)(s < 1 ? 1 : s);
 }
 
-size_t srft_attend_workspace_floats(int d) {
-    return (size_t)(kMaxAttendStripes + kAttendFan) * 32 * d + (size_t)(kMaxAttendStripes + kAttendFan) * 32;
-}
-
 int srft_launch_attend(const srft_plan* p, const float* w, int n_q, const uint8_t* codes, const float* scales,
                        long long n_keys, float* out, float* part, hipStream_t st) {
     switch (p->d) {

@@ -488,6 +488,7 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     const bool narrow = n_keys <= 32 * kWaves * grid;
     const long long n_tiles = narrow ? (n_keys + 31) / 32 : (n_keys + 63) / 64;
     if (grid > n_tiles) grid = n_tiles;
+    static_assert((size_t)kScanGridMax * 32 * (2 + D) <= srft_attend_workspace_floats(D), "fits what callers are told to bring");
     float* part_max = (float*)workspace;                     // [32][kScanGridMax] each
     float* part_sum = part_max + kScanGridMax * 32;
     float* part = part_sum + kScanGridMax * 32;              // [workgroup][n_q][D]
