@@ -48,8 +48,7 @@ __device__ __forceinline__ void hold_in_registers(half8 (&a)[N][M], half8 (&b)[N
 // one dispatched first ran 25 % ahead of the others and left the unit early, while the kernel waited for the
 // last one.  Every workgroup therefore walks through the four wavefront priorities, one per stage, offset by its
 // place in the dispatch order: over four stages each has held each priority once, and they finish together
-// (end times of the workgroups 440..620 us -> 565..600 us at d = 128, 8 M vectors; launches 1.5-3.5 % shorter, the
-// scores kernel 5-12 %).  Not used where two workgroups per unit take turns on one accumulator set (the folded
+// (end times of the workgroups 440..620 us -> 565..600 us at d = 128, 8 M vectors; launches 1.5-3.5 % shorter).  Not used where two workgroups per unit take turns on one accumulator set (the folded
 // write path at d = 256), which measured 1 % slower with it.
 __device__ __forceinline__ void rotate_priority(int stage) {
     switch (((int)(blockIdx.x * 4 / gridDim.x) + stage) & 3) {
@@ -103,8 +102,10 @@ __device__ __forceinline__ uint32_t pack4_bytes(const floatx16& acc, int base, f
 // table took 50 ns per segment in front of everything else: a read launch of 64 plans x 32 vectors 7.7 -> 5.7 us).
 // Workgroups are dealt to the 8 accelerator dies round robin, each die with an L2 of its own; here a die takes a
 // contiguous eighth of the list, so that the workgroups of one plan share one copy of its matrix table instead of pulling
-// it into every L2.  Measured against workgroup b = place b: 64 plans x 512 vectors at d = 96, write 6.7 -> 5.6 us;
-// 52 x 4096 at d = 256, read 40.6 -> 37.0 us; 56 x 8192 at d = 128, write 38.3 -> 37.1 us; 4 x 1,048,576 within 0.5 %.
+// it into every L2.  Measured against workgroup b = place b: 64 plans x 512 vectors at d = 96, write 6.8 -> 5.8 us;
+// 52 x 4096 at d = 256, read 40.6 -> 36.6 us; 56 x 8192 at d = 128, write 37.3 -> 36.6 us; 4 x 1,048,576 within 0.5 %.  Over 2 to 64
+// plans and 5 to 600 MB at d = 96, 128, 256: reads 0 to 33 % and writes 0 to 33 % shorter, most where a plan has few tiles; at 2 and 3
+// plans with one to two tiles a workgroup it lost up to 10 % until such segments were cut where the dies meet (launch_shape.h).
 template <int N>
 __device__ __forceinline__ int srft_segment_of_block(const srft_batch<N>& a, int& place) {
     static_assert(N <= 64 && (N & (N - 1)) == 0, "a lane per boundary");
@@ -207,25 +208,10 @@ __device__ __forceinline__ void publish_amax(const float* part, unsigned int* am
 }
 
 // Which tiles a workgroup of a per-plan launch walks: first tile, stride, and the end (exclusive) of its range.
-// SRFT_XCD_MAP = 0: tile = blockIdx + k gridDim over all tiles.  SRFT_XCD_MAP = 1: workgroups are dealt to the 8
-// accelerator dies round-robin (die = blockIdx mod 8), and each die gets one contiguous eighth of the tiles, which
-// its workgroups walk with stride gridDim / 8 (grids that are not a multiple of 8 fall back to the plain map).
-#ifndef SRFT_XCD_MAP
-#define SRFT_XCD_MAP 0
-#endif
 __device__ __forceinline__ bool srft_tile_range(long long n_vec, int& t0, int& stride, int& t_end) {
-    const int n_tiles = (int)((n_vec + kTileVecs - 1) / kTileVecs);
     t0 = blockIdx.x;
     stride = gridDim.x;
-    t_end = n_tiles;
-#if SRFT_XCD_MAP
-    if ((gridDim.x & 7) == 0 && n_tiles >= (int)gridDim.x) {
-        const int per_die = (n_tiles + 7) >> 3, die = blockIdx.x & 7;
-        stride = gridDim.x >> 3;
-        t0 = die * per_die + (blockIdx.x >> 3);
-        t_end = min(n_tiles, (die + 1) * per_die);
-    }
-#endif
+    t_end = (int)((n_vec + kTileVecs - 1) / kTileVecs);
     return t0 < t_end;
 }
 

@@ -11,7 +11,7 @@ quantize_kernel_t by_output(int out) {
 }
 template <int D>
 quantize_kernel_t pick(int slabs, int out) {
-    if constexpr ((D / 32) % 2 == 0) {
+    if constexpr (D == 64) {
         if (slabs == 2) return by_output<D, 2>(out);
     }
     return by_output<D, 1>(out);

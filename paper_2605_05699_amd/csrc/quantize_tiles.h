@@ -8,14 +8,12 @@
 // ------------------------------------------------------------------------------------------
 // wfrag : [D/32 slabs][D/16 k-steps][hi, lo][64 lanes] 16-byte A-operand fragments of W
 // x     : [n_vec][D/8] 16-byte units of fp16 input
-// S     : slabs (= quantization groups) per wavefront; the workgroup has D / (32 S) wavefronts.  With S = 2
-//         every B fragment read from LDS feeds four MFMAs instead of two and half as many wavefronts read the
-//         tile; the price is a 2 x larger register-resident slab (at d = 256 it only fits with one wavefront
-//         per SIMD, the slab in the accumulation half of the register file).
+// S     : slabs (= quantization groups) per wavefront; the workgroup has D / (32 S) wavefronts.  With S = 2 (d = 64) every
+//         B fragment read from LDS feeds four MFMAs instead of two; the price is a 2 x larger register-resident slab.
 // OUT   : kOutCodes: the quantizer.  kOutRaw: store the fp32 coefficients w instead (srft_kv_forward_f32).
 //         kOutAmax: no per-vector output; every lane keeps the running maximum of |w| of its 16 channels over the
-//         tiles it sees, lanes are reduced once at the end and one atomic max per channel and workgroup goes
-//         to wout, read as float[d] (srft_kv_channel_absmax: the statistic lambda is calibrated from, Sec. 7.1).
+//         tiles it sees, the lanes' maxima meet in LDS once at the end and one atomic max per channel and workgroup
+//         goes to wout, read as float[d] (srft_kv_channel_absmax: the statistic lambda is calibrated from, Sec. 7.1).
 // GM    : group mode.  kGroup32: one scale per slab (g = 32, the deployed format).  kGroup16: one scale per
 //         lane (g = 16; a lane's 16 outputs are one group, no cross-lane step).  kGroupWide: g = 32 * gw with
 //         gw >= 2 slabs per group, up to the per-token case g = d; the slab maxima meet in LDS, which costs
