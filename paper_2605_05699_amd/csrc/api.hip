@@ -56,33 +56,34 @@ int launch_dequantize(const srft_plan* p, const uint8_t* codes, const float* sca
     return SRFT_OK;
 }
 
-// What a launch of `Batch` takes: the shares' tiles of the segments' buffers.
-template <class Batch>
-Batch batch_table(const srft_plan* p, bool write_path, const srft_segment* segments, const srft_share* shares, int n) {
-    Batch a;
-    const long long code_bytes = (long long)p->d * p->bits / 8, row_bytes = 2LL * p->d;
-    for (int i = 0; i < Batch::kSegments; ++i) a.first_block[i] = i < n ? shares[i].first_block : INT32_MAX;
-    for (int i = 0; i < n; ++i) {
-        const srft_share& sh = shares[i];
-        srft_segment& s = a.seg[i] = segments[sh.segment];
-        const long long v0 = sh.tile * kTileVecs;
-        s.in = (const char*)s.in + v0 * (write_path ? row_bytes : code_bytes);
-        s.out = (char*)s.out + v0 * (write_path ? code_bytes : row_bytes);
-        s.scales += v0 * (p->d / p->g);
-        s.n_vec = std::min(s.n_vec - v0, sh.tiles * kTileVecs);
-        s.blocks = sh.blocks;
-    }
-    return a;
+// The part of a segment that a share walks.
+srft_segment segment_part(const srft_plan* p, bool write_path, const srft_segment& whole, const srft_share& sh) {
+    const long long code_bytes = (long long)p->d * p->bits / 8, row_bytes = 2LL * p->d, v0 = sh.tile * kTileVecs;
+    srft_segment s = whole;
+    s.in = (const char*)s.in + v0 * (write_path ? row_bytes : code_bytes);
+    s.out = (char*)s.out + v0 * (write_path ? code_bytes : row_bytes);
+    s.scales += v0 * (p->d / p->g);
+    s.n_vec = std::min(s.n_vec - v0, sh.tiles * kTileVecs);
+    return s;
 }
 
-// One batched launch over up to kMaxBatch segments.
-int launch_batched(const srft_plan* p, const srft_segment* segments, int count, bool write_path, hipStream_t st) {
+// One batched launch over the first `count` segments of the table, which is complete except for the workgroups.
+int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool write_path, hipStream_t st) {
     long long tiles[kMaxBatch];
-    for (int i = 0; i < count; ++i) tiles[i] = (segments[i].n_vec + kTileVecs - 1) / kTileVecs;
+    for (int i = 0; i < count; ++i) tiles[i] = (whole.seg[i].n_vec + kTileVecs - 1) / kTileVecs;
     srft_share shares[kMaxBatch];
     int next = 0;
     const int n = srft_share_out(tiles, count, p->max_wgs > 0 ? p->max_wgs : write_path ? p->grid_q : p->grid_dq, shares,
                                  kMaxBatch, &next);
+    srft_batch_many cut;
+    if (n > count)
+        for (int i = 0; i < n; ++i) cut.seg[i] = segment_part(p, write_path, whole.seg[shares[i].segment], shares[i]);
+    srft_batch_many& a = n > count ? cut : whole;
+    for (int i = 0; i < n; ++i) {
+        a.first_block[i] = shares[i].first_block;
+        a.seg[i].blocks = shares[i].blocks;
+    }
+    for (int i = n; i < kMaxBatch; ++i) a.first_block[i] = INT32_MAX;
     batched_kernels_t kernel;
     int threads = 0;
     if (write_path) {
@@ -106,11 +107,14 @@ int launch_batched(const srft_plan* p, const srft_segment* segments, int count, 
         threads = 2 * p->d / p->slabs_dq;
     }
     if (!kernel.many) return SRFT_ERR_BAD_D;
-    const dim3 grid((unsigned)next), block(threads);
-    if (n <= kFewBatch)
-        hipLaunchKernelGGL(kernel.few, grid, block, 0, st, batch_table<srft_batch_few>(p, write_path, segments, shares, n), p->gw);
-    else
-        hipLaunchKernelGGL(kernel.many, grid, block, 0, st, batch_table<srft_batch_many>(p, write_path, segments, shares, n), p->gw);
+    if (n <= kFewBatch) {
+        srft_batch_few few;
+        std::copy_n(a.first_block, kFewBatch, few.first_block);
+        std::copy_n(a.seg, n, few.seg);
+        hipLaunchKernelGGL(kernel.few, dim3((unsigned)next), dim3(threads), 0, st, few, p->gw);
+    } else {
+        hipLaunchKernelGGL(kernel.many, dim3((unsigned)next), dim3(threads), 0, st, a, p->gw);
+    }
     SRFT_HIP(hipGetLastError());
     return SRFT_OK;
 }
@@ -134,11 +138,11 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
         if (!in0[i] || !out0[i] || !small) return SRFT_ERR_NULL;
         if (!srft_aligned(in0[i], 16) || !srft_aligned(out0[i], 16) || !srft_aligned(small, 4)) return SRFT_ERR_ALIGN;
     }
-    srft_segment segments[kMaxBatch];
+    srft_batch_many a;
     int k = 0;
     for (int i = 0; i <= count; ++i) {
         if (i < count && n_vec[i] > 0) {
-            srft_segment& s = segments[k++];
+            srft_segment& s = a.seg[k++];
             s.frag = write_path ? (plans[i]->fold4_q ? plans[i]->wfold4 : plans[i]->fold_q ? plans[i]->wfold : plans[i]->wfrag)
                                 : srft_plan_read_table(plans[i]);
             s.in = in0[i];
@@ -148,7 +152,7 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
             s.unscale = write_path ? plans[i]->unscale_w : srft_plan_read_unscale(plans[i]);
         }
         if (k == kMaxBatch || (i == count && k > 0)) {
-            const int rc = launch_batched(plans[0], segments, k, write_path, st);
+            const int rc = launch_batched(plans[0], a, k, write_path, st);
             if (rc != SRFT_OK) return rc;
             k = 0;
         }

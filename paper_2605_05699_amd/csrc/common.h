@@ -100,7 +100,6 @@ struct srft_segment {
 };
 template <int N>
 struct srft_batch {
-    static constexpr int kSegments = N;
     int first_block[N];
     srft_segment seg[N];
 };
