@@ -32,7 +32,8 @@ int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* cod
     int threads = 0;
     const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads);
     if (!kernel) return SRFT_ERR_BAD_D;
-    const bool fold4 = p->fold4_q && out == kOutCodes, fold = p->fold_q && (out == kOutCodes || out == kOutAmax);
+    const bool fold4 = out == kOutCodes ? p->fold4_q : out == kOutAmax && p->wfold4;
+    const bool fold = p->fold_q && (out == kOutCodes || out == kOutAmax);
     // the twice-folded form carries the matrix scaling inside its per-channel factors
     const float unscale = fold4 ? 1.0f : p->unscale_w;
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, st,
@@ -88,7 +89,7 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
     int threads = 0;
     if (write_path) {
         if (p->fold4_q) {
-            kernel = srft_pick_quantize_fold4_batched(p->bits);
+            kernel = srft_pick_quantize_fold4_batched(p->bits, p->gm);
             threads = 256;
         } else if (p->fold_q) {
             kernel = srft_pick_quantize_fold_batched(p->d, p->bits, p->gm == kGroupWide);

@@ -125,7 +125,7 @@ struct srft_plan {
     uint4* rfrag = nullptr;     // read-path matrix fragments (device)
     uint4* rfold = nullptr;     // read-path fragments of the folded form (device), when fold_dq
     uint4* wfold = nullptr;     // write-path fragments of the folded form (device), when fold_q
-    uint4* wfold4 = nullptr;    // write-path table of the twice-folded form (device), when fold4_q
+    uint4* wfold4 = nullptr;    // write-path table of the twice-folded form (device): d = 256, DFT
     uint4* rfold4 = nullptr;    // read-path table of the twice-folded form (device), when fold4_dq
     float* rmat_f32 = nullptr;  // R^T in fp32, [k][n] = s_n Q[k][n] / max(lambda_k, 1e-6) (device): the one inverse transform per
                                 // query of srft_kv_attend
@@ -164,11 +164,12 @@ batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
 quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out);
 // write path, folded form (d = 128, 256)
 quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide);
-quantize_kernel_t srft_pick_quantize_fold_amax(int d);      // the abs-max statistic through the once-folded contraction
+quantize_kernel_t srft_pick_quantize_fold_amax(void);       // the abs-max statistic through the once-folded contraction (d = 128)
 batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide);
-// write path, folded twice (d = 256, g = 32); the size of its table in 16-byte units
-quantize_kernel_t srft_pick_quantize_fold4(int bits);
-batched_kernels_t srft_pick_quantize_fold4_batched(int bits);
+// write path, folded twice (d = 256; g = 16, 32 and 256); the abs-max statistic; the size of its table in 16-byte units
+quantize_kernel_t srft_pick_quantize_fold4(int bits, int gm);
+quantize_kernel_t srft_pick_quantize_fold4_amax(void);
+batched_kernels_t srft_pick_quantize_fold4_batched(int bits, int gm);
 int srft_fold4_table_units(void);
 // read path
 dequantize_kernel_t srft_pick_dequantize_b4(int d, int slabs, int gm, bool fold);

@@ -252,9 +252,9 @@ int srft_hip_fail(hipError_t e) {
 }
 
 quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads) {
-    if (out == kOutAmax && p->fold_q) {                  // the statistic does not depend on the groups: folded wherever the table exists
+    if (out == kOutAmax && (p->wfold4 || p->fold_q)) {   // the statistic does not depend on the groups: folded wherever a table exists
         *threads = p->d;
-        return srft_pick_quantize_fold_amax(p->d);
+        return p->wfold4 ? srft_pick_quantize_fold4_amax() : srft_pick_quantize_fold_amax();
     }
     if (out != kOutCodes) {
         *threads = 2 * p->d / p->slabs_q;
@@ -262,7 +262,7 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
     }
     if (p->fold4_q) {
         *threads = 256;
-        return srft_pick_quantize_fold4(p->bits);
+        return srft_pick_quantize_fold4(p->bits, p->gm);
     }
     if (p->fold_q) {
         *threads = p->d;
@@ -413,8 +413,10 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
                 }
             }
     }
-    // Folded write path where it applies (d a multiple of 128, g >= 32).
-    p->fold_q = (d % 128 == 0) && p->gm != kGroup16 && transform == SRFT_TRANSFORM_DFT;
+    // Twice-folded write path at d = 256, once-folded at d = 128 and for the group sizes between 32 and d at d = 256.
+    const bool has_fold4 = d == 256 && transform == SRFT_TRANSFORM_DFT;
+    p->fold4_q = has_fold4 && (group_size <= 32 || group_size == d);
+    p->fold_q = !p->fold4_q && (d % 128 == 0) && p->gm != kGroup16 && transform == SRFT_TRANSFORM_DFT;
     std::vector<uint16_t> wfold;
     if (p->fold_q) {
         // Wavefront w < M/2 owns cosine rows k = 32w + i, the others sine rows; row i of its E (O) slab is row
@@ -455,10 +457,8 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
             }
         }
     }
-    // Twice-folded write path at d = 256 with the deployed group size; it replaces the once-folded form there.
-    p->fold4_q = (d == 256) && p->gm == kGroup32 && transform == SRFT_TRANSFORM_DFT;
     std::vector<uint32_t> wfold4;
-    if (p->fold4_q) build_fold4_table(p->signs, lam, wfold4);
+    if (has_fold4) build_fold4_table(p->signs, lam, wfold4);
     // Twice-folded read path at d = 128 and 256 (any g >= 32); it replaces the once-folded form there.
     p->fold4_dq = (d == 128 || d == 256) && p->gm != kGroup16 && transform == SRFT_TRANSFORM_DFT;
     std::vector<uint32_t> rfold4;
@@ -502,8 +502,8 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
     if (e == hipSuccess && p->fold_q) e = hipMemcpy(p->wfold, wfold.data(), wfold.size() * 2, hipMemcpyHostToDevice);
     if (e == hipSuccess && !bfly.empty()) e = hipMalloc((void**)&p->bfly, bfly.size() * 4);
     if (e == hipSuccess && !bfly.empty()) e = hipMemcpy(p->bfly, bfly.data(), bfly.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess && p->fold4_q) e = hipMalloc((void**)&p->wfold4, wfold4.size() * 4);
-    if (e == hipSuccess && p->fold4_q) e = hipMemcpy(p->wfold4, wfold4.data(), wfold4.size() * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess && has_fold4) e = hipMalloc((void**)&p->wfold4, wfold4.size() * 4);
+    if (e == hipSuccess && has_fold4) e = hipMemcpy(p->wfold4, wfold4.data(), wfold4.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess && p->fold4_dq) e = hipMalloc((void**)&p->rfold4, rfold4.size() * 4);
     if (e == hipSuccess && p->fold4_dq) e = hipMemcpy(p->rfold4, rfold4.data(), rfold4.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess && p->fold_dq) e = hipMalloc((void**)&p->rfold, rfold.size() * 2);

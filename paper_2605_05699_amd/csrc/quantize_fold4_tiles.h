@@ -1,4 +1,4 @@
-// quantize_fold4_tiles.h -- write path at d = 256, folded twice: a quarter of the dense matrix work.
+// quantize_fold4_tiles.h -- write path at d = 256 (g = 16, 32, 256), folded twice: a quarter of the dense matrix work.
 //
 // Split the input positions by n mod 4 into four classes and write the bin as k = k1 + 64 k2 (Eq. 1 with the
 // sum over n regrouped; the transform stays exactly the one of Eq. 1-2).  With
@@ -35,6 +35,15 @@
 // Nyquist = P0 - P0' (direct element 0 of wave 2, which computes it from the two published halves), and
 // z64 = sqrt 2 M0, z192 = -sqrt 2 M0' (the rows k1 = 0 have the DC scaling 1/sqrt d; sqrt 2 is folded into rho).
 //
+// GM: kGroup16 (a lane's two runs are a group each), kGroup32, or kGroupWide with g = d (the maxima of a vector's eight runs
+// meet in LDS, one more barrier per tile).  The group sizes in between stay on the once-folded form.
+// BITS = 8 stores its 16-byte pieces of the code rows where they are formed; through LDS, as the 8-byte pieces of 4-bit rows
+// go, the workgroup takes 88 KB and has its compute unit to itself.
+// AMAX: no record; the running maximum of |w| per packed index, as in the once-folded form.
+// Measured, us, against the plain form (g = 16), the once-folded one (g = 256, AMAX) and 88 KB (8-bit, g = 32), for 60,001 and
+// 700,001 vectors: g = 16 17.5 / 169 -> 13.1 / 106; g = 256 17.5 / 139 -> 12.8 / 101; 8-bit 14.5 / 122 -> 13.3 / 115; 52 plans x
+// 4096 vectors 59.4 -> 38.2, 49.3 -> 36.6 and 45.2 -> 43.3; AMAX, 100,000 and 1,000,000 vectors 24.0 / 162 -> 22.7 / 142.
+//
 // wf4: [4 waves][a, c][4 k-steps][hi, lo][64 lanes] 16-byte fragments, then [4 waves][rho_d[32], rho_m[32]] floats,
 //      then [4 waves] (beta1, beta2, nyquist scale, tau).  All scalings by 2^-e of the matrix are inside rho / beta.
 #ifndef SRFT_QUANTIZE_FOLD4_TILES_H
@@ -45,28 +54,32 @@ constexpr int kFold4FragUnits = 4 * 2 * 4 * 2 * 64;          // 16-byte units of
 constexpr int kFold4RhoFloats = 4 * 64;
 constexpr int kFold4Units = kFold4FragUnits + kFold4RhoFloats / 4 + 4;
 
-template <int BITS>
+template <int BITS, int GM, bool AMAX = false>
 __device__ __forceinline__ void
 srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict__ x, long long n_vec,
                           uint2* __restrict__ codes, float* __restrict__ scales, float scale_mul, const int t0,
-                          const int stride, const int t_end) {
+                          const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr) {
     constexpr int D = 256;
     constexpr int G = D / 32;            // groups per vector
     constexpr int T = 4;                 // k-steps per class (K = 64)
     constexpr int U = D / 8;             // 16-byte units per input row
     constexpr int ROW = U + 1;
     constexpr int NT = 256;
-    constexpr int NSLOT = 7;             // exchange slots per vector: A0, A2, Am, Ap, P0, P0', unused
-    __shared__ uint4 lds[2][kTileVecs * ROW];            // the tile, split by class: row = [class][8 units]
+    constexpr int SR = GM == kGroup16 ? 2 * G : G;       // staged scales (per token: maxima of the 32-runs) per vector
+    constexpr bool STAGE = BITS == 4 && !AMAX;           // codes go through LDS
+    // the tile, split by class: row = [class][8 units], then a unit that keeps the rows on different banks and holds the
+    // exchange values A0, A2, Am, Ap of the row's vector; behind the rows P0, P0' and a slot that nobody reads, 32 floats each.
+    // (Two workgroups of 80 KB fit a compute unit; the exchange values in an array of their own made it 82,176 bytes at g = 16.)
+    constexpr int TAIL = kTileVecs * ROW;
+    __shared__ uint4 lds[2][TAIL + 3 * kTileVecs / 4];
     __shared__ uint4 exch[2][4][4][64];                  // send of every wavefront: [wave][4 x 4 floats][lane]
-    __shared__ float xch[2][NSLOT * kTileVecs];
     __shared__ __align__(16) float rho_s[4][64];
     // the record of a finished tile, staged for coalesced stores one stage later: code rows of CROW 8-byte units
     // (one more than a row has, so that the lanes of a wavefront hit different banks), 8 scales per vector
-    constexpr int CU8 = (BITS == 8 ? D : D / 2) / 8;     // 8-byte units per code row
+    constexpr int CU8 = D / 16;                          // 8-byte units per code row
     constexpr int CROW = CU8 + 1;
-    __shared__ uint2 cstage[2][kTileVecs * CROW];
-    __shared__ __align__(16) float sstage[2][kTileVecs * G];
+    __shared__ uint2 cstage[2][STAGE ? kTileVecs * CROW : 1];
+    __shared__ __align__(16) float sstage[2][AMAX ? 4 : kTileVecs * SR];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -82,11 +95,12 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     const bool kill_keep = k0 && wave == 3, kill_recv = k0 && wave == 1;
     const bool take_nyquist = k0 && wave == 2;
     // what the k1 = 0 lanes publish: a[0], c[0] (wave 2: A0, A2), send[0], keep[0] (wave 3: Am, Ap; wave 0: keep = P0;
-    // wave 1: send = P0'); everything else goes to the unused slot
-    const int slot_a = (k0 && wave == 2) ? 0 : 6, slot_c = (k0 && wave == 2) ? 1 : 6;
-    const int slot_s = !k0 ? 6 : wave == 3 ? 2 : wave == 1 ? 5 : 6;
-    const int slot_k = !k0 ? 6 : wave == 3 ? 3 : wave == 0 ? 4 : 6;
-    const int slot_x1 = (wave == 0 || wave == 3) ? 0 : 1, slot_x2 = (wave == 0 || wave == 3) ? 2 : 3;
+    // wave 1: send = P0'); everything else goes to the slot that nobody reads.  Offsets in floats from lds[b].
+    const int pad = (col * ROW + U) * 4, slot_p0 = TAIL * 4 + col, slot_p1 = slot_p0 + kTileVecs, nowhere = slot_p1 + kTileVecs;
+    const int slot_a = (k0 && wave == 2) ? pad : nowhere, slot_c = (k0 && wave == 2) ? pad + 1 : nowhere;
+    const int slot_s = !k0 ? nowhere : wave == 3 ? pad + 2 : wave == 1 ? slot_p1 : nowhere;
+    const int slot_k = !k0 ? nowhere : wave == 3 ? pad + 3 : wave == 0 ? slot_p0 : nowhere;
+    const int slot_x = pad + ((wave == 0 || wave == 3) ? 0 : 1);         // A0 and Am, or A2 and Ap
 
     half8 ahi[T], alo[T], chi[T], clo[T];
 #pragma unroll
@@ -146,17 +160,17 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     // end of the stage that contracts a tile: a <- keep = a + c; send = a - c goes to LDS together with what the
     // k1 = 0 lanes owe the other wavefronts (straight-line code: lanes with nothing to say write the unused slot)
     auto hand_over = [&](int b, floatx16& a, const floatx16& c) __attribute__((always_inline)) {
-        float* slots = &xch[b][col];
-        slots[slot_a * kTileVecs] = a[0];
-        slots[slot_c * kTileVecs] = c[0];
+        float* slots = reinterpret_cast<float*>(&lds[b][0]);
+        slots[slot_a] = a[0];
+        slots[slot_c] = c[0];
         float send[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             send[v] = a[v] - c[v];
             a[v] = a[v] + c[v];
         }
-        slots[slot_s * kTileVecs] = send[0];
-        slots[slot_k * kTileVecs] = a[0];
+        slots[slot_s] = send[0];
+        slots[slot_k] = a[0];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             exch[b][wave][i][lane] = make_uint4(__float_as_uint(send[4 * i]), __float_as_uint(send[4 * i + 1]),
@@ -190,13 +204,19 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
         inv = __builtin_amdgcn_rcpf(scale);
         if (!(scale >= kMinScale)) { scale = 0.0f; inv = 0.0f; }
     };
-    // vector-ALU tail of the tile whose keep is in `keep` and whose exchange values are in exch[b] / xch[b]
+    float amd[AMAX ? 16 : 1] = {}, amm[AMAX ? 16 : 1] = {};     // running maxima of the direct and the mirror run (AMAX)
+    auto row_max = [&](const float* row) __attribute__((always_inline)) {
+        const float4 a = reinterpret_cast<const float4*>(row)[0], c = reinterpret_cast<const float4*>(row)[1];
+        return fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), fmaxf(fmaxf(c.x, c.y), fmaxf(c.z, c.w)));
+    };
+    // vector-ALU tail of the tile whose keep is in `keep` and whose exchange values are in exch[b] / lds[b]
     auto finish = [&](int b, const floatx16& keep, int tile) __attribute__((always_inline)) {
         const long long row0 = (long long)tile * kTileVecs;
         const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;
         const int c = min(col, lim);
-        float x1 = xch[b][slot_x1 * kTileVecs + col], x2 = xch[b][slot_x2 * kTileVecs + col];
-        float n1 = xch[b][4 * kTileVecs + col], n2 = xch[b][5 * kTileVecs + col];
+        const float* slots = reinterpret_cast<const float*>(&lds[b][0]);
+        float x1 = slots[slot_x], x2 = slots[slot_x + 2];
+        float n1 = slots[slot_p0], n2 = slots[slot_p1];
         asm volatile("" : "+v"(x1), "+v"(x2), "+v"(n1), "+v"(n2));      // read by every lane: no branch around the loads
         const float below = fmaf(beta2, x2, beta1 * x1);                // packed index 32 * slot_in
         const float nyquist = nyq_scale * (n1 - n2);
@@ -226,24 +246,45 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
         // bottom element of this lane's aligned mirror block
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mv[0]), __float_as_uint(mv[0]), false, false);
         const float bottom = half ? below : __uint_as_float(sw[1]);      // [1]: the upper lanes' value, in all lanes
+        if constexpr (AMAX) {                    // rows past the end alias to the last row: a maximum does not mind
+            amm[0] = fmaxf(amm[0], fabsf(bottom));
+            amd[0] = fmaxf(amd[0], fabsf(dv[0]));
+#pragma unroll
+            for (int v = 1; v < 16; ++v) {
+                amd[v] = fmaxf(amd[v], fabsf(dv[v]));
+                amm[v] = fmaxf(amm[v], fabsf(mv[v]));
+            }
+            return;
+        }
         float md = fmaxf(fabsf(dv[0]), fabsf(dv[1])), mm = fmaxf(fabsf(bottom), fabsf(mv[1]));
 #pragma unroll
         for (int v = 2; v < 16; ++v) {
             md = fmaxf(md, fabsf(dv[v]));
             mm = fmaxf(mm, fabsf(mv[v]));
         }
-        md = other_half_max(md);
-        mm = other_half_max(mm);
+        if constexpr (GM != kGroup16) {          // (g = 16: a lane's two runs are a group each)
+            md = other_half_max(md);
+            mm = other_half_max(mm);
+        }
+        float* const srow = &sstage[b][col * SR];
+        if constexpr (GM == kGroupWide) {        // g = d: the vector's eight runs meet in LDS
+            srow[half ? slot_in : base_d / 32] = half ? mm : md;
+            __syncthreads();
+            md = mm = row_max(srow);
+        }
         float sd, id, sm, im;
         scale_of(md, sd, id);
         scale_of(mm, sm, im);
-        uint2* crow = &cstage[b][col * CROW];
-        if constexpr (BITS == 8) {               // 16 values = 16 bytes = two 8-byte units
-            crow[base_d / 8 + 2 * half] = make_uint2(pack4v(dv[0], dv[1], dv[2], dv[3], id), pack4v(dv[4], dv[5], dv[6], dv[7], id));
-            crow[base_d / 8 + 2 * half + 1] = make_uint2(pack4v(dv[8], dv[9], dv[10], dv[11], id), pack4v(dv[12], dv[13], dv[14], dv[15], id));
-            crow[p_top / 8 - 2 - 2 * half] = make_uint2(pack4v(bottom, mv[15], mv[14], mv[13], im), pack4v(mv[12], mv[11], mv[10], mv[9], im));
-            crow[p_top / 8 - 1 - 2 * half] = make_uint2(pack4v(mv[8], mv[7], mv[6], mv[5], im), pack4v(mv[4], mv[3], mv[2], mv[1], im));
+        if constexpr (BITS == 8) {               // 16 values = 16 bytes
+            const uint4 pd = make_uint4(pack4v(dv[0], dv[1], dv[2], dv[3], id), pack4v(dv[4], dv[5], dv[6], dv[7], id),
+                                        pack4v(dv[8], dv[9], dv[10], dv[11], id), pack4v(dv[12], dv[13], dv[14], dv[15], id));
+            const uint4 pm = make_uint4(pack4v(bottom, mv[15], mv[14], mv[13], im), pack4v(mv[12], mv[11], mv[10], mv[9], im),
+                                        pack4v(mv[8], mv[7], mv[6], mv[5], im), pack4v(mv[4], mv[3], mv[2], mv[1], im));
+            uint4* crow = reinterpret_cast<uint4*>(codes) + row0 * (D / 16);
+            crow[(unsigned)(c * (D / 16) + base_d / 16 + half)] = pd;
+            crow[(unsigned)(c * (D / 16) + p_top / 16 - 1 - half)] = pm;
         } else {
+            uint2* crow = &cstage[b][STAGE ? col * CROW : 0];
             uint2 pd, pm;
             pd.x = pack8v(dv[0], dv[1], dv[2], dv[3], dv[4], dv[5], dv[6], dv[7], id);
             pd.y = pack8v(dv[8], dv[9], dv[10], dv[11], dv[12], dv[13], dv[14], dv[15], id);
@@ -252,8 +293,13 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
             crow[base_d / 16 + half] = pd;
             crow[p_top / 16 - 1 - half] = pm;
         }
-        // both halves hold both scales: the lower lanes stage the direct group's, the upper lanes the mirror group's
-        sstage[b][col * G + (half ? slot_in : base_d / 32)] = half ? sm : sd;
+        if constexpr (GM == kGroup16) {
+            srow[base_d / 16 + half] = sd;
+            srow[p_top / 16 - 1 - half] = sm;
+        } else if constexpr (GM == kGroup32) {
+            // both halves hold both scales: the lower lanes stage the direct group's, the upper lanes the mirror group's
+            srow[half ? slot_in : base_d / 32] = half ? sm : sd;
+        }
     };
 
     // staged record of `tile` -> global memory: 16 bytes per thread, whole rows next to each other (rows past the end
@@ -261,18 +307,40 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     auto flush = [&](int b, int tile) __attribute__((always_inline)) {
         const long long row0 = (long long)tile * kTileVecs;
         const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;
-        constexpr int PIECES = CU8 / 2;                  // 16-byte pieces per code row
-        uint4* cbase = reinterpret_cast<uint4*>(codes) + row0 * PIECES;
-#pragma unroll
-        for (int i = 0; i < kTileVecs * PIECES / NT; ++i) {
-            const int u = tid + i * NT, r = u / PIECES, pc = u % PIECES;
+        if constexpr (STAGE) {
+            constexpr int PIECES = CU8 / 2;              // 16-byte pieces per code row
+            static_assert(kTileVecs * PIECES == NT, "one piece per thread");
+            uint4* cbase = reinterpret_cast<uint4*>(codes) + row0 * PIECES;
+            const int r = tid / PIECES, pc = tid % PIECES;
             const uint2 lo = cstage[b][r * CROW + 2 * pc], hi = cstage[b][r * CROW + 2 * pc + 1];
             cbase[(unsigned)(min(r, lim) * PIECES + pc)] = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
-        if (wave == 0) {                                 // uniform per wavefront
-            const int r = lane >> 1, hf = lane & 1;
-            const float4 v = *reinterpret_cast<const float4*>(&sstage[b][r * G + 4 * hf]);
-            reinterpret_cast<float4*>(scales + row0 * G)[(unsigned)(min(r, lim) * 2 + hf)] = v;
+        if constexpr (AMAX) {
+        } else if constexpr (GM == kGroupWide) {
+            float scale, inv;
+            if (tid < kTileVecs) {
+                scale_of(row_max(&sstage[b][tid * SR]), scale, inv);
+                (scales + row0)[(unsigned)min(tid, lim)] = scale;
+            }
+        } else if (tid < kTileVecs * SR / 4) {           // uniform per wavefront
+            const int r = tid / (SR / 4), q = tid % (SR / 4);
+            const float4 v = *reinterpret_cast<const float4*>(&sstage[b][r * SR + 4 * q]);
+            reinterpret_cast<float4*>(scales + row0 * SR)[(unsigned)(min(r, lim) * (SR / 4) + q)] = v;
+        }
+    };
+    // AMAX: lanes of one half hold the same 32 indices for 32 different vectors: they meet in LDS (the tile buffers,
+    // which no wavefront reads any more), then one atomic per channel
+    auto emit_amax = [&]() __attribute__((always_inline)) {
+        if constexpr (AMAX) {
+            static_assert(sizeof(lds) >= sizeof(float) * kTileVecs * kAmaxRow<D>, "the tile buffers hold 32 rows of maxima");
+            __syncthreads();
+            float* part = reinterpret_cast<float*>(&lds[0][0]) + col * kAmaxRow<D>;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                part[base_d + 16 * half + v] = amd[v];
+                part[p_top - 16 * half - (v == 0 ? 16 : v)] = amm[v];
+            }
+            publish_amax<D>(reinterpret_cast<float*>(&lds[0][0]), amax, 1.0f);
         }
     };
 
@@ -332,26 +400,37 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
         __syncthreads();
         flush(0, tl);
     }
+    emit_amax();
 }
 
-template <int BITS>
+template <int BITS, int GM>
 __global__ void __launch_bounds__(256, 2)
 srft_quantize_fold4_kernel(const uint4* __restrict__ wf4, const uint4* __restrict__ x, long long n_vec,
                            uint2* __restrict__ codes, float* __restrict__ scales, float4* __restrict__,
                            float, float scale_mul, int) {
     int t0, stride, t_end;
     if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
-    srft_quantize_fold4_tiles<BITS>(wf4, x, n_vec, codes, scales, scale_mul, t0, stride, t_end);
+    srft_quantize_fold4_tiles<BITS, GM>(wf4, x, n_vec, codes, scales, scale_mul, t0, stride, t_end);
 }
 
-template <int BITS, int N>
+// the abs-max statistic: amax is float[256] read as unsigned, updated with atomic maxima
+__global__ void __launch_bounds__(256, 2)
+srft_quantize_fold4_amax_kernel(const uint4* __restrict__ wf4, const uint4* __restrict__ x, long long n_vec,
+                                uint2* __restrict__, float* __restrict__, float4* __restrict__ amax, float, float, int) {
+    int t0, stride, t_end;
+    if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
+    srft_quantize_fold4_tiles<4, kGroup32, true>(wf4, x, n_vec, nullptr, nullptr, 1.0f, t0, stride, t_end,
+                                                 reinterpret_cast<unsigned int*>(amax));
+}
+
+template <int BITS, int GM, int N>
 __global__ void __launch_bounds__(256, 2)
 srft_quantize_fold4_batched_kernel(const srft_batch<N> a, int) {
     int t0;
     const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
-    srft_quantize_fold4_tiles<BITS>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
-                                    1.0f / (BITS == 8 ? 127.0f : 7.0f), t0, s.blocks,
-                                    (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
+    srft_quantize_fold4_tiles<BITS, GM>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
+                                        1.0f / (BITS == 8 ? 127.0f : 7.0f), t0, s.blocks,
+                                        (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 
 #endif  // SRFT_QUANTIZE_FOLD4_TILES_H

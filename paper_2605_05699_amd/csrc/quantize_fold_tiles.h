@@ -480,10 +480,8 @@ srft_quantize_fold_kernel(const uint4* __restrict__ wfold, const uint4* __restri
 }
 
 // the abs-max statistic through the folded contraction: amax is float[d] read as unsigned, updated with atomic maxima
-// (at d = 256 the 32 running maxima do not fit beside the matrix in 256 registers, and with them in scratch the kernel
-// takes twice as long: one workgroup per compute unit)
 template <int D>
-__global__ void __launch_bounds__(D, (D >= 256 ? 1 : 2))
+__global__ void __launch_bounds__(D, 2)
 srft_quantize_fold_amax_kernel(const uint4* __restrict__ wfold, const uint4* __restrict__ x, long long n_vec,
                                uint2* __restrict__, float* __restrict__, float4* __restrict__ amax, float unscale,
                                float scale_mul, int gw) {

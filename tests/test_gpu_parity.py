@@ -499,3 +499,32 @@ def test_read_path_with_one_accumulator_set_through_its_stages(B, d, g, bits, tr
     for n in (1, 32, 33, 64, 65, 100, 160, 192, 200, 255, 256, 320, 383, 384):
         assert torch.equal(plan.dequantize(codes[:n].contiguous(), scales[:n].contiguous()), whole[:n]), n
     plan.close()
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("g", [16, 32, 64, 256])
+def test_write_path_at_d256_through_its_stages_for_every_group_size(B, g, bits):
+    """One to six tiles per workgroup (every way the two-stage loop can end), ragged last tiles, one plan and batched: the same
+    record as one workgroup per tile, byte for byte, and the oracle's.  A zero vector is stored as
+    zeros; nothing is written past the last vector."""
+    d, lam = 256, W.lognormal_lambda(256, seed=g + bits)
+    plan = B.Plan(d, g, 90 + g, lam, bits=bits)
+    xh = W.gaussian_with_outliers(12 * 32, d, seed=g, outliers=2)
+    xh[5] = 0
+    x = torch.from_numpy(xh).cuda()
+    codes, scales = plan.quantize(x)
+    P.check_quantize(xh, plan.signs, lam, g, codes.cpu().numpy(), scales.cpu().numpy(), bits=bits)
+    assert not codes[5].any() and not scales[5].any()
+    B.srft_plan_set_max_workgroups(plan.handle, 2)
+    for n in (1, 31, 32, 33, 64, 65, 100, 160, 192, 200, 255, 256, 320, 383, 384):
+        c = torch.full((n + 1, d * bits // 8), 0xA5, dtype=torch.uint8, device="cuda")
+        s = torch.full((n + 1, d // g), -1.0, device="cuda")
+        B.srft_kv_quantize(plan.handle, x[:n], c[:n], s[:n])
+        assert torch.equal(c[:n], codes[:n]) and torch.equal(s[:n], scales[:n]), n
+        assert (c[n] == 0xA5).all() and (s[n] == -1.0).all(), n
+        rest = 384 - n
+        cb, sb = torch.zeros_like(codes), torch.zeros_like(scales)
+        parts = [slice(0, n), slice(n, 384)][:2 if rest else 1]
+        B.srft_kv_quantize_batched(B.BatchTable([plan.handle] * len(parts), [x[p] for p in parts], [cb[p] for p in parts], [sb[p] for p in parts]))
+        assert torch.equal(cb, codes) and torch.equal(sb, scales), n
+    plan.close()
