@@ -36,11 +36,8 @@ int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* cod
     const bool fold = p->fold_q && (out == kOutCodes || out == kOutAmax);
     // the twice-folded form carries the matrix scaling inside its per-channel factors
     const float unscale = fold4 ? 1.0f : p->unscale_w;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, st,
-                       fold4 ? p->wfold4 : fold ? p->wfold : p->wfrag, (const uint4*)x, n, (uint2*)codes, scales,
-                       (float4*)wout, unscale, unscale / (p->bits == 8 ? 127.0f : 7.0f), p->gw);
-    SRFT_HIP(hipGetLastError());
-    return SRFT_OK;
+    return srft_launch(kernel, dim3((unsigned)grid), threads, st, fold4 ? p->wfold4 : fold ? p->wfold : p->wfrag, (const uint4*)x,
+                       n, (uint2*)codes, scales, (float4*)wout, unscale, unscale / (p->bits == 8 ? 127.0f : 7.0f), p->gw);
 }
 
 int launch_dequantize(const srft_plan* p, const uint8_t* codes, const float* scales, long long n, void* out,
@@ -51,10 +48,8 @@ int launch_dequantize(const srft_plan* p, const uint8_t* codes, const float* sca
     int threads = 0;
     const dequantize_kernel_t kernel = srft_plan_dequantize_kernel(p, &threads);
     if (!kernel) return SRFT_ERR_BAD_D;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(threads), 0, st, srft_plan_read_table(p),
-                       (const uint2*)codes, scales, n, (uint4*)out, srft_plan_read_unscale(p), p->gw);
-    SRFT_HIP(hipGetLastError());
-    return SRFT_OK;
+    return srft_launch(kernel, dim3((unsigned)grid), threads, st, srft_plan_read_table(p), (const uint2*)codes, scales, n,
+                       (uint4*)out, srft_plan_read_unscale(p), p->gw);
 }
 
 // The part of a segment that a share walks.
@@ -66,6 +61,30 @@ srft_segment segment_part(const srft_plan* p, bool write_path, const srft_segmen
     s.scales += v0 * (p->d / p->g);
     s.n_vec = std::min(s.n_vec - v0, sh.tiles * kTileVecs);
     return s;
+}
+
+// The kernels of a plan's batched launches, and their block size.
+batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, int* threads) {
+    if (write_path && p->fold4_q) {
+        *threads = 256;
+        return srft_pick_quantize_fold4_batched(p->bits, p->gm);
+    }
+    if (write_path && p->fold_q) {
+        *threads = p->d;
+        return srft_pick_quantize_fold_batched(p->d, p->bits, p->gm == kGroupWide);
+    }
+    if (write_path) {
+        *threads = 2 * p->d / p->slabs_q;
+        return p->bits == 8 ? srft_pick_quantize_plain_batched_b8(p->d, p->slabs_q, p->gm)
+                            : srft_pick_quantize_plain_batched_b4(p->d, p->slabs_q, p->gm);
+    }
+    if (p->fold4_dq) {
+        *threads = p->d;
+        return srft_pick_dequantize_fold4_batched(p->d, p->bits);
+    }
+    *threads = 2 * p->d / p->slabs_dq;
+    return p->bits == 8 ? srft_pick_dequantize_batched_b8(p->d, p->slabs_dq, p->gm, p->fold_dq)
+                        : srft_pick_dequantize_batched_b4(p->d, p->slabs_dq, p->gm, p->fold_dq);
 }
 
 // One batched launch over the first `count` segments of the table, which is complete except for the workgroups.
@@ -85,39 +104,42 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
         a.seg[i].blocks = shares[i].blocks;
     }
     for (int i = n; i < kMaxBatch; ++i) a.first_block[i] = INT32_MAX;
-    batched_kernels_t kernel;
     int threads = 0;
-    if (write_path) {
-        if (p->fold4_q) {
-            kernel = srft_pick_quantize_fold4_batched(p->bits, p->gm);
-            threads = 256;
-        } else if (p->fold_q) {
-            kernel = srft_pick_quantize_fold_batched(p->d, p->bits, p->gm == kGroupWide);
-            threads = p->d;
-        } else {
-            kernel = p->bits == 8 ? srft_pick_quantize_plain_batched_b8(p->d, p->slabs_q, p->gm)
-                                  : srft_pick_quantize_plain_batched_b4(p->d, p->slabs_q, p->gm);
-            threads = 2 * p->d / p->slabs_q;
-        }
-    } else if (p->fold4_dq) {
-        kernel = srft_pick_dequantize_fold4_batched(p->d, p->bits);
-        threads = p->d;
-    } else {
-        kernel = p->bits == 8 ? srft_pick_dequantize_batched_b8(p->d, p->slabs_dq, p->gm, p->fold_dq)
-                              : srft_pick_dequantize_batched_b4(p->d, p->slabs_dq, p->gm, p->fold_dq);
-        threads = 2 * p->d / p->slabs_dq;
-    }
+    const batched_kernels_t kernel = batched_kernels(p, write_path, &threads);
     if (!kernel.many) return SRFT_ERR_BAD_D;
     if (n <= kFewBatch) {
         srft_batch_few few;
         std::copy_n(a.first_block, kFewBatch, few.first_block);
         std::copy_n(a.seg, n, few.seg);
-        hipLaunchKernelGGL(kernel.few, dim3((unsigned)next), dim3(threads), 0, st, few, p->gw);
-    } else {
-        hipLaunchKernelGGL(kernel.many, dim3((unsigned)next), dim3(threads), 0, st, a, p->gw);
+        return srft_launch(kernel.few, dim3((unsigned)next), threads, st, few, p->gw);
     }
-    SRFT_HIP(hipGetLastError());
-    return SRFT_OK;
+    return srft_launch(kernel.many, dim3((unsigned)next), threads, st, a, p->gw);
+}
+
+// The whole batch as one launch without a table, where its counts are equal and its addresses and plan entries a constant step
+// apart (srft_batch_even); blocks: workgroups per segment.  False: not such a batch.
+bool even_batch(const srft_plan_t* const* plans, const void* const* in, void* const* out, const void* const* scales,
+                const int64_t* n_vec, int count, bool write_path, srft_batch_even* a) {
+    for (int i = 1; i < count; ++i)
+        if (n_vec[i] != n_vec[0]) return false;
+    if (n_vec[0] == 0 || !plans[0]->entry) return false;
+    a->plan_step = count > 1 ? (long long)((uintptr_t)plans[1]->entry - (uintptr_t)plans[0]->entry) : 0;
+    for (int i = 1; i < count; ++i)
+        if (!plans[i]->entry || (uintptr_t)plans[i]->entry - (uintptr_t)plans[i - 1]->entry != (uintptr_t)a->plan_step) return false;
+    if (!srft_even_step(in, count, &a->in_step) || !srft_even_step(out, count, &a->out_step) ||
+        !srft_even_step(scales, count, &a->scales_step))
+        return false;
+    const srft_plan* p = plans[0];
+    a->blocks = srft_even_blocks((n_vec[0] + kTileVecs - 1) / kTileVecs, count,
+                                 p->max_wgs > 0 ? p->max_wgs : write_path ? p->grid_q : p->grid_dq);
+    if (a->blocks == 0) return false;
+    a->magic = srft_even_magic(a->blocks);
+    a->plan = p->entry;
+    a->in = (const char*)in[0];
+    a->out = (char*)out[0];
+    a->scales = (char*)scales[0];
+    a->n_vec = n_vec[0];
+    return true;
 }
 
 }  // namespace
@@ -139,13 +161,19 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
         if (!in0[i] || !out0[i] || !small) return SRFT_ERR_NULL;
         if (!srft_aligned(in0[i], 16) || !srft_aligned(out0[i], 16) || !srft_aligned(small, 4)) return SRFT_ERR_ALIGN;
     }
+    srft_batch_even even;
+    if (even_batch(plans, in0, out0, write_path ? (const void* const*)out1 : in1, n_vec, count, write_path, &even)) {
+        int threads = 0;
+        const batched_kernels_t kernel = batched_kernels(plans[0], write_path, &threads);
+        if (!kernel.even) return SRFT_ERR_BAD_D;
+        return srft_launch(kernel.even, dim3((unsigned)(even.blocks * count)), threads, st, even, plans[0]->gw);
+    }
     srft_batch_many a;
     int k = 0;
     for (int i = 0; i <= count; ++i) {
         if (i < count && n_vec[i] > 0) {
             srft_segment& s = a.seg[k++];
-            s.frag = write_path ? (plans[i]->fold4_q ? plans[i]->wfold4 : plans[i]->fold_q ? plans[i]->wfold : plans[i]->wfrag)
-                                : srft_plan_read_table(plans[i]);
+            s.frag = write_path ? srft_plan_write_table(plans[i]) : srft_plan_read_table(plans[i]);
             s.in = in0[i];
             s.out = out0[i];
             s.scales = (float*)(write_path ? out1[i] : in1[i]);

@@ -11,17 +11,29 @@ namespace {
 // Cache append: the new tokens of every plan, [n_seq][t_all][units] 16-byte units each, of which t go to their place in the
 // paged fp16 view [block][n_seq][R][units]: token slot0 + j of sequence q lands in block block0 + (slot0 + j) / R, slot
 // (slot0 + j) % R.  One thread per unit, blockIdx.y the plan, blockIdx.z the first sequence.  A decode step moves a few
-// kilobytes, so the launch is all there is: 1 KB of arguments instead of the 3.8 KB table of the batched kernels and 32-bit
-// index arithmetic (one token of 2 sequences x 56 plans: 2.9 -> 2.3 us on the device); a prompt is a copy at 4.7 TB/s.
+// kilobytes, so the launch is all there is: 32-bit index arithmetic (one token of 2 sequences x 56 plans: 2.9 -> 2.3 us on the
+// device) and no table of addresses where they lie a constant step apart (72 bytes of arguments against 1 KB: 3.0 against 4.2 us
+// of the host; a prompt of 1000 tokens and 24 steps over 56 plans, with the conversions' launches, 151 -> 135 us).  A prompt is a
+// copy at 4.7 TB/s.
 struct scatter_args {
     const uint4* in[kMaxBatch];
     uint4* out[kMaxBatch];
+    __device__ const uint4* from(int plan) const { return in[plan]; }
+    __device__ uint4* to(int plan) const { return out[plan]; }
 };
+struct scatter_even {               // addresses a constant number of bytes apart
+    const char* in;
+    char* out;
+    long long in_step, out_step;
+    __device__ const uint4* from(int plan) const { return reinterpret_cast<const uint4*>(in + plan * in_step); }
+    __device__ uint4* to(int plan) const { return reinterpret_cast<uint4*>(out + plan * out_step); }
+};
+template <class A>
 __global__ void __launch_bounds__(256)
-srft_cache_scatter_kernel(const scatter_args a, int n_seq, unsigned t, long long t_all, unsigned units, unsigned R,
+srft_cache_scatter_kernel(const A a, int n_seq, unsigned t, long long t_all, unsigned units, unsigned R,
                           long long block0, unsigned slot0) {
-    const uint4* const in = a.in[blockIdx.y];
-    uint4* const out = a.out[blockIdx.y];
+    const uint4* const in = a.from(blockIdx.y);
+    uint4* const out = a.to(blockIdx.y);
     for (int seq = blockIdx.z; seq < n_seq; seq += gridDim.z)
         for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < t * units; i += gridDim.x * blockDim.x) {
             const unsigned tok = i / units, u = i % units, at = slot0 + tok, page = at / R, slot = at % R;
@@ -107,24 +119,37 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
     hipStream_t st = (hipStream_t)hip_stream;
     const int units = cache->plans[0]->d / 8;
     // 1. the new tokens join the window: an exact fp16 copy into the view
+    scatter_even even;
+    const bool is_even = np <= 4096 && srft_even_step(new_f16_dev, (int)np, &even.in_step) &&
+                         srft_even_step(cache->view.data(), (int)np, &even.out_step);
+    const size_t most = is_even ? np : kMaxBatch;
     for (int part = 0; part < srft_copy_launches(t); ++part)
-        for (size_t p0 = 0; p0 < np; p0 += kMaxBatch) {
+        for (size_t p0 = 0; p0 < np; p0 += most) {
             const int64_t t0 = srft_copy_first(part);
             const unsigned n = srft_copy_tokens(part, t);
-            const int plans = (int)std::min<size_t>(kMaxBatch, np - p0);
-            scatter_args a;
-            for (int k = 0; k < plans; ++k) {
-                a.in[k] = (const uint4*)new_f16_dev[p0 + k] + (size_t)t0 * units;
-                a.out[k] = (uint4*)cache->view[p0 + k];
-            }
+            const int plans = (int)std::min<size_t>(most, np - p0);
             const unsigned threads = std::min(256u, (n * units + 63) / 64 * 64);
             const int seqs = std::min(cache->n_seq, 64);     // (the grid: at most about 16 workgroups per compute unit)
             const unsigned blocks = std::max(1u, std::min((n * units + threads - 1) / threads, 4096u / (plans * seqs)));
             const int64_t pos = cache->tokens + t0;
-            hipLaunchKernelGGL(srft_cache_scatter_kernel, dim3(blocks, plans, seqs), dim3(threads), 0, st, a, cache->n_seq, n,
-                               (long long)t, (unsigned)units, (unsigned)cache->R, (long long)(pos / cache->R),
-                               (unsigned)(pos % cache->R));
-            SRFT_HIP(hipGetLastError());
+            const auto copy = [&](auto kernel, const auto& a) {
+                return srft_launch(kernel, dim3(blocks, plans, seqs), (int)threads, st, a, cache->n_seq, n, (long long)t,
+                                   (unsigned)units, (unsigned)cache->R, (long long)(pos / cache->R), (unsigned)(pos % cache->R));
+            };
+            int rc;
+            if (is_even) {
+                even.in = (const char*)new_f16_dev[0] + (size_t)t0 * units * 16;
+                even.out = (char*)cache->view[0];
+                rc = copy(srft_cache_scatter_kernel<scatter_even>, even);
+            } else {
+                scatter_args a;
+                for (int k = 0; k < plans; ++k) {
+                    a.in[k] = (const uint4*)new_f16_dev[p0 + k] + (size_t)t0 * units;
+                    a.out[k] = (uint4*)cache->view[p0 + k];
+                }
+                rc = copy(srft_cache_scatter_kernel<scatter_args>, a);
+            }
+            if (rc != SRFT_OK) return rc;
         }
     cache->tokens += t;
     // 2. every window that is now full is quantized into the store and replaced, in the view, by what the store

@@ -103,6 +103,30 @@ struct srft_batch {
     int first_block[N];
     srft_segment seg[N];
 };
+// What the kernels need of a plan, per path (0 = write, 1 = read): an entry of the device's plan table (plan.hip).
+struct srft_plan_entry {
+    uint64_t table[2];                                        // device addresses
+    float unscale[2];
+    uint64_t unused;
+};
+// Segments of one length whose addresses (and whose plans' entries) lie a constant number of bytes apart: a cache that is one
+// tensor over its layers, a step that appends the same number of vectors to each.  blocks workgroups per segment.  A launch of up
+// to 104 bytes of arguments takes 2.7-2.9 us of the host, one of 112 to 900 3.5, one of 3.8 KiB 4.2, and any number of segments
+// fits.  us a call, against the tables: write 2 plans x 256 vectors at d = 128 4.1 -> 3.8, 64 x 512 at d = 96 4.9 -> 4.3, 100 x 700
+// at d = 128 13.7 -> 8.9 (two launches before), read 9 x 100 at d = 96 5.3 -> 4.6; 56 x 8192 and 4 x 1,048,576 within 0.5 %.
+template <>
+struct srft_batch<0> {
+    const srft_plan_entry* plan;
+    const char* in;
+    char* out;
+    char* scales;
+    long long plan_step, in_step, out_step, scales_step;      // bytes
+    long long n_vec;                                          // of each segment
+    int blocks;
+    uint32_t magic;                                           // srft_even_magic(blocks)
+};
+using srft_batch_even = srft_batch<0>;
+static_assert(sizeof(srft_batch_even) + sizeof(int) <= 96, "a small launch");
 using srft_batch_many = srft_batch<kMaxBatch>;
 using srft_batch_few = srft_batch<kFewBatch>;
 static_assert(sizeof(srft_batch_many) + sizeof(int) <= 4096, "kernel arguments are limited to 4 KiB");
@@ -112,10 +136,12 @@ typedef void (*dequantize_kernel_t)(const uint4*, const uint2*, const float*, lo
 struct batched_kernels_t {
     void (*many)(const srft_batch_many, int);
     void (*few)(const srft_batch_few, int);
-    batched_kernels_t(std::nullptr_t = nullptr) : many(nullptr), few(nullptr) {}
-    batched_kernels_t(void (*m)(const srft_batch_many, int), void (*f)(const srft_batch_few, int)) : many(m), few(f) {}
+    void (*even)(const srft_batch_even, int);
+    batched_kernels_t(std::nullptr_t = nullptr) : many(nullptr), few(nullptr), even(nullptr) {}
+    batched_kernels_t(void (*m)(const srft_batch_many, int), void (*f)(const srft_batch_few, int), void (*e)(const srft_batch_even, int))
+        : many(m), few(f), even(e) {}
 };
-#define SRFT_BATCHED(kernel, ...) batched_kernels_t(kernel<__VA_ARGS__, kMaxBatch>, kernel<__VA_ARGS__, kFewBatch>)
+#define SRFT_BATCHED(kernel, ...) batched_kernels_t(kernel<__VA_ARGS__, kMaxBatch>, kernel<__VA_ARGS__, kFewBatch>, kernel<__VA_ARGS__, 0>)
 
 struct srft_plan {
     int d = 0, g = 0, bits = 4, transform = 0, device = 0;
@@ -143,6 +169,7 @@ struct srft_plan {
     int slabs_q = 1, slabs_dq = 1;  // slabs of the matrix per wavefront in the write / read kernel
     int gm = 1, gw = 1;             // group mode (kGroup16 / kGroup32 / kGroupWide) and slabs per group
     int max_wgs = 0;
+    srft_plan_entry* entry = nullptr;   // this plan's entry in the device's plan table (device; null where the table is full)
 };
 
 struct srft_cache {
@@ -210,10 +237,20 @@ int srft_hip_fail(hipError_t e);         // records the error for srft_last_hip_
         if (e_ != hipSuccess) return srft_hip_fail(e_);  \
     } while (0)
 
+// One launch.  (The triple-chevron form and hipLaunchKernelGGL park the configuration and fetch it back, 0.1-0.2 us.)
+template <class T> struct srft_same { using type = T; };
+template <class... P>
+int srft_launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t st, const typename srft_same<P>::type&... args) {
+    void* p[] = {const_cast<void*>(static_cast<const void*>(&args))...};
+    SRFT_HIP(hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3((unsigned)threads), p, 0, st));
+    return SRFT_OK;
+}
+
 // the kernels a plan launches, and their block sizes
 quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads);
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads);
-// the table and the matrix scaling the read-path kernel of a plan takes
+// the tables and the matrix scaling the kernels of a plan take
+inline const uint4* srft_plan_write_table(const srft_plan* p) { return p->fold4_q ? p->wfold4 : p->fold_q ? p->wfold : p->wfrag; }
 inline const uint4* srft_plan_read_table(const srft_plan* p) { return p->fold4_dq ? p->rfold4 : p->fold_dq ? p->rfold : p->rfrag; }
 inline float srft_plan_read_unscale(const srft_plan* p) { return p->fold4_dq ? p->unscale_r4 : p->unscale_r; }
 // batched launches over plans that share shape and kernel choice (api.hip)

@@ -327,10 +327,9 @@ srft_dequantize_fold4_kernel(const uint4* __restrict__ tab, const uint2* __restr
 template <int D, int BITS, int N>
 __global__ void __launch_bounds__(D / 64 * 64, 2)
 srft_dequantize_fold4_batched_kernel(const srft_batch<N> a, int gw) {
-    int t0;
-    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    const srft_work s = srft_work_of_block<false>(a);
     srft_dequantize_fold4_tiles<D, BITS>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
-                                         s.unscale, gw, t0, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
+                                         s.unscale, gw, s.place, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 
 #endif  // SRFT_DEQUANTIZE_FOLD4_TILES_H

@@ -428,10 +428,9 @@ srft_dequantize_kernel(const uint4* __restrict__ rfrag, const uint2* __restrict_
 template <int D, int S, int KS, bool FOLD, int BITS, int N>
 __global__ void __launch_bounds__(2 * D / S, 1)
 srft_dequantize_batched_kernel(const srft_batch<N> a, int gw) {
-    int t0;
-    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    const srft_work s = srft_work_of_block<false>(a);
     srft_dequantize_tiles<D, S, KS, FOLD, BITS>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
-                                    s.unscale, gw, t0, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
+                                    s.unscale, gw, s.place, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 
 #endif  // SRFT_DEQUANTIZE_TILES_H

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "launch_shape.h"
 
 // Streaming (non-temporal) accesses for data touched once.  Measured: non-temporal stores of full rows help both
 // paths (+2.5 to +3 %); non-temporal loads help where one load instruction covers whole cache lines (the read
@@ -97,7 +98,7 @@ __device__ __forceinline__ uint32_t pack4_bytes(const floatx16& acc, int base, f
     return (hi << 16) | lo;
 }
 
-// Which segment of the table a workgroup serves, and its place among that segment's workgroups.  Lane l compares
+// What a workgroup of a batched launch works on: its segment, and its place among that segment's workgroups.  Lane l compares
 // boundary l of the (ascending) table, so one load and one ballot find it whatever the number of segments (a scan of the
 // table took 50 ns per segment in front of everything else: a read launch of 64 plans x 32 vectors 7.7 -> 5.7 us).
 // Workgroups are dealt to the 8 accelerator dies round robin, each die with an L2 of its own; here a die takes a
@@ -106,15 +107,32 @@ __device__ __forceinline__ uint32_t pack4_bytes(const floatx16& acc, int base, f
 // 52 x 4096 at d = 256, read 40.6 -> 36.6 us; 56 x 8192 at d = 128, write 37.3 -> 36.6 us; 4 x 1,048,576 within 0.5 %.  Over 2 to 64
 // plans and 5 to 600 MB at d = 96, 128, 256: reads 0 to 33 % and writes 0 to 33 % shorter, most where a plan has few tiles; at 2 and 3
 // plans with one to two tiles a workgroup it lost up to 10 % until such segments were cut where the dies meet (launch_shape.h).
-template <int N>
-__device__ __forceinline__ int srft_segment_of_block(const srft_batch<N>& a, int& place) {
+struct srft_work {
+    const uint4* frag;
+    const void* in;
+    void* out;
+    float* scales;
+    long long n_vec;
+    float unscale;
+    int blocks, place;              // workgroups of the segment, this one's place among them
+};
+template <bool WRITE, int N>
+__device__ __forceinline__ srft_work srft_work_of_block(const srft_batch<N>& a) {
     static_assert(N <= 64 && (N & (N - 1)) == 0, "a lane per boundary");
     const int q = gridDim.x >> 3, r = gridDim.x & 7, die = blockIdx.x & 7;
     const int block = die * q + min(die, r) + (int)(blockIdx.x >> 3);        // a permutation of 0 .. gridDim.x - 1
-    const int lane = threadIdx.x & 63, first = lane < N ? a.first_block[lane & (N - 1)] : INT32_MAX;
-    const int i = (int)__popcll(__ballot(first <= block)) - 1;
-    place = block - __builtin_amdgcn_readlane(first, i);
-    return i;
+    if constexpr (N == 0) {                                  // segments of one length, a constant step apart
+        const int i = srft_even_segment((uint32_t)block, a.magic);
+        const srft_plan_entry* e = reinterpret_cast<const srft_plan_entry*>(reinterpret_cast<const char*>(a.plan) + i * a.plan_step);
+        return {(const uint4*)(const __attribute__((address_space(1))) uint4*)e->table[WRITE ? 0 : 1], a.in + i * a.in_step, a.out + i * a.out_step,
+                reinterpret_cast<float*>(a.scales + i * a.scales_step), a.n_vec, e->unscale[WRITE ? 0 : 1], a.blocks,
+                block - i * a.blocks};
+    } else {
+        const int lane = threadIdx.x & 63, first = lane < N ? a.first_block[lane & (N - 1)] : INT32_MAX;
+        const int i = (int)__popcll(__ballot(first <= block)) - 1;
+        const srft_segment& s = a.seg[i];
+        return {s.frag, s.in, s.out, s.scales, s.n_vec, s.unscale, s.blocks, block - __builtin_amdgcn_readlane(first, i)};
+    }
 }
 
 // ------------------------------------------------------------------------------------------

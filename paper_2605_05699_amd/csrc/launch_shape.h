@@ -2,8 +2,15 @@
 #ifndef SRFT_LAUNCH_SHAPE_H
 #define SRFT_LAUNCH_SHAPE_H
 #include <algorithm>
+#include <cstdint>
 
-constexpr int kDies = 8;                     // accelerator dies; a launch's workgroups run die by die (srft_segment_of_block)
+#ifdef __HIPCC__
+#define SRFT_HOST_DEVICE __host__ __device__
+#else
+#define SRFT_HOST_DEVICE
+#endif
+
+constexpr int kDies = 8;                     // accelerator dies; a launch's workgroups run die by die (srft_work_of_block)
 
 // Workgroups first_block .. first_block + blocks - 1 walk the tiles tile .. tile + tiles - 1 of a segment, each with stride
 // `blocks`.
@@ -55,6 +62,29 @@ inline int srft_share_out(const long long* tiles, int count, long long budget, s
         part(s.first_block);
     }
     return count + cuts;
+}
+
+// A launch over segments of one length with `blocks` workgroups each: workgroup -> segment as one multiplication.  Exact while
+// grid * blocks < 2^31: with magic = 2^31 / blocks + e, 0 <= e < 1, the product exceeds the true quotient by block * e / 2^31 <
+// 1 / blocks.
+constexpr uint32_t srft_even_magic(int blocks) { return (uint32_t)(((1ULL << 31) + blocks - 1) / blocks); }
+SRFT_HOST_DEVICE constexpr int srft_even_segment(uint32_t block, uint32_t magic) { return (int)(((uint64_t)(2 * block) * magic) >> 32); }
+
+// Workgroups per segment for `count` segments of `tiles` tiles each, as srft_share_out would share them out; 0: the segments go out
+// cut where the dies meet (see there), or there are more than `budget` of them.
+constexpr int srft_even_blocks(long long tiles, long long count, long long budget) {
+    if (count > budget) return 0;
+    const long long blocks = tiles * count <= budget ? tiles : std::min(std::max(budget / count, 1LL), tiles);
+    if (blocks * count * blocks >= (1LL << 31)) return 0;
+    return count <= kDies / 2 && tiles > blocks && tiles < 4 * blocks ? 0 : (int)blocks;
+}
+
+// True when count addresses lie a constant step apart; *step is that step in bytes (0 for one).
+inline bool srft_even_step(const void* const* p, int count, long long* step) {
+    *step = count > 1 ? (long long)((uintptr_t)p[1] - (uintptr_t)p[0]) : 0;
+    for (int i = 2; i < count; ++i)
+        if ((uintptr_t)p[i] - (uintptr_t)p[i - 1] != (uintptr_t)*step) return false;
+    return true;
 }
 
 // The cache's copy of t new tokens: launch i of srft_copy_launches(t) copies srft_copy_tokens(i, t) tokens from

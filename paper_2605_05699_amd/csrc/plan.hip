@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "common.h"
@@ -221,6 +222,61 @@ int build_rfold4_table(int d, const std::vector<int8_t>& signs, const std::vecto
         consts[w * 4] = sine ? 0.0f : (float)std::ldexp(1.0 / (std::sqrt((double)d) * std::fmax(lam[h], 1e-6)), e);
     }
     return e;
+}
+
+// The plan table of a device: one entry per plan, for the launches that name their plans by a first entry and a step.  Entries are
+// handed out in turn, so that plans created one after the other follow one another whatever has been destroyed before them; the
+// table goes with the device's last plan.  A plan that finds it full has no entry and its batches travel in a table of their own.
+constexpr int kPlanEntries = 8192, kMaxDevices = 64;
+struct plan_table {
+    srft_plan_entry* dev = nullptr;
+    std::vector<bool> taken;
+    int next = 0, live = 0;
+};
+std::mutex g_plan_mutex;
+plan_table g_plan_tables[kMaxDevices];
+
+hipError_t take_entry(srft_plan* p) {
+    if (p->device < 0 || p->device >= kMaxDevices) return hipSuccess;
+    std::lock_guard<std::mutex> lock(g_plan_mutex);
+    plan_table& t = g_plan_tables[p->device];
+    if (!t.dev) {
+        const hipError_t e = hipMalloc((void**)&t.dev, kPlanEntries * sizeof(srft_plan_entry));
+        if (e != hipSuccess) return e;
+        t.taken.assign(kPlanEntries, false);
+        t.next = 0;
+    }
+    if (t.live == kPlanEntries) return hipSuccess;
+    while (t.taken[t.next]) t.next = (t.next + 1) % kPlanEntries;
+    srft_plan_entry* at = t.dev + t.next;
+    const srft_plan_entry entry = {{(uint64_t)srft_plan_write_table(p), (uint64_t)srft_plan_read_table(p)},
+                                   {p->unscale_w, srft_plan_read_unscale(p)}, 0};
+    const hipError_t e = hipMemcpy(at, &entry, sizeof(entry), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        if (t.live == 0) {
+            (void)hipFree(t.dev);
+            t.dev = nullptr;
+        }
+        return e;
+    }
+    t.taken[t.next] = true;
+    t.next = (t.next + 1) % kPlanEntries;
+    ++t.live;
+    p->entry = at;
+    return hipSuccess;
+}
+
+// (after the plan's own memory is gone: freeing that waits for the launches that read the entry)
+hipError_t give_back_entry(srft_plan* p) {
+    if (!p->entry) return hipSuccess;
+    std::lock_guard<std::mutex> lock(g_plan_mutex);
+    plan_table& t = g_plan_tables[p->device];
+    t.taken[p->entry - t.dev] = false;
+    p->entry = nullptr;
+    if (--t.live > 0) return hipSuccess;
+    srft_plan_entry* dev = t.dev;
+    t.dev = nullptr;
+    return hipFree(dev);
 }
 
 // resident workgroups per compute unit of a kernel with `threads` threads per workgroup
@@ -508,6 +564,7 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
     if (e == hipSuccess && p->fold4_dq) e = hipMemcpy(p->rfold4, rfold4.data(), rfold4.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess && p->fold_dq) e = hipMalloc((void**)&p->rfold, rfold.size() * 2);
     if (e == hipSuccess && p->fold_dq) e = hipMemcpy(p->rfold, rfold.data(), rfold.size() * 2, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = take_entry(p);
     int rc = (e == hipSuccess) ? occupancy_grids(p, cus) : srft_hip_fail(e);
     if (rc != SRFT_OK) {
         srft_plan_destroy(p);
@@ -546,6 +603,8 @@ int srft_plan_destroy(srft_plan_t* plan) {
         const hipError_t e5 = hipFree(plan->inv_lam2);
         if (e3 == hipSuccess) e3 = e5;
     }
+    const hipError_t e10 = give_back_entry(plan);
+    if (e3 == hipSuccess) e3 = e10;
     delete plan;
     if (e1 != hipSuccess) return srft_hip_fail(e1);
     if (e2 != hipSuccess) return srft_hip_fail(e2);

@@ -426,10 +426,9 @@ srft_quantize_fold4_amax_kernel(const uint4* __restrict__ wf4, const uint4* __re
 template <int BITS, int GM, int N>
 __global__ void __launch_bounds__(256, 2)
 srft_quantize_fold4_batched_kernel(const srft_batch<N> a, int) {
-    int t0;
-    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    const srft_work s = srft_work_of_block<true>(a);
     srft_quantize_fold4_tiles<BITS, GM>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
-                                        1.0f / (BITS == 8 ? 127.0f : 7.0f), t0, s.blocks,
+                                        1.0f / (BITS == 8 ? 127.0f : 7.0f), s.place, s.blocks,
                                         (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 

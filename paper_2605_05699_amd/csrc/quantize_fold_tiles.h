@@ -494,10 +494,9 @@ srft_quantize_fold_amax_kernel(const uint4* __restrict__ wfold, const uint4* __r
 template <int D, int BITS, bool WIDE, int N>
 __global__ void __launch_bounds__(D, (D >= 256 ? SRFT_QF_WG_PER_CU_256 : 2))
 srft_quantize_fold_batched_kernel(const srft_batch<N> a, int gw) {
-    int t0;
-    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    const srft_work s = srft_work_of_block<true>(a);
     srft_quantize_fold_tiles<D, BITS, WIDE>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
-                                            s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, t0, s.blocks,
+                                            s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, s.place, s.blocks,
                                             (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 

@@ -227,10 +227,9 @@ srft_quantize_kernel(const uint4* __restrict__ wfrag, const uint4* __restrict__ 
 template <int D, int S, int GM, int BITS, int N>
 __global__ void __launch_bounds__(2 * D / S)
 srft_quantize_batched_kernel(const srft_batch<N> a, int gw) {
-    int t0;
-    const srft_segment& s = a.seg[srft_segment_of_block(a, t0)];
+    const srft_work s = srft_work_of_block<true>(a);
     srft_quantize_tiles<D, S, kOutCodes, GM, BITS>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
-                                         nullptr, s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, t0, s.blocks);
+                                         nullptr, s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, s.place, s.blocks);
 }
 
 #endif  // SRFT_QUANTIZE_TILES_H

@@ -219,3 +219,40 @@ def test_segments_cut_where_the_dies_meet(B, d, g, bits, counts, cap):
     _assert_same(ref, _batched(B, plans, xs, d, g, bits))
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("d,g,bits,entries,n,cap", [
+    (32, 32, 4, 3, 1, 0), (64, 32, 8, 5, 33, 0), (96, 16, 4, 64, 70, 0), (128, 32, 4, 101, 65, 0), (128, 128, 8, 9, 1000, 0),
+    (192, 32, 4, 6, 500, 0), (256, 32, 4, 7, 999, 20), (256, 16, 8, 5, 700, 9), (128, 32, 4, 2, 3000, 7), (96, 32, 4, 1, 4000, 3),
+])
+def test_entries_of_one_length_and_a_constant_step(B, d, g, bits, entries, n, cap):
+    """One tensor over all entries (the launch has no table), the same with a gap after every entry, entries in descending
+    order, plans in an order of no constant step, one plan for all: the per-plan calls' results, and no byte outside."""
+    plans, xs, ref = _make(B, d, g, [n] * entries, seed0=31 * d + g, cap=cap, bits=bits)
+    cols = (d * bits // 8, d // g, d)
+    for gap, order in ((0, "up"), (3, "up"), (0, "down"), (0, "mixed"), (0, "same")):
+        ids = list(range(entries))
+        if order == "down":
+            ids.reverse()
+        if order == "mixed":
+            ids = ids[1::2] + ids[0::2]
+        own = [0] * entries if order == "same" else ids
+        fill = [torch.full((entries, n + gap, c), v, dtype=t, device="cuda")
+                for c, v, t in zip(cols, (0xAB, -1.0, 77.0), (torch.uint8, torch.float32, torch.float16))]
+        codes, scales, out = ([f[i, :n] for i in ids] for f in fill)
+        x = torch.zeros(entries, n + gap, d, dtype=torch.float16, device="cuda")
+        for slot, src in zip(ids, own):
+            x[slot, :n] = xs[src]
+        h = [plans[i].handle for i in own]
+        B.srft_kv_quantize_batched(B.BatchTable(h, [x[i, :n] for i in ids], codes, scales))
+        B.srft_kv_dequantize_batched(B.BatchTable(h, out, codes, scales))
+        _assert_same([ref[i] for i in own], (codes, scales, out))
+        for f, v in zip(fill, (0xAB, -1.0, 77.0)):
+            assert bool((f[:, n:] == v).all())
+    for p in plans:
+        p.close()
+    # plans made after others went: the freed places in the device's table are taken again
+    plans, xs, ref = _make(B, d, g, [n] * entries, seed0=77 * d + g, bits=bits)
+    _assert_same(ref, _batched(B, plans, xs, d, g, bits))
+    for p in plans:
+        p.close()

@@ -13,6 +13,9 @@ SOURCE = """
 extern "C" int share_out(const long long* tiles, int count, long long budget, srft_share* out, int most, int* grid) {
     return srft_share_out(tiles, count, budget, out, most, grid);
 }
+extern "C" int even_blocks(long long tiles, long long count, long long budget) { return srft_even_blocks(tiles, count, budget); }
+extern "C" int even_segment(unsigned block, int blocks) { return srft_even_segment(block, srft_even_magic(blocks)); }
+extern "C" int even_step(const void* const* p, int count, long long* step) { return srft_even_step(p, count, step); }
 extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
 extern "C" long long copy_first(int i) { return srft_copy_first(i); }
 extern "C" unsigned copy_tokens(int i, int t) { return srft_copy_tokens(i, t); }
@@ -107,3 +110,46 @@ def test_the_copy_of_new_tokens_takes_every_one_of_them_once(lib, t):
         assert lib.copy_first(i) == done and 0 < lib.copy_tokens(i, t) <= 2 ** 24
         done += lib.copy_tokens(i, t)
     assert done == t                                     # (a 32-bit count of tokens never got past 127 x 2^24)
+
+
+def test_segments_of_one_length_share_like_the_table(lib, share_out):
+    """Where a batch of equal segments goes out without a table, every segment gets the workgroups the table would give it."""
+    rng, even = random.Random(6), 0
+    for _ in range(4000):
+        count = rng.choice([1, 2, 3, 4, 5, 8, 9, 33, 56, 64])
+        tiles = rng.choice([1, 2, rng.randint(1, 40), rng.randint(1, 40000), 2 ** 28])
+        budget = rng.choice([1, 3, 7, 8, 20, 256, 512, 768, 1024, 1280, 10 ** 6])
+        blocks = lib.even_blocks(C.c_longlong(tiles), C.c_longlong(count), C.c_longlong(budget))
+        shares, grid = share_out([tiles] * count, budget)
+        if not blocks:
+            assert count > budget or len(shares) > count or blocks_too_many(grid, shares) or count <= 4
+            continue
+        even += 1
+        assert grid == blocks * count                    # (grids of a few workgroups are cut as well: parts of a segment add up)
+        assert all(sum(s.blocks for s in shares if s.segment == i) == blocks for i in range(count))
+        assert len(shares) == count or blocks < 8
+    assert even > 2000
+
+
+def blocks_too_many(grid, shares):
+    return grid * max(s.blocks for s in shares) >= 2 ** 31
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 3, 7, 18, 19, 85, 256, 511, 512, 1023, 1280, 46340])
+def test_workgroup_to_segment_without_a_table(lib, blocks):
+    for count in (1, 2, 3, 64, 101, 1280, 8192):
+        grid = blocks * count
+        if grid * blocks >= 2 ** 31:
+            continue
+        for block in {0, grid - 1} | {k * blocks + e for k in range(0, count, max(1, count // 50)) for e in (0, blocks - 1)}:
+            assert lib.even_segment(block, blocks) == block // blocks, (blocks, count, block)
+
+
+def test_addresses_a_constant_step_apart(lib):
+    def step(*p):
+        out = C.c_longlong()
+        return (out.value if lib.even_step((C.c_void_p * len(p))(*p), len(p), C.byref(out)) else None)
+    assert step(4096) == 0 and step(4096, 4096, 4096) == 0
+    assert step(4096, 8192, 12288) == 4096 and step(2 ** 40, 2 ** 40 - 16, 2 ** 40 - 32) == -16
+    assert step(4096, 8192, 12304) is None and step(16, 32, 48, 16) is None
+    assert step(0x7F0000000000, 0x10) == 0x10 - 0x7F0000000000
