@@ -81,17 +81,8 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
     const int last_lim = (int)(n_vec - 1 - (long long)(n_tiles - 1) * kTileVecs);
 
     half8 rhi[2][GH], rlo[2][GH];                // [class][group]
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int j = 0; j < GH; ++j) {
-            const int f = ((wave * 2 + c) * GH + j) * 2;
-            rhi[c][j] = __builtin_bit_cast(half8, tab[(f + 0) * 64 + lane]);
-            rlo[c][j] = __builtin_bit_cast(half8, tab[(f + 1) * 64 + lane]);
-        }
     __shared__ uint4 s_half[kHalfUnits];   // per (wavefront, lane half): 4 units of sign masks, 2 of coefficients
-    if (tid < kHalfUnits) s_half[tid] = tab[kFragUnits + tid];     // visible after the first barrier
-    const float c_nyq = __uint_as_float(tab[kFragUnits + kHalfUnits + wave].x);   // uniform; 0 on the sine side
+    float c_nyq;                                 // uniform; 0 on the sine side
     const uint4* mine = &s_half[(wave * 2 + half) * 6];
 
     // ---- loads and decode: as in the once-folded kernel (two code units and one scale per thread) ----
@@ -268,9 +259,24 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
     CodeUnit pa0, pa1, pb0, pb1;
     float pas, pbs;
     fetch(pa0, pa1, pas, t0);
+    // The first tile is asked for ahead of the matrix (it comes from farther away, and does not wait for the plan's entry), the
+    // second one behind it: the first tile goes to LDS while the matrix is on its way.
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int j = 0; j < GH; ++j) {
+            const int f = ((wave * 2 + c) * GH + j) * 2;
+            rhi[c][j] = __builtin_bit_cast(half8, tab[(f + 0) * 64 + lane]);
+            rlo[c][j] = __builtin_bit_cast(half8, tab[(f + 1) * 64 + lane]);
+        }
+    c_nyq = __uint_as_float(tab[kFragUnits + kHalfUnits + wave].x);
+    const uint4 half_unit = tab[kFragUnits + min(tid, kHalfUnits - 1)];
+    __builtin_amdgcn_sched_barrier(0);
     fetch(pb0, pb1, pbs, t0 + stride);
-    hold_in_registers(rhi, rlo);
     to_lds(0, pa0, pa1, pas);
+    hold_in_registers(rhi, rlo);
+    if (tid < kHalfUnits) s_half[tid] = half_unit;               // visible after the first barrier
     fetch(pa0, pa1, pas, t0 + 2 * stride);
     // Two stages per trip, so that the two prefetch register sets keep their names.
     __syncthreads();                             // stage 0: nothing to flush yet

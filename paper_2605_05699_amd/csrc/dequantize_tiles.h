@@ -73,25 +73,7 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     const int last_lim = (int)(n_vec - 1 - (long long)(n_tiles - 1) * kTileVecs);   // last valid row of the last tile
 
     half8 rhi[S * G][KS], rlo[S * G][KS];        // [s * G + group][k-step within the group]
-#pragma unroll
-    for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int j = 0; j < G; ++j)
-#pragma unroll
-            for (int t = 0; t < KS; ++t) {
-                const int slab = wave * S + s, kstep = j * KS + t;
-                const int f = FOLD ? slab * G + j : slab * (D / 16) + kstep;
-                rhi[s * G + j][t] = __builtin_bit_cast(half8, rfrag[(f * 2 + 0) * 64 + lane]);
-                rlo[s * G + j][t] = __builtin_bit_cast(half8, rfrag[(f * 2 + 1) * 64 + lane]);
-            }
     uint4 flip0 = {}, flip1 = {};                // sign-bit masks of this lane's 16 outputs n + d/2 (FOLD)
-    if constexpr (FOLD) {
-        const uint4* masks = rfrag + (D / 32) * G * 2 * 64;
-        flip0 = masks[(wave * 64 + lane) * 2];
-        flip1 = masks[(wave * 64 + lane) * 2 + 1];
-        asm volatile("" : "+v"(flip0.x), "+v"(flip0.y), "+v"(flip0.z), "+v"(flip0.w));
-        asm volatile("" : "+v"(flip1.x), "+v"(flip1.y), "+v"(flip1.z), "+v"(flip1.w));
-    }
 
     // each thread decodes S 8-byte units of the 32 x D/2 code tile (32 * C = S * NT units) and carries up to
     // PS floats of the 32 x ns scale tile (float e = tid + i * NT; past the end it re-reads the last one)
@@ -314,9 +296,33 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     float pas, pat, pbs, pbt;                    // and up to two floats each of their scale tiles
     float s_last;                                // scale of the last group of the tile contracted last
     fetch(pa0, pa1, pas, pat, t0);
+    // The first tile is asked for ahead of the matrix (it comes from farther away, and does not wait for the plan's entry), the
+    // second one behind it: the first tile goes to LDS while the matrix is on its way.
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+#pragma unroll
+            for (int t = 0; t < KS; ++t) {
+                const int slab = wave * S + s, kstep = j * KS + t;
+                const int f = FOLD ? slab * G + j : slab * (D / 16) + kstep;
+                rhi[s * G + j][t] = __builtin_bit_cast(half8, rfrag[(f * 2 + 0) * 64 + lane]);
+                rlo[s * G + j][t] = __builtin_bit_cast(half8, rfrag[(f * 2 + 1) * 64 + lane]);
+            }
+    if constexpr (FOLD) {
+        const uint4* masks = rfrag + (D / 32) * G * 2 * 64;
+        flip0 = masks[(wave * 64 + lane) * 2];
+        flip1 = masks[(wave * 64 + lane) * 2 + 1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     fetch(pb0, pb1, pbs, pbt, t0 + stride);
-    hold_in_registers(rhi, rlo);
     to_lds(0, pa0, pa1, pas, pat);
+    hold_in_registers(rhi, rlo);
+    if constexpr (FOLD) {
+        asm volatile("" : "+v"(flip0.x), "+v"(flip0.y), "+v"(flip0.z), "+v"(flip0.w));
+        asm volatile("" : "+v"(flip1.x), "+v"(flip1.y), "+v"(flip1.z), "+v"(flip1.w));
+    }
     fetch(pa0, pa1, pas, pat, t0 + 2 * stride);
     if constexpr (LEAN) {
         // stage k: barrier; flush T_{k-1}; contract, fold and stage T_k; decode T_{k+1}.  Two stages per trip,

@@ -103,20 +103,7 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     const int slot_x = pad + ((wave == 0 || wave == 3) ? 0 : 1);         // A0 and Am, or A2 and Ap
 
     half8 ahi[T], alo[T], chi[T], clo[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        ahi[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 0) * T + t) * 2 + 0) * 64 + lane]);
-        alo[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 0) * T + t) * 2 + 1) * 64 + lane]);
-        chi[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 1) * T + t) * 2 + 0) * 64 + lane]);
-        clo[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 1) * T + t) * 2 + 1) * 64 + lane]);
-    }
-    {
-        const float* rho_g = reinterpret_cast<const float*>(wf4 + kFold4FragUnits);
-        rho_s[wave][lane] = rho_g[wave * 64 + lane];
-    }
-    const uint4 misc = wf4[kFold4FragUnits + kFold4RhoFloats / 4 + wave];
-    const float beta1 = __uint_as_float(misc.x), beta2 = __uint_as_float(misc.y);
-    const float nyq_scale = __uint_as_float(misc.z), tau = __uint_as_float(misc.w);
+    float beta1, beta2, nyq_scale, tau;
 
     // each thread moves one 64-byte chunk (32 consecutive inputs) per tile: chunk tid % 8 of row tid / 8
     const int frow = tid >> 3, fchunk = tid & 7;
@@ -348,10 +335,26 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     uint4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
     floatx16 aa, ca, ab, cb;                     // two accumulator sets; after hand_over the a of a set holds keep
     fetch(pa0, pa1, pa2, pa3, t0);
+    // The first tile is asked for ahead of the matrix (it comes from farther away, and does not wait for the plan's entry), the
+    // second one behind it: the first tile goes to LDS while the matrix is on its way.
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        ahi[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 0) * T + t) * 2 + 0) * 64 + lane]);
+        alo[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 0) * T + t) * 2 + 1) * 64 + lane]);
+        chi[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 1) * T + t) * 2 + 0) * 64 + lane]);
+        clo[t] = __builtin_bit_cast(half8, wf4[(((wave * 2 + 1) * T + t) * 2 + 1) * 64 + lane]);
+    }
+    const float rho = reinterpret_cast<const float*>(wf4 + kFold4FragUnits)[wave * 64 + lane];
+    const uint4 misc = wf4[kFold4FragUnits + kFold4RhoFloats / 4 + wave];
+    __builtin_amdgcn_sched_barrier(0);
     fetch(pb0, pb1, pb2, pb3, t0 + stride);
+    to_lds(0, pa0, pa1, pa2, pa3);
     hold_in_registers(ahi, alo);
     hold_in_registers(chi, clo);
-    to_lds(0, pa0, pa1, pa2, pa3);
+    rho_s[wave][lane] = rho;
+    beta1 = __uint_as_float(misc.x), beta2 = __uint_as_float(misc.y);
+    nyq_scale = __uint_as_float(misc.z), tau = __uint_as_float(misc.w);
     fetch(pa0, pa1, pa2, pa3, t0 + 2 * stride);
     // stage 0
     __syncthreads();

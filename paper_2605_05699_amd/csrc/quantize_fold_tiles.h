@@ -94,28 +94,11 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
     const int slot_in = p_top / 32 - 1;                      // bottom of the mirror group
 
     half8 ehi[T], elo[T], ohi[T], olo[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        ehi[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 0) * T + t) * 2 + 0) * 64 + lane]);
-        elo[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 0) * T + t) * 2 + 1) * 64 + lane]);
-        ohi[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 1) * T + t) * 2 + 0) * 64 + lane]);
-        olo[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 1) * T + t) * 2 + 1) * 64 + lane]);
-    }
     // rho: in registers, or (large d, where registers are short) in LDS, re-read for every tile
     constexpr bool RHO_LDS = (D >= SRFT_QF_RHO_LDS_MIN_D);
     __shared__ uint4 rho_s[RHO_LDS ? 4 * NT : 1];
     float rho[16];
     float amd[AMAX ? 16 : 1] = {}, amm[AMAX ? 16 : 1] = {};     // running maxima of the direct and the mirror run (AMAX)
-    {
-        const uint4* rp = wfold + M * 2 * T * 2 * 64 + (wave * 64 + lane) * 4;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint4 r = rp[i];
-            if constexpr (RHO_LDS) rho_s[i * NT + tid] = r;
-            rho[4 * i] = __uint_as_float(r.x); rho[4 * i + 1] = __uint_as_float(r.y);
-            rho[4 * i + 2] = __uint_as_float(r.z); rho[4 * i + 3] = __uint_as_float(r.w);
-        }
-    }
     auto load_rho = [&]() __attribute__((always_inline)) {
         if constexpr (RHO_LDS) {
 #pragma unroll
@@ -357,10 +340,31 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
     uint4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
     floatx16 ea, oa, eb, ob;
     fetch(pa0, pa1, pa2, pa3, t0);
+    // The first tile is asked for ahead of the matrix (it comes from farther away, and does not wait for the plan's entry), the
+    // second one behind it: the first tile goes to LDS while the matrix is on its way.
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        ehi[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 0) * T + t) * 2 + 0) * 64 + lane]);
+        elo[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 0) * T + t) * 2 + 1) * 64 + lane]);
+        ohi[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 1) * T + t) * 2 + 0) * 64 + lane]);
+        olo[t] = __builtin_bit_cast(half8, wfold[(((wave * 2 + 1) * T + t) * 2 + 1) * 64 + lane]);
+    }
+    {
+        const uint4* rp = wfold + M * 2 * T * 2 * 64 + (wave * 64 + lane) * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 r = rp[i];
+            if constexpr (RHO_LDS) rho_s[i * NT + tid] = r;
+            rho[4 * i] = __uint_as_float(r.x); rho[4 * i + 1] = __uint_as_float(r.y);
+            rho[4 * i + 2] = __uint_as_float(r.z); rho[4 * i + 3] = __uint_as_float(r.w);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
     fetch(pb0, pb1, pb2, pb3, t0 + stride);
+    to_lds(0, pa0, pa1, pa2, pa3);
     hold_in_registers(ehi, elo);
     hold_in_registers(ohi, olo);
-    to_lds(0, pa0, pa1, pa2, pa3);
     fetch(pa0, pa1, pa2, pa3, t0 + 2 * stride);
     if constexpr (LEAN) {
         // One accumulator set.  Stage k: barrier; quantize T_{k-1} out of the accumulators (its exchange values,

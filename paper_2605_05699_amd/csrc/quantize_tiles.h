@@ -43,13 +43,6 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
     const int last_lim = (int)(n_vec - 1 - (long long)(n_tiles - 1) * kTileVecs);   // last valid row of the last tile
 
     half8 ahi[S][T], alo[S][T];
-#pragma unroll
-    for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            ahi[s][t] = __builtin_bit_cast(half8, wfrag[(((wave * S + s) * T + t) * 2 + 0) * 64 + lane]);
-            alo[s][t] = __builtin_bit_cast(half8, wfrag[(((wave * S + s) * T + t) * 2 + 1) * 64 + lane]);
-        }
 
     // The PER prefetched units of one tile live in separately named registers (PER = 2 uses a and b only).
     // Addresses are a uniform tile base (scalar registers) plus a 32-bit per-lane offset; rows past the end
@@ -166,9 +159,20 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
     uint4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
     Acc acc_a, acc_b;
     fetch(pa0, pa1, pa2, pa3, t0);
+    // The first tile is asked for ahead of the matrix (it comes from farther away, and does not wait for the plan's entry), the
+    // second one behind it: the first tile goes to LDS while the matrix is on its way.
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            ahi[s][t] = __builtin_bit_cast(half8, wfrag[(((wave * S + s) * T + t) * 2 + 0) * 64 + lane]);
+            alo[s][t] = __builtin_bit_cast(half8, wfrag[(((wave * S + s) * T + t) * 2 + 1) * 64 + lane]);
+        }
+    __builtin_amdgcn_sched_barrier(0);
     fetch(pb0, pb1, pb2, pb3, t0 + stride);
-    hold_in_registers(ahi, alo);                 // the matrix slab has arrived before the pipeline starts
     to_lds(0, pa0, pa1, pa2, pa3);
+    hold_in_registers(ahi, alo);                 // the matrix slab has arrived before the pipeline starts
     fetch(pa0, pa1, pa2, pa3, t0 + 2 * stride);
     // stage 0
     __syncthreads();
