@@ -147,6 +147,7 @@ struct srft_plan {
     int d = 0, g = 0, bits = 4, transform = 0, device = 0;
     uint64_t seed = 0;
     std::vector<int8_t> signs;
+    char* memory = nullptr;     // the allocation that holds the tables below (device)
     uint4* wfrag = nullptr;     // write-path matrix fragments (device)
     uint4* rfrag = nullptr;     // read-path matrix fragments (device)
     uint4* rfold = nullptr;     // read-path fragments of the folded form (device), when fold_dq
