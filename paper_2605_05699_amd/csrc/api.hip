@@ -10,27 +10,21 @@ namespace {
 
 // Workgroups of the abs-max statistic.  Each ends with one request per 32 channels to the same few cache lines, served one
 // after the other (about 11 ns a workgroup at d = 128, all at once at the end), so more workgroups shorten the streaming
-// and lengthen the end: the sum is smallest near sqrt(tiles) times a constant.  At most what reaches the read rate: one
-// workgroup per compute unit where it has four and more wavefronts (d >= 160), two with three wavefronts (d = 96); with one or
-// two wavefronts (d <= 64, 128) all that the write path's grid holds.  Measured, us for 20,000 / 100,000 / 600,000 vectors,
-// against the write path's grid: d = 96: 15.7 / 27.4 / 51.6 -> 11 / 14 / 33;  d = 128: 16.5 / 26.2 / 48.7 -> 11 / 17 / 44;
-// d = 256: 16.5 / 29.7 / 104 -> 13 / 25 / 98.  With at most two per unit at d = 32 and 64 too: 1,000,000 vectors 26 and 44 us
-// against 23 and 38, 8,000,000 148 and 264 against 89 and 176; one per unit or the whole grid at d >= 160: 8,000,000 vectors
-// equal, 100,000 at d = 256 25 against 37.
-long long amax_grid(const srft_plan* p, long long n_tiles) {
-    long long g = (long long)(5.0 * std::sqrt((double)n_tiles)) + 1;
-    const long long most = p->d >= 160 ? p->compute_units : p->d == 96 ? 2LL * p->compute_units : p->grid_q;
-    if (g > most) g = most;
-    return g < p->grid_q ? g : p->grid_q;
+// and lengthen the end: the sum is smallest near sqrt(tiles) times a constant, and one per compute unit, which fills it with teams
+// of wavefronts (srft_amax_teams), is the most.
+long long amax_grid(const srft_plan* p, long long n_tiles, int teams) {
+    const long long most = teams == 1 && p->fold_q && !p->wfold4 ? p->grid_q : p->compute_units;      // (four of two wavefronts each fill a unit)
+    return std::min((long long)(5.0 * std::sqrt((double)n_tiles)) + 1, most);
 }
 
 int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* codes, float* scales, float* wout,
                     int out, hipStream_t st) {
     const long long n_tiles = (n + kTileVecs - 1) / kTileVecs;
-    long long grid = p->max_wgs > 0 ? p->max_wgs : out == kOutAmax ? amax_grid(p, n_tiles) : p->grid_q;
-    if (grid > n_tiles) grid = n_tiles;
+    const int teams = out == kOutAmax ? srft_plan_amax_teams(p, n_tiles) : 1;
+    long long grid = p->max_wgs > 0 ? p->max_wgs : out == kOutAmax ? amax_grid(p, n_tiles, teams) : p->grid_q;
+    grid = std::min(grid, (n_tiles + teams - 1) / teams);    // no workgroup without a tile
     int threads = 0;
-    const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads);
+    const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads, n_tiles);
     if (!kernel) return SRFT_ERR_BAD_D;
     const bool fold4 = out == kOutCodes ? p->fold4_q : out == kOutAmax && p->wfold4;
     const bool fold = p->fold_q && (out == kOutCodes || out == kOutAmax);

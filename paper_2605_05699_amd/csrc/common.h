@@ -192,7 +192,16 @@ batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
 quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out);
 // write path, folded form (d = 128, 256)
 quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide);
-quantize_kernel_t srft_pick_quantize_fold_amax(void);       // the abs-max statistic through the once-folded contraction (d = 128)
+// Teams of wavefronts per workgroup of the abs-max statistic, by head dimension and form of the write path (0 plain, 1 once, 2 twice
+// folded): as many as one workgroup per compute unit needs to fill its registers, so that as few workgroups as that update the
+// statistic's cache lines, one after the other.  us, one team per workgroup (up to 2048 workgroups) -> teams, 100,000 / 300,000 / 1,000,000
+// vectors: d = 32 (8 teams) 9.5 / 15 / 23 -> 9.5 / 10.6 / 15.7, d = 64 (8) 15.6 / 23 / 38 -> 10.7 / 14.4 / 26.4, d = 96 (4) 14.0 / 19.4 / 46 -> 12.8 / 19.0 / 38.9,
+// d = 128 (4) 17.6 / 26.3 / 55.5 -> 14.6 / 23.0 / 46.5 (2: 18.0 / 26.2 / 49), d = 256 (2) 24.7 / 46.9 / 156 -> 22.5 / 39.1 / 123.
+// The teams share their barriers, which costs 2 % of the rate at d = 128: from kAmaxAlone tiles on, one team there (3,000,000 vectors 156 us against 161, 6,000,000
+// 293 against 300; elsewhere teams are faster there too).
+constexpr long long kAmaxAlone = 1 << 16;
+constexpr int srft_amax_teams(int d, int form) { return form == 2 ? 2 : form == 1 ? 4 : d <= 64 ? 8 : d == 96 ? 4 : d == 128 ? 2 : 1; }
+quantize_kernel_t srft_pick_quantize_fold_amax(int teams);  // the abs-max statistic through the once-folded contraction (d = 128)
 batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide);
 // write path, folded twice (d = 256; g = 16, 32 and 256); the abs-max statistic; the size of its table in 16-byte units
 quantize_kernel_t srft_pick_quantize_fold4(int bits, int gm);
@@ -248,9 +257,12 @@ int srft_launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t st, co
 }
 
 // the kernels a plan launches, and their block sizes
-quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads);
+quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles = 0);
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads);
 // the tables and the matrix scaling the kernels of a plan take
+inline int srft_plan_amax_teams(const srft_plan* p, long long n_tiles) {
+    return p->fold_q && !p->wfold4 && n_tiles >= kAmaxAlone ? 1 : srft_amax_teams(p->d, p->wfold4 ? 2 : p->fold_q ? 1 : 0);
+}
 inline const uint4* srft_plan_write_table(const srft_plan* p) { return p->fold4_q ? p->wfold4 : p->fold_q ? p->wfold : p->wfrag; }
 inline const uint4* srft_plan_read_table(const srft_plan* p) { return p->fold4_dq ? p->rfold4 : p->fold_dq ? p->rfold : p->rfrag; }
 inline float srft_plan_read_unscale(const srft_plan* p) { return p->fold4_dq ? p->unscale_r4 : p->unscale_r; }

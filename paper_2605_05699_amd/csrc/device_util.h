@@ -219,15 +219,27 @@ __device__ __forceinline__ void atomic_max_nonneg(unsigned int* p, float v) {
 // zero every workgroup's request is sent (they all end together), and a launch over 1,000,003 vectors at d = 128 spent
 // 190 of its 231 us in them.
 template <int D> constexpr int kAmaxRow = D + 4;         // padded: the lanes that write a column hit different banks
-template <int D>
-__device__ __forceinline__ void publish_amax(const float* part, unsigned int* amax, float unscale) {
+// SUB teams of threads each bring 32 rows, team_floats apart, and add up their own before the first team updates amax.
+template <int D, int SUB = 1>
+__device__ __forceinline__ void publish_amax(float* part, size_t team_floats, unsigned int* amax, float unscale) {
+    const int team = SUB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / (blockDim.x / SUB)) : 0;
+    const int c = threadIdx.x - team * (blockDim.x / SUB);
+    float* const mine = part + team * team_floats;
     __syncthreads();
-    if (threadIdx.x < D) {
-        float m = part[threadIdx.x];
+    float m = 0.0f;
+    if (c < D) {
+        m = mine[c];
 #pragma unroll
-        for (int r = 1; r < kTileVecs; ++r) m = fmaxf(m, part[r * kAmaxRow<D> + threadIdx.x]);
-        atomic_max_nonneg(&amax[threadIdx.x], m * unscale);
+        for (int r = 1; r < kTileVecs; ++r) m = fmaxf(m, mine[r * kAmaxRow<D> + c]);
+        if constexpr (SUB > 1) mine[c] = m;                  // (row 0 of this channel: nobody else reads it)
     }
+    if constexpr (SUB > 1) {
+        __syncthreads();
+        if (team > 0) return;
+#pragma unroll
+        for (int k = 1; k < SUB; ++k) m = fmaxf(m, part[k * team_floats + (c < D ? c : 0)]);
+    }
+    if (c < D) atomic_max_nonneg(&amax[c], m * unscale);
 }
 
 // Which tiles a workgroup of a per-plan launch walks: first tile, stride, and the end (exclusive) of its range.

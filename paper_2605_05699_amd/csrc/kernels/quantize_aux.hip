@@ -6,7 +6,7 @@ namespace {
 template <int D, int S>
 quantize_kernel_t by_output(int out) {
     if (out == kOutRaw) return srft_quantize_kernel<D, S, kOutRaw, kGroup32, 4>;
-    if (out == kOutAmax) return srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4>;
+    if (out == kOutAmax) return srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, srft_amax_teams(D, 0)>;
     return nullptr;
 }
 template <int D>

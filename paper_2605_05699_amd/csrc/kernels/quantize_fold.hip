@@ -22,7 +22,9 @@ batched_kernels_t pick_batched(int bits, bool wide) {
 quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide) {
     return d == 128 ? pick<128>(bits, wide) : d == 256 ? pick<256>(bits, wide) : nullptr;
 }
-quantize_kernel_t srft_pick_quantize_fold_amax(void) { return srft_quantize_fold_amax_kernel<128>; }
+quantize_kernel_t srft_pick_quantize_fold_amax(int teams) {
+    return teams == 1 ? srft_quantize_fold_amax_kernel<128, 1> : srft_quantize_fold_amax_kernel<128, srft_amax_teams(128, 1)>;
+}
 batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide) {
     return d == 128 ? pick_batched<128>(bits, wide) : d == 256 ? pick_batched<256>(bits, wide) : nullptr;
 }

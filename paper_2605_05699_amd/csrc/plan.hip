@@ -307,13 +307,14 @@ int srft_hip_fail(hipError_t e) {
     return SRFT_ERR_HIP;
 }
 
-quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads) {
+quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles) {
+    const int teams = out == kOutAmax ? srft_plan_amax_teams(p, n_tiles) : 1;
     if (out == kOutAmax && (p->wfold4 || p->fold_q)) {   // the statistic does not depend on the groups: folded wherever a table exists
-        *threads = p->d;
-        return p->wfold4 ? srft_pick_quantize_fold4_amax() : srft_pick_quantize_fold_amax();
+        *threads = p->d * teams;
+        return p->wfold4 ? srft_pick_quantize_fold4_amax() : srft_pick_quantize_fold_amax(teams);
     }
     if (out != kOutCodes) {
-        *threads = 2 * p->d / p->slabs_q;
+        *threads = 2 * p->d / p->slabs_q * teams;
         return srft_pick_quantize_aux(p->d, p->slabs_q, out);
     }
     if (p->fold4_q) {

@@ -54,11 +54,12 @@ constexpr int kFold4FragUnits = 4 * 2 * 4 * 2 * 64;          // 16-byte units of
 constexpr int kFold4RhoFloats = 4 * 64;
 constexpr int kFold4Units = kFold4FragUnits + kFold4RhoFloats / 4 + 4;
 
-template <int BITS, int GM, bool AMAX = false>
+template <int BITS, int GM, bool AMAX = false, int SUB = 1>
 __device__ __forceinline__ void
 srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict__ x, long long n_vec,
-                          uint2* __restrict__ codes, float* __restrict__ scales, float scale_mul, const int t0,
-                          const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr) {
+                          uint2* __restrict__ codes, float* __restrict__ scales, float scale_mul,
+                          const int first_tile, const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr) {
+    static_assert(SUB == 1 || AMAX, "records are written by one team");
     constexpr int D = 256;
     constexpr int G = D / 32;            // groups per vector
     constexpr int T = 4;                 // k-steps per class (K = 64)
@@ -71,8 +72,8 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     // exchange values A0, A2, Am, Ap of the row's vector; behind the rows P0, P0' and a slot that nobody reads, 32 floats each.
     // (Two workgroups of 80 KB fit a compute unit; the exchange values in an array of their own made it 82,176 bytes at g = 16.)
     constexpr int TAIL = kTileVecs * ROW;
-    __shared__ uint4 lds[2][TAIL + 3 * kTileVecs / 4];
-    __shared__ uint4 exch[2][4][4][64];                  // send of every wavefront: [wave][4 x 4 floats][lane]
+    __shared__ uint4 lds_of[SUB][2][TAIL + 3 * kTileVecs / 4];
+    __shared__ uint4 exch_of[SUB][2][4][4][64];                // send of every wavefront: [wave][4 x 4 floats][lane]
     __shared__ __align__(16) float rho_s[4][64];
     // the record of a finished tile, staged for coalesced stores one stage later: code rows of CROW 8-byte units
     // (one more than a row has, so that the lanes of a wavefront hit different banks), 8 scales per vector
@@ -81,7 +82,10 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     __shared__ uint2 cstage[2][STAGE ? kTileVecs * CROW : 1];
     __shared__ __align__(16) float sstage[2][AMAX ? 4 : kTileVecs * SR];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int team = SUB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0, t0 = first_tile + team;
+    auto& lds = lds_of[team];
+    auto& exch = exch_of[team];
+    const int tid = threadIdx.x - team * NT, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
     const int n_tiles = (int)((n_vec + kTileVecs - 1) / kTileVecs);
     const int last_lim = (int)(n_vec - 1 - (long long)(n_tiles - 1) * kTileVecs);
@@ -327,11 +331,11 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
                 part[base_d + 16 * half + v] = amd[v];
                 part[p_top - 16 * half - (v == 0 ? 16 : v)] = amm[v];
             }
-            publish_amax<D>(reinterpret_cast<float*>(&lds[0][0]), amax, 1.0f);
+            publish_amax<D, SUB>(reinterpret_cast<float*>(&lds_of[0][0][0]), sizeof(lds_of[0]) / sizeof(float), amax, 1.0f);
         }
     };
 
-    const int m = (t_end - 1 - t0) / stride + 1;            // tiles of this workgroup: t0, t0 + stride, ... < t_end
+    const int m = (t_end - 1 - first_tile) / stride + 1;    // tiles of a team: t0, t0 + stride, ... (< t_end for the first one)
     uint4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
     floatx16 aa, ca, ab, cb;                     // two accumulator sets; after hand_over the a of a set holds keep
     fetch(pa0, pa1, pa2, pa3, t0);
@@ -366,7 +370,7 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     for (; k + 1 < m; k += 2) {
         const int tk = t0 + k * stride;
         __syncthreads();                         // stage k (odd)
-        rotate_priority(k);
+        rotate_priority(k + team);
         if (k >= 2) flush(1, tk - 2 * stride);
         contract(1, ab, cb);
         finish(0, aa, tk - stride);
@@ -374,7 +378,7 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
         fetch(pa0, pa1, pa2, pa3, tk + 3 * stride);
         hand_over(1, ab, cb);
         __syncthreads();                         // stage k + 1 (even)
-        rotate_priority(k + 1);
+        rotate_priority(k + 1 + team);
         flush(0, tk - stride);
         contract(0, aa, ca);
         finish(1, ab, tk);
@@ -417,13 +421,14 @@ srft_quantize_fold4_kernel(const uint4* __restrict__ wf4, const uint4* __restric
 }
 
 // the abs-max statistic: amax is float[256] read as unsigned, updated with atomic maxima
-__global__ void __launch_bounds__(256, 2)
+template <int SUB>
+__global__ void __launch_bounds__(SUB * 256, 2)
 srft_quantize_fold4_amax_kernel(const uint4* __restrict__ wf4, const uint4* __restrict__ x, long long n_vec,
                                 uint2* __restrict__, float* __restrict__, float4* __restrict__ amax, float, float, int) {
-    int t0, stride, t_end;
-    if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
-    srft_quantize_fold4_tiles<4, kGroup32, true>(wf4, x, n_vec, nullptr, nullptr, 1.0f, t0, stride, t_end,
-                                                 reinterpret_cast<unsigned int*>(amax));
+    const int n_tiles = (int)((n_vec + kTileVecs - 1) / kTileVecs);
+    if ((int)blockIdx.x * SUB >= n_tiles) return;
+    srft_quantize_fold4_tiles<4, kGroup32, true, SUB>(wf4, x, n_vec, nullptr, nullptr, 1.0f, blockIdx.x * SUB, gridDim.x * SUB,
+                                                      n_tiles, reinterpret_cast<unsigned int*>(amax));
 }
 
 template <int BITS, int GM, int N>

@@ -53,11 +53,15 @@
 //       the bottom element of its mirror block: together the lanes of a vector cover every index once) over all the
 //       tiles it sees; at the end the 32 vectors' lanes are reduced and one atomic maximum per channel goes to `amax`,
 //       read as unsigned[d] (srft_kv_channel_absmax: the statistic lambda is calibrated from, Sec. 7.1).
-template <int D, int BITS, bool WIDE, bool AMAX = false>
+// SUB: teams of M wavefronts per workgroup, each with tiles of its own (t0 + team, and stride counts tiles of all teams); they share
+//       the barriers and, at the end, one update of the statistic (AMAX).  All of them walk as many tiles as the first: past
+//       the end a team sees the last tile again, which a maximum does not mind.
+template <int D, int BITS, bool WIDE, bool AMAX = false, int SUB = 1>
 __device__ __forceinline__ void
 srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restrict__ x, long long n_vec,
                          uint2* __restrict__ codes, float* __restrict__ scales, float unscale, float scale_mul,
-                         int gw, const int t0, const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr) {
+                         int gw, const int first_tile, const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr) {
+    static_assert(SUB == 1 || AMAX, "records are written by one team");
     constexpr int M = D / 64;            // wavefronts per workgroup
     constexpr int G = D / 32;            // groups per vector
     constexpr int T = D / 32;            // k-steps per slab (K = D / 2)
@@ -67,8 +71,8 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
     constexpr int DUMMY = 2 * M + 1;     // exchange slot for values nobody reads
     constexpr bool LEAN = (D >= SRFT_QF_LEAN_MIN_D);    // registers for one accumulator set only
     static_assert(M % 2 == 0, "the cosine and the sine block each need whole wavefronts");
-    __shared__ uint4 lds[2][kTileVecs * ROW];
-    __shared__ float xch[2][(DUMMY + 1) * kTileVecs];
+    __shared__ uint4 lds_of[SUB][2][kTileVecs * ROW];
+    __shared__ float xch_of[SUB][2][(DUMMY + 1) * kTileVecs];
     __shared__ float gmax[WIDE ? 2 : 1][WIDE ? kTileVecs * G : 1];     // maxima of the 32-runs of a tile (WIDE)
     // The record of a finished tile is staged here and stored one stage later, 16 bytes per thread over whole rows:
     // stored directly, a tile's record is 8-byte pieces and single floats, a write request each.
@@ -79,7 +83,10 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
     __shared__ uint2 cstage[STAGE ? 2 : 1][STAGE ? kTileVecs * CROW : 1];
     __shared__ float sstage[STAGE ? 2 : 1][STAGE ? kTileVecs * G : 1];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int team = SUB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0, t0 = first_tile + team;
+    auto& lds = lds_of[team];
+    auto& xch = xch_of[team];
+    const int tid = threadIdx.x - team * NT, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
     const int n_tiles = (int)((n_vec + kTileVecs - 1) / kTileVecs);
     const int last_lim = (int)(n_vec - 1 - (long long)(n_tiles - 1) * kTileVecs);
@@ -333,10 +340,10 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
                 part[base_d + 16 * half + v] = amd[v];
                 part[p_top - 16 * half - (v == 0 ? 16 : v)] = amm[v];
             }
-            publish_amax<D>(reinterpret_cast<float*>(&lds[0][0]), amax, unscale);
+            publish_amax<D, SUB>(reinterpret_cast<float*>(&lds_of[0][0][0]), sizeof(lds_of[0]) / sizeof(float), amax, unscale);
         }
     };
-    const int m = (t_end - 1 - t0) / stride + 1;            // tiles of this workgroup: t0, t0 + stride, ... < t_end
+    const int m = (t_end - 1 - first_tile) / stride + 1;    // tiles of a team: t0, t0 + stride, ... (< t_end for the first one)
     uint4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
     floatx16 ea, oa, eb, ob;
     fetch(pa0, pa1, pa2, pa3, t0);
@@ -433,7 +440,7 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
     for (; k + 1 < m; k += 2) {
         const int tk = t0 + k * stride;
         __syncthreads();                         // stage k (odd)
-        rotate_priority(k);
+        rotate_priority(k + team);
         if (k >= 2) flush(1, tk - 2 * stride);
         contract(1, eb, ob);
         finish(0, ea, oa, tk - stride);
@@ -441,7 +448,7 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
         fetch(pa0, pa1, pa2, pa3, tk + 3 * stride);
         publish(1, eb, ob);
         __syncthreads();                         // stage k + 1 (even)
-        rotate_priority(k + 1);
+        rotate_priority(k + 1 + team);
         flush(0, tk - stride);
         contract(0, ea, oa);
         finish(1, eb, ob, tk);
@@ -484,15 +491,15 @@ srft_quantize_fold_kernel(const uint4* __restrict__ wfold, const uint4* __restri
 }
 
 // the abs-max statistic through the folded contraction: amax is float[d] read as unsigned, updated with atomic maxima
-template <int D>
-__global__ void __launch_bounds__(D, 2)
+template <int D, int SUB>
+__global__ void __launch_bounds__(SUB * D, 2)
 srft_quantize_fold_amax_kernel(const uint4* __restrict__ wfold, const uint4* __restrict__ x, long long n_vec,
                                uint2* __restrict__, float* __restrict__, float4* __restrict__ amax, float unscale,
                                float scale_mul, int gw) {
-    int t0, stride, t_end;
-    if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
-    srft_quantize_fold_tiles<D, 4, false, true>(wfold, x, n_vec, nullptr, nullptr, unscale, scale_mul, gw, t0, stride, t_end,
-                                                reinterpret_cast<unsigned int*>(amax));
+    const int n_tiles = (int)((n_vec + kTileVecs - 1) / kTileVecs);
+    if ((int)blockIdx.x * SUB >= n_tiles) return;
+    srft_quantize_fold_tiles<D, 4, false, true, SUB>(wfold, x, n_vec, nullptr, nullptr, unscale, scale_mul, gw, blockIdx.x * SUB,
+                                                     gridDim.x * SUB, n_tiles, reinterpret_cast<unsigned int*>(amax));
 }
 
 template <int D, int BITS, bool WIDE, int N>

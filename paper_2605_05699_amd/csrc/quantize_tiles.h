@@ -20,11 +20,13 @@
 //         two more barriers per tile.
 // The work of one workgroup: tiles t0, t0 + stride, ... of one plan's n_vec vectors (t0 < number of tiles).
 // BITS  : 4 (two nibbles per byte) or 8 (one byte per value, scale = abs-max / 127; Sec. 3.2 steps 3-4)
-template <int D, int S, int OUT, int GM, int BITS>
+// SUB   : teams of G / S wavefronts per workgroup (kOutAmax), as in srft_quantize_fold_tiles
+template <int D, int S, int OUT, int GM, int BITS, int SUB = 1>
 __device__ __forceinline__ void
 srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x, long long n_vec,
                     uint2* __restrict__ codes, float* __restrict__ scales, float4* __restrict__ wout,
-                    float unscale, float scale_mul, int gw, const int t0, const int stride) {
+                    float unscale, float scale_mul, int gw, const int first_tile, const int stride) {
+    static_assert(SUB == 1 || OUT == kOutAmax, "records are written by one team");
     constexpr int G = D / 32;            // quantization groups per vector = slabs of the matrix
     constexpr int T = D / 16;            // MFMA k-steps
     constexpr int U = D / 8;             // 16-byte units per input row
@@ -33,10 +35,12 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
     constexpr int PER = 2 * S;           // 16-byte units each thread moves per tile (32 * U = PER * NT)
     constexpr int TB = (T < 8) ? T : 8;  // B fragments read from LDS ahead of their MFMAs
     static_assert(G % S == 0, "slabs per wavefront must divide the number of groups");
-    __shared__ uint4 lds[2][kTileVecs * ROW];
+    __shared__ uint4 lds_of[SUB][2][kTileVecs * ROW];
     __shared__ float gmax[GM == kGroupWide ? kTileVecs * G : 1];     // per (vector, slab) abs-max
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int team = SUB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0, t0 = first_tile + team;
+    auto& lds = lds_of[team];
+    const int tid = threadIdx.x - team * NT, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
     // tile indices are 32-bit (the host bounds n_vec), so that the uniform index arithmetic stays scalar
     const int n_tiles = (int)((n_vec + kTileVecs - 1) / kTileVecs);
@@ -155,7 +159,7 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
         }
     };
 
-    const int m = (n_tiles - 1 - t0) / stride + 1;           // tiles of this workgroup
+    const int m = (n_tiles - 1 - first_tile) / stride + 1;   // tiles of a team: t0, t0 + stride, ...
     uint4 pa0, pa1, pa2, pa3, pb0, pb1, pb2, pb3;
     Acc acc_a, acc_b;
     fetch(pa0, pa1, pa2, pa3, t0);
@@ -183,13 +187,13 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
     for (; k + 1 < m; k += 2) {
         const int tk = t0 + k * stride;
         __syncthreads();                         // stage k (odd)
-        rotate_priority(k);
+        rotate_priority(k + team);
         contract(1, acc_b);
         finish(acc_a, tk - stride);
         to_lds(0, pa0, pa1, pa2, pa3);
         fetch(pa0, pa1, pa2, pa3, tk + 3 * stride);
         __syncthreads();                         // stage k + 1 (even)
-        rotate_priority(k + 1);
+        rotate_priority(k + 1 + team);
         contract(0, acc_a);
         finish(acc_b, tk);
         to_lds(1, pb0, pb1, pb2, pb3);
@@ -214,17 +218,17 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
         for (int s = 0; s < S; ++s)
 #pragma unroll
             for (int v = 0; v < 16; ++v) part[col * kAmaxRow<D> + 32 * (wave * S + s) + 16 * half + v] = cmax[s][v];
-        publish_amax<D>(part, reinterpret_cast<unsigned int*>(wout), unscale);
+        publish_amax<D, SUB>(reinterpret_cast<float*>(&lds_of[0][0][0]), sizeof(lds_of[0]) / sizeof(float), reinterpret_cast<unsigned int*>(wout), unscale);
     }
 }
 
-template <int D, int S, int OUT, int GM, int BITS>
-__global__ void __launch_bounds__(2 * D / S)
+template <int D, int S, int OUT, int GM, int BITS, int SUB = 1>
+__global__ void __launch_bounds__(2 * D / S * SUB)
 srft_quantize_kernel(const uint4* __restrict__ wfrag, const uint4* __restrict__ x, long long n_vec,
                      uint2* __restrict__ codes, float* __restrict__ scales, float4* __restrict__ wout,
                      float unscale, float scale_mul, int gw) {
-    srft_quantize_tiles<D, S, OUT, GM, BITS>(wfrag, x, n_vec, codes, scales, wout, unscale, scale_mul, gw, blockIdx.x,
-                                       gridDim.x);       // the grid never exceeds the number of tiles
+    srft_quantize_tiles<D, S, OUT, GM, BITS, SUB>(wfrag, x, n_vec, codes, scales, wout, unscale, scale_mul, gw, blockIdx.x * SUB,
+                                       gridDim.x * SUB);     // no workgroup without a tile
 }
 
 // Several plans in one launch (see srft_batch).

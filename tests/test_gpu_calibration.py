@@ -88,6 +88,32 @@ def test_many_workgroups_meet_on_one_statistic(B, d):
     plan.close()
 
 
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
+@pytest.mark.parametrize("tiles", [2, 4, 5, 8, 9, 25])
+@pytest.mark.parametrize("cap", [0, 1])
+def test_teams_of_a_workgroup(B, d, tiles, cap):
+    """2 to 8 teams share a workgroup and a statistic: counts of tiles that leave teams without one, the largest value of
+    the batch in a last tile of one row."""
+    n = 32 * (tiles - 1) + 1
+    x = W.gaussian_with_outliers(n, d, seed=3 * d + tiles, outliers=1, gain=4.0)
+    x[-1] *= np.float16(8.0)
+    plan = B.Plan(d, 32, 40 + d)
+    B.srft_plan_set_max_workgroups(plan.handle, cap)
+    _check(plan.channel_absmax(torch.from_numpy(x).cuda()).cpu().numpy(), x, plan.signs, None)
+    plan.close()
+
+
+def test_one_team_at_many_tiles(B):
+    """d = 128 from 2^16 tiles on: as the maximum over the parts of the batch, bit for bit."""
+    n, d = (1 << 21) + 7, 128
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    x = torch.randn(n, d, generator=gen, device="cuda", dtype=torch.float16)
+    plan = B.Plan(d, 32, 9)
+    parts = torch.stack([plan.channel_absmax(p) for p in x.split(1 << 20)]).amax(dim=0)
+    assert torch.equal(plan.channel_absmax(x), parts)
+    plan.close()
+
+
 def test_closed_form_and_calibrated_plan_round_trip(B):
     """Constant vectors move only the DC channel; lambda from the statistic makes every channel of the
     calibration batch peak at 1, and the plan built from it quantizes to the oracle's codes."""
