@@ -158,7 +158,7 @@ struct srft_plan {
                                 // query of srft_kv_attend
     int compute_units = 0;
     float* bfly = nullptr;      // table of the butterfly form of the write path (device), d = 128 or 256 / g = 32 / 4-bit only
-    float* inv_lam2 = nullptr;  // 1 / (lambda * max(lambda, 1e-6)) per channel (device): scores in the rotated domain
+    float* q_table = nullptr;   // table of the queries' transform (device; rotated_queries.h), d a multiple of 64
     bool fold_dq = false;       // read path contracts even and odd codes separately (half the matrix work)
     bool fold_q = false;        // write path contracts even and odd inputs separately (half the matrix work)
     bool fold4_q = false;       // write path contracts the inputs in four classes n mod 4 (a quarter of the work)

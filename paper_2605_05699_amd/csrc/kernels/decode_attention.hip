@@ -71,8 +71,8 @@ __device__ __forceinline__ float wave_sum(float x) {
 // registers than two wavefronts per SIMD leave: 250 spilled at d = 128.)
 template <int D, int KEYS, bool WIDE>
 __global__ void __launch_bounds__(64 * kWaves, 2)
-srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ wfrag,
-                           const float* __restrict__ q_scale, float unscale, const uint8_t* __restrict__ k_codes,
+srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ q_table,
+                           int hadamard, float q_sign, const uint8_t* __restrict__ k_codes,
                            const float* __restrict__ k_scales, int k_gw, const uint8_t* __restrict__ v_codes,
                            const float* __restrict__ v_scales, int v_gw, long long n_keys, float softmax_scale,
                            float* __restrict__ part, float* __restrict__ part_max, float* __restrict__ part_sum) {
@@ -93,7 +93,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     __shared__ float meet[2][W][16];
 
     // all arguments in one go: loaded where they are used, each is a round trip of its own in the chain of one tile
-    asm volatile("" :: "s"(unscale), "s"(softmax_scale), "s"(part), "s"(part_max), "s"(part_sum), "s"(q_scale));
+    asm volatile("" :: "s"(hadamard), "s"(q_sign), "s"(softmax_scale), "s"(part), "s"(part_max), "s"(part_sum), "s"(q_table),
+                 "s"(k_codes), "s"(k_scales), "s"(v_codes), "s"(v_scales), "s"(n_keys));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // (uniform: tile addresses in scalar registers)
     const int l16 = lane & 15, a = lane >> 4;                // query (or key / channel of a block of 16), quarter
     unsigned char* const vt = lds + wave * WAVE_BYTES;       // this wavefront's V tile and scales: no other one touches them
@@ -156,8 +157,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     auto v_at = [&](int row) __attribute__((always_inline)) { return vt + row * VROW + (row / KQ) * 8; };
 
     // ---- the operands of the queries, while the first tile is on its way
-    static_assert(srft_query_scratch_bytes<D, W, 1>() <= LDS_BYTES, "the tiles' LDS serves it first");
-    srft_query_operands<D, W, 1>(q, n_q, q0, wfrag, q_scale, unscale, lds, qs, [&]() __attribute__((always_inline)) {
+    static_assert(srft_query_scratch_bytes<D, 1>() <= LDS_BYTES, "the tiles' LDS serves it first");
+    srft_query_operands<D, W, 1>(q, n_q, q0, q_table, hadamard, q_sign, lds, qs, [&]() __attribute__((always_inline)) {
         fetch_k(min(first, n_tiles - 1), first < n_tiles);
         fetch_v(min(first, n_tiles - 1), first < n_tiles);
     });
@@ -497,7 +498,7 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     auto kernel = narrow ? (wide ? srft_attention_scan_kernel<D, 32, true> : srft_attention_scan_kernel<D, 32, false>)
                          : (wide ? srft_attention_scan_kernel<D, 64, true> : srft_attention_scan_kernel<D, 64, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid, blocks), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q,
-                       (const uint4*)pk->wfrag, (const float*)pk->inv_lam2, sign * pk->unscale_w, k_codes, k_scales, pk->gw, v_codes,
+                       (const uint4*)pk->q_table, (int)(pk->transform == SRFT_TRANSFORM_HADAMARD), sign, k_codes, k_scales, pk->gw, v_codes,
                        v_scales, pv->gw, n_keys, sign * softmax_scale, part, part_max, part_sum);
     SRFT_HIP(hipGetLastError());
     hipLaunchKernelGGL(srft_attention_finish_kernel<D>, dim3((unsigned)n_q, D / 64), dim3(1024), 0, st, (const float*)part,

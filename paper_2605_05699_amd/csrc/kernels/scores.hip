@@ -28,12 +28,12 @@ template <int D, int RB> constexpr int kTileKeys = D * RB > 256 || D == 256 ? 32
 // codes [n_keys][D / 2] bytes, scales [n_keys][D / 32 / gw], out [n_q][n_keys]
 template <int D, int RB, bool WIDE, bool STAGE>
 __global__ void __launch_bounds__(64 * kWaves, 2)
-srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ wfrag, const float* __restrict__ q_scale,
-                   float unscale, const uint8_t* __restrict__ codes, const float* __restrict__ scales, int gw,
+srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ q_table, int hadamard,
+                   const uint8_t* __restrict__ codes, const float* __restrict__ scales, int gw,
                    long long n_keys, float* __restrict__ out) {
     constexpr int G = D / 32, QUADS = G / 4, REST = G % 4;   // a row of codes: QUADS x 64 bytes, then REST x 16 bytes
     constexpr int ROW = D / 2, W = kWaves, KEYS = kTileKeys<D, RB>, BK = KEYS / 16;
-    constexpr int SCRATCH = srft_query_scratch_bytes<D, W, RB>(), TILES = W * G * KEYS * 4;
+    constexpr int SCRATCH = srft_query_scratch_bytes<D, RB>(), TILES = W * G * KEYS * 4;
     __shared__ __align__(16) unsigned char lds[SCRATCH > TILES ? SCRATCH : TILES];
     __shared__ uint4 qs[RB * G * 2 * 64];
     constexpr int SROW = KEYS + 4;                           // padded
@@ -73,7 +73,7 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
             for (int j = G / 4 * 4; j < G; ++j) ps[j / 4][j % 4] = row[j];
         }
     };
-    srft_query_operands<D, W, RB>(q, n_q, 0, wfrag, q_scale, unscale, lds, qs, [&]() __attribute__((always_inline)) {
+    srft_query_operands<D, W, RB>(q, n_q, 0, q_table, hadamard, 1.0f, lds, qs, [&]() __attribute__((always_inline)) {
         fetch(min(first, n_tiles - 1), first < n_tiles);
     });
 
@@ -177,8 +177,8 @@ int launch(const srft_plan* p, const void* q, int n_q, const uint8_t* codes, con
     auto kernel = n_q <= 8    ? (wide ? srft_scores_kernel<D, 1, true, false> : srft_scores_kernel<D, 1, false, false>)
                   : n_q <= 16 ? (wide ? srft_scores_kernel<D, 1, true, true> : srft_scores_kernel<D, 1, false, true>)
                               : (wide ? srft_scores_kernel<D, 2, true, true> : srft_scores_kernel<D, 2, false, true>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q, (const uint4*)p->wfrag,
-                       (const float*)p->inv_lam2, p->unscale_w, codes, scales, p->gw, n_keys, out);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q, (const uint4*)p->q_table,
+                       (int)(p->transform == SRFT_TRANSFORM_HADAMARD), codes, scales, p->gw, n_keys, out);
     SRFT_HIP(hipGetLastError());
     return SRFT_OK;
 }

@@ -224,6 +224,26 @@ int build_rfold4_table(int d, const std::vector<int8_t>& signs, const std::vecto
     return e;
 }
 
+// Table of the queries' transform (d a multiple of 64): see rotated_queries.h for what the kernels do with it.
+void build_query_table(int d, int transform, const std::vector<int8_t>& signs, const std::vector<double>& lam, std::vector<float>& out) {
+    const int L = d / 16;
+    const double pi = 3.14159265358979323846;
+    out.assign((size_t)L * 20 + d, 0.0f);
+    for (int j = 0; j < L; ++j) {
+        for (int k = 1; k <= 8; ++k) {
+            out[20 * j + 2 * (k - 1)] = (float)std::cos(2.0 * pi * j * k / d);
+            out[20 * j + 2 * (k - 1) + 1] = (float)-std::sin(2.0 * pi * j * k / d);
+        }
+        uint32_t mask = 0;
+        for (int i = 0; i < 16; ++i) mask |= (signs[L * i + j] < 0 ? 1u : 0u) << i;
+        std::memcpy(&out[20 * j + 16], &mask, 4);
+    }
+    for (int p = 0; p < d; ++p) {
+        const bool one = transform == SRFT_TRANSFORM_HADAMARD || p == 0 || p == d / 2;
+        out[20 * L + p] = (float)(std::sqrt((one ? 1.0 : 2.0) / d) / std::fmax(lam[p], 1e-6));
+    }
+}
+
 // The plan table of a device: one entry per plan, for the launches that name their plans by a first entry and a step.  Entries are
 // handed out in turn, so that plans created one after the other follow one another whatever has been destroyed before them; the
 // table goes with the device's last plan.  A plan that finds it full has no entry and its batches travel in a table of their own.
@@ -538,10 +558,11 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
             std::memcpy(&bfly[d + j], &m, 4);
         }
     }
-    std::vector<float> rmat((size_t)d * d), il2(d);
+    std::vector<float> rmat((size_t)d * d);
     for (int n = 0; n < d; ++n)
         for (int k = 0; k < d; ++k) rmat[(size_t)k * d + n] = (float)R[(size_t)n * d + k];
-    for (int k = 0; k < d; ++k) il2[k] = (float)(1.0 / (lam[k] * std::fmax(lam[k], 1e-6)));
+    std::vector<float> q_table;
+    if (d % 64 == 0) build_query_table(d, transform, p->signs, lam, q_table);
     // All tables of a plan in one allocation, sent in one copy (creating a plan at d = 128: 1.13 -> 1.06 ms).
     std::vector<unsigned char> image;
     const auto place = [&image](const auto& table) {         // (256-byte aligned)
@@ -550,7 +571,7 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
         if (bytes) std::memcpy(image.data() + at, table.data(), bytes);
         return at;
     };
-    const size_t at_wfrag = place(wf), at_rfrag = place(rf), at_rmat = place(rmat), at_il2 = place(il2), at_wfold = place(wfold),
+    const size_t at_wfrag = place(wf), at_rfrag = place(rf), at_rmat = place(rmat), at_query = place(q_table), at_wfold = place(wfold),
                  at_bfly = place(bfly), at_wfold4 = place(wfold4), at_rfold4 = place(rfold4), at_rfold = place(rfold);
     hipError_t e = hipGetDevice(&p->device);
     int cus = 0;
@@ -563,7 +584,7 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
         p->wfrag = (uint4*)table(at_wfrag, true);
         p->rfrag = (uint4*)table(at_rfrag, true);
         p->rmat_f32 = (float*)table(at_rmat, true);
-        p->inv_lam2 = (float*)table(at_il2, true);
+        p->q_table = (float*)table(at_query, !q_table.empty());
         p->wfold = (uint4*)table(at_wfold, p->fold_q);
         p->bfly = (float*)table(at_bfly, !bfly.empty());
         p->wfold4 = (uint4*)table(at_wfold4, has_fold4);

@@ -93,6 +93,27 @@ def test_every_query_count_and_nothing_written_outside(B, d):
     plan.close()
 
 
+@pytest.mark.parametrize("d,transform", [(64, "dft"), (128, "dft"), (192, "dft"), (256, "dft"), (64, "hadamard"), (256, "hadamard")])
+@pytest.mark.parametrize("n_q", [1, 9, 16, 17, 32])
+def test_every_channel_of_the_transformed_queries(B, d, transform, n_q):
+    """Keys with one code of 1 in channel t: the score is channel t of the query's own transform, held to 1e-6 of |q| / lambda_t
+    (fp32 butterflies over log2 d levels and the fp16 split: about 2^-21)."""
+    lam = W.lognormal_lambda(d, seed=d + 1)
+    plan = B.Plan(d, 32, 70 + d, lam, transform=transform)
+    t = np.arange(d)
+    codes = np.zeros((d, d // 2), dtype=np.uint8)
+    codes[t, t // 2] = np.where(t % 2, 16, 1)
+    scales = np.ones((d, d // 32), dtype=np.float32)
+    q = W.gaussian_with_outliers(n_q, d, seed=n_q + d, outliers=1, gain=4.0)
+    q[0] = 0
+    q[0, d // 3] = 2.0                                       # an impulse among them
+    got = plan.scores(torch.from_numpy(q).cuda(), torch.from_numpy(codes).cuda(), torch.from_numpy(scales).cuda()).cpu().numpy()
+    ref = O.attention_scores(q, codes, scales, plan.signs, lam, 32, form="hadamard" if transform == "hadamard" else "dense")
+    tol = 1e-6 * np.linalg.norm(q.astype(np.float64), axis=1)[:, None] / lam[None, :].astype(np.float64)
+    assert np.all(np.abs(got - ref) <= tol), float((np.abs(got - ref) / tol).max())
+    plan.close()
+
+
 def test_scores_argument_errors(B):
     L = B.lib()
     plan = B.Plan(128, 32, 1)
