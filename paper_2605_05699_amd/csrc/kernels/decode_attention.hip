@@ -12,15 +12,15 @@
 //    not depend on timing), divided by the sum of the weights and taken through the inverse transform.
 //
 // What bounds it: at 131,072 keys and d = 128 the record is 21 MB (4 us at the rate of a copy) and every wavefront of the chip
-// has one tile, so the time is the latency of the launches and of one tile's chain (about 18,000 clocks in the scan: 3,000
-// until q' and the tile are there, 3,700 for q' to reach every wavefront, 4,000 scores, 700 softmax, 2,300 values, 4,900 to
+// has one tile, so the time is the latency of the launches and of one tile's chain (about 19,000 clocks in the scan: 6,500 until
+// q' has reached every wavefront, 3,600 more until the tile is there, 1,000 scores, 1,700 softmax, 2,900 values, 1,900 to
 // meet).  Scores and weights therefore never leave the registers: with keys on the rows and queries on the columns of the
 // score product, a lane holds, for ITS query (lane % 16), the keys of its quarter of the wavefront (lane / 16), which is what
 // the second product takes as its B operand and what a running maximum and its correction need; with channels on the rows and
 // queries on the columns of the second product the sums belong to the same query.
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
-// d = 128, 8 queries, 131,072 keys 36.6 -> 15.6, 400,000 keys 51 -> 26; 32 queries, 400,000 keys 111 -> 39; d = 256, 4 queries,
-// 4096 keys 27.7 -> 15.6; d = 64, 1 query, 500 keys 21.9 -> 11.2.  Error against 64 bits 6e-6 -> 4e-7.
+// d = 128, 8 queries, 131,072 keys 36.6 -> 14.0, 400,000 keys 51 -> 24; 32 queries, 400,000 keys 111 -> 38; d = 256, 4 queries,
+// 4096 keys 27.7 -> 12.7; d = 64, 1 query, 500 keys 21.9 -> 10.5.  Error against 64 bits 6e-6 -> 4e-7.
 #include <algorithm>
 
 #include "../rotated_queries.h"
@@ -281,7 +281,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             const int fit_now = 140 - max((int)((__float_as_uint(big) >> 23) & 0xFF), 27);    // 13 - exponent, at most 113
             const float change = __builtin_ldexpf(down, fit_now - fit);
             fit = fit_now;
-            if (__ballot(change != 1.0f))                    // uniform
+            if (tile != first && __ballot(change != 1.0f))   // uniform
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b] *= change;
 #pragma unroll
@@ -332,13 +332,29 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
         meet[0][wave][l16] = top;
         meet[1][wave][l16] = den;
     }
+    float* const dst = part + ((size_t)blockIdx.x * n_q + q0) * D;
+    if (active == 1) {                                       // nobody to meet (short prefixes: 2200 clocks at d = 256 otherwise)
+        if (wave == 0) {
+            const float f = __builtin_ldexpf(1.0f, -fit);
+            if (tid < nq) {
+                part_max[(q0 + l16) * kScanGridMax + blockIdx.x] = top;
+                part_sum[(q0 + l16) * kScanGridMax + blockIdx.x] = den;
+            }
+            if (l16 < nq)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) *reinterpret_cast<floatx4*>(&dst[l16 * D + 16 * b + 4 * a]) = acc[b] * f;
+        }
+        return;
+    }
     __syncthreads();
-    float t = meet[0][0][l16];
-    for (int k = 1; k < active; ++k) t = fmaxf(t, meet[0][k][l16]);
+    float t = meet[0][0][l16];                               // (wavefronts without a tile: kLowest and 0)
+#pragma unroll
+    for (int k = 1; k < W; ++k) t = fmaxf(t, meet[0][k][l16]);
     const float f = __builtin_ldexpf(__builtin_amdgcn_exp2f(top - t), -fit);
     if (tid < nq) {
         float s = 0.0f;
-        for (int k = 0; k < active; ++k) s = fmaf(meet[1][k][l16], __builtin_amdgcn_exp2f(meet[0][k][l16] - t), s);
+#pragma unroll
+        for (int k = 0; k < W; ++k) s = fmaf(meet[1][k][l16], __builtin_amdgcn_exp2f(meet[0][k][l16] - t), s);
         part_max[(q0 + l16) * kScanGridMax + blockIdx.x] = t;
         part_sum[(q0 + l16) * kScanGridMax + blockIdx.x] = s;
     }
@@ -348,7 +364,6 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     int nb = NB;
     while (active * nq * (16 * nb + 4) * 4 > LDS_BYTES) nb = (nb + 1) / 2;
     const int mrow = 16 * nb + 4;                            // padded
-    float* const dst = part + ((size_t)blockIdx.x * n_q + q0) * D;
     for (int b0 = 0; b0 < NB; b0 += nb) {
         const int b1 = min(NB, b0 + nb);
         if (b0) __syncthreads();
@@ -358,13 +373,22 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
                 if (b >= b0 && b < b1)                       // uniform
                     *reinterpret_cast<floatx4*>(&merge[(wave * nq + l16) * mrow + 16 * (b - b0) + 4 * a]) = acc[b] * f;
         __syncthreads();
-        const int per = 4 * (b1 - b0);                       // 16-byte pieces per query
-        for (int e = tid; e < nq * per; e += 64 * W) {
-            const int r = e / per, p = e % per;
-            floatx4 s = *reinterpret_cast<const floatx4*>(&merge[r * mrow + 4 * p]);
-            for (int k = 1; k < active; ++k) s += *reinterpret_cast<const floatx4*>(&merge[(k * nq + r) * mrow + 4 * p]);
+        const auto add = [&](int r, int p) __attribute__((always_inline)) {      // 16-byte piece p of query r
+            const float* const from = &merge[r * mrow + 4 * p];
+            floatx4 s = *reinterpret_cast<const floatx4*>(from);
+            if (active == W) {                               // (all reads on their way together)
+#pragma unroll
+                for (int k = 1; k < W; ++k) s += *reinterpret_cast<const floatx4*>(from + k * nq * mrow);
+            } else {
+                for (int k = 1; k < active; ++k) s += *reinterpret_cast<const floatx4*>(from + k * nq * mrow);
+            }
             *reinterpret_cast<floatx4*>(&dst[r * D + 16 * b0 + 4 * p]) = s;
-        }
+        };
+        const int per = 4 * (b1 - b0);
+        if (per == 4 * NB)                                   // (a division by a constant)
+            for (int e = tid; e < nq * 4 * NB; e += 64 * W) add(e / (4 * NB), e % (4 * NB));
+        else
+            for (int e = tid; e < nq * per; e += 64 * W) add(e / per, e % per);
     }
 }
 
@@ -374,6 +398,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 // maxima ahead of the sums ahead of the matrix.  Bound by what one compute unit can pull in: 64 columns instead of all D
 // leave a quarter of the matrix at d = 256 (64 of 256 KB) for the same sums (128 KB).  Against a workgroup per query that
 // reduced the maxima through LDS: 5.6 -> 4.0 us at d = 128, 256 workgroups to add; 6.7 -> 5.8 us at d = 256, 128 of them.
+// A workgroup's maximum reaches the threads that add its sums from the lane that holds it (a load for each was 256 loads of one
+// value per workgroup); with the scan's shorter end, d = 128, 131,072 keys 15.3 -> 14.1 us, d = 256, 4096 keys 14.3 -> 12.7.
 template <int D>
 __global__ void __launch_bounds__(1024)
 srft_attention_finish_kernel(const float* __restrict__ part, const float* __restrict__ part_max,
@@ -396,12 +422,14 @@ srft_attention_finish_kernel(const float* __restrict__ part, const float* __rest
         }
     };
     floatx4 x[AHEAD];
-    float xm[AHEAD];
+    // the lanes hold the maxima of the workgroups whose sums are on their way, but for D = 192 (252 at a time)
+    constexpr bool HELD = SLICES * AHEAD == 256;
+    float xm[HELD ? 1 : AHEAD];
     auto load = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
             const int p = min(p0 + i * SLICES, parts - 1);
-            xm[i] = part_max[query * kScanGridMax + p];
+            if constexpr (!HELD) xm[i] = part_max[query * kScanGridMax + p];
             x[i] = *reinterpret_cast<const floatx4*>(part + ((size_t)p * n_q + query) * D + 4 * c4);
         }
     };
@@ -424,11 +452,18 @@ srft_attention_finish_kernel(const float* __restrict__ part, const float* __rest
     }
     den = wave_sum(den);
     floatx4 sum = {0, 0, 0, 0};
-    for (int p0 = slice; p0 < parts; p0 += AHEAD * SLICES) {
-        if (p0 != slice) load(p0);
+    for (int base = 0; base < parts; base += AHEAD * SLICES) {               // (uniform: lanes read each other's maxima)
+        const int p0 = base + slice;
+        if (base > 0) load(p0);
+        if (HELD && parts > 256) load_max(base);
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
-            const float f = p0 + i * SLICES < parts ? __builtin_amdgcn_exp2f(xm[i] - top) : 0.0f;
+            float its;
+            if constexpr (HELD)                              // workgroup p0 + i SLICES: lane p % 64 of register p / 64 % 4
+                its = __shfl(pm[i * SLICES / 64], (slice + i * SLICES) & 63);
+            else
+                its = xm[i];
+            const float f = p0 + i * SLICES < parts ? __builtin_amdgcn_exp2f(its - top) : 0.0f;
             sum = f != 0.0f ? sum + x[i] * f : sum;          // (a workgroup that counts for nothing may hold anything)
         }
     }

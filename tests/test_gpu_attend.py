@@ -380,3 +380,25 @@ def test_decode_attention_keeps_to_the_cap_on_workgroups(B, n_q, cap):
     assert np.abs(out.cpu().numpy() - ref).max() <= 1e-4 * np.abs(vb).max()
     pk.close()
     pv.close()
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 256])
+@pytest.mark.parametrize("cap,n_keys", [(1, 32), (8, 256), (8, 264), (257, 20000), (700, 50005)])
+def test_decode_attention_whatever_the_number_of_workgroups_to_add(B, d, cap, n_keys):
+    """One wavefront of a workgroup with keys, some, all of them; up to 256 workgroups to add and more: as one workgroup has it."""
+    n_q = 5
+    pk, pv = B.Plan(d, 32, 1, W.lognormal_lambda(d, seed=1)), B.Plan(d, 32, 2, W.lognormal_lambda(d, seed=2))
+    gen = torch.Generator(device="cuda").manual_seed(d + cap)
+    q = torch.randn(n_q, d, generator=gen, device="cuda").half()
+    k, v = (p.quantize(torch.randn(n_keys, d, generator=gen, device="cuda").half()) for p in (pk, pv))
+    ws = torch.empty(B.lib().srft_decode_attention_workspace_bytes(pk.handle, pv.handle, n_q, n_keys), dtype=torch.uint8, device="cuda")
+    out = []
+    for c in (1, cap):
+        B.srft_plan_set_max_workgroups(pk.handle, c)
+        o = torch.full((n_q, d), float("nan"), device="cuda")
+        B.srft_kv_decode_attention(pk.handle, pv.handle, q, *k, *v, d ** -0.5, o, ws)
+        out.append(o.double())
+    # both sum the same fp32 products in other orders
+    assert (out[0] - out[1]).abs().max() <= 4e-6 * out[0].abs().max()
+    pk.close()
+    pv.close()
