@@ -155,7 +155,8 @@ __device__ __forceinline__ void srft_wht(float (&x)[L]) {
 // Everything is multiplied by factor (1 or -1).  `fetch` is called when the loads of the queries and the table are on their way, for the caller's own: their wait does not include it.
 // scratch: srft_query_scratch_bytes bytes of LDS, 16-byte aligned, free again on return (all wavefronts have passed a barrier).
 template <int D, int RB> constexpr int kQueryMid = 16 * RB * 9 * (D / 16 + 1) * 8;       // bytes: [query][k1][j], padded
-template <int D> constexpr int kQueryRow = D + 4;            // floats: [query][p], padded; [D] takes what nobody reads
+template <int D> constexpr int kQueryRow = D + 12;           // floats: [query][p], padded (9 bins of 5 queries side by side, 4 channels of 16
+                                                             // queries on different banks); [D] takes what nobody reads
 template <int D, int RB>
 constexpr int srft_query_scratch_bytes() {
     return kQueryMid<D, RB> + 16 * RB * kQueryRow<D> * 4;
@@ -187,7 +188,7 @@ srft_query_operands(const uint4* __restrict__ q, int n_q, int q0, const uint4* _
 #pragma unroll
         for (int i = 0; i < PER; ++i)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) mul[i][e] = reinterpret_cast<const floatx4*>(table)[5 * L + 2 * ((tid + NT * i) % U) + e];
+            for (int e = 0; e < 2; ++e) mul[i][e] = reinterpret_cast<const floatx4*>(table)[5 * L + 2 * ((tid + NT * i) / 16 % U) + e];
     __builtin_amdgcn_sched_barrier(0);
     fetch();
     __builtin_amdgcn_sched_barrier(0);
@@ -250,7 +251,8 @@ srft_query_operands(const uint4* __restrict__ q, int n_q, int q0, const uint4* _
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int at = tid + NT * i, query = at / U, u = at % U;
+        // (16 neighbouring lanes have the 16 queries of a block: the other way round their writes all hit the same banks)
+        const int at = tid + NT * i, u = at / 16 % U, query = at % 16 + at / (16 * U) * 16;
         if (16 * RB * U % NT == 0 || query < 16 * RB) {
             const float* const row = z + query * kQueryRow<D> + 8 * u;
             const floatx4 lo4 = *reinterpret_cast<const floatx4*>(row), hi4 = *reinterpret_cast<const floatx4*>(row + 4);
