@@ -20,7 +20,7 @@
 // queries on the columns of the second product the sums belong to the same query.
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
 // d = 128, 8 queries, 131,072 keys 36.6 -> 14.0, 400,000 keys 51 -> 24; 32 queries, 400,000 keys 111 -> 38; d = 256, 4 queries,
-// 4096 keys 27.7 -> 12.7; d = 64, 1 query, 500 keys 21.9 -> 10.5.  Error against 64 bits 6e-6 -> 4e-7.
+// 4096 keys 27.7 -> 10.8; d = 64, 1 query, 500 keys 21.9 -> 10.5.  Error against 64 bits 6e-6 -> 4e-7.
 #include <algorithm>
 
 #include "../rotated_queries.h"
@@ -247,7 +247,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
                 for (int i = 0; i < 4; ++i) w[b][i] = j == 0 ? s[i] * scv[i] : fmaf(s[i], scv[i], w[b][i]);
             }
             kc = kn;
-            __builtin_amdgcn_sched_barrier(0);               // one group's operands at a time (registers)
+            // one group's operands at a time, or two where a group is two chains of products only (registers)
+            if (KEYS == 64 || j % 2) __builtin_amdgcn_sched_barrier(0);
         }
         fetch_k(more ? tile + stride : tile, more);
         VStep vc, vn;
@@ -321,7 +322,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
                 }
             }
             vc = vn;
-            __builtin_amdgcn_sched_barrier(0);
+            if (KEYS == 64 || j % 2) __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
@@ -400,66 +401,71 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 // reduced the maxima through LDS: 5.6 -> 4.0 us at d = 128, 256 workgroups to add; 6.7 -> 5.8 us at d = 256, 128 of them.
 // A workgroup's maximum reaches the threads that add its sums from the lane that holds it (a load for each was 256 loads of one
 // value per workgroup); with the scan's shorter end, d = 128, 131,072 keys 15.3 -> 14.1 us, d = 256, 4096 keys 14.3 -> 12.7.
-template <int D>
+// AHEAD: rows of sums a thread asks for at once, for 64, 128 or 256 (D = 192: 63, 126, 252) workgroups to add in one pass; what is
+// not needed costs as much as what is (4096 keys at d = 256, 128 of them, 12.8 -> 12.0 us; a branch around each load 0.3 us where all
+// are needed).
+template <int D, int AHEAD>
 __global__ void __launch_bounds__(1024)
 srft_attention_finish_kernel(const float* __restrict__ part, const float* __restrict__ part_max,
                              const float* __restrict__ part_sum, int parts, int n_q, const float4* __restrict__ rmat,
                              float* __restrict__ out) {
-    constexpr int C4 = D / 4, SLICES = 1024 / C4, AHEAD = D / 16, KS = D / 64;
+    constexpr int C4 = D / 4, SLICES = 1024 / C4, KS = D / 64;
+    constexpr bool HELD = D != 192;                          // the lanes hold the maxima of the workgroups whose sums are on their way
+    constexpr int PM = HELD ? SLICES * AHEAD / 64 : 4;       // of 64 PM workgroups
+    static_assert(!HELD || PM * 64 == SLICES * AHEAD, "whole wavefronts of them");
     constexpr int ROWS = D == 192 ? SLICES : 16;             // partial sums that meet in LDS (else one per wavefront)
     __shared__ __align__(16) float red[ROWS * D];
     __shared__ __align__(16) float accs[D];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, query = blockIdx.x;
     const int c4 = tid % C4, slice = tid / C4;
     // every wavefront finds the maximum and the sum of the weights for itself
-    float pm[4], ps[4];
+    float pm[PM], ps[PM];
     auto load_max = [&](int p0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < PM; ++i) {
             const int p = min(p0 + 64 * i + lane, parts - 1);
             pm[i] = part_max[query * kScanGridMax + p];
             ps[i] = p0 + 64 * i + lane < parts ? part_sum[query * kScanGridMax + p] : 0.0f;
         }
     };
     floatx4 x[AHEAD];
-    // the lanes hold the maxima of the workgroups whose sums are on their way, but for D = 192 (252 at a time)
-    constexpr bool HELD = SLICES * AHEAD == 256;
     float xm[HELD ? 1 : AHEAD];
-    auto load = [&](int p0) __attribute__((always_inline)) {
+    auto load = [&](int base) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
-            const int p = min(p0 + i * SLICES, parts - 1);
+            const int p = min(base + slice + i * SLICES, parts - 1);
             if constexpr (!HELD) xm[i] = part_max[query * kScanGridMax + p];
             x[i] = *reinterpret_cast<const floatx4*>(part + ((size_t)p * n_q + query) * D + 4 * c4);
         }
     };
     load_max(0);
-    load(slice);
+    load(0);
     float4 m[KS];
 #pragma unroll
     for (int i = 0; i < KS; ++i) m[i] = rmat[(KS * (tid / 16) + i) * C4 + 16 * blockIdx.y + tid % 16];
     float top = kLowest;
-    for (int p0 = 0; p0 < parts; p0 += 256) {                // (one pass up to 256 workgroups)
+    for (int p0 = 0; p0 < parts; p0 += 64 * PM) {            // (one pass but where a cap asks for more than 256 workgroups)
         if (p0) load_max(p0);
-        top = fmaxf(top, fmaxf(fmaxf(pm[0], pm[1]), fmaxf(pm[2], pm[3])));
+#pragma unroll
+        for (int i = 0; i < PM; ++i) top = fmaxf(top, pm[i]);
     }
     top = wave_max(top);
     float den = 0.0f;
-    for (int p0 = 0; p0 < parts; p0 += 256) {
-        if (parts > 256) load_max(p0);
+    for (int p0 = 0; p0 < parts; p0 += 64 * PM) {
+        if (parts > 64 * PM) load_max(p0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) den = fmaf(ps[i], __builtin_amdgcn_exp2f(pm[i] - top), den);
+        for (int i = 0; i < PM; ++i) den = fmaf(ps[i], __builtin_amdgcn_exp2f(pm[i] - top), den);
     }
     den = wave_sum(den);
     floatx4 sum = {0, 0, 0, 0};
     for (int base = 0; base < parts; base += AHEAD * SLICES) {               // (uniform: lanes read each other's maxima)
         const int p0 = base + slice;
-        if (base > 0) load(p0);
-        if (HELD && parts > 256) load_max(base);
+        if (base > 0) load(base);
+        if (HELD && parts > 64 * PM) load_max(base);
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
             float its;
-            if constexpr (HELD)                              // workgroup p0 + i SLICES: lane p % 64 of register p / 64 % 4
+            if constexpr (HELD)                              // workgroup p0 + i SLICES: lane p % 64 of register p / 64 % PM
                 its = __shfl(pm[i * SLICES / 64], (slice + i * SLICES) & 63);
             else
                 its = xm[i];
@@ -524,6 +530,10 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     const bool narrow = n_keys <= 32 * kWaves * grid;
     const long long n_tiles = narrow ? (n_keys + 31) / 32 : (n_keys + 63) / 64;
     if (grid > n_tiles) grid = n_tiles;
+    // (63, 126 or 252 are what the finish adds in one pass at D = 192: 8192 keys, 8 queries 14.2 -> 12.4 us)
+    if (D == 192)
+        for (const long long one_pass : {63, 126, 252})
+            if (grid > one_pass && grid <= one_pass + one_pass / 63) grid = one_pass;
     static_assert((size_t)kScanGridMax * 32 * (2 + D) <= srft_attend_workspace_floats(D), "fits what callers are told to bring");
     float* part_max = (float*)workspace;                     // [32][kScanGridMax] each
     float* part_sum = part_max + kScanGridMax * 32;
@@ -536,7 +546,11 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
                        (const uint4*)pk->q_table, (int)(pk->transform == SRFT_TRANSFORM_HADAMARD), sign, k_codes, k_scales, pk->gw, v_codes,
                        v_scales, pv->gw, n_keys, sign * softmax_scale, part, part_max, part_sum);
     SRFT_HIP(hipGetLastError());
-    hipLaunchKernelGGL(srft_attention_finish_kernel<D>, dim3((unsigned)n_q, D / 64), dim3(1024), 0, st, (const float*)part,
+    constexpr int A = D / 16, most_at_once = D == 192 ? 252 : 256;
+    const auto finish = grid <= most_at_once / 4   ? srft_attention_finish_kernel<D, A / 4>
+                        : grid <= most_at_once / 2 ? srft_attention_finish_kernel<D, A / 2>
+                                                   : srft_attention_finish_kernel<D, A>;
+    hipLaunchKernelGGL(finish, dim3((unsigned)n_q, D / 64), dim3(1024), 0, st, (const float*)part,
                        (const float*)part_max, (const float*)part_sum, (int)grid, n_q, (const float4*)pv->rmat_f32, out);
     SRFT_HIP(hipGetLastError());
     return SRFT_OK;

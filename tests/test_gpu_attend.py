@@ -383,7 +383,8 @@ def test_decode_attention_keeps_to_the_cap_on_workgroups(B, n_q, cap):
 
 
 @pytest.mark.parametrize("d", [64, 128, 192, 256])
-@pytest.mark.parametrize("cap,n_keys", [(1, 32), (8, 256), (8, 264), (257, 20000), (700, 50005)])
+@pytest.mark.parametrize("cap,n_keys", [(1, 32), (8, 256), (8, 264), (64, 4000), (65, 4000), (128, 5000), (129, 5000), (256, 20000),
+                                        (257, 20000), (700, 50005)])
 def test_decode_attention_whatever_the_number_of_workgroups_to_add(B, d, cap, n_keys):
     """One wavefront of a workgroup with keys, some, all of them; up to 256 workgroups to add and more: as one workgroup has it."""
     n_q = 5
