@@ -111,7 +111,7 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
 }
 
 // The whole batch as one launch without a table, where its counts are equal and its addresses and plan entries a constant step
-// apart (srft_batch_even); blocks: workgroups per segment.  False: not such a batch.
+// apart (srft_batch_even).  False: not such a batch.
 bool even_batch(const srft_plan_t* const* plans, const void* const* in, void* const* out, const void* const* scales,
                 const int64_t* n_vec, int count, bool write_path, srft_batch_even* a) {
     for (int i = 1; i < count; ++i)
@@ -124,10 +124,10 @@ bool even_batch(const srft_plan_t* const* plans, const void* const* in, void* co
         !srft_even_step(scales, count, &a->scales_step))
         return false;
     const srft_plan* p = plans[0];
-    a->blocks = srft_even_blocks((n_vec[0] + kTileVecs - 1) / kTileVecs, count,
-                                 p->max_wgs > 0 ? p->max_wgs : write_path ? p->grid_q : p->grid_dq);
-    if (a->blocks == 0) return false;
-    a->magic = srft_even_magic(a->blocks);
+    const long long tiles = (n_vec[0] + kTileVecs - 1) / kTileVecs, budget = p->max_wgs > 0 ? p->max_wgs : write_path ? p->grid_q : p->grid_dq;
+    const int blocks = srft_even_blocks(tiles, count, budget);
+    if (blocks == 0) return false;
+    a->shape = srft_even_spread(tiles, count, write_path ? (long long)blocks * count : budget, blocks);
     a->plan = p->entry;
     a->in = (const char*)in[0];
     a->out = (char*)out[0];
@@ -160,7 +160,7 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
         int threads = 0;
         const batched_kernels_t kernel = batched_kernels(plans[0], write_path, &threads);
         if (!kernel.even) return SRFT_ERR_BAD_D;
-        return srft_launch(kernel.even, dim3((unsigned)(even.blocks * count)), threads, st, even, plans[0]->gw);
+        return srft_launch(kernel.even, dim3((unsigned)srft_even_grid(even.shape, count)), threads, st, even, plans[0]->gw);
     }
     srft_batch_many a;
     int k = 0;

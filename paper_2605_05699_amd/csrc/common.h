@@ -57,6 +57,7 @@
 #include <cstdint>
 #include <vector>
 
+#include "launch_shape.h"
 #include "srft_kv.h"
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -110,7 +111,7 @@ struct srft_plan_entry {
     uint64_t unused;
 };
 // Segments of one length whose addresses (and whose plans' entries) lie a constant number of bytes apart: a cache that is one
-// tensor over its layers, a step that appends the same number of vectors to each.  blocks workgroups per segment.  A launch of up
+// tensor over its layers, a step that appends the same number of vectors to each.  A launch of up
 // to 104 bytes of arguments takes 2.7-2.9 us of the host, one of 112 to 900 3.5, one of 3.8 KiB 4.2, and any number of segments
 // fits.  us a call, against the tables: write 2 plans x 256 vectors at d = 128 4.1 -> 3.8, 64 x 512 at d = 96 4.9 -> 4.3, 100 x 700
 // at d = 128 13.7 -> 8.9 (two launches before), read 9 x 100 at d = 96 5.3 -> 4.6; 56 x 8192 and 4 x 1,048,576 within 0.5 %.
@@ -122,8 +123,7 @@ struct srft_batch<0> {
     char* scales;
     long long plan_step, in_step, out_step, scales_step;      // bytes
     long long n_vec;                                          // of each segment
-    int blocks;
-    uint32_t magic;                                           // srft_even_magic(blocks)
+    srft_even_shape shape;                                    // which workgroups serve which
 };
 using srft_batch_even = srft_batch<0>;
 static_assert(sizeof(srft_batch_even) + sizeof(int) <= 96, "a small launch");

@@ -122,11 +122,11 @@ __device__ __forceinline__ srft_work srft_work_of_block(const srft_batch<N>& a) 
     const int q = gridDim.x >> 3, r = gridDim.x & 7, die = blockIdx.x & 7;
     const int block = die * q + min(die, r) + (int)(blockIdx.x >> 3);        // a permutation of 0 .. gridDim.x - 1
     if constexpr (N == 0) {                                  // segments of one length, a constant step apart
-        const int i = srft_even_segment((uint32_t)block, a.magic);
+        const int i = srft_even_segment(block, a.shape), start = srft_even_start(i, a.shape);
         const srft_plan_entry* e = reinterpret_cast<const srft_plan_entry*>(reinterpret_cast<const char*>(a.plan) + i * a.plan_step);
         return {(const uint4*)(const __attribute__((address_space(1))) uint4*)e->table[WRITE ? 0 : 1], a.in + i * a.in_step, a.out + i * a.out_step,
-                reinterpret_cast<float*>(a.scales + i * a.scales_step), a.n_vec, e->unscale[WRITE ? 0 : 1], a.blocks,
-                block - i * a.blocks};
+                reinterpret_cast<float*>(a.scales + i * a.scales_step), a.n_vec, e->unscale[WRITE ? 0 : 1],
+                srft_even_start(i + 1, a.shape) - start, block - start};
     } else {
         const int lane = threadIdx.x & 63, first = lane < N ? a.first_block[lane & (N - 1)] : INT32_MAX;
         const int i = (int)__popcll(__ballot(first <= block)) - 1;

@@ -15,6 +15,17 @@ extern "C" int share_out(const long long* tiles, int count, long long budget, sr
 }
 extern "C" int even_blocks(long long tiles, long long count, long long budget) { return srft_even_blocks(tiles, count, budget); }
 extern "C" int even_segment(unsigned block, int blocks) { return srft_even_segment(block, srft_even_magic(blocks)); }
+extern "C" int spread(long long tiles, long long count, long long budget, int* segment, int* place, int* blocks, int most) {
+    const int each = srft_even_blocks(tiles, count, budget);
+    if (!each) return 0;
+    const srft_even_shape e = srft_even_spread(tiles, count, budget, each);
+    const int grid = srft_even_grid(e, count);
+    for (int b = 0; b < grid && b < most; ++b) {
+        const int i = srft_even_segment(b, e), start = srft_even_start(i, e);
+        segment[b] = i, place[b] = b - start, blocks[b] = srft_even_start(i + 1, e) - start;
+    }
+    return grid;
+}
 extern "C" int even_step(const void* const* p, int count, long long* step) { return srft_even_step(p, count, step); }
 extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
 extern "C" long long copy_first(int i) { return srft_copy_first(i); }
@@ -153,3 +164,23 @@ def test_addresses_a_constant_step_apart(lib):
     assert step(4096, 8192, 12288) == 4096 and step(2 ** 40, 2 ** 40 - 16, 2 ** 40 - 32) == -16
     assert step(4096, 8192, 12304) is None and step(16, 32, 48, 16) is None
     assert step(0x7F0000000000, 0x10) == 0x10 - 0x7F0000000000
+
+
+@pytest.mark.parametrize("count,tiles,budget", [(1, 5, 3), (52, 128, 512), (56, 256, 1024), (80, 300, 1024), (100, 22, 768), (7, 9, 8), (5, 3, 14),
+                                                (9, 1, 9), (3, 1000, 7), (1000, 3, 2048), (64, 16, 512), (33, 4096, 1024), (2048, 100, 2048)])
+def test_leftover_workgroups_are_spread(lib, count, tiles, budget):
+    most = 1 << 16
+    segment, place, blocks = ((C.c_int * most)() for _ in range(3))
+    grid = lib.spread(C.c_longlong(tiles), C.c_longlong(count), C.c_longlong(budget), segment, place, blocks, most)
+    each = lib.even_blocks(C.c_longlong(tiles), C.c_longlong(count), C.c_longlong(budget))
+    if not each:
+        return
+    assert grid <= most and each * count <= grid <= max(budget, each * count) and grid <= tiles * count
+    assert grid == min(budget, tiles * count) or grid * grid * count >= 2 ** 31 or min(budget, tiles * count) ** 2 * count >= 2 ** 31
+    seen = {}
+    for b in range(grid):                                # every segment once, in order, its workgroups 0 .. blocks - 1
+        assert segment[b] == (segment[b - 1] if b and place[b] else (segment[b - 1] + 1 if b else 0))
+        assert place[b] == (place[b - 1] + 1 if b and segment[b] == segment[b - 1] else 0)
+        seen[segment[b]] = seen.get(segment[b], 0) + 1
+    assert sorted(seen) == list(range(count))
+    assert all(blocks[b] == seen[segment[b]] and seen[segment[b]] in (each, each + 1) and blocks[b] <= tiles for b in range(grid))
