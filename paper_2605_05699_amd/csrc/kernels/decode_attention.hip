@@ -19,7 +19,7 @@
 // the second product takes as its B operand and what a running maximum and its correction need; with channels on the rows and
 // queries on the columns of the second product the sums belong to the same query.
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
-// d = 128, 8 queries, 131,072 keys 36.6 -> 14.0, 400,000 keys 51 -> 24; 32 queries, 400,000 keys 111 -> 38; d = 256, 4 queries,
+// d = 128, 8 queries, 131,072 keys 36.6 -> 13.6, 400,000 keys 51 -> 23; 32 queries, 400,000 keys 111 -> 38; d = 256, 4 queries,
 // 4096 keys 27.7 -> 10.8; d = 64, 1 query, 500 keys 21.9 -> 10.5.  Error against 64 bits 6e-6 -> 4e-7.
 #include <algorithm>
 
@@ -69,7 +69,10 @@ __device__ __forceinline__ float wave_sum(float x) {
 // D: head dimension.  KEYS: keys per tile, 64 or 32.  WIDE: groups of gw > 1 runs of 32 channels share a scale.
 // blockIdx.y: block of 16 queries.  (Both blocks of 32 queries in one wavefront -- the codes decoded once -- needs more
 // registers than two wavefronts per SIMD leave: 250 spilled at d = 128.)
-template <int D, int KEYS, bool WIDE>
+// ONE: no wavefront has more than one tile (up to 131,072 keys and 16 queries on a whole chip): nothing is asked for behind it and
+// nothing scaled down (and 110 registers do where 201 did, d = 128).  us: 8 queries, 131,072 keys at d = 128 13.8 -> 13.6, at d = 256
+// 22.9 -> 22.4; 16 queries, 9000 keys at d = 256 15.3 -> 15.0; 8 queries, 60,000 keys at d = 192 15.0 -> 14.75.
+template <int D, int KEYS, bool WIDE, bool ONE>
 __global__ void __launch_bounds__(64 * kWaves, 2)
 srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ q_table,
                            int hadamard, float q_sign, const uint8_t* __restrict__ k_codes,
@@ -219,7 +222,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         // The next tile goes into the registers that have just been read.  Not under a branch (the compiler then keeps both
         // sets: 100 registers more at d = 128): past the end every lane reads the first row of this tile again.
-        fetch_v(more ? tile + stride : tile, more);
+        if constexpr (!ONE) fetch_v(more ? tile + stride : tile, more);
         // ---- scores: keys on the rows, queries on the columns
         float w[BK][4];
 #pragma unroll
@@ -247,10 +250,10 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
                 for (int i = 0; i < 4; ++i) w[b][i] = j == 0 ? s[i] * scv[i] : fmaf(s[i], scv[i], w[b][i]);
             }
             kc = kn;
-            // one group's operands at a time, or two where a group is two chains of products only (registers)
-            if (KEYS == 64 || j % 2) __builtin_amdgcn_sched_barrier(0);
+            // one group's operands at a time (registers), or two where they allow it
+            if ((KEYS == 64 && !ONE) || j % 2) __builtin_amdgcn_sched_barrier(0);
         }
-        fetch_k(more ? tile + stride : tile, more);
+        if constexpr (!ONE) fetch_k(more ? tile + stride : tile, more);
         VStep vc, vn;
         load_v(vc, 0);
         // ---- running softmax, per query (column)
@@ -282,7 +285,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             const int fit_now = 140 - max((int)((__float_as_uint(big) >> 23) & 0xFF), 27);    // 13 - exponent, at most 113
             const float change = __builtin_ldexpf(down, fit_now - fit);
             fit = fit_now;
-            if (tile != first && __ballot(change != 1.0f))   // uniform
+            if (!ONE && tile != first && __ballot(change != 1.0f))           // uniform
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b] *= change;
 #pragma unroll
@@ -322,9 +325,10 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
                 }
             }
             vc = vn;
-            if (KEYS == 64 || j % 2) __builtin_amdgcn_sched_barrier(0);
+            if ((KEYS == 64 && !ONE) || j % 2) __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if constexpr (ONE) break;
     }
     // ---- the wavefronts of the workgroup that had a tile meet
     const int active = (int)min((long long)W, (n_tiles - 1 - blockIdx.x) / gridDim.x + 1);
@@ -540,20 +544,23 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     float* part = part_sum + kScanGridMax * 32;              // [workgroup][n_q][D]
     const bool wide = pk->gw > 1 || pv->gw > 1;
     const float sign = softmax_scale < 0.0f ? -1.0f : 1.0f;  // goes into the queries: the kernel's scale is not negative
-    auto kernel = narrow ? (wide ? srft_attention_scan_kernel<D, 32, true> : srft_attention_scan_kernel<D, 32, false>)
-                         : (wide ? srft_attention_scan_kernel<D, 64, true> : srft_attention_scan_kernel<D, 64, false>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid, blocks), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q,
-                       (const uint4*)pk->q_table, (int)(pk->transform == SRFT_TRANSFORM_HADAMARD), sign, k_codes, k_scales, pk->gw, v_codes,
-                       v_scales, pv->gw, n_keys, sign * softmax_scale, part, part_max, part_sum);
-    SRFT_HIP(hipGetLastError());
+    const bool one = n_tiles <= kWaves * grid;
+    const auto pick = [&](auto many, auto once) { return one ? once : many; };
+    const auto kernel =
+        narrow ? (wide ? pick(srft_attention_scan_kernel<D, 32, true, false>, srft_attention_scan_kernel<D, 32, true, true>)
+                       : pick(srft_attention_scan_kernel<D, 32, false, false>, srft_attention_scan_kernel<D, 32, false, true>))
+               : (wide ? pick(srft_attention_scan_kernel<D, 64, true, false>, srft_attention_scan_kernel<D, 64, true, true>)
+                       : pick(srft_attention_scan_kernel<D, 64, false, false>, srft_attention_scan_kernel<D, 64, false, true>));
+    const int rc = srft_launch(kernel, dim3((unsigned)grid, blocks), 64 * kWaves, st, (const uint4*)q, n_q, (const uint4*)pk->q_table,
+                               (int)(pk->transform == SRFT_TRANSFORM_HADAMARD), sign, k_codes, k_scales, pk->gw, v_codes, v_scales,
+                               pv->gw, n_keys, sign * softmax_scale, part, part_max, part_sum);
+    if (rc != SRFT_OK) return rc;
     constexpr int A = D / 16, most_at_once = D == 192 ? 252 : 256;
     const auto finish = grid <= most_at_once / 4   ? srft_attention_finish_kernel<D, A / 4>
                         : grid <= most_at_once / 2 ? srft_attention_finish_kernel<D, A / 2>
                                                    : srft_attention_finish_kernel<D, A>;
-    hipLaunchKernelGGL(finish, dim3((unsigned)n_q, D / 64), dim3(1024), 0, st, (const float*)part,
-                       (const float*)part_max, (const float*)part_sum, (int)grid, n_q, (const float4*)pv->rmat_f32, out);
-    SRFT_HIP(hipGetLastError());
-    return SRFT_OK;
+    return srft_launch(finish, dim3((unsigned)n_q, D / 64), 1024, st, (const float*)part, (const float*)part_max, (const float*)part_sum,
+                       (int)grid, n_q, (const float4*)pv->rmat_f32, out);
 }
 
 }  // namespace

@@ -177,10 +177,8 @@ int launch(const srft_plan* p, const void* q, int n_q, const uint8_t* codes, con
     auto kernel = n_q <= 8    ? (wide ? srft_scores_kernel<D, 1, true, false> : srft_scores_kernel<D, 1, false, false>)
                   : n_q <= 16 ? (wide ? srft_scores_kernel<D, 1, true, true> : srft_scores_kernel<D, 1, false, true>)
                               : (wide ? srft_scores_kernel<D, 2, true, true> : srft_scores_kernel<D, 2, false, true>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * kWaves), 0, st, (const uint4*)q, n_q, (const uint4*)p->q_table,
+    return srft_launch(kernel, dim3((unsigned)grid), 64 * kWaves, st, (const uint4*)q, n_q, (const uint4*)p->q_table,
                        (int)(p->transform == SRFT_TRANSFORM_HADAMARD), codes, scales, p->gw, n_keys, out);
-    SRFT_HIP(hipGetLastError());
-    return SRFT_OK;
 }
 
 }  // namespace
