@@ -248,12 +248,15 @@ int srft_hip_fail(hipError_t e);         // records the error for srft_last_hip_
     } while (0)
 
 // One launch.  (The triple-chevron form and hipLaunchKernelGGL park the configuration and fetch it back, 0.1-0.2 us.)
+// A refusal is told once, by the return value: HIP's last error, which the caller's own checks read, is cleared.
 template <class T> struct srft_same { using type = T; };
 template <class... P>
 int srft_launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t st, const typename srft_same<P>::type&... args) {
     void* p[] = {const_cast<void*>(static_cast<const void*>(&args))...};
-    SRFT_HIP(hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3((unsigned)threads), p, 0, st));
-    return SRFT_OK;
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3((unsigned)threads), p, 0, st);
+    if (e == hipSuccess) return SRFT_OK;
+    (void)hipGetLastError();
+    return srft_hip_fail(e);
 }
 
 // the kernels a plan launches, and their block sizes

@@ -3,6 +3,7 @@ and rejects bad arguments before touching HIP."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -153,3 +154,34 @@ def test_workload_table_matches_the_stated_shapes():
     seed, lam, gain = W.plan_constants(w["tiny"], 0)
     assert lam.shape == (128,) and (lam > 0).all() and int((gain == 20).sum()) == 4
     assert np.isclose(float(a.float().std()), float(np.sqrt((gain ** 2).mean())), rtol=0.1)
+
+
+LAUNCH = """
+#include <cstdio>
+#include <utility>
+#include "common.h"
+int told = 0;
+hipError_t last = hipSuccess;
+// in place of the runtime's (which, without a device, has the same answer to every call)
+extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return last = hipErrorInvalidConfiguration; }
+extern "C" hipError_t hipGetLastError() { return std::exchange(last, hipSuccess); }
+int srft_hip_fail(hipError_t e) {
+    told = (int)e;
+    return SRFT_ERR_HIP;
+}
+__global__ void nothing(int) {}
+int main() {
+    const int rc = srft_launch(nothing, dim3(1), 64, nullptr, 3);
+    std::printf("%d %d %d", told, rc, (int)hipGetLastError());
+}
+"""
+
+
+def test_a_refused_launch_leaves_no_error_behind(tmp_path):
+    """The error comes back from the call; the caller's own next check of HIP's last error is not told it again."""
+    from paper_2605_05699_amd import build
+    src, exe = tmp_path / "launch.hip", tmp_path / "launch"
+    src.write_text(LAUNCH)
+    subprocess.run([build.hipcc(), *build.FLAGS, "-I", build.CSRC, str(src), "-o", str(exe)], check=True, capture_output=True)
+    told, rc, left = map(int, subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout.split())
+    assert (told, rc, left) == (9, -6, 0)                    # (9: hipErrorInvalidConfiguration)
