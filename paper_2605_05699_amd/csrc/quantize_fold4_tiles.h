@@ -315,8 +315,8 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
             }
         } else if (tid < kTileVecs * SR / 4) {           // uniform per wavefront
             const int r = tid / (SR / 4), q = tid % (SR / 4);
-            const float4 v = *reinterpret_cast<const float4*>(&sstage[b][r * SR + 4 * q]);
-            reinterpret_cast<float4*>(scales + row0 * SR)[(unsigned)(min(r, lim) * (SR / 4) + q)] = v;
+            const floatx4 v = *reinterpret_cast<const floatx4*>(&sstage[b][r * SR + 4 * q]);
+            reinterpret_cast<floatx4u*>(scales + row0 * SR)[(unsigned)(min(r, lim) * (SR / 4) + q)] = v;
         }
     };
     // AMAX: lanes of one half hold the same 32 indices for 32 different vectors: they meet in LDS (the tile buffers,

@@ -4,8 +4,6 @@
 #define SRFT_ROTATED_QUERIES_H
 #include "device_util.h"
 
-typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));     // scales and scores are 4-byte aligned
-
 __device__ __forceinline__ uint2 swap16(uint32_t a, uint32_t b) {
     const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
     return make_uint2(r[0], r[1]);

@@ -528,3 +528,22 @@ def test_write_path_at_d256_through_its_stages_for_every_group_size(B, g, bits):
         B.srft_kv_quantize_batched(B.BatchTable([plan.handle] * len(parts), [x[p] for p in parts], [cb[p] for p in parts], [sb[p] for p in parts]))
         assert torch.equal(cb, codes) and torch.equal(sb, scales), n
     plan.close()
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("d,g", [(256, 16), (256, 32), (256, 64), (256, 256), (128, 32), (96, 16)])
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_scales_aligned_to_four_bytes_only(B, d, g, bits, off):
+    """Scales `off` floats behind a 16-byte boundary: the same record, nothing beside it, and read back alike."""
+    n = 200
+    plan = B.Plan(d, g, 5 + g, W.lognormal_lambda(d, seed=g), bits=bits)
+    x = torch.from_numpy(W.gaussian_with_outliers(n, d, seed=d + g, outliers=1)).cuda()
+    codes, scales = plan.quantize(x)
+    room = torch.full((n * (d // g) + 8,), -1.0, device="cuda")
+    shifted, c = room[off:off + n * (d // g)].view(n, d // g), torch.empty_like(codes)
+    assert shifted.data_ptr() % 16 == 4 * off
+    B.srft_kv_quantize(plan.handle, x, c, shifted)
+    assert torch.equal(c, codes) and torch.equal(shifted, scales)
+    assert bool((room[:off] == -1.0).all()) and bool((room[off + scales.numel():] == -1.0).all())
+    assert torch.equal(plan.dequantize(codes, shifted), plan.dequantize(codes, scales))
+    plan.close()
