@@ -1,7 +1,7 @@
 // cache.hip -- cache manager: host bookkeeping around the batched kernels (int4 store, fp16 residual window,
 // dequantized view), and the small scatter kernel that places new tokens in the paged view.
 #include <algorithm>
-#include <new>
+#include <memory>
 
 #include "common.h"
 #include "launch_shape.h"
@@ -60,17 +60,18 @@ int srft_cache_create(srft_cache_t** out, const srft_plan_t* const* plans, int n
         if (!srft_aligned(codes_dev[i], 16) || !srft_aligned(scales_dev[i], 4) || !srft_aligned(view_f16_dev[i], 16))
             return SRFT_ERR_ALIGN;
     }
-    srft_cache* c = new (std::nothrow) srft_cache();
-    if (!c) return SRFT_ERR_HIP;
-    c->plans.assign(plans, plans + n_plans);
-    c->codes.assign(codes_dev, codes_dev + n_plans);
-    c->scales.assign(scales_dev, scales_dev + n_plans);
-    c->view.assign(view_f16_dev, view_f16_dev + n_plans);
-    c->n_seq = n_seq;
-    c->R = residual_tokens;
-    c->capacity = capacity_tokens;
-    *out = c;
-    return SRFT_OK;
+    return srft_no_throw([&] {
+        auto c = std::make_unique<srft_cache>();
+        c->plans.assign(plans, plans + n_plans);
+        c->codes.assign(codes_dev, codes_dev + n_plans);
+        c->scales.assign(scales_dev, scales_dev + n_plans);
+        c->view.assign(view_f16_dev, view_f16_dev + n_plans);
+        c->n_seq = n_seq;
+        c->R = residual_tokens;
+        c->capacity = capacity_tokens;
+        *out = c.release();
+        return (int)SRFT_OK;
+    });
 }
 
 int srft_cache_destroy(srft_cache_t* cache) {
@@ -156,7 +157,7 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
     //    decodes to (the window is "re-quantized when full"; the dequantized prefix is refreshed only here)
     const int64_t full = cache->tokens / cache->R * cache->R;
     if (full > cache->quantized) {
-        const int rc = cache_convert(cache, cache->quantized, full - cache->quantized, true, st);
+        const int rc = srft_no_throw([&] { return cache_convert(cache, cache->quantized, full - cache->quantized, true, st); });
         if (rc != SRFT_OK) return rc;
         cache->quantized = full;
     }
@@ -166,7 +167,7 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
 int srft_cache_rebuild_view(srft_cache_t* cache, void* hip_stream) {
     if (!cache) return SRFT_ERR_NULL;
     if (cache->quantized == 0) return SRFT_OK;
-    return cache_convert(cache, 0, cache->quantized, false, (hipStream_t)hip_stream);
+    return srft_no_throw([&] { return cache_convert(cache, 0, cache->quantized, false, (hipStream_t)hip_stream); });
 }
 
 }  // extern "C"

@@ -248,6 +248,16 @@ int srft_hip_fail(hipError_t e);         // records the error for srft_last_hip_
         if (e_ != hipSuccess) return srft_hip_fail(e_);  \
     } while (0)
 
+// The body of an entry point that allocates on the host: what it throws becomes a status.
+template <class F>
+int srft_no_throw(F body) {
+    try {
+        return body();
+    } catch (...) {
+        return srft_hip_fail(hipErrorOutOfMemory);
+    }
+}
+
 // One launch.  (The triple-chevron form and hipLaunchKernelGGL park the configuration and fetch it back, 0.1-0.2 us.)
 // A refusal is told once, by the return value: HIP's last error, which the caller's own checks read, is cleared.
 template <class T> struct srft_same { using type = T; };

@@ -2,11 +2,12 @@
 // fp16 hi + lo split in MFMA operand order (plain and folded forms), the choice of kernel instances, and the
 // persistent grid sizes.
 #include <algorithm>
+#include <bitset>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
-#include <new>
 
 #include "common.h"
 
@@ -260,7 +261,7 @@ void build_query_table(int d, int transform, const std::vector<int8_t>& signs, c
 constexpr int kPlanEntries = 8192, kMaxDevices = 64;
 struct plan_table {
     srft_plan_entry* dev = nullptr;
-    std::vector<bool> taken;
+    std::bitset<kPlanEntries> taken;
     int next = 0, live = 0;
 };
 std::mutex g_plan_mutex;
@@ -273,7 +274,7 @@ hipError_t take_entry(srft_plan* p) {
     if (!t.dev) {
         const hipError_t e = hipMalloc((void**)&t.dev, kPlanEntries * sizeof(srft_plan_entry));
         if (e != hipSuccess) return e;
-        t.taken.assign(kPlanEntries, false);
+        t.taken.reset();
         t.next = 0;
     }
     if (t.live == kPlanEntries) return hipSuccess;
@@ -388,8 +389,8 @@ int srft_plan_create_bits(srft_plan_t** out, int d, int group_size, int bits, ui
     return srft_plan_create_ex(out, d, group_size, bits, SRFT_TRANSFORM_DFT, sign_seed, lambda_host);
 }
 
-int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int transform, uint64_t sign_seed,
-                        const float* lambda_host) {
+static int plan_create(srft_plan_t** out, int d, int group_size, int bits, int transform, uint64_t sign_seed,
+                       const float* lambda_host) {
     if (!out) return SRFT_ERR_NULL;
     *out = nullptr;
     if (bits != 4 && bits != 8) return SRFT_ERR_BAD_BITS;
@@ -410,8 +411,8 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
         if (hi / lo > 65536.0) return SRFT_ERR_BAD_LAMBDA;
     }
 
-    srft_plan* p = new (std::nothrow) srft_plan();
-    if (!p) return SRFT_ERR_HIP;
+    std::unique_ptr<srft_plan, int (*)(srft_plan*)> owner(new srft_plan(), srft_plan_destroy);     // (until the plan is whole)
+    srft_plan* const p = owner.get();
     p->d = d;
     p->g = group_size;
     p->bits = bits;
@@ -603,13 +604,14 @@ int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int 
         p->rfold = (uint4*)table(at_rfold, p->fold_dq);
     }
     if (e == hipSuccess) e = take_entry(p);
-    int rc = (e == hipSuccess) ? occupancy_grids(p, cus) : srft_hip_fail(e);
-    if (rc != SRFT_OK) {
-        srft_plan_destroy(p);
-        return rc;
-    }
-    *out = p;
-    return SRFT_OK;
+    const int rc = (e == hipSuccess) ? occupancy_grids(p, cus) : srft_hip_fail(e);
+    if (rc == SRFT_OK) *out = owner.release();
+    return rc;
+}
+
+int srft_plan_create_ex(srft_plan_t** out, int d, int group_size, int bits, int transform, uint64_t sign_seed,
+                        const float* lambda_host) {
+    return srft_no_throw([&] { return plan_create(out, d, group_size, bits, transform, sign_seed, lambda_host); });
 }
 
 int srft_plan_destroy(srft_plan_t* plan) {
