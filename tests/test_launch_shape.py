@@ -166,14 +166,18 @@ def test_addresses_a_constant_step_apart(lib):
     assert step(0x7F0000000000, 0x10) == 0x10 - 0x7F0000000000
 
 
-@pytest.mark.parametrize("count,tiles,budget", [(1, 5, 3), (52, 128, 512), (56, 256, 1024), (80, 300, 1024), (100, 22, 768), (7, 9, 8), (5, 3, 14),
-                                                (9, 1, 9), (3, 1000, 7), (1000, 3, 2048), (64, 16, 512), (33, 4096, 1024), (2048, 100, 2048)])
-def test_leftover_workgroups_are_spread(lib, count, tiles, budget):
+# `each`: workgroups that every segment gets, 0 where the batch goes out with a table (one segment cut where the dies meet; more
+# segments than workgroups)
+@pytest.mark.parametrize("count,tiles,budget,each", [
+    (1, 5, 3, 0), (10, 4, 9, 0), (52, 128, 512, 9), (56, 256, 1024, 18), (80, 300, 1024, 12), (100, 22, 768, 7), (7, 9, 8, 1), (5, 3, 14, 2),
+    (9, 1, 9, 1), (3, 1000, 7, 2), (1000, 3, 2048, 2), (64, 16, 512, 8), (33, 4096, 1024, 31), (2048, 100, 2048, 1)])
+def test_leftover_workgroups_are_spread(lib, count, tiles, budget, each):
     most = 1 << 16
     segment, place, blocks = ((C.c_int * most)() for _ in range(3))
     grid = lib.spread(C.c_longlong(tiles), C.c_longlong(count), C.c_longlong(budget), segment, place, blocks, most)
-    each = lib.even_blocks(C.c_longlong(tiles), C.c_longlong(count), C.c_longlong(budget))
-    if not each:
+    assert lib.even_blocks(C.c_longlong(tiles), C.c_longlong(count), C.c_longlong(budget)) == each
+    if each == 0:
+        assert grid == 0
         return
     assert grid <= most and each * count <= grid <= max(budget, each * count) and grid <= tiles * count
     assert grid == min(budget, tiles * count) or grid * grid * count >= 2 ** 31 or min(budget, tiles * count) ** 2 * count >= 2 ** 31
