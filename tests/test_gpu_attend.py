@@ -403,3 +403,28 @@ def test_decode_attention_whatever_the_number_of_workgroups_to_add(B, d, cap, n_
     assert (out[0] - out[1]).abs().max() <= 4e-6 * out[0].abs().max()
     pk.close()
     pv.close()
+
+
+@pytest.mark.parametrize("transforms", [("hadamard", "hadamard"), ("hadamard", "dft"), ("dft", "hadamard")])
+@pytest.mark.parametrize("d,g,n_q,n_keys,cap,scale", [(64, 32, 5, 33, 0, 0.1), (64, 64, 17, 5000, 1, -0.1), (128, 32, 8, 1601, 0, 0.1),
+                                                      (128, 128, 32, 900, 2, -0.1), (256, 32, 16, 769, 3, -0.1), (256, 32, 20, 4096, 0, 0.1)])
+def test_decode_attention_of_hadamard_plans(B, transforms, d, g, n_q, n_keys, cap, scale):
+    """Keys and values under either transform, both signs of the scale, one and two blocks of 16 queries."""
+    k = W.gaussian_with_outliers(n_keys, d, seed=d + n_keys, outliers=1, gain=15.0)
+    v = W.gaussian_with_outliers(n_keys, d, seed=d + n_keys + 1, outliers=0)
+    q = W.gaussian_with_outliers(n_q, d, seed=d + n_keys + 2, outliers=1, gain=4.0)
+    lam = [W.lognormal_lambda(d, seed=s) for s in (1, 2)]
+    plans = [B.Plan(d, g, 61 + i, lam[i], transform=t) for i, t in enumerate(transforms)]
+    record = [t for p, x in zip(plans, (k, v)) for t in p.quantize(torch.from_numpy(x).cuda())]
+    B.srft_plan_set_max_workgroups(plans[1].handle, cap)
+    got = _decode_attention(B, *plans, torch.from_numpy(q).cuda(), *record, scale).double().cpu().numpy()
+    host = [t.cpu().numpy() for t in record]
+    kb, vb = (O.dequantize_f64(*host[2 * i:2 * i + 2], plans[i].signs, lam[i], g, form="hadamard" if t == "hadamard" else "dense")
+              for i, t in enumerate(transforms))
+    ref = O.softmax_rows(q.astype(np.float64) @ kb.T, scale) @ vb
+    # the bound of test_decode_attention_matches_the_definition
+    ds = 4e-6 * abs(scale) * np.linalg.norm(q.astype(np.float64), axis=1).max() * np.linalg.norm(kb, axis=1).max() + 2e-7
+    tol = (2 * ds + 6e-6) * np.abs(vb).max()
+    assert np.abs(got - ref).max() <= tol, float(np.abs(got - ref).max() / tol)
+    for p in plans:
+        p.close()

@@ -103,6 +103,22 @@ def test_teams_of_a_workgroup(B, d, tiles, cap):
     plan.close()
 
 
+@pytest.mark.parametrize("d,g,transform", [(64, 32, "hadamard"), (128, 16, "dft"), (128, 32, "hadamard"), (256, 16, "dft"), (256, 32, "hadamard")])
+@pytest.mark.parametrize("tiles,cap", [(1, 0), (2, 0), (3, 1), (4, 0), (5, 1), (9, 0), (25, 1), (2188, 0)])
+def test_forms_that_groups_of_16_and_hadamard_take(B, d, g, transform, tiles, cap):
+    """The plain form with one, two and eight teams at the dimensions whose DFT is folded, and the folded one at groups of 16."""
+    n = 32 * (tiles - 1) + 1
+    x = W.gaussian_with_outliers(n, d, seed=5 * d + tiles, outliers=1, gain=4.0)
+    x[-1] *= np.float16(8.0)
+    plan = B.Plan(d, g, 60 + d, transform=transform)
+    B.srft_plan_set_max_workgroups(plan.handle, cap)
+    got = plan.channel_absmax(torch.from_numpy(x).cuda()).cpu().numpy().astype(np.float64)
+    ref = np.abs(O.srft_forward(x.astype(np.float64), plan.signs, form="hadamard" if transform == "hadamard" else "dense")).max(axis=0)
+    tol = AMAX_ERR * np.linalg.norm(x.astype(np.float64), axis=1).max() + 2.0 ** -23 * ref
+    assert np.all(np.abs(got - ref) <= tol), float((np.abs(got - ref) / tol).max())
+    plan.close()
+
+
 def test_one_team_at_many_tiles(B):
     """d = 128 from 2^16 tiles on: as the maximum over the parts of the batch, bit for bit."""
     n, d = (1 << 21) + 7, 128
