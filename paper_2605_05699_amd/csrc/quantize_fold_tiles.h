@@ -71,6 +71,7 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
     constexpr int DUMMY = 2 * M + 1;     // exchange slot for values nobody reads
     constexpr bool LEAN = (D >= SRFT_QF_LEAN_MIN_D);    // registers for one accumulator set only
     static_assert(M % 2 == 0, "the cosine and the sine block each need whole wavefronts");
+    static_assert(!AMAX || !LEAN, "the statistic at d = 256 is taken through the twice-folded form");
     __shared__ uint4 lds_of[SUB][2][kTileVecs * ROW];
     __shared__ float xch_of[SUB][2][(DUMMY + 1) * kTileVecs];
     __shared__ float gmax[WIDE ? 2 : 1][WIDE ? kTileVecs * G : 1];     // maxima of the 32-runs of a tile (WIDE)
@@ -427,7 +428,6 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
             if constexpr (STAGE) __syncthreads();
             flush(0, tl);
         }
-        emit_amax();
         return;
     }
     // stage 0
