@@ -12,12 +12,12 @@
 //    not depend on timing), divided by the sum of the weights and taken through the inverse transform.
 //
 // What bounds it: at 131,072 keys and d = 128 the record is 21 MB (4 us at the rate of a copy) and every wavefront of the chip
-// has one tile, so the time is the latency of the launches and of one tile's chain (about 19,000 clocks in the scan: 6,500 until
-// q' has reached every wavefront, 3,600 more until the tile is there, 1,000 scores, 1,700 softmax, 2,900 values, 1,900 to
-// meet).  Scores and weights therefore never leave the registers: with keys on the rows and queries on the columns of the
-// score product, a lane holds, for ITS query (lane % 16), the keys of its quarter of the wavefront (lane / 16), which is what
-// the second product takes as its B operand and what a running maximum and its correction need; with channels on the rows and
-// queries on the columns of the second product the sums belong to the same query.
+// has one tile, so the time is the latency of the launches and of one tile's chain (about 18,400 clocks in the scan: 5,800 until
+// q' has reached every wavefront, 1,000 more until the tile is in LDS, 2,800 scores, 800 softmax, 2,200 values, 5,100 to meet,
+// 3,000 of them with the wait for the slowest wavefront).  Scores and weights therefore never leave the registers: with keys on
+// the rows and queries on the columns of the score product, a lane holds, for ITS query (lane % 16), the keys of its quarter of
+// the wavefront (lane / 16), which is what the second product takes as its B operand and what a running maximum and its
+// correction need; with channels on the rows and queries on the columns of the second product the sums belong to the same query.
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
 // d = 128, 8 queries, 131,072 keys 36.6 -> 13.6, 400,000 keys 51 -> 23; 32 queries, 400,000 keys 111 -> 38; d = 256, 4 queries,
 // 4096 keys 27.7 -> 10.8; d = 64, 1 query, 500 keys 21.9 -> 10.5.  Error against 64 bits 6e-6 -> 4e-7.
