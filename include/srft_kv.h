@@ -16,7 +16,8 @@
  * Conventions
  *   - "dev" pointers are device (HBM) addresses on the GPU that was current when the plan was
  *     created; "host" pointers are ordinary host memory.  The caller owns every buffer it passes;
- *     the library allocates only the plan's own constant tables and frees them in srft_plan_destroy.
+ *     the library allocates only the plan's own constant tables, which srft_plan_destroy frees, and a
+ *     256 KB table of all plans of a device, which goes with the last of them.
  *   - Calls that take a stream enqueue on it and return without synchronising.  hip_stream is a
  *     hipStream_t passed as void* (NULL = the default stream).
  *   - Every function returns SRFT_OK (0) or a negative srft_status; nothing aborts or throws.
@@ -60,7 +61,7 @@ typedef enum srft_status {
  *   sign_seed    the sign diagonal is the splitmix64 stream started at this seed: s_n = -1 iff the
  *                top bit of the n-th output is set (the signs are fixed when the plan is made, Sec. 3.1).
  *   lambda_host  d floats > 0 on the host, or NULL for all ones.  Copied; not kept.
- * Allocates device tables on the current GPU (about 4*d*d bytes) and copies them once.
+ * Allocates device tables on the current GPU (12*d*d to 16*d*d bytes) and copies them once.
  */
 int srft_plan_create(srft_plan_t** out, int d, int group_size, uint64_t sign_seed,
                      const float* lambda_host);

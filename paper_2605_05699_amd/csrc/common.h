@@ -116,6 +116,9 @@ struct srft_plan_entry {
 // to 104 bytes of arguments takes 2.7-2.9 us of the host, one of 112 to 900 3.5, one of 3.8 KiB 4.2, and any number of segments
 // fits.  us a call, against the tables: write 2 plans x 256 vectors at d = 128 4.1 -> 3.8, 64 x 512 at d = 96 4.9 -> 4.3, 100 x 700
 // at d = 128 13.7 -> 8.9 (two launches before), read 9 x 100 at d = 96 5.3 -> 4.6; 56 x 8192 and 4 x 1,048,576 within 0.5 %.
+// The entry is one more load in front of the matrix.  With a gigabyte of other traffic before every call: write 64 x 512 at d = 96
+// 10.6 -> 10.2, 2 x 256 at d = 128 6.4 and 6.4, read 9 x 100 at d = 96 6.8 -> 6.4, 56 x 16 at d = 128 7.1 -> 6.7; over 48, 300, 150 and
+// 48 sets of plans and buffers in turn 6.65 -> 6.2, 3.6 and 3.6, 3.85 -> 3.5, 4.2 -> 3.65.
 template <>
 struct srft_batch<0> {
     const srft_plan_entry* plan;

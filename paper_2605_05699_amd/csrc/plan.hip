@@ -98,7 +98,7 @@ int split_hi_lo(const std::vector<double>& m, std::vector<uint16_t>& hi, std::ve
     return e;
 }
 
-// Table of the twice-folded write path (d = 256, g = 32): see quantize_fold4_tiles.h for what the kernel does with it.
+// Table of the twice-folded write path (d = 256, any g): see quantize_fold4_tiles.h for what the kernel does with it.
 // Wavefront w = 0 .. 3 is (cosine, classes 0|2), (cosine, 1|3), (sine, 0|2), (sine, 1|3).  Its two 32 x 64 slabs a
 // and c hold, for k1 = 0 .. 31 and the inputs n = 4 n1 + class, the entries Q[k1][n] s_n (cosine) or Q[128 + k1][n] s_n
 // (sine), the c slab of the odd-class wavefronts negated.  Row k1 = 0 of the sine slabs carries the row k = 32 of the
@@ -575,7 +575,8 @@ static int plan_create(srft_plan_t** out, int d, int group_size, int bits, int t
         for (int k = 0; k < d; ++k) rmat[(size_t)k * d + n] = (float)R[(size_t)n * d + k];
     std::vector<float> q_table;
     if (d % 64 == 0) build_query_table(d, transform, p->signs, lam, q_table);
-    // All tables of a plan in one allocation, sent in one copy (creating a plan at d = 128: 1.13 -> 1.06 ms, both before the cosines were shared).
+    // All tables of a plan in one allocation, sent in one copy (creating a plan at d = 128, before the cosines were shared:
+    // 1.13 -> 1.06 ms).
     std::vector<unsigned char> image;
     const auto place = [&image](const auto& table) {         // (256-byte aligned)
         const size_t at = image.size(), bytes = table.size() * sizeof(table[0]);
