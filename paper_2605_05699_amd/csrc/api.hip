@@ -10,8 +10,8 @@ namespace {
 
 // Workgroups of the abs-max statistic.  Each ends with one request per 32 channels to the same few cache lines, served one
 // after the other (about 11 ns a workgroup at d = 128, all at once at the end), so more workgroups shorten the streaming
-// and lengthen the end: the sum is smallest near sqrt(tiles) times a constant, and one per compute unit, which fills it with teams
-// of wavefronts (srft_amax_teams), is the most.
+// and lengthen the end: the sum is smallest near sqrt(tiles) times a constant, and one per compute unit, which fills it with
+// teams of wavefronts (srft_amax_teams), is the most.
 long long amax_grid(const srft_plan* p, long long n_tiles, int teams) {
     const long long most = teams == 1 && p->fold_q && !p->wfold4 ? p->grid_q : p->compute_units;      // (four of two wavefronts each fill a unit)
     return std::min((long long)(5.0 * std::sqrt((double)n_tiles)) + 1, most);

@@ -114,11 +114,12 @@ struct srft_plan_entry {
 // Segments of one length whose addresses (and whose plans' entries) lie a constant number of bytes apart: a cache that is one
 // tensor over its layers, a step that appends the same number of vectors to each.  A launch of up
 // to 104 bytes of arguments takes 2.7-2.9 us of the host, one of 112 to 900 3.5, one of 3.8 KiB 4.2, and any number of segments
-// fits.  us a call, against the tables: write 2 plans x 256 vectors at d = 128 4.1 -> 3.8, 64 x 512 at d = 96 4.9 -> 4.3, 100 x 700
-// at d = 128 13.7 -> 8.9 (two launches before), read 9 x 100 at d = 96 5.3 -> 4.6; 56 x 8192 and 4 x 1,048,576 within 0.5 %.
-// The entry is one more load in front of the matrix.  With a gigabyte of other traffic before every call: write 64 x 512 at d = 96
-// 10.6 -> 10.2, 2 x 256 at d = 128 6.4 and 6.4, read 9 x 100 at d = 96 6.8 -> 6.4, 56 x 16 at d = 128 7.1 -> 6.7; over 48, 300, 150 and
-// 48 sets of plans and buffers in turn 6.65 -> 6.2, 3.6 and 3.6, 3.85 -> 3.5, 4.2 -> 3.65.
+// fits.  us a call, against the tables: write 2 plans x 256 vectors at d = 128 4.1 -> 3.8, 64 x 512 at d = 96 4.9 -> 4.3,
+// 100 x 700 at d = 128 13.7 -> 8.9 (two launches before), read 9 x 100 at d = 96 5.3 -> 4.6; 56 x 8192 and 4 x 1,048,576
+// within 0.5 %.
+// The entry is one more load in front of the matrix.  With a gigabyte of other traffic before every call: write 64 x 512 at
+// d = 96 10.6 -> 10.2, 2 x 256 at d = 128 6.4 and 6.4, read 9 x 100 at d = 96 6.8 -> 6.4, 56 x 16 at d = 128 7.1 -> 6.7;
+// over 48, 300, 150 and 48 sets of plans and buffers in turn 6.65 -> 6.2, 3.6 and 3.6, 3.85 -> 3.5, 4.2 -> 3.65.
 template <>
 struct srft_batch<0> {
     const srft_plan_entry* plan;
@@ -196,13 +197,15 @@ batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
 quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out);
 // write path, folded form (d = 128, 256)
 quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide);
-// Teams of wavefronts per workgroup of the abs-max statistic, by head dimension and form of the write path (0 plain, 1 once, 2 twice
-// folded): as many as one workgroup per compute unit needs to fill its registers, so that as few workgroups as that update the
-// statistic's cache lines, one after the other.  us, one team per workgroup (up to 2048 workgroups) -> teams, 100,000 / 300,000 / 1,000,000
-// vectors: d = 32 (8 teams) 9.5 / 15 / 23 -> 9.5 / 10.6 / 15.7, d = 64 (8) 15.6 / 23 / 38 -> 10.7 / 14.4 / 26.4, d = 96 (4) 14.0 / 19.4 / 46 -> 12.8 / 19.0 / 38.9,
-// d = 128 (4) 17.6 / 26.3 / 55.5 -> 14.6 / 23.0 / 46.5 (2: 18.0 / 26.2 / 49), d = 256 (2) 24.7 / 46.9 / 156 -> 22.5 / 39.1 / 123.
-// The teams share their barriers, which costs 2 % of the rate at d = 128: from kAmaxAlone tiles on, one team there (3,000,000 vectors 156 us against 161, 6,000,000
-// 293 against 300; elsewhere teams are faster there too).
+// Teams of wavefronts per workgroup of the abs-max statistic, by head dimension and form of the write path (0 plain, 1 once,
+// 2 twice folded): as many as one workgroup per compute unit needs to fill its registers, so that as few workgroups as that
+// update the statistic's cache lines, one after the other.  us, one team per workgroup (up to 2048 workgroups) -> teams,
+// 100,000 / 300,000 / 1,000,000 vectors:
+//   d = 32 (8 teams) 9.5 / 15 / 23 -> 9.5 / 10.6 / 15.7        d = 64 (8) 15.6 / 23 / 38 -> 10.7 / 14.4 / 26.4
+//   d = 96 (4) 14.0 / 19.4 / 46 -> 12.8 / 19.0 / 38.9          d = 128 (4) 17.6 / 26.3 / 55.5 -> 14.6 / 23.0 / 46.5
+//                           with 2 18.0 / 26.2 / 49          d = 256 (2) 24.7 / 46.9 / 156 -> 22.5 / 39.1 / 123
+// The teams share their barriers, which costs 2 % of the rate at d = 128: from kAmaxAlone tiles on, one team there
+// (3,000,000 vectors 156 us against 161, 6,000,000 293 against 300; elsewhere teams are faster there too).
 constexpr long long kAmaxAlone = 1 << 16;
 constexpr int srft_amax_teams(int d, int form) { return form == 2 ? 2 : form == 1 ? 4 : d <= 64 ? 8 : d == 96 ? 4 : d == 128 ? 2 : 1; }
 quantize_kernel_t srft_pick_quantize_fold_amax(int teams);  // the abs-max statistic through the once-folded contraction (d = 128)

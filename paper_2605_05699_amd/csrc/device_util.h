@@ -49,8 +49,9 @@ __device__ __forceinline__ void hold_in_registers(half8 (&a)[N][M], half8 (&b)[N
 // one dispatched first ran 25 % ahead of the others and left the unit early, while the kernel waited for the
 // last one.  Every workgroup therefore walks through the four wavefront priorities, one per stage, offset by its
 // place in the dispatch order: over four stages each has held each priority once, and they finish together
-// (end times of the workgroups 440..620 us -> 565..600 us at d = 128, 8 M vectors; launches 1.5-3.5 % shorter).  Not used where two workgroups per unit take turns on one accumulator set (the folded
-// write path at d = 256), which measured 1 % slower with it.
+// (end times of the workgroups 440..620 us -> 565..600 us at d = 128, 8 M vectors; launches 1.5-3.5 % shorter).  Not used
+// where two workgroups per unit take turns on one accumulator set (the folded write path at d = 256), which measured 1 %
+// slower with it.
 __device__ __forceinline__ void rotate_priority(int stage) {
     switch (((int)(blockIdx.x * 4 / gridDim.x) + stage) & 3) {
         case 0: __builtin_amdgcn_s_setprio(0); break;
@@ -104,9 +105,10 @@ __device__ __forceinline__ uint32_t pack4_bytes(const floatx16& acc, int base, f
 // Workgroups are dealt to the 8 accelerator dies round robin, each die with an L2 of its own; here a die takes a
 // contiguous eighth of the list, so that the workgroups of one plan share one copy of its matrix table instead of pulling
 // it into every L2.  Measured against workgroup b = place b: 64 plans x 512 vectors at d = 96, write 6.8 -> 5.8 us;
-// 52 x 4096 at d = 256, read 40.6 -> 36.6 us; 56 x 8192 at d = 128, write 37.3 -> 36.6 us; 4 x 1,048,576 within 0.5 %.  Over 2 to 64
-// plans and 5 to 600 MB at d = 96, 128, 256: reads 0 to 33 % and writes 0 to 33 % shorter, most where a plan has few tiles; at 2 and 3
-// plans with one to two tiles a workgroup it lost up to 10 % until such segments were cut where the dies meet (launch_shape.h).
+// 52 x 4096 at d = 256, read 40.6 -> 36.6 us; 56 x 8192 at d = 128, write 37.3 -> 36.6 us; 4 x 1,048,576 within 0.5 %.  Over
+// 2 to 64 plans and 5 to 600 MB at d = 96, 128, 256: reads 0 to 33 % and writes 0 to 33 % shorter, most where a plan has few
+// tiles; at 2 and 3 plans with one to two tiles a workgroup it lost up to 10 % until such segments were cut where the dies
+// meet (launch_shape.h).
 struct srft_work {
     const uint4* frag;
     const void* in;
@@ -193,9 +195,9 @@ __device__ __forceinline__ uint32_t pack_half2(float a, float b) {
 // that every wavefront has finished reading buffer (k+1) % 2, which (3) overwrites.
 //
 // The start of a workgroup is the round trip of its loads: T_0 first, then the matrix, then T_1, and T_0 goes to LDS while the
-// matrix is on its way.  Against the matrix first and T_0 behind it, us: read 8 plans x 3000 at d = 128 5.1 -> 4.7, 60,000 vectors
-// 6.6 -> 6.2 (write 7.5 -> 7.3), read 64 x 512 at d = 96 6.0 -> 5.8, 9 x 2000 at d = 224 9.3 -> 8.9; T_1 ahead of the matrix as
-// well: 4.7, 6.6 (7.9), 6.0, 9.1.
+// matrix is on its way.  Against the matrix first and T_0 behind it, us: read 8 plans x 3000 at d = 128 5.1 -> 4.7, 60,000
+// vectors 6.6 -> 6.2 (write 7.5 -> 7.3), read 64 x 512 at d = 96 6.0 -> 5.8, 9 x 2000 at d = 224 9.3 -> 8.9; T_1 ahead of
+// the matrix as well: 4.7, 6.6 (7.9), 6.0, 9.1.
 //
 // Rows past the end of the input alias to the last row, in the loads AND in the stores: surplus lanes
 // compute the last vector again and store the same bytes to the same place.  Prefetches past the last

@@ -69,9 +69,10 @@ __device__ __forceinline__ float wave_sum(float x) {
 // D: head dimension.  KEYS: keys per tile, 64 or 32.  WIDE: groups of gw > 1 runs of 32 channels share a scale.
 // blockIdx.y: block of 16 queries.  (Both blocks of 32 queries in one wavefront -- the codes decoded once -- needs more
 // registers than two wavefronts per SIMD leave: 250 spilled at d = 128.)
-// ONE: no wavefront has more than one tile (up to 131,072 keys and 16 queries on a whole chip): nothing is asked for behind it and
-// nothing scaled down (and 110 registers do where 201 did, d = 128).  us: 8 queries, 131,072 keys at d = 128 13.8 -> 13.6, at d = 256
-// 22.9 -> 22.4; 16 queries, 9000 keys at d = 256 15.3 -> 15.0; 8 queries, 60,000 keys at d = 192 15.0 -> 14.75.
+// ONE: no wavefront has more than one tile (up to 131,072 keys and 16 queries on a whole chip): nothing is asked for behind
+// it and nothing scaled down (and 110 registers do where 201 did, d = 128).  us: 8 queries, 131,072 keys at d = 128 13.8 ->
+// 13.6, at d = 256 22.9 -> 22.4; 16 queries, 9000 keys at d = 256 15.3 -> 15.0; 8 queries, 60,000 keys at d = 192 15.0 ->
+// 14.75.
 template <int D, int KEYS, bool WIDE, bool ONE>
 __global__ void __launch_bounds__(64 * kWaves, 2)
 srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ q_table,
@@ -405,9 +406,9 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 // reduced the maxima through LDS: 5.6 -> 4.0 us at d = 128, 256 workgroups to add; 6.7 -> 5.8 us at d = 256, 128 of them.
 // A workgroup's maximum reaches the threads that add its sums from the lane that holds it (a load for each was 256 loads of one
 // value per workgroup); with the scan's shorter end, d = 128, 131,072 keys 15.3 -> 14.1 us, d = 256, 4096 keys 14.3 -> 12.7.
-// AHEAD: rows of sums a thread asks for at once, for 64, 128 or 256 (D = 192: 63, 126, 252) workgroups to add in one pass; what is
-// not needed costs as much as what is (4096 keys at d = 256, 128 of them, 12.8 -> 12.0 us; a branch around each load 0.3 us where all
-// are needed).
+// AHEAD: rows of sums a thread asks for at once, for 64, 128 or 256 (D = 192: 63, 126, 252) workgroups to add in one pass;
+// what is not needed costs as much as what is (4096 keys at d = 256, 128 of them, 12.8 -> 12.0 us; a branch around each load
+// 0.3 us where all are needed).
 template <int D, int AHEAD>
 __global__ void __launch_bounds__(1024)
 srft_attention_finish_kernel(const float* __restrict__ part, const float* __restrict__ part_max,

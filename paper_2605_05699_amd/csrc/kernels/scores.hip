@@ -4,14 +4,15 @@
 // the transform is orthogonal, so the keys never have to be reconstructed; the kernel reads the 4-bit record
 // only (d/2 + 4 d/g bytes per key instead of the 2d of a dequantized prefix) and writes n_q floats per key.
 //
-// One launch.  Every workgroup forms q' (rotated_queries.h); a wavefront walks over tiles of 64 or 32 keys.  Keys are the rows and
-// queries the columns of v_mfma_f32_16x16x32_f16: the codes of a key go from global memory into the A operand with a
-// transpose over the wavefront's quarters and never through LDS, and a lane ends up with 4 consecutive keys of ITS query per block
-// of 16 -- one 16-byte store, 64 bytes next to each other per query (with more than 8 queries whole lines, by way of LDS).  With more than 16 queries both blocks of 16 take the same
-// decoded keys.  At many keys it is bound by memory, at few by the chain of one launch.  Measured, us, against a launch for q'
-// and a scan by one-wavefront workgroups that decoded the codes into LDS (and wrote a query's keys with 4-byte stores):
-// d = 128, 8 queries: 20,000 keys 13.1 -> 7.9, 1,000,000 keys 30.0 -> 21.6 (112 MB: 5.2 TB/s); 32 queries, 300,000 keys
-// 24.6 -> 15.2; d = 64, 8 queries, 1,000,000 keys 20.6 -> 14.8; d = 256 59.4 -> 36.4.
+// One launch.  Every workgroup forms q' (rotated_queries.h); a wavefront walks over tiles of 64 or 32 keys.  Keys are the
+// rows and queries the columns of v_mfma_f32_16x16x32_f16: the codes of a key go from global memory into the A operand with
+// a transpose over the wavefront's quarters and never through LDS, and a lane ends up with 4 consecutive keys of ITS query
+// per block of 16 -- one 16-byte store, 64 bytes next to each other per query (with more than 8 queries whole lines, by way
+// of LDS).  With more than 16 queries both blocks of 16 take the same decoded keys.  At many keys it is bound by memory, at
+// few by the chain of one launch.  Measured, us, against a launch for q' and a scan by one-wavefront workgroups that decoded
+// the codes into LDS (and wrote a query's keys with 4-byte stores): d = 128, 8 queries: 20,000 keys 13.1 -> 7.9, 1,000,000
+// keys 30.0 -> 21.6 (112 MB: 5.2 TB/s); 32 queries, 300,000 keys 24.6 -> 15.2; d = 64, 8 queries, 1,000,000 keys 20.6 ->
+// 14.8; d = 256 59.4 -> 36.4.
 #include "../rotated_queries.h"
 
 namespace {

@@ -70,8 +70,8 @@ inline int srft_share_out(const long long* tiles, int count, long long budget, s
 constexpr uint32_t srft_even_magic(int blocks) { return (uint32_t)(((1ULL << 31) + blocks - 1) / blocks); }
 SRFT_HOST_DEVICE constexpr int srft_even_segment(uint32_t block, uint32_t magic) { return (int)(((uint64_t)(2 * block) * magic) >> 32); }
 
-// Workgroups per segment for `count` segments of `tiles` tiles each, as srft_share_out would share them out; 0: the segments go out
-// cut where the dies meet (see there), or there are more than `budget` of them.
+// Workgroups per segment for `count` segments of `tiles` tiles each, as srft_share_out would share them out; 0: the segments
+// go out cut where the dies meet (see there), or there are more than `budget` of them.
 constexpr int srft_even_blocks(long long tiles, long long count, long long budget) {
     if (count > budget) return 0;
     const long long blocks = tiles * count <= budget ? tiles : std::min(std::max(budget / count, 1LL), tiles);
@@ -80,11 +80,11 @@ constexpr int srft_even_blocks(long long tiles, long long count, long long budge
 }
 
 // Workgroups that `blocks` for every one of `count` segments leaves over are spread evenly over the segments, so that all of the
-// budget is at work: workgroup b serves segment (b S + S - 1) / W, whose workgroups start at i W / S, with W workgroups on S = count
-// segments (where nothing is left over, or the products get too large to divide exactly, W = blocks on S = 1).  52 x 4096 vectors at
-// d = 256, read (512 workgroups for 52 plans: 9 each and 44 over) 36.3 -> 35.5 us, 8-bit 37.6 -> 36.9, 52 x 40,000 306 -> 301; d = 128, 80 x 3000
-// 20.3 -> 20.0; 56 x 10,000 at d = 96 33.3 -> 33.1.  Writes are bound by memory whichever way: d = 128, 80 x 3000 16.6 -> 16.75; they keep
-// `blocks` each.
+// budget is at work: workgroup b serves segment (b S + S - 1) / W, whose workgroups start at i W / S, with W workgroups on S
+// = count segments (where nothing is left over, or the products get too large to divide exactly, W = blocks on S = 1).  52 x
+// 4096 vectors at d = 256, read (512 workgroups for 52 plans: 9 each and 44 over) 36.3 -> 35.5 us, 8-bit 37.6 -> 36.9, 52 x
+// 40,000 306 -> 301; d = 128, 80 x 3000 20.3 -> 20.0; 56 x 10,000 at d = 96 33.3 -> 33.1.  Writes are bound by memory
+// whichever way: d = 128, 80 x 3000 16.6 -> 16.75; they keep `blocks` each.
 struct srft_even_shape {
     int w, s;
     uint32_t w_magic, s_magic;

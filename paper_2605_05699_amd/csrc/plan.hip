@@ -53,7 +53,8 @@ double hadamard_entry(int d, int k, int n) {
 }
 
 // Q[k][n] of the packed unitary real DFT (Eq. 1-2), rfft sign convention.
-// The sines and cosines of a size are few: each is computed once (creating a plan: d = 128 1.07 -> 0.94 ms, d = 256 4.77 -> 4.28).
+// The sines and cosines of a size are few: each is computed once (creating a plan: d = 128 1.07 -> 0.94 ms, d = 256 4.77 ->
+// 4.28).
 struct dft_matrix {
     int d;
     std::vector<double> cosine, sine;                        // of row entries with 2 pi j / d
@@ -255,9 +256,10 @@ void build_query_table(int d, int transform, const std::vector<int8_t>& signs, c
     }
 }
 
-// The plan table of a device: one entry per plan, for the launches that name their plans by a first entry and a step.  Entries are
-// handed out in turn, so that plans created one after the other follow one another whatever has been destroyed before them; the
-// table goes with the device's last plan.  A plan that finds it full has no entry and its batches travel in a table of their own.
+// The plan table of a device: one entry per plan, for the launches that name their plans by a first entry and a step.
+// Entries are handed out in turn, so that plans created one after the other follow one another whatever has been destroyed
+// before them; the table goes with the device's last plan.  A plan that finds it full has no entry and its batches travel in
+// a table of their own.
 constexpr int kPlanEntries = 8192, kMaxDevices = 64;
 struct plan_table {
     srft_plan_entry* dev = nullptr;

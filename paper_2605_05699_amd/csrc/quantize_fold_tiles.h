@@ -53,9 +53,9 @@
 //       the bottom element of its mirror block: together the lanes of a vector cover every index once) over all the
 //       tiles it sees; at the end the 32 vectors' lanes are reduced and one atomic maximum per channel goes to `amax`,
 //       read as unsigned[d] (srft_kv_channel_absmax: the statistic lambda is calibrated from, Sec. 7.1).
-// SUB: teams of M wavefronts per workgroup, each with tiles of its own (t0 + team, and stride counts tiles of all teams); they share
-//       the barriers and, at the end, one update of the statistic (AMAX).  All of them walk as many tiles as the first: past
-//       the end a team sees the last tile again, which a maximum does not mind.
+// SUB: teams of M wavefronts per workgroup, each with tiles of its own (t0 + team, and stride counts tiles of all teams);
+//       they share the barriers and, at the end, one update of the statistic (AMAX).  All of them walk as many tiles as the
+//       first: past the end a team sees the last tile again, which a maximum does not mind.
 template <int D, int BITS, bool WIDE, bool AMAX = false, int SUB = 1>
 __device__ __forceinline__ void
 srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restrict__ x, long long n_vec,

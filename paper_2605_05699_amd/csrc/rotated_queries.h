@@ -26,7 +26,8 @@ __device__ __forceinline__ uint2 srft_pair_transpose(const uint2& r) {
     return swap32(x.x, x.y);
 }
 
-// ---- the transform of the queries: a Cooley-Tukey FFT in fp32 (or the Walsh-Hadamard butterflies), D = 16 L points, 16 points per lane
+// ---- the transform of the queries: a Cooley-Tukey FFT in fp32 (or the Walsh-Hadamard butterflies), D = 16 L points, 16
+// points per lane
 struct srft_cf { float x, y; };
 __device__ __forceinline__ srft_cf operator+(srft_cf a, srft_cf b) { return {a.x + b.x, a.y + b.y}; }
 __device__ __forceinline__ srft_cf operator-(srft_cf a, srft_cf b) { return {a.x - b.x, a.y - b.y}; }
@@ -135,22 +136,25 @@ __device__ __forceinline__ void srft_wht(float (&x)[L]) {
             }
 }
 
-// The operands of 16 RB queries for a workgroup of W wavefronts: q'_p = z_p / max(lambda_p, 1e-6), z the packed transform (Eq. 1-2)
-// of the query, split into fp16 hi + lo.  qs: [block of 16][group][hi, lo][64 lanes]: lane l holds query l % 16 and the 8 codes of
-// unit l / 16 of the group, in the order decode8 lays them out (element e <-> code e / 2 + 4 (e % 2)).  Queries past n_q are zero.
+// The operands of 16 RB queries for a workgroup of W wavefronts: q'_p = z_p / max(lambda_p, 1e-6), z the packed transform
+// (Eq. 1-2) of the query, split into fp16 hi + lo.  qs: [block of 16][group][hi, lo][64 lanes]: lane l holds query l % 16
+// and the 8 codes of unit l / 16 of the group, in the order decode8 lays them out (element e <-> code e / 2 + 4 (e % 2)).
+// Queries past n_q are zero.
 //
 // Every workgroup does this for itself (a launch of its own took 3.0 us at d = 128, 4.6 us at d = 256), so what counts is its
-// latency, and as a product with the dense matrix that was the 64 KB (d = 128) or 256 KB (d = 256) that a compute unit had to pull in:
-// 5,400 of the 12,200 clocks of the decode attention's scan over 1000 keys at d = 128, 12,500 of 26,300 at d = 256.  As an FFT it reads the query and 80 bytes per lane.  n = L i + j: lane (query, j) transforms
-// its 16 values over i (real, 9 coefficients k1), turns them by exp(-2 pi i j k1 / D); lane (query, k1) transforms over j, which gives
-// the bins k1 + 16 k2 (past D / 2: the conjugates of D - k); then every thread scales and splits a unit of 8.  The three
-// exchanges go through LDS.
-// us, against the matrix: scores of 8 queries, 300,000 keys at d = 256 15.2 -> 13.0, 1,000,000 at d = 64 14.2 -> 13.5, 32 queries, 300,000
-// keys at d = 128 13.2 -> 12.5; decode attention of 4 queries, 4096 keys at d = 256 15.5 -> 14.3, d = 192 13.3 -> 12.2.  Error against 64
-// bits 1.7e-7 -> 1.2e-7 (scores at d = 256), 1.3e-7 -> 1.1e-7 (d = 128).
+// latency, and as a product with the dense matrix that was the 64 KB (d = 128) or 256 KB (d = 256) that a compute unit had
+// to pull in: 5,400 of the 12,200 clocks of the decode attention's scan over 1000 keys at d = 128, 12,500 of 26,300 at
+// d = 256.  As an FFT it reads the query and 80 bytes per lane.  n = L i + j: lane (query, j) transforms its 16 values over i
+// (real, 9 coefficients k1), turns them by exp(-2 pi i j k1 / D); lane (query, k1) transforms over j, which gives the bins
+// k1 + 16 k2 (past D / 2: the conjugates of D - k); then every thread scales and splits a unit of 8.  The three exchanges go
+// through LDS.
+// us, against the matrix: scores of 8 queries, 300,000 keys at d = 256 15.2 -> 13.0, 1,000,000 at d = 64 14.2 -> 13.5, 32
+// queries, 300,000 keys at d = 128 13.2 -> 12.5; decode attention of 4 queries, 4096 keys at d = 256 15.5 -> 14.3, d = 192
+// 13.3 -> 12.2.  Error against 64 bits 1.7e-7 -> 1.2e-7 (scores at d = 256), 1.3e-7 -> 1.1e-7 (d = 128).
 // table: [L] x 5 units of 16 bytes: exp(-2 pi i j k1 / D) for k1 = 1 .. 8, then the signs of n = L i + j (bit i); then D floats:
 // the packing constant (1 / sqrt(D) or sqrt(2 / D)) / max(lambda_p, 1e-6).
-// Everything is multiplied by factor (1 or -1).  `fetch` is called when the loads of the queries and the table are on their way, for the caller's own: their wait does not include it.
+// Everything is multiplied by factor (1 or -1).  `fetch` is called when the loads of the queries and the table are on their
+// way, for the caller's own: their wait does not include it.
 // scratch: srft_query_scratch_bytes bytes of LDS, 16-byte aligned, free again on return (all wavefronts have passed a barrier).
 template <int D, int RB> constexpr int kQueryMid = 16 * RB * 9 * (D / 16 + 1) * 8;       // bytes: [query][k1][j], padded
 template <int D> constexpr int kQueryRow = D + 12;           // floats: [query][p], padded (9 bins of 5 queries side by side, 4 channels of 16
@@ -169,8 +173,8 @@ srft_query_operands(const uint4* __restrict__ q, int n_q, int q0, const uint4* _
     const bool first_step = 64 * wave < nq * L, last_step = 64 * wave < 16 * RB * U;     // wavefronts that have a part in them
     float* const mid = reinterpret_cast<float*>(scratch);
     float* const z = reinterpret_cast<float*>(scratch + kQueryMid<D, RB>);
-    // (threads without a query repeat the last one's loads; wavefronts of them have none: 8 wavefronts of 23 loads held the tiles'
-    // loads back by 2000 clocks)
+    // (threads without a query repeat the last one's loads; wavefronts of them have none: 8 wavefronts of 23 loads held the
+    // tiles' loads back by 2000 clocks)
     const int j = tid % L, mine = min(tid / L, nq - 1);
     const unsigned short* const xq = reinterpret_cast<const unsigned short*>(q) + (size_t)(q0 + mine) * D + j;
     uint32_t raw[16], signs = 0;
@@ -232,8 +236,8 @@ srft_query_operands(const uint4* __restrict__ q, int n_q, int q0, const uint4* _
             const int k1 = tid % 9;
             float* const up = z + tid / 9 * kQueryRow<D> + k1;
             float* const down = z + tid / 9 * kQueryRow<D> - k1;
-            // (in this order: the imaginary part of bin 0 lands where the real part of bin D / 2 goes, behind it, and that of bin D / 2
-            // at [D]; bins that a lane has twice, k1 = 0 and 8, are written twice)
+            // (in this order: the imaginary part of bin 0 lands where the real part of bin D / 2 goes, behind it, and that
+            // of bin D / 2 at [D]; bins that a lane has twice, k1 = 0 and 8, are written twice)
 #pragma unroll
             for (int k = 0; k < L / 2; ++k) {
                 up[16 * k] = out[k].x;
