@@ -10,10 +10,12 @@ namespace {
 
 // Workgroups of the abs-max statistic.  Each ends with one request per 32 channels to the same few cache lines, served one
 // after the other (about 11 ns a workgroup at d = 128, all at once at the end), so more workgroups shorten the streaming
-// and lengthen the end: the sum is smallest near sqrt(tiles) times a constant, and one per compute unit, which fills it with
-// teams of wavefronts (srft_amax_teams), is the most.
+// and lengthen the end: the sum is smallest near sqrt(tiles) times a constant.  At most what reaches the read rate: with teams
+// (srft_amax_teams) and where one team is five wavefronts or more (d >= 160) one per compute unit, two with three wavefronts
+// (d = 96), with one to four wavefronts what the write path's grid holds.  us for 100,000 / 200,000 / 300,000 vectors at d = 192, up
+// to one per unit against up to two: 15.5 / 27.7 / 43.5 and 25.0 / 33.8 / 48.9.
 long long amax_grid(const srft_plan* p, long long n_tiles, int teams) {
-    const long long most = teams == 1 && p->fold_q && !p->wfold4 ? p->grid_q : p->compute_units;      // (four of two wavefronts each fill a unit)
+    const long long cus = p->compute_units, most = teams > 1 || p->d >= 160 ? cus : p->d == 96 ? 2 * cus : p->grid_q;
     return std::min((long long)(5.0 * std::sqrt((double)n_tiles)) + 1, most);
 }
 

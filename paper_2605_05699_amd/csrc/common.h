@@ -194,25 +194,40 @@ quantize_kernel_t srft_pick_quantize_plain_b8(int d, int slabs, int gm);
 batched_kernels_t srft_pick_quantize_plain_batched_b4(int d, int slabs, int gm);
 batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
 // write path, plain form, other outputs (kOutRaw, kOutAmax)
-quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out);
+quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out, int teams);
 // write path, folded form (d = 128, 256)
 quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide);
-// Teams of wavefronts per workgroup of the abs-max statistic, by head dimension and form of the write path (0 plain, 1 once,
-// 2 twice folded): as many as one workgroup per compute unit needs to fill its registers, so that as few workgroups as that
-// update the statistic's cache lines, one after the other.  us, one team per workgroup (up to 2048 workgroups) -> teams,
-// 100,000 / 300,000 / 1,000,000 vectors:
-//   d = 32 (8 teams) 9.5 / 15 / 23 -> 9.5 / 10.6 / 15.7        d = 64 (8) 15.6 / 23 / 38 -> 10.7 / 14.4 / 26.4
-//   d = 96 (4) 14.0 / 19.4 / 46 -> 12.8 / 19.0 / 38.9          d = 128 (4) 17.6 / 26.3 / 55.5 -> 14.6 / 23.0 / 46.5
-//                           with 2 18.0 / 26.2 / 49          d = 256 (2) 24.7 / 46.9 / 156 -> 22.5 / 39.1 / 123
-// The teams share their barriers, which costs 2 % of the rate at d = 128: from kAmaxAlone tiles on, one team there
-// (3,000,000 vectors 156 us against 161, 6,000,000 293 against 300; elsewhere teams are faster there too).
-constexpr long long kAmaxAlone = 1 << 16;
-constexpr int srft_amax_teams(int d, int form) { return form == 2 ? 2 : form == 1 ? 4 : d <= 64 ? 8 : d == 96 ? 4 : d == 128 ? 2 : 1; }
+// Teams of wavefronts per workgroup of the abs-max statistic, by head dimension, form of the write path (0 plain, 1 once, 2
+// twice folded) and tiles.  Teams leave fewer workgroups, up to one per compute unit, that update the statistic's cache lines one
+// after the other; but they start later (each with its matrix), share their barriers, and a call of few tiles wants them on
+// different compute units.  So: one team up to a few hundred tiles, teams from there on, and one team again where the rate counts
+// and not the end.  us, one team -> the teams of this rule, a statistic that has its values / one that starts at zero (cleared by
+// a kernel in front, 2.3 us):
+//   d = 32   8,000 vectors 2.5 / 5.4 (eight teams: 2.7 / 5.3)   24,000 3.0 / 6.4 -> 2.8 / 5.8   1,000,003 13.4 / 25.4 -> 11.9 / 15.7
+//   d = 64   3,000 2.5 / 5.4 (four: 3.1 / 5.7)   8,000 3.5 / 7.1 -> 3.1 / 6.3   1,000,003 23.1 / 41.6 -> 23.5 / 28.9 (eight: 24.9 /
+//            29.3)   8,000,000 166 / 186 (four: 189 / 191, eight: 177 / 174)
+//   d = 96   60,000 5.5 / 10.8 (four: 6.6 / 13.4)   400,000 14.7 / 24.2 (15.9 / 22.0)   1,000,003 39.5 / 51.4 -> 41.2 / 42.8
+//            4,000,000 164 / 167 -> 137 / 139
+//   d = 128  plain: 60,000 6.6 / 12.0 (two: 7.4 / 13.8)   200,000 13.5 / 18.5 -> 13.1 / 19.3   524,288 35.1 / 43.1 -> 32.9 / 37.6
+//            2,000,000 107 / 117 (two: 115 / 118)
+//   d = 128  folded: 3,000 3.1 / 6.1 (two: 3.9 / 6.7)   8,000 4.6 / 8.4 -> 4.3 / 7.9 (four: 5.7 / 8.8)   100,000 12.7 / 19.2 -> 9.6 /
+//            15.9 (four: 10.3 / 18.1)   1,000,003 49.9 / 61.8 -> 50.3 / 54.0 (two: 60.8 / 64.1)   3,000,000 132 / 141 (four: 137 / 140)
+//   d = 256  8,000 6.5 / 10.4 (two: 6.8 / 9.9)   24,000 9.2 / 14.2 -> 9.7 / 13.0   300,000 43.0 / 48.5 -> 37.5 / 44.4
+//            1,000,003 146 / 148 -> 120 / 123
+constexpr int srft_amax_teams(int d, int form, long long tiles) {
+    if (form == 2) return tiles < 512 ? 1 : 2;
+    if (form == 1) return tiles < 200 || tiles >= 65536 ? 1 : tiles < 8192 ? 2 : 4;
+    if (d == 32) return tiles < 400 ? 1 : 8;
+    if (d == 64) return tiles < 200 || tiles >= 131072 ? 1 : 4;
+    if (d == 96) return tiles < 16384 ? 1 : 4;
+    if (d == 128) return tiles < 2560 || tiles >= 32768 ? 1 : 2;
+    return 1;
+}
 quantize_kernel_t srft_pick_quantize_fold_amax(int teams);  // the abs-max statistic through the once-folded contraction (d = 128)
 batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide);
 // write path, folded twice (d = 256; g = 16, 32 and 256); the abs-max statistic; the size of its table in 16-byte units
 quantize_kernel_t srft_pick_quantize_fold4(int bits, int gm);
-quantize_kernel_t srft_pick_quantize_fold4_amax(void);
+quantize_kernel_t srft_pick_quantize_fold4_amax(int teams);
 batched_kernels_t srft_pick_quantize_fold4_batched(int bits, int gm);
 int srft_fold4_table_units(void);
 // read path
@@ -281,7 +296,7 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads);
 // the tables and the matrix scaling the kernels of a plan take
 inline int srft_plan_amax_teams(const srft_plan* p, long long n_tiles) {
-    return p->fold_q && !p->wfold4 && n_tiles >= kAmaxAlone ? 1 : srft_amax_teams(p->d, p->wfold4 ? 2 : p->fold_q ? 1 : 0);
+    return srft_amax_teams(p->d, p->wfold4 ? 2 : p->fold_q ? 1 : 0, n_tiles);
 }
 inline const uint4* srft_plan_write_table(const srft_plan* p) { return p->fold4_q ? p->wfold4 : p->fold_q ? p->wfold : p->wfrag; }
 inline const uint4* srft_plan_read_table(const srft_plan* p) { return p->fold4_dq ? p->rfold4 : p->fold_dq ? p->rfold : p->rfrag; }

@@ -4,18 +4,21 @@
 
 namespace {
 template <int D, int S>
-quantize_kernel_t by_output(int out) {
+quantize_kernel_t by_output(int out, int teams) {
     if (out == kOutRaw) return srft_quantize_kernel<D, S, kOutRaw, kGroup32, 4>;
-    if (out == kOutAmax) return srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, srft_amax_teams(D, 0)>;
-    return nullptr;
+    if (out != kOutAmax) return nullptr;
+    constexpr int MANY = D == 32 ? 8 : D == 64 || D == 96 ? 4 : D == 128 ? 2 : 1;
+    return teams == 1      ? srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, 1>
+           : teams == MANY ? srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, MANY>
+                           : nullptr;
 }
 template <int D>
-quantize_kernel_t pick(int slabs, int out) {
+quantize_kernel_t pick(int slabs, int out, int teams) {
     if constexpr (D == 64) {
-        if (slabs == 2) return by_output<D, 2>(out);
+        if (slabs == 2) return by_output<D, 2>(out, teams);
     }
-    return by_output<D, 1>(out);
+    return by_output<D, 1>(out, teams);
 }
 }  // namespace
 
-quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out) { SRFT_DISPATCH_D(d, pick, slabs, out) }
+quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out, int teams) { SRFT_DISPATCH_D(d, pick, slabs, out, teams) }

@@ -23,7 +23,10 @@ quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide) {
     return d == 128 ? pick<128>(bits, wide) : d == 256 ? pick<256>(bits, wide) : nullptr;
 }
 quantize_kernel_t srft_pick_quantize_fold_amax(int teams) {
-    return teams == 1 ? srft_quantize_fold_amax_kernel<128, 1> : srft_quantize_fold_amax_kernel<128, srft_amax_teams(128, 1)>;
+    return teams == 1   ? srft_quantize_fold_amax_kernel<128, 1>
+           : teams == 2 ? srft_quantize_fold_amax_kernel<128, 2>
+           : teams == 4 ? srft_quantize_fold_amax_kernel<128, 4>
+                        : nullptr;
 }
 batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide) {
     return d == 128 ? pick_batched<128>(bits, wide) : d == 256 ? pick_batched<256>(bits, wide) : nullptr;

@@ -17,6 +17,8 @@ batched_kernels_t pick_batched(int gm) {
 }  // namespace
 
 quantize_kernel_t srft_pick_quantize_fold4(int bits, int gm) { return bits == 8 ? pick<8>(gm) : pick<4>(gm); }
-quantize_kernel_t srft_pick_quantize_fold4_amax(void) { return srft_quantize_fold4_amax_kernel<srft_amax_teams(256, 2)>; }
+quantize_kernel_t srft_pick_quantize_fold4_amax(int teams) {
+    return teams == 1 ? srft_quantize_fold4_amax_kernel<1> : teams == 2 ? srft_quantize_fold4_amax_kernel<2> : nullptr;
+}
 batched_kernels_t srft_pick_quantize_fold4_batched(int bits, int gm) { return bits == 8 ? pick_batched<8>(gm) : pick_batched<4>(gm); }
 int srft_fold4_table_units(void) { return kFold4Units; }

@@ -344,11 +344,11 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
     const int teams = out == kOutAmax ? srft_plan_amax_teams(p, n_tiles) : 1;
     if (out == kOutAmax && (p->wfold4 || p->fold_q)) {   // the statistic does not depend on the groups: folded wherever a table exists
         *threads = p->d * teams;
-        return p->wfold4 ? srft_pick_quantize_fold4_amax() : srft_pick_quantize_fold_amax(teams);
+        return p->wfold4 ? srft_pick_quantize_fold4_amax(teams) : srft_pick_quantize_fold_amax(teams);
     }
     if (out != kOutCodes) {
         *threads = 2 * p->d / p->slabs_q * teams;
-        return srft_pick_quantize_aux(p->d, p->slabs_q, out);
+        return srft_pick_quantize_aux(p->d, p->slabs_q, out, teams);
     }
     if (p->fold4_q) {
         *threads = 256;

@@ -92,8 +92,7 @@ def test_many_workgroups_meet_on_one_statistic(B, d):
 @pytest.mark.parametrize("tiles", [2, 4, 5, 8, 9, 25])
 @pytest.mark.parametrize("cap", [0, 1])
 def test_teams_of_a_workgroup(B, d, tiles, cap):
-    """2 to 8 teams share a workgroup and a statistic: counts of tiles that leave teams without one, the largest value of
-    the batch in a last tile of one row."""
+    """Few tiles, the largest value of the batch in a last tile of one row."""
     n = 32 * (tiles - 1) + 1
     x = W.gaussian_with_outliers(n, d, seed=3 * d + tiles, outliers=1, gain=4.0)
     x[-1] *= np.float16(8.0)
@@ -106,7 +105,7 @@ def test_teams_of_a_workgroup(B, d, tiles, cap):
 @pytest.mark.parametrize("d,g,transform", [(64, 32, "hadamard"), (128, 16, "dft"), (128, 32, "hadamard"), (256, 16, "dft"), (256, 32, "hadamard")])
 @pytest.mark.parametrize("tiles,cap", [(1, 0), (2, 0), (3, 1), (4, 0), (5, 1), (9, 0), (25, 1), (2188, 0)])
 def test_forms_that_groups_of_16_and_hadamard_take(B, d, g, transform, tiles, cap):
-    """The plain form with one, two and eight teams at the dimensions whose DFT is folded, and the folded one at groups of 16."""
+    """The plain form at the dimensions whose DFT is folded, and the folded one at groups of 16, against the oracle."""
     n = 32 * (tiles - 1) + 1
     x = W.gaussian_with_outliers(n, d, seed=5 * d + tiles, outliers=1, gain=4.0)
     x[-1] *= np.float16(8.0)
@@ -116,6 +115,32 @@ def test_forms_that_groups_of_16_and_hadamard_take(B, d, g, transform, tiles, ca
     ref = np.abs(O.srft_forward(x.astype(np.float64), plan.signs, form="hadamard" if transform == "hadamard" else "dense")).max(axis=0)
     tol = AMAX_ERR * np.linalg.norm(x.astype(np.float64), axis=1).max() + 2.0 ** -23 * ref
     assert np.all(np.abs(got - ref) <= tol), float((np.abs(got - ref) / tol).max())
+    plan.close()
+
+
+# where the number of teams per workgroup changes (srft_amax_teams), one tile before and after it, and counts that leave one team
+# and more of the last workgroup without a tile
+TEAM_EDGES = ([(32, 32, "dft", t) for t in (399, 400, 401, 403, 407)] + [(64, 32, "dft", t) for t in (199, 200, 201, 203, 131071, 131072)] +
+              [(96, 32, "dft", t) for t in (16383, 16384, 16385, 16387)] + [(128, 16, "dft", t) for t in (2559, 2560, 2561, 32767, 32768)] +
+              [(128, 32, "dft", t) for t in (199, 200, 201, 8191, 8192, 8193, 8195, 65535, 65536)] +
+              [(256, 32, "dft", t) for t in (511, 512, 513)] + [(256, 32, "hadamard", 513), (128, 32, "hadamard", 2561)])
+
+
+@pytest.mark.parametrize("d,g,transform,tiles", TEAM_EDGES)
+def test_teams_where_their_number_changes(B, d, g, transform, tiles):
+    """As the maximum over parts of a hundred tiles (one team, which the tests above hold against the oracle), bit for bit, whatever
+    the number of workgroups; the largest value of the batch in a last tile of one row."""
+    n = 32 * (tiles - 1) + 1
+    gen = torch.Generator(device="cuda").manual_seed(d + tiles)
+    x = torch.randn(n, d, generator=gen, device="cuda", dtype=torch.float16)
+    x[-1] *= 8.0
+    plan = B.Plan(d, g, 80 + d, transform=transform)
+    ref = torch.zeros(d, device="cuda")
+    for part in x.split(3200):
+        plan.channel_absmax(part, ref)
+    for cap in (0, 1, 3, 1_000_000):
+        B.srft_plan_set_max_workgroups(plan.handle, cap)
+        assert torch.equal(plan.channel_absmax(x), ref), cap
     plan.close()
 
 
