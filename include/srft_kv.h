@@ -235,9 +235,10 @@ int srft_kv_scores_static(const srft_plan_t* plan, const void* q_f16_dev, int n_
  * srft_cache_create   records the geometry and the pointers (host arrays of n_plans entries, copied); no HIP
  *                     calls.  capacity_tokens must be a positive multiple of residual_tokens (>= 1).
  * srft_cache_append   new_f16_dev: host array of n_plans device pointers, each [n_seq, t, d] fp16 (16-byte
- *                     aligned): t new tokens per sequence.  Enqueues: a copy of the tokens into the view; then, if
- *                     one or more pages became full, ONE batched quantize of those pages over all plans and one
- *                     batched dequantize of them back into the view.  Exceeding the capacity is SRFT_ERR_BAD_N
+ *                     aligned): t new tokens per sequence.  Enqueues a copy of the tokens into the view or, if one or
+ *                     more pages became full, their quantization over all plans, out of the new tokens and of what the
+ *                     window holds, and their decoding into the view, in one launch or two (three where the plans'
+ *                     buffers do not lie a constant step apart).  Exceeding the capacity is SRFT_ERR_BAD_N
  *                     (nothing is enqueued).  The result does not depend on how the tokens are split into calls.
  * srft_cache_rebuild_view  dequantizes the whole store into the view again (for a caller that dropped or
  *                     overwrote the view); O(prefix).  The window part of the view is not touched.

@@ -1,4 +1,4 @@
-// cache.hip -- cache manager: host bookkeeping around the batched kernels (int4 store, fp16 residual window,
+// cache.hip -- cache manager: host bookkeeping around the batched kernels and the flush (int4 store, fp16 residual window,
 // dequantized view), and the small scatter kernel that places new tokens in the paged view.
 #include <algorithm>
 #include <memory>
@@ -107,6 +107,49 @@ static int cache_convert(const srft_cache* c, int64_t first, int64_t count, bool
     return srft_run_batched(c->plans.data(), cd.data(), sc.data(), xo.data(), nullptr, n.data(), (int)np, false, st);
 }
 
+// The append of t tokens that fills `count` tokens of pages per sequence, without a copy into the view in front (cache_flush.h):
+// one launch, or two, the second one the read path's.  False: not for this cache, its buffers or its sizes.
+static bool cache_flush(const srft_cache* c, const void* const* fresh, int t, int64_t count, hipStream_t st, int* rc) {
+    const int np = (int)c->plans.size();
+    const srft_plan* p = c->plans[0];
+    const int64_t page_rows = (int64_t)c->n_seq * c->R, n_vec = count * c->n_seq, v0 = c->quantized * c->n_seq;
+    if (!p->entry || !srft_flush_fits(n_vec, page_rows, c->n_seq, t, p->d / 8)) return false;
+    srft_flush a;
+    if (!srft_even_step(fresh, np, &a.fresh_step) || !srft_even_step(c->view.data(), np, &a.view_step) ||
+        !srft_even_step((const void* const*)c->codes.data(), np, &a.codes_step) ||
+        !srft_even_step((const void* const*)c->scales.data(), np, &a.scales_step))
+        return false;
+    a.plan_step = np > 1 ? (long long)((uintptr_t)c->plans[1]->entry - (uintptr_t)p->entry) : 0;
+    for (int i = 1; i < np; ++i)
+        if (!c->plans[i]->entry || (uintptr_t)c->plans[i]->entry - (uintptr_t)c->plans[i - 1]->entry != (uintptr_t)a.plan_step) return false;
+    int threads = 0;
+    const flush_kernels_t kernels = srft_plan_flush_kernels(p, &threads);
+    const long long tiles = (n_vec + kTileVecs - 1) / kTileVecs;
+    const bool whole = kernels.whole && tiles * np <= (long long)srft_flush_whole_tiles(p->d, p->g) * p->grid_flush;
+    const long long budget = p->max_wgs > 0 ? p->max_wgs : whole ? p->grid_flush : p->grid_q;
+    if (np > budget) return false;
+    const long long blocks = std::min(tiles, budget / np);
+    if (blocks * np * blocks >= (1LL << 31)) return false;
+    a.shape = srft_even_spread(tiles, np, budget, (int)blocks);
+    a.plan = p->entry;
+    a.fresh = (const char*)fresh[0];
+    a.view = (char*)c->view[0] + v0 * p->d * 2;
+    a.codes = (char*)c->codes[0] + v0 * (p->d * p->bits / 8);
+    a.scales = (char*)(c->scales[0] + v0 * (p->d / p->g));
+    a.n_vec = (int)n_vec;
+    a.page_rows = (int)page_rows;
+    a.R = c->R;
+    a.held = (int)(c->tokens - c->quantized);
+    a.t_all = t;
+    a.tail = (int)(a.held + t - count);
+    a.page_magic = srft_even_magic(a.page_rows);
+    a.slot_magic = srft_even_magic(a.R);
+    a.gw = p->gw;
+    *rc = srft_launch(whole ? kernels.whole : kernels.write, dim3((unsigned)srft_even_grid(a.shape, np)), threads, st, a);
+    if (*rc == SRFT_OK && !whole) *rc = srft_no_throw([&] { return cache_convert(c, c->quantized, count, false, st); });
+    return true;
+}
+
 int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t, void* hip_stream) {
     if (!cache) return SRFT_ERR_NULL;
     if (t < 0 || cache->tokens + t > cache->capacity) return SRFT_ERR_BAD_N;
@@ -119,6 +162,13 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
     }
     hipStream_t st = (hipStream_t)hip_stream;
     const int units = cache->plans[0]->d / 8;
+    const int64_t full = (cache->tokens + t) / cache->R * cache->R;
+    if (int rc; full > cache->quantized && cache_flush(cache, new_f16_dev, t, full - cache->quantized, st, &rc)) {
+        if (rc != SRFT_OK) return rc;
+        cache->tokens += t;
+        cache->quantized = full;
+        return SRFT_OK;
+    }
     // 1. the new tokens join the window: an exact fp16 copy into the view
     scatter_even even;
     const bool is_even = np <= 4096 && srft_even_step(new_f16_dev, (int)np, &even.in_step) &&
@@ -153,9 +203,8 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
             if (rc != SRFT_OK) return rc;
         }
     cache->tokens += t;
-    // 2. every window that is now full is quantized into the store and replaced, in the view, by what the store
+    // 2. (buffers that do not lie a constant step apart) every window that is now full is quantized into the store and replaced, in the view, by what the store
     //    decodes to (the window is "re-quantized when full"; the dequantized prefix is refreshed only here)
-    const int64_t full = cache->tokens / cache->R * cache->R;
     if (full > cache->quantized) {
         const int rc = srft_no_throw([&] { return cache_convert(cache, cache->quantized, full - cache->quantized, true, st); });
         if (rc != SRFT_OK) return rc;

@@ -136,6 +136,26 @@ using srft_batch_many = srft_batch<kMaxBatch>;
 using srft_batch_few = srft_batch<kFewBatch>;
 static_assert(sizeof(srft_batch_many) + sizeof(int) <= 4096, "kernel arguments are limited to 4 KiB");
 
+// A cache's pages that became full, over all its plans (cache_flush.h): buffers and plan entries lie a constant step apart, as in
+// srft_batch_even.  codes, scales and view start at the first of these pages, fresh at the new tokens.
+struct srft_flush {
+    const srft_plan_entry* plan;
+    const char* fresh;
+    char *view, *codes, *scales;
+    long long plan_step, fresh_step, view_step, codes_step, scales_step;      // bytes
+    srft_even_shape shape;
+    int n_vec;                              // of each plan
+    int page_rows, R, held, t_all, tail;    // rows of a page (n_seq R); tokens a sequence's window holds, brings, and keeps
+    uint32_t page_magic, slot_magic;        // division by page_rows and R
+    int gw;
+};
+struct flush_kernels_t {
+    typedef void (*kernel)(const srft_flush);
+    kernel write, whole;                    // without and with the read path (null where the two paths' workgroups differ in size)
+    flush_kernels_t(std::nullptr_t = nullptr) : write(nullptr), whole(nullptr) {}
+    flush_kernels_t(kernel w, kernel all) : write(w), whole(all) {}
+};
+
 typedef void (*quantize_kernel_t)(const uint4*, const uint4*, long long, uint2*, float*, float4*, float, float, int);
 typedef void (*dequantize_kernel_t)(const uint4*, const uint2*, const float*, long long, uint4*, float, int);
 struct batched_kernels_t {
@@ -172,6 +192,7 @@ struct srft_plan {
     float unscale_r = 1.0f;
     float unscale_r4 = 1.0f;    // 2^-e of the twice-folded read table
     int grid_q = 0, grid_dq = 0;    // default persistent grid sizes
+    int grid_flush = 0;             // ... of a cache's flush with both paths in one launch (0: there is no such kernel)
     int slabs_q = 1, slabs_dq = 1;  // slabs of the matrix per wavefront in the write / read kernel
     int gm = 1, gw = 1;             // group mode (kGroup16 / kGroup32 / kGroupWide) and slabs per group
     int max_wgs = 0;
@@ -239,6 +260,10 @@ batched_kernels_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm, bool
 dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits);
 batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits);
 int srft_rfold4_table_units(int d);
+// a cache's flush (cache_flush.h)
+flush_kernels_t srft_pick_cache_flush_plain(int d, int bits, int gm);
+flush_kernels_t srft_pick_cache_flush_fold(int d, int bits, int gm, bool fold4_q);
+flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads);
 // write path with the transform as FFT butterflies on the vector ALU (d = 128 or 256, g = 32, 4-bit; the comparison form)
 int srft_launch_quantize_butterfly(int d, const float* table_dev, const void* x, long long n_vec, uint8_t* codes,
                                    float* scales, int max_workgroups, hipStream_t st);

@@ -118,11 +118,14 @@ struct srft_work {
     float unscale;
     int blocks, place;              // workgroups of the segment, this one's place among them
 };
+__device__ __forceinline__ int srft_block_by_die() {
+    const int q = gridDim.x >> 3, r = gridDim.x & 7, die = blockIdx.x & 7;
+    return die * q + min(die, r) + (int)(blockIdx.x >> 3);                   // a permutation of 0 .. gridDim.x - 1
+}
 template <bool WRITE, int N>
 __device__ __forceinline__ srft_work srft_work_of_block(const srft_batch<N>& a) {
     static_assert(N <= 64 && (N & (N - 1)) == 0, "a lane per boundary");
-    const int q = gridDim.x >> 3, r = gridDim.x & 7, die = blockIdx.x & 7;
-    const int block = die * q + min(die, r) + (int)(blockIdx.x >> 3);        // a permutation of 0 .. gridDim.x - 1
+    const int block = srft_block_by_die();
     if constexpr (N == 0) {                                  // segments of one length, a constant step apart
         const int i = srft_even_segment(block, a.shape), start = srft_even_start(i, a.shape);
         const srft_plan_entry* e = reinterpret_cast<const srft_plan_entry*>(reinterpret_cast<const char*>(a.plan) + i * a.plan_step);
@@ -243,6 +246,24 @@ __device__ __forceinline__ void publish_amax(float* part, size_t team_floats, un
     }
     if (c < D) atomic_max_nonneg(&amax[c], m * unscale);
 }
+
+// Where the input rows of the write path lie.  srft_rows_dense: one after the other from x on.
+struct srft_rows_dense {};
+// srft_rows_paged: the rows of a cache's pages that a flush converts (cache_flush.h).  Row v is slot v % R of sequence v / R %
+// n_seq of page v / (n_seq R), token j = page R + slot of its sequence counted from the first page on; the first `held` tokens of
+// a sequence are in the view already, in the place of row v, the others are where the caller has them, [n_seq][t_all][U units].
+// Row and unit numbers are 32-bit, and the divisions exact, by the host's check (srft_flush_fits).
+struct srft_rows_paged {
+    const uint4 *fresh, *view;
+    int page_rows, R, held, t_all;
+    uint32_t page_magic, slot_magic;
+    template <int U>
+    __device__ __forceinline__ const uint4* row(int v) const {
+        const int page = srft_even_segment((uint32_t)v, page_magic), in_page = v - page * page_rows;
+        const int seq = srft_even_segment((uint32_t)in_page, slot_magic), j = page * R + in_page - seq * R;
+        return j < held ? view + (unsigned)(v * U) : fresh + (unsigned)((seq * t_all + j - held) * U);
+    }
+};
 
 // Which tiles a workgroup of a per-plan launch walks: first tile, stride, and the end (exclusive) of its range.
 __device__ __forceinline__ bool srft_tile_range(long long n_vec, int& t0, int& stride, int& t_end) {

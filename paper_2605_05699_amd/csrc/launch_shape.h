@@ -102,6 +102,17 @@ SRFT_HOST_DEVICE constexpr int srft_even_start(int segment, const srft_even_shap
     return srft_even_segment((uint32_t)(segment * e.w), e.s_magic);
 }
 
+// A flush of n_vec rows in pages of page_rows = n_seq * R rows, out of new tokens [n_seq][t][units]: its kernel counts rows and
+// 16-byte units with 32 bits, and divides by page_rows and R as above.
+constexpr bool srft_flush_fits(long long n_vec, long long page_rows, long long n_seq, long long t, long long units) {
+    constexpr long long most = 1LL << 31;
+    return n_vec < most / page_rows && (n_vec + page_rows) * units < most && n_seq * t < most / units;
+}
+
+// Up to this many tiles per workgroup that fits the chip, a flush is one launch with both paths in it (cache_flush.h has the
+// figures): d = 256 and 32 lose from 4 on, d = 128 with g = 16 from 1 on, the others between 8 and 12 or (d = 96) not at all.
+constexpr int srft_flush_whole_tiles(int d, int g) { return d == 128 && g == 16 ? 1 : d == 256 || d == 32 ? 4 : 8; }
+
 // True when count addresses lie a constant step apart; *step is that step in bytes (0 for one).
 inline bool srft_even_step(const void* const* p, int count, long long* step) {
     *step = count > 1 ? (long long)((uintptr_t)p[1] - (uintptr_t)p[0]) : 0;

@@ -330,6 +330,11 @@ int occupancy_grids(srft_plan* p, int cus) {
     rc = resident_blocks((const void*)dk, threads, &blocks);
     if (rc != SRFT_OK) return rc;
     p->grid_dq = cus * blocks;
+    const flush_kernels_t fk = srft_plan_flush_kernels(p, &threads);
+    if (!fk.whole) return SRFT_OK;
+    rc = resident_blocks((const void*)fk.whole, threads, &blocks);
+    if (rc != SRFT_OK) return rc;
+    p->grid_flush = cus * blocks;
     return SRFT_OK;
 }
 
@@ -371,6 +376,17 @@ dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads
     *threads = 2 * p->d / p->slabs_dq;
     return p->bits == 8 ? srft_pick_dequantize_b8(p->d, p->slabs_dq, p->gm, p->fold_dq)
                         : srft_pick_dequantize_b4(p->d, p->slabs_dq, p->gm, p->fold_dq);
+}
+
+flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads) {
+    if (p->fold4_q || p->fold_q) {
+        *threads = p->d;
+        return srft_pick_cache_flush_fold(p->d, p->bits, p->gm, p->fold4_q);
+    }
+    *threads = 2 * p->d / p->slabs_q;
+    flush_kernels_t k = srft_pick_cache_flush_plain(p->d, p->bits, p->gm);
+    if (p->fold_dq || p->fold4_dq) k.whole = nullptr;        // (the read path that goes with it there is the plain one)
+    return k;
 }
 
 bool srft_plans_compatible(const srft_plan* a, const srft_plan* b) {

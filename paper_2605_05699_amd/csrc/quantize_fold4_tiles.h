@@ -54,11 +54,12 @@ constexpr int kFold4FragUnits = 4 * 2 * 4 * 2 * 64;          // 16-byte units of
 constexpr int kFold4RhoFloats = 4 * 64;
 constexpr int kFold4Units = kFold4FragUnits + kFold4RhoFloats / 4 + 4;
 
-template <int BITS, int GM, bool AMAX = false, int SUB = 1>
+template <int BITS, int GM, bool AMAX = false, int SUB = 1, class ROWS = srft_rows_dense>
 __device__ __forceinline__ void
 srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict__ x, long long n_vec,
                           uint2* __restrict__ codes, float* __restrict__ scales, float scale_mul,
-                          const int first_tile, const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr) {
+                          const int first_tile, const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr,
+                          const ROWS& rows = ROWS()) {
     static_assert(SUB == 1 || AMAX, "records are written by one team");
     constexpr int D = 256;
     constexpr int G = D / 32;            // groups per vector
@@ -114,7 +115,9 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
     auto fetch = [&](uint4& a, uint4& b, uint4& c, uint4& d, int tile) __attribute__((always_inline)) {
         if (tile > n_tiles - 1) tile = n_tiles - 1;
         const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;
-        const uint4* src = x + (long long)tile * kTileVecs * U + (unsigned)(min(frow, lim) * U + 4 * fchunk);
+        const uint4* src;
+        if constexpr (std::is_same_v<ROWS, srft_rows_dense>) src = x + (long long)tile * kTileVecs * U + (unsigned)(min(frow, lim) * U + 4 * fchunk);
+        else src = rows.template row<U>(tile * kTileVecs + min(frow, lim)) + 4 * fchunk;
         a = src[0];          // plain loads: four loads touch every line, and non-temporal ones then fetch it again
         b = src[1];
         c = src[2];

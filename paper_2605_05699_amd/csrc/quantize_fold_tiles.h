@@ -56,11 +56,12 @@
 // SUB: teams of M wavefronts per workgroup, each with tiles of its own (t0 + team, and stride counts tiles of all teams);
 //       they share the barriers and, at the end, one update of the statistic (AMAX).  All of them walk as many tiles as the
 //       first: past the end a team sees the last tile again, which a maximum does not mind.
-template <int D, int BITS, bool WIDE, bool AMAX = false, int SUB = 1>
+template <int D, int BITS, bool WIDE, bool AMAX = false, int SUB = 1, class ROWS = srft_rows_dense>
 __device__ __forceinline__ void
 srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restrict__ x, long long n_vec,
                          uint2* __restrict__ codes, float* __restrict__ scales, float unscale, float scale_mul,
-                         int gw, const int first_tile, const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr) {
+                         int gw, const int first_tile, const int stride, const int t_end, unsigned int* __restrict__ amax = nullptr,
+                         const ROWS& rows = ROWS()) {
     static_assert(SUB == 1 || AMAX, "records are written by one team");
     constexpr int M = D / 64;            // wavefronts per workgroup
     constexpr int G = D / 32;            // groups per vector
@@ -119,9 +120,11 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
     };
 
     // each thread moves two pairs of adjacent units (32 contiguous bytes each) per tile: pair q = tid + i NT
-    auto fetch2 = [&](uint4& a, uint4& b, int i, const uint4* tile_base, int lim) __attribute__((always_inline)) {
+    auto fetch2 = [&](uint4& a, uint4& b, int i, const uint4* tile_base, int lim, int tile) __attribute__((always_inline)) {
         const int q = tid + i * NT, r = q / (U / 2), c = q % (U / 2);
-        const uint4* src = tile_base + (unsigned)(min(r, lim) * U + 2 * c);
+        const uint4* src;
+        if constexpr (std::is_same_v<ROWS, srft_rows_dense>) src = tile_base + (unsigned)(min(r, lim) * U + 2 * c);
+        else src = rows.template row<U>(tile * kTileVecs + min(r, lim)) + 2 * c;
         a = src[0];
         b = src[1];
     };
@@ -129,8 +132,8 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
         if (tile > n_tiles - 1) tile = n_tiles - 1;
         const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;
         const uint4* tile_base = x + (long long)tile * kTileVecs * U;
-        fetch2(a, b, 0, tile_base, lim);
-        fetch2(c, d, 1, tile_base, lim);
+        fetch2(a, b, 0, tile_base, lim, tile);
+        fetch2(c, d, 1, tile_base, lim, tile);
     };
     // 16 consecutive inputs -> the 8 at even and the 8 at odd positions
     auto put2 = [&](int buf, const uint4& a, const uint4& b, int i) __attribute__((always_inline)) {

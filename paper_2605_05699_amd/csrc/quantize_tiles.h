@@ -21,11 +21,11 @@
 // The work of one workgroup: tiles t0, t0 + stride, ... of one plan's n_vec vectors (t0 < number of tiles).
 // BITS  : 4 (two nibbles per byte) or 8 (one byte per value, scale = abs-max / 127; Sec. 3.2 steps 3-4)
 // SUB   : teams of G / S wavefronts per workgroup (kOutAmax), as in srft_quantize_fold_tiles
-template <int D, int S, int OUT, int GM, int BITS, int SUB = 1>
+template <int D, int S, int OUT, int GM, int BITS, int SUB = 1, class ROWS = srft_rows_dense>
 __device__ __forceinline__ void
 srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x, long long n_vec,
                     uint2* __restrict__ codes, float* __restrict__ scales, float4* __restrict__ wout,
-                    float unscale, float scale_mul, int gw, const int first_tile, const int stride) {
+                    float unscale, float scale_mul, int gw, const int first_tile, const int stride, const ROWS& rows = ROWS()) {
     static_assert(SUB == 1 || OUT == kOutAmax, "records are written by one team");
     constexpr int G = D / 32;            // quantization groups per vector = slabs of the matrix
     constexpr int T = D / 16;            // MFMA k-steps
@@ -51,18 +51,19 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
     // The PER prefetched units of one tile live in separately named registers (PER = 2 uses a and b only).
     // Addresses are a uniform tile base (scalar registers) plus a 32-bit per-lane offset; rows past the end
     // alias to the last row through `lim`, the index of the last valid row of the tile (uniform).
-    auto fetch1 = [&](uint4& v, int i, const uint4* tile_base, int lim) __attribute__((always_inline)) {
+    auto fetch1 = [&](uint4& v, int i, const uint4* tile_base, int lim, int tile) __attribute__((always_inline)) {
         const int u = tid + i * NT, r = u / U, c = u % U;
-        v = tile_base[(unsigned)(min(r, lim) * U + c)];
+        if constexpr (std::is_same_v<ROWS, srft_rows_dense>) v = tile_base[(unsigned)(min(r, lim) * U + c)];
+        else v = rows.template row<U>(tile * kTileVecs + min(r, lim))[c];
     };
     auto fetch = [&](uint4& a, uint4& b, uint4& c, uint4& d, int tile) __attribute__((always_inline)) {
         if (tile > n_tiles - 1) tile = n_tiles - 1;          // prefetch past the end re-reads the last tile
         const long long row0 = (long long)tile * kTileVecs;
         const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;
         const uint4* tile_base = x + row0 * U;
-        fetch1(a, 0, tile_base, lim);
-        fetch1(b, 1, tile_base, lim);
-        if constexpr (PER > 2) { fetch1(c, 2, tile_base, lim); fetch1(d, 3, tile_base, lim); }
+        fetch1(a, 0, tile_base, lim, tile);
+        fetch1(b, 1, tile_base, lim, tile);
+        if constexpr (PER > 2) { fetch1(c, 2, tile_base, lim, tile); fetch1(d, 3, tile_base, lim, tile); }
     };
     auto put1 = [&](int buf, const uint4& v, int i) __attribute__((always_inline)) {
         const int u = tid + i * NT, r = u / U, c = u % U;

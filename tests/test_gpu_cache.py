@@ -176,3 +176,62 @@ def test_new_tokens_are_copied_to_their_place(B, d, n_plans, n_seq, R, schedule)
         view = _tokens(cache.view[p], 2 * R)
         assert torch.equal(view[:, :T], x[p])
         assert bool((view[:, T:] == 3.0).all())
+
+
+# One launch, two, and three.  Flushes of one tile and less; of many tiles, where the read path is a launch of its own from
+# 1, 4 or 8 tiles per resident workgroup on (d = 128 with g = 16, d = 256, d = 128 and 64); forms whose two paths' workgroups
+# differ (d = 192, d = 256 with g = 16); windows that held tokens before; and buffers that lie a constant step apart or not.
+@pytest.mark.parametrize("even", [True, False])
+@pytest.mark.parametrize("d,g,bits,transform,R,n_seq,schedule", [
+    (128, 32, 4, "dft", 16, 2, [5, 11, 1, 70]), (128, 32, 8, "dft", 16, 3, [100, 1]), (128, 128, 4, "dft", 5, 2, [3, 3, 31]),
+    (128, 16, 4, "dft", 16, 8, [7, 1100, 3]), (128, 32, 4, "hadamard", 16, 2, [40]), (128, 32, 4, "dft", 16, 16, [9, 5000]),
+    (256, 32, 4, "dft", 16, 2, [15, 2]), (256, 32, 8, "dft", 7, 3, [50]), (256, 256, 4, "dft", 16, 1, [33]), (256, 64, 4, "dft", 16, 2, [60]),
+    (256, 16, 4, "dft", 16, 3, [40, 9]), (256, 32, 4, "dft", 16, 8, [2500]), (256, 32, 8, "hadamard", 16, 2, [20]),
+    (64, 32, 4, "dft", 16, 1, [20, 12]), (64, 16, 8, "dft", 3, 5, [8, 2]), (64, 64, 4, "dft", 16, 2, [47]), (96, 32, 4, "dft", 16, 6, [1, 100]),
+    (96, 96, 8, "dft", 1, 2, [1, 2]), (32, 32, 4, "dft", 16, 2, [18]), (192, 32, 4, "dft", 16, 2, [17, 40]), (160, 16, 8, "dft", 16, 2, [35]),
+    (224, 224, 4, "dft", 16, 1, [33]),
+])
+def test_a_flush_stores_and_shows_what_the_plans_own_paths_give(B, d, g, bits, transform, R, n_seq, schedule, even):
+    n_plans, T = 3, sum(schedule)
+    pages = -(-T // R) + 1
+    plans = [B.Plan(d, g, 90 + p, W.lognormal_lambda(d, seed=7 * p + d), bits=bits, transform=transform) for p in range(n_plans)]
+    lead = [0, 0, 0] if even else [0, 64, 16]                # 16-byte steps in front of a plan's buffers
+
+    def buffers(shape, dtype, fill):
+        n = int(np.prod(shape))
+        room = n + 1024
+        flat = torch.full((n_plans * room,), fill, dtype=dtype, device="cuda")
+        return [flat[p * room + lead[p]:p * room + lead[p] + n].view(shape) for p in range(n_plans)]
+
+    codes = buffers((pages, n_seq, R, d * bits // 8), torch.uint8, 9)
+    scales = buffers((pages, n_seq, R, d // g), torch.float32, 9)
+    view = buffers((pages, n_seq, R, d), torch.float16, 9)
+    x = [(torch.randn(n_seq, T, d, device="cuda", generator=torch.Generator("cuda").manual_seed(p)) * 3).to(torch.float16) for p in range(n_plans)]
+    L, arr = B.lib(), C.c_void_p * n_plans
+    handle = C.c_void_p()
+    assert L.srft_cache_create(C.byref(handle), arr(*[p.handle for p in plans]), n_plans, n_seq, pages * R, R,
+                               *[arr(*[t.data_ptr() for t in b]) for b in (codes, scales, view)]) == 0
+    pos = 0
+    for t in schedule:
+        new = buffers((n_seq, t, d), torch.float16, 9)
+        for p in range(n_plans):
+            new[p].copy_(x[p][:, pos:pos + t])
+        assert L.srft_cache_append(handle, arr(*[b.data_ptr() for b in new]), t, torch.cuda.current_stream().cuda_stream) == 0
+        pos += t
+    assert L.srft_cache_quantized_tokens(handle) == T // R * R
+    torch.cuda.synchronize()
+    full = T // R
+    for p in range(n_plans):
+        flushed = x[p][:, :full * R].reshape(n_seq, full, R, d).transpose(0, 1).contiguous().view(-1, d)
+        c, s = plans[p].quantize(flushed)
+        back = plans[p].dequantize(c, s)
+        assert torch.equal(codes[p][:full].reshape(c.shape), c)
+        assert torch.equal(scales[p][:full].reshape(s.shape).view(torch.int32), s.view(torch.int32))
+        assert torch.equal(view[p][:full].reshape(back.shape).view(torch.int16), back.view(torch.int16))
+        tail = _tokens(view[p], pages * R)[:, full * R:]
+        assert torch.equal(tail[:, :T - full * R], x[p][:, full * R:])
+        # nothing else is written
+        assert bool((tail[:, T - full * R:] == 9).all()) and bool((codes[p][full:] == 9).all()) and bool((scales[p][full:] == 9).all())
+    L.srft_cache_destroy(handle)
+    for pl in plans:
+        pl.close()

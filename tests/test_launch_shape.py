@@ -27,6 +27,9 @@ extern "C" int spread(long long tiles, long long count, long long budget, int* s
     return grid;
 }
 extern "C" int even_step(const void* const* p, int count, long long* step) { return srft_even_step(p, count, step); }
+extern "C" int flush_fits(long long n_vec, long long page_rows, long long n_seq, long long t, long long units) {
+    return srft_flush_fits(n_vec, page_rows, n_seq, t, units);
+}
 extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
 extern "C" long long copy_first(int i) { return srft_copy_first(i); }
 extern "C" unsigned copy_tokens(int i, int t) { return srft_copy_tokens(i, t); }
@@ -154,6 +157,29 @@ def test_workgroup_to_segment_without_a_table(lib, blocks):
             continue
         for block in {0, grid - 1} | {k * blocks + e for k in range(0, count, max(1, count // 50)) for e in (0, blocks - 1)}:
             assert lib.even_segment(block, blocks) == block // blocks, (blocks, count, block)
+
+
+@pytest.mark.parametrize("n_seq,R", [(1, 1), (1, 16), (2, 16), (3, 7), (8, 16), (70, 5), (512, 16), (46340, 1)])
+def test_rows_of_a_flush_divide_exactly(lib, n_seq, R):
+    """Row v of a flush is in page v / (n_seq R), there of sequence rest / R, for every size that is let through."""
+    page_rows, ll = n_seq * R, C.c_longlong
+    most = (2 ** 31 // page_rows - 1) // page_rows * page_rows
+    assert most >= page_rows
+    rng = random.Random(page_rows)
+    for v in {0, most - 1} | {rng.randrange(most) for _ in range(300)} | {k * page_rows + e for k in range(1, most // page_rows, max(1, most // page_rows // 50)) for e in (-1, 0)}:
+        page = lib.even_segment(v, page_rows)
+        assert page == v // page_rows and lib.even_segment(v - page * page_rows, R) == v % page_rows // R
+    # what no longer divides or counts exactly is refused: the rows, the view's units, the new tokens' units
+    assert lib.flush_fits(ll(page_rows), ll(page_rows), ll(n_seq), ll(R), ll(4)) == 1
+    assert lib.flush_fits(ll(2 ** 31 // page_rows), ll(page_rows), ll(n_seq), ll(R), ll(4)) == 0
+    assert lib.flush_fits(ll(page_rows), ll(page_rows), ll(n_seq), ll(2 ** 31 // 4 // n_seq + 1), ll(4)) == 0
+
+
+def test_a_flush_as_large_as_its_units_are_counted(lib):
+    ll = C.c_longlong
+    assert lib.flush_fits(ll(2 ** 26 - 33), ll(16), ll(1), ll(2 ** 26 - 1), ll(32)) == 1
+    assert lib.flush_fits(ll(2 ** 26 - 16), ll(16), ll(1), ll(2 ** 26 - 1), ll(32)) == 0
+    assert lib.flush_fits(ll(2 ** 26 - 33), ll(16), ll(1), ll(2 ** 26), ll(32)) == 0
 
 
 def test_addresses_a_constant_step_apart(lib):
