@@ -20,7 +20,7 @@
 // correction need; with channels on the rows and queries on the columns of the second product the sums belong to the same query.
 // Measured, us, against a scan that stores the scores, a value pass over 2048 one-wavefront workgroups and two reductions:
 // d = 128, 8 queries, 131,072 keys 36.6 -> 13.6, 400,000 keys 51 -> 23; 32 queries, 400,000 keys 111 -> 38; d = 256, 4 queries,
-// 4096 keys 27.7 -> 10.8; d = 64, 1 query, 500 keys 21.9 -> 10.5.  Error against 64 bits 6e-6 -> 4e-7.
+// 4096 keys 27.7 -> 9.15; d = 64, 1 query, 500 keys 21.9 -> 10.5.  Error against 64 bits 6e-6 -> 4e-7.
 #include <algorithm>
 
 #include "../rotated_queries.h"
@@ -66,41 +66,54 @@ __device__ __forceinline__ float wave_sum(float x) {
     return quarters_sum(x);
 }
 
-// D: head dimension.  KEYS: keys per tile, 64 or 32.  WIDE: groups of gw > 1 runs of 32 channels share a scale.
+// D: head dimension.  KEYS: keys per tile, 64 or 32 (then ONE).  WIDE: groups of gw > 1 runs of 32 channels share a scale.
 // blockIdx.y: block of 16 queries.  (Both blocks of 32 queries in one wavefront -- the codes decoded once -- needs more
 // registers than two wavefronts per SIMD leave: 250 spilled at d = 128.)
 // ONE: no wavefront has more than one tile (up to 131,072 keys and 16 queries on a whole chip): nothing is asked for behind
 // it and nothing scaled down (and 110 registers do where 201 did, d = 128).  us: 8 queries, 131,072 keys at d = 128 13.8 ->
 // 13.6, at d = 256 22.9 -> 22.4; 16 queries, 9000 keys at d = 256 15.3 -> 15.0; 8 queries, 60,000 keys at d = 192 15.0 ->
 // 14.75.
-template <int D, int KEYS, bool WIDE, bool ONE>
+// TEAM: wavefronts to a tile, each with D / 32 / TEAM groups of it on both sides.  With few tiles most of a workgroup's wavefronts
+// had none, and the chain of one tile, a third of it vector instructions of one wavefront, was what the scan took (4096 keys at
+// d = 256: 2,100 clocks scores, 2,300 values, 1,200 the sums' way to the workspace, of 11,400).  The members add up their shares
+// of the scores in LDS, in one order, so all hold the same scores and weights, and their sums of the values are of different
+// channels: nothing is left to meet for.  us, a wavefront to a tile -> teams: 4 queries, 4096 keys at d = 256 10.45 -> 9.15, 500 9.25
+// -> 7.95, 12,000 13.9 -> 12.65; of two wavefronts, 20,000 14.05 -> 13.65, 16 queries, 30,000 15.95 -> 14.45; d = 192, 8 queries,
+// 5000 10.95 -> 10.05, 16,000 12.05 -> 11.15; d = 128, 2000 7.5 -> 7.05, 9000 9.65 -> 8.85, 30,000 9.35 -> 9.05.
+template <int D, int KEYS, bool WIDE, bool ONE, int TEAM = 1>
 __global__ void __launch_bounds__(64 * kWaves, 2)
 srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ q_table,
                            int hadamard, float q_sign, const uint8_t* __restrict__ k_codes,
                            const float* __restrict__ k_scales, int k_gw, const uint8_t* __restrict__ v_codes,
                            const float* __restrict__ v_scales, int v_gw, long long n_keys, float softmax_scale,
                            float* __restrict__ part, float* __restrict__ part_max, float* __restrict__ part_sum) {
-    constexpr int G = D / 32, QUADS = G / 4, REST = G % 4;   // a row of codes: QUADS x 64 bytes, then REST x 16 bytes
-    constexpr int W = kWaves;
-    constexpr int ROW = D / 2;                               // bytes
+    constexpr int ALL = D / 32, G = ALL / TEAM;              // groups of a row, and of those this wavefront's
+    constexpr int QUADS = G / 4, REST = G % 4;               // its part of a row of codes: QUADS x 64 bytes, then REST x 16 bytes
+    constexpr int W = kWaves, TEAMS = W / TEAM;
+    constexpr int ROW = D / 2, MINE = 16 * G;                // bytes of a row, of the part
     constexpr int BK = KEYS / 16;                            // blocks of 16 keys
     constexpr int KQ = KEYS / 4;                             // keys per quarter of the wavefront
-    constexpr int VROW = ROW + 16;                           // padded: the 16 rows of a transposed read hit different banks
+    constexpr int VROW = MINE + 16;                          // padded: the 16 rows of a transposed read hit different banks
     constexpr int VTILE = KEYS * VROW + 4 * 8;               // and 8 bytes more per quarter's rows keep the quarters apart
     constexpr int NV = KEYS * G / 64;                        // 16-byte pieces of a V tile per lane
-    constexpr int NB = D / 16;                               // blocks of 16 channels
+    constexpr int NB = 2 * G;                                // blocks of 16 channels
     constexpr int WAVE_BYTES = VTILE + (2 * G + 1) * KEYS * 4;
-    constexpr int LDS_BYTES = W * WAVE_BYTES;
+    constexpr int TILE_BYTES = W * WAVE_BYTES, MEET_BYTES = TEAMS * 16 * (D + 4) * 4, QUERY_BYTES = srft_query_scratch_bytes<D, 1>();
+    constexpr int LDS_BYTES = TEAM == 1 ? TILE_BYTES : std::max(TILE_BYTES, std::max(MEET_BYTES, QUERY_BYTES));
     static_assert(D % 64 == 0 && VTILE % 16 == 0 && (KEYS == 32 || KEYS == 64), "layout");
+    static_assert(TEAM == 1 || (ONE && KEYS == 32 && (G == 2 || G == 4) && G * TEAM == ALL), "a team has one tile, two or four groups a wavefront");
+    static_assert(KEYS == 64 || ONE, "tiles of 32 keys are for short prefixes");
     __shared__ __align__(16) unsigned char lds[LDS_BYTES];
-    __shared__ uint4 qs[G * 2 * 64];
+    __shared__ uint4 qs[ALL * 2 * 64];
     __shared__ float meet[2][W][16];
+    __shared__ floatx4 shares[TEAM > 1 ? W : 1][TEAM > 1 ? KEYS / 16 : 1][TEAM > 1 ? 64 : 1];    // of the scores, per wavefront
 
     // all arguments in one go: loaded where they are used, each is a round trip of its own in the chain of one tile
     asm volatile("" :: "s"(hadamard), "s"(q_sign), "s"(softmax_scale), "s"(part), "s"(part_max), "s"(part_sum), "s"(q_table),
                  "s"(k_codes), "s"(k_scales), "s"(v_codes), "s"(v_scales), "s"(n_keys));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // (uniform: tile addresses in scalar registers)
     const int l16 = lane & 15, a = lane >> 4;                // query (or key / channel of a block of 16), quarter
+    const int team = wave / TEAM, member = wave % TEAM, g0 = member * G;     // (wavefronts left over: a team that has no tile)
     unsigned char* const vt = lds + wave * WAVE_BYTES;       // this wavefront's V tile and scales: no other one touches them
     float* const ks = reinterpret_cast<float*>(vt + VTILE);  // [group][key]
     float* const vs = ks + G * KEYS;
@@ -108,9 +121,9 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     const int q0 = 16 * blockIdx.y, nq = min(16, n_q - q0);  // the queries of this workgroup
 
     const long long n_tiles = (n_keys + KEYS - 1) / KEYS;
-    const long long stride = (long long)gridDim.x * W;
-    // tiles wave * grid + workgroup + k * stride: a short prefix is spread over as many compute units as it has tiles
-    const long long first = (long long)wave * gridDim.x + blockIdx.x;
+    const long long stride = (long long)gridDim.x * TEAMS;
+    // tiles team * grid + workgroup + k * stride: a short prefix is spread over as many compute units as it has tiles
+    const long long first = (long long)team * gridDim.x + blockIdx.x;
 
     // Which key a lane loads as row m = l16 of block b of the K tile: KQ (m / 4) + 4 b + m % 4.  The score product's result
     // register i of quarter a is row 4 a + i, so a quarter ends up with the keys KQ a .. KQ a + KQ - 1 (register [b][i]:
@@ -121,11 +134,11 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     floatx4 pks[(G + 3) / 4], pvs[(G + 3) / 4];
     auto fetch_scales = [&](floatx4 (&dst)[(G + 3) / 4], const float* src, int gw, long long t0, int rl) __attribute__((always_inline)) {
         if constexpr (WIDE) {
-            const int ns = G / gw;
+            const int ns = ALL / gw;
 #pragma unroll
-            for (int j = 0; j < G; ++j) dst[j / 4][j % 4] = (src + t0 * ns)[(unsigned)(rl * ns + j / gw)];
+            for (int j = 0; j < G; ++j) dst[j / 4][j % 4] = (src + t0 * ns)[(unsigned)(rl * ns + (g0 + j) / gw)];
         } else {
-            const float* row = src + t0 * G + (unsigned)(rl * G);
+            const float* row = src + t0 * ALL + (unsigned)(rl * ALL + g0);
 #pragma unroll
             for (int j = 0; j + 4 <= G; j += 4) dst[j / 4] = *reinterpret_cast<const floatx4u*>(row + j);
 #pragma unroll
@@ -137,7 +150,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     auto fetch_k = [&](long long tile, bool all) __attribute__((always_inline)) {
         const long long t0 = tile * KEYS;
         const int lim = all ? lim_of(t0) : 0;
-        const uint8_t* kb = k_codes + t0 * ROW;
+        const uint8_t* kb = k_codes + t0 * ROW + 16 * g0;
 #pragma unroll
         for (int b = 0; b < BK; ++b) {
             const unsigned row = (unsigned)min(KQ * (l16 >> 2) + 4 * b + (l16 & 3), lim) * ROW;
@@ -150,7 +163,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     auto fetch_v = [&](long long tile, bool all) __attribute__((always_inline)) {
         const long long t0 = tile * KEYS;
         const int lim = all ? lim_of(t0) : 0;
-        const uint8_t* vb = v_codes + t0 * ROW;
+        const uint8_t* vb = v_codes + t0 * ROW + 16 * g0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int u = lane + 64 * i;
@@ -185,8 +198,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     // The LDS operands of a step are read one step ahead of their use.
     struct KStep { uint4 h, l; float4 sc[BK]; };
     auto load_k = [&](KStep& f, int j) __attribute__((always_inline)) {
-        f.h = qs[(j * 2 + 0) * 64 + lane];
-        f.l = qs[(j * 2 + 1) * 64 + lane];
+        f.h = qs[((g0 + j) * 2 + 0) * 64 + lane];
+        f.l = qs[((g0 + j) * 2 + 1) * 64 + lane];
 #pragma unroll
         for (int b = 0; b < BK; ++b) f.sc[b] = *reinterpret_cast<const float4*>(&ks[j * KEYS + KQ * a + 4 * b]);
     };
@@ -201,8 +214,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
 #pragma unroll
         for (int b = 0; b < BK; ++b) f.sc[b] = *reinterpret_cast<const float4*>(&vs[j * KEYS + KQ * a + 4 * b]);
     };
-    for (long long tile = first; tile < n_tiles; tile += stride) {
-        const bool more = tile + stride < n_tiles;
+    float w[BK][4];                                          // scores, then weights: keys KQ a + 4 b + i of query l16
+    const auto scores = [&](const long long tile, const bool more) __attribute__((always_inline)) {
         // LDS of one wavefront: its accesses complete in program order
 #pragma unroll
         for (int j = 0; j < G; ++j) {
@@ -225,7 +238,6 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
         // sets: 100 registers more at d = 128): past the end every lane reads the first row of this tile again.
         if constexpr (!ONE) fetch_v(more ? tile + stride : tile, more);
         // ---- scores: keys on the rows, queries on the columns
-        float w[BK][4];
 #pragma unroll
         for (int b = 0; b < BK; ++b) {
 #pragma unroll
@@ -255,6 +267,8 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             if ((KEYS == 64 && !ONE) || j % 2) __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (!ONE) fetch_k(more ? tile + stride : tile, more);
+    };
+    const auto values = [&](const long long tile) __attribute__((always_inline)) {
         VStep vc, vn;
         load_v(vc, 0);
         // ---- running softmax, per query (column)
@@ -329,18 +343,45 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             if ((KEYS == 64 && !ONE) || j % 2) __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if constexpr (ONE) break;
+    };
+    if constexpr (TEAM > 1) {
+        if (first < n_tiles) {
+            scores(first, false);
+#pragma unroll
+            for (int b = 0; b < BK; ++b) shares[wave][b][lane] = floatx4{w[b][0], w[b][1], w[b][2], w[b][3]};
+        }
+        __syncthreads();
+        if (first < n_tiles) {
+            floatx4 s[BK];                                   // the members' shares in their order: all of them get the same scores
+#pragma unroll
+            for (int b = 0; b < BK; ++b) s[b] = shares[team * TEAM][b][lane];
+#pragma unroll
+            for (int k = 1; k < TEAM; ++k)
+#pragma unroll
+                for (int b = 0; b < BK; ++b) s[b] += shares[team * TEAM + k][b][lane];
+#pragma unroll
+            for (int b = 0; b < BK; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[b][i] = s[b][i];
+            values(first);
+        }
+    } else {
+        for (long long tile = first; tile < n_tiles; tile += stride) {
+            scores(tile, tile + stride < n_tiles);
+            values(tile);
+            if constexpr (ONE) break;
+        }
     }
-    // ---- the wavefronts of the workgroup that had a tile meet
-    const int active = (int)min((long long)W, (n_tiles - 1 - blockIdx.x) / gridDim.x + 1);
+    // ---- the teams of the workgroup that had a tile meet
+    const int active = (int)min((long long)TEAMS, (n_tiles - 1 - blockIdx.x) / gridDim.x + 1);
     den = quarters_sum(den);
-    if (a == 0) {
-        meet[0][wave][l16] = top;
-        meet[1][wave][l16] = den;
+    if (member == 0 && team < TEAMS && a == 0) {
+        meet[0][team][l16] = top;
+        meet[1][team][l16] = den;
     }
     float* const dst = part + ((size_t)blockIdx.x * n_q + q0) * D;
     if (active == 1) {                                       // nobody to meet (short prefixes: 2200 clocks at d = 256 otherwise)
-        if (wave == 0) {
+        if (team == 0) {
             const float f = __builtin_ldexpf(1.0f, -fit);
             if (tid < nq) {
                 part_max[(q0 + l16) * kScanGridMax + blockIdx.x] = top;
@@ -348,23 +389,39 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
             }
             if (l16 < nq)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) *reinterpret_cast<floatx4*>(&dst[l16 * D + 16 * b + 4 * a]) = acc[b] * f;
+                for (int b = 0; b < NB; ++b) *reinterpret_cast<floatx4*>(&dst[l16 * D + 32 * g0 + 16 * b + 4 * a]) = acc[b] * f;
         }
         return;
     }
     __syncthreads();
-    float t = meet[0][0][l16];                               // (wavefronts without a tile: kLowest and 0)
+    float t = meet[0][0][l16];                               // (teams without a tile: kLowest and 0)
 #pragma unroll
-    for (int k = 1; k < W; ++k) t = fmaxf(t, meet[0][k][l16]);
+    for (int k = 1; k < TEAMS; ++k) t = fmaxf(t, meet[0][k][l16]);
     const float f = __builtin_ldexpf(__builtin_amdgcn_exp2f(top - t), -fit);
     if (tid < nq) {
         float s = 0.0f;
 #pragma unroll
-        for (int k = 0; k < W; ++k) s = fmaf(meet[1][k][l16], __builtin_amdgcn_exp2f(meet[0][k][l16] - t), s);
+        for (int k = 0; k < TEAMS; ++k) s = fmaf(meet[1][k][l16], __builtin_amdgcn_exp2f(meet[0][k][l16] - t), s);
         part_max[(q0 + l16) * kScanGridMax + blockIdx.x] = t;
         part_sum[(q0 + l16) * kScanGridMax + blockIdx.x] = s;
     }
-    // sums: [wavefront][query][channel], as many channels at a time as fit
+    if constexpr (TEAM > 1) {                                // sums: [team][query][channel]
+        float* const merge = reinterpret_cast<float*>(lds);
+        constexpr int MROW = D + 4;                          // padded
+        __syncthreads();                                     // (the tiles have been read)
+        if (team < active && l16 < nq)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) *reinterpret_cast<floatx4*>(&merge[(team * nq + l16) * MROW + 32 * g0 + 16 * b + 4 * a]) = acc[b] * f;
+        __syncthreads();
+        for (int e = tid; e < nq * (D / 4); e += 64 * W) {
+            const int r = e / (D / 4), p = e % (D / 4);
+            floatx4 s = *reinterpret_cast<const floatx4*>(&merge[r * MROW + 4 * p]);
+            for (int k = 1; k < active; ++k) s += *reinterpret_cast<const floatx4*>(&merge[(k * nq + r) * MROW + 4 * p]);
+            *reinterpret_cast<floatx4*>(&dst[r * D + 4 * p]) = s;
+        }
+        return;
+    }
+    // (a wavefront to a tile) sums: [wavefront][query][channel], as many channels at a time as fit
     float* const merge = reinterpret_cast<float*>(lds);
     static_assert(W * 16 * (16 + 4) * 4 <= LDS_BYTES, "at least one block at a time");
     int nb = NB;
@@ -523,8 +580,8 @@ template <int D>
 int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, const uint8_t* k_codes, const float* k_scales,
            const uint8_t* v_codes, const float* v_scales, long long n_keys, float softmax_scale, float* out, void* workspace,
            hipStream_t st) {
-    // Tiles of 64 keys, or of 32 where that still leaves every wavefront of the chip at most one: the chain of one tile is then
-    // half as long.  Workgroups: one per tile, up to one per compute unit (its eight wavefronts fill the register file); with
+    // Tiles of 64 keys, or of 32 where that still leaves every wavefront of the chip at most one (and then wavefronts in teams, while
+    // every team has at most one): the chain of one tile is then half as long.  Workgroups: one per tile, up to one per compute unit (its eight wavefronts fill the register file); with
     // two blocks of queries half of that each, so that both read a tile at about the same time.
     const int blocks = n_q <= 16 ? 1 : 2;
     long long most = pv->compute_units;
@@ -532,26 +589,31 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     if (pv->max_wgs > 0 && (pk->max_wgs == 0 || pv->max_wgs < most)) most = pv->max_wgs;
     long long grid = std::max(most / blocks, 1LL);           // (a cap is on all of them; one for each block of queries is the least)
     if (grid > kScanGridMax) grid = kScanGridMax;
+    // (63, 126 or 252 are what the finish adds in one pass at D = 192: 8192 keys, 8 queries 14.2 -> 12.4 us)
+    const auto in_one_pass = [](long long n) {
+        if (D == 192)
+            for (const long long one_pass : {63, 126, 252})
+                if (n > one_pass && n <= one_pass + one_pass / 63) return one_pass;
+        return n;
+    };
+    grid = in_one_pass(grid);
     const bool narrow = n_keys <= 32 * kWaves * grid;
     const long long n_tiles = narrow ? (n_keys + 31) / 32 : (n_keys + 63) / 64;
-    if (grid > n_tiles) grid = n_tiles;
-    // (63, 126 or 252 are what the finish adds in one pass at D = 192: 8192 keys, 8 queries 14.2 -> 12.4 us)
-    if (D == 192)
-        for (const long long one_pass : {63, 126, 252})
-            if (grid > one_pass && grid <= one_pass + one_pass / 63) grid = one_pass;
+    grid = in_one_pass(std::min(grid, n_tiles));
     static_assert((size_t)kScanGridMax * 32 * (2 + D) <= srft_attend_workspace_floats(D), "fits what callers are told to bring");
     float* part_max = (float*)workspace;                     // [32][kScanGridMax] each
     float* part_sum = part_max + kScanGridMax * 32;
     float* part = part_sum + kScanGridMax * 32;              // [workgroup][n_q][D]
-    const bool wide = pk->gw > 1 || pv->gw > 1;
     const float sign = softmax_scale < 0.0f ? -1.0f : 1.0f;  // goes into the queries: the kernel's scale is not negative
-    const bool one = n_tiles <= kWaves * grid;
-    const auto pick = [&](auto many, auto once) { return one ? once : many; };
+    const auto pick = [&](auto shared, auto plain) { return pk->gw > 1 || pv->gw > 1 ? shared : plain; };
+    // as many wavefronts to a tile (two groups each, or four) as leaves every team at most one
+    constexpr int TWO = D / 64, FOUR = D == 256 ? 2 : 1;
     const auto kernel =
-        narrow ? (wide ? pick(srft_attention_scan_kernel<D, 32, true, false>, srft_attention_scan_kernel<D, 32, true, true>)
-                       : pick(srft_attention_scan_kernel<D, 32, false, false>, srft_attention_scan_kernel<D, 32, false, true>))
-               : (wide ? pick(srft_attention_scan_kernel<D, 64, true, false>, srft_attention_scan_kernel<D, 64, true, true>)
-                       : pick(srft_attention_scan_kernel<D, 64, false, false>, srft_attention_scan_kernel<D, 64, false, true>));
+        narrow && n_tiles <= kWaves / TWO * grid    ? pick(srft_attention_scan_kernel<D, 32, true, true, TWO>, srft_attention_scan_kernel<D, 32, false, true, TWO>)
+        : narrow && n_tiles <= kWaves / FOUR * grid ? pick(srft_attention_scan_kernel<D, 32, true, true, FOUR>, srft_attention_scan_kernel<D, 32, false, true, FOUR>)
+        : narrow                                    ? pick(srft_attention_scan_kernel<D, 32, true, true>, srft_attention_scan_kernel<D, 32, false, true>)
+        : n_tiles <= kWaves * grid                  ? pick(srft_attention_scan_kernel<D, 64, true, true>, srft_attention_scan_kernel<D, 64, false, true>)
+                                                    : pick(srft_attention_scan_kernel<D, 64, true, false>, srft_attention_scan_kernel<D, 64, false, false>);
     const int rc = srft_launch(kernel, dim3((unsigned)grid, blocks), 64 * kWaves, st, (const uint4*)q, n_q, (const uint4*)pk->q_table,
                                (int)(pk->transform == SRFT_TRANSFORM_HADAMARD), sign, k_codes, k_scales, pk->gw, v_codes, v_scales,
                                pv->gw, n_keys, sign * softmax_scale, part, part_max, part_sum);

@@ -428,3 +428,15 @@ def test_decode_attention_of_hadamard_plans(B, transforms, d, g, n_q, n_keys, ca
     assert np.abs(got - ref).max() <= tol, float(np.abs(got - ref).max() / tol)
     for p in plans:
         p.close()
+
+
+# Tiles of 32 keys, by wavefronts in teams of d / 64 (up to 8 / team tiles a workgroup), of two (d = 256, up to 4) and alone: the
+# last size of each form and the first of the next, at 3 workgroups and at the 126 of 128 that d = 192 takes; one key; a last
+# tile of one key; groups of 32 channels and of all d.
+@pytest.mark.parametrize("n_q", [1, 16, 17])
+@pytest.mark.parametrize("d,g,n_keys,cap", [
+    (256, 32, 1, 3), (256, 256, 31, 3), (256, 32, 97, 3), (256, 256, 192, 3), (256, 32, 193, 3), (256, 256, 384, 3), (256, 32, 385, 3), (256, 32, 769, 3),
+    (192, 32, 33, 3), (192, 192, 192, 3), (192, 32, 193, 3), (192, 192, 4064, 128), (192, 32, 8064, 128), (192, 32, 8065, 128),
+    (128, 32, 32, 3), (128, 128, 384, 3), (128, 32, 385, 3), (128, 32, 768, 3), (128, 128, 769, 3), (64, 32, 768, 3), (64, 64, 769, 3)])
+def test_decode_attention_at_the_edges_of_its_teams(B, d, g, n_q, n_keys, cap):
+    test_decode_attention_at_the_edges_of_its_tiles_and_grid(B, d, g, n_q, n_keys, cap, 0.1)
