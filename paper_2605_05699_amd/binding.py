@@ -13,6 +13,11 @@ import os
 import numpy as np
 import torch
 
+try:                                    # native marshalling of the calls that are made step after step (csrc/host/marshal.cpp)
+    from . import _marshal
+except ImportError:                     # (not built: the same calls through ctypes)
+    _marshal = None
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("SRFT_KV_LIB") or os.path.join(_PKG, "libsrft_kv.so")
 _lib = None
@@ -94,6 +99,12 @@ def lib() -> C.CDLL:
     L.srft_decode_attention_workspace_bytes.restype = i64
     L.srft_cache_tokens.restype = i64
     L.srft_cache_quantized_tokens.restype = i64
+    if _marshal is not None:
+        _marshal.bind(*[C.cast(getattr(L, name), vp).value for name in (
+            "srft_kv_quantize", "srft_kv_dequantize", "srft_kv_quantize_batched", "srft_kv_dequantize_batched", "srft_kv_scores",
+            "srft_kv_decode_attention", "srft_kv_channel_absmax", "srft_cache_append", "srft_scores_workspace_bytes",
+            "srft_decode_attention_workspace_bytes", "srft_plan_d")])
+        L.srft_cache_append = _marshal.append(L.srft_cache_append, vp, C.Array)
     _lib = L
     return L
 
@@ -101,6 +112,15 @@ def lib() -> C.CDLL:
 def _check(status: int, where: str) -> None:
     if status != 0:
         raise SrftError(status, where)
+
+
+def _fast(name: str):
+    """The native form of a call on the current stream: its status, or None where it was not made (see csrc/host/marshal.cpp)."""
+    return getattr(_marshal, name, lambda *a: None)
+
+
+_fast_quantize, _fast_dequantize, _fast_scores, _fast_attention, _fast_absmax = map(_fast, ("quantize", "dequantize", "scores", "attention", "absmax"))
+_fast_quantize_batched, _fast_dequantize_batched = map(_fast, ("quantize_batched", "dequantize_batched"))
 
 
 # The handle of the current stream without building a torch.cuda.Stream object around it: 0.3 us against 2.8 us a call,
@@ -154,6 +174,10 @@ def srft_plan_destroy(plan: int) -> None:
 
 
 def srft_kv_quantize(plan: int, x: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, stream=None) -> None:
+    if stream is None:
+        status = _fast_quantize(plan, x, codes, scales)
+        if status is not None:
+            return _check(status, "srft_kv_quantize") if status else None
     n = x.shape[0]
     _check(lib().srft_kv_quantize(plan, _dev_ptr(x, torch.float16, "x"), n,
                                   _dev_ptr(codes, torch.uint8, "codes"),
@@ -169,6 +193,10 @@ def srft_kv_quantize_butterfly(plan: int, x: torch.Tensor, codes: torch.Tensor, 
 
 
 def srft_kv_dequantize(plan: int, codes: torch.Tensor, scales: torch.Tensor, out: torch.Tensor, stream=None) -> None:
+    if stream is None:
+        status = _fast_dequantize(plan, codes, scales, out)
+        if status is not None:
+            return _check(status, "srft_kv_dequantize") if status else None
     n = codes.shape[0]
     _check(lib().srft_kv_dequantize(plan, _dev_ptr(codes, torch.uint8, "codes"),
                                     _dev_ptr(scales, torch.float32, "scales"), n,
@@ -208,11 +236,19 @@ class BatchTable:
 
 
 def srft_kv_quantize_batched(table: BatchTable, stream=None) -> None:
+    if stream is None:
+        status = _fast_quantize_batched(table)
+        if status is not None:
+            return _check(status, "srft_kv_quantize_batched") if status else None
     _check(lib().srft_kv_quantize_batched(table.plans, table.big, table.n_vec, table.codes, table.scales,
                                           table.count, _stream_handle(stream)), "srft_kv_quantize_batched")
 
 
 def srft_kv_dequantize_batched(table: BatchTable, stream=None) -> None:
+    if stream is None:
+        status = _fast_dequantize_batched(table)
+        if status is not None:
+            return _check(status, "srft_kv_dequantize_batched") if status else None
     _check(lib().srft_kv_dequantize_batched(table.plans, table.codes, table.scales, table.n_vec, table.big,
                                             table.count, _stream_handle(stream)), "srft_kv_dequantize_batched")
 
@@ -226,6 +262,10 @@ def srft_kv_forward_f32(plan: int, x: torch.Tensor, w: torch.Tensor, stream=None
 def srft_kv_scores(plan: int, q: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, scores: torch.Tensor,
                    workspace: torch.Tensor, stream=None) -> None:
     """scores [n_q, n_keys] fp32 <- inner products of q [n_q, d] with the keys stored as (codes, scales)."""
+    if stream is None:
+        status = _fast_scores(plan, q, codes, scales, scores, workspace)
+        if status is not None:
+            return _check(status, "srft_kv_scores") if status else None
     if workspace.numel() * workspace.element_size() < lib().srft_scores_workspace_bytes(plan):
         raise ValueError("workspace too small")
     if scores.shape != (q.shape[0], codes.shape[0]):
@@ -264,6 +304,10 @@ def srft_kv_decode_attention(plan_k: int, plan_v: int, q: torch.Tensor, k_codes:
                              v_codes: torch.Tensor, v_scales: torch.Tensor, softmax_scale: float, out: torch.Tensor,
                              workspace: torch.Tensor, stream=None) -> None:
     """out [n_q, d] fp32 <- softmax(softmax_scale * q K^T) V over the two stored records."""
+    if stream is None:
+        status = _fast_attention(plan_k, plan_v, q, k_codes, k_scales, v_codes, v_scales, softmax_scale, out, workspace)
+        if status is not None:
+            return _check(status, "srft_kv_decode_attention") if status else None
     n_q, n_keys = q.shape[0], k_codes.shape[0]
     if workspace.numel() * workspace.element_size() < lib().srft_decode_attention_workspace_bytes(plan_k, plan_v, n_q, n_keys):
         raise ValueError("workspace too small")
@@ -278,6 +322,10 @@ def srft_kv_decode_attention(plan_k: int, plan_v: int, q: torch.Tensor, k_codes:
 
 def srft_kv_channel_absmax(plan: int, x: torch.Tensor, amax: torch.Tensor, stream=None) -> None:
     """amax (d fp32 on the device, >= 0) becomes max(amax, per-channel abs-max of the transform of x)."""
+    if stream is None:
+        status = _fast_absmax(plan, x, amax)
+        if status is not None:
+            return _check(status, "srft_kv_channel_absmax") if status else None
     if amax.numel() != lib().srft_plan_d(plan):
         raise ValueError("amax must have d entries")
     _check(lib().srft_kv_channel_absmax(plan, _dev_ptr(x, torch.float16, "x"), x.shape[0],

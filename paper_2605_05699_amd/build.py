@@ -1,4 +1,5 @@
-"""Build libsrft_kv.so (the product) and libsrft_measure.so (measurement aids) in-tree with hipcc, for gfx950.
+"""Build libsrft_kv.so (the product) and libsrft_measure.so (measurement aids) in-tree with hipcc, for gfx950, and the
+binding's native marshalling (_marshal.so, host code) with g++.
 
 Every translation unit under csrc/ is compiled to an object of its own (in parallel), then linked; objects whose
 source and headers are older than they are are reused unless ``force`` is set.
@@ -17,6 +18,8 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsrft_kv.so")
 LIB_MEASURE = os.path.join(PKG, "libsrft_measure.so")
+SRC_MARSHAL = os.path.join(CSRC, "host", "marshal.cpp")
+LIB_MARSHAL = os.path.join(PKG, "_marshal.so")
 SRC = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "kernels", "*.hip")))
 SRC_MEASURE = sorted(glob.glob(os.path.join(CSRC, "measure", "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h")))
@@ -55,13 +58,30 @@ def _object(src: str, force: bool, verbose: bool, extra: list[str]) -> str:
     return obj
 
 
+def _marshal(force: bool, verbose: bool) -> None:
+    """The CPython extension that binding.py calls: torch's headers, no HIP code."""
+    if not force and os.path.exists(LIB_MARSHAL) and os.path.getmtime(LIB_MARSHAL) > max(os.path.getmtime(f) for f in (SRC_MARSHAL, os.path.abspath(__file__))):
+        return
+    import sysconfig
+    import torch
+    at = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    _run([shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", sysconfig.get_paths()["include"],
+          "-isystem", os.path.join(at, "include"), "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
+          "-isystem", os.path.join(rocm, "include"), SRC_MARSHAL, "-o", LIB_MARSHAL, "-L", os.path.join(at, "lib"),
+          "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
+
+
 def build(verbose: bool = False, extra: list[str] | None = None, force: bool = True, jobs: int | None = None) -> str:
-    """Compile and link both libraries; returns the path of libsrft_kv.so."""
+    """Compile and link the libraries and the extension; returns the path of libsrft_kv.so."""
     os.makedirs(OBJ, exist_ok=True)
     extra = list(extra or [])
     jobs = jobs or min(8, os.cpu_count() or 1)
     with cf.ThreadPoolExecutor(max_workers=jobs) as pool:
+        marshal = pool.submit(_marshal, force, verbose)
         objs = list(pool.map(lambda s: _object(s, force, verbose, extra), SRC + SRC_MEASURE))
+        marshal.result()
     n = len(SRC)
     _run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs[:n], "-o", LIB], verbose)
     _run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs[n:], "-o", LIB_MEASURE], verbose)

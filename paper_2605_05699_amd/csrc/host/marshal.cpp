@@ -1,0 +1,309 @@
+// marshal.cpp -- the calls of binding.py that programs make step after step, marshalled in native code (a CPython extension; host
+// only, no HIP call of its own).
+//
+// What bounds it: a small launch takes 2.0-2.5 us of the host, and ctypes and the checks of the tensors in Python cost as much again
+// (1.0 us a call of seven arguments, 0.65 us a tensor).  Host time of a call, us, through ctypes -> here: a batched write of 2 plans
+// 4.2 -> 3.0, of 64 4.3 -> 3.4; one plan's write 4.9 -> 3.1, read 4.7 -> 3.0; scores 6.1 -> 3.2; decode attention (two launches)
+// 9.4 -> 6.0; srft_cache_append by way of lib() 0.3 less.
+//
+// A function here makes the call where everything is as binding.py wants it (plain tensors of the right type on the device, no
+// stream named) and returns the status; it returns None where anything is not, before the call, and binding.py goes its own way,
+// which raises what there is to raise.
+#include <Python.h>
+
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <cstdint>
+#include <cstring>
+
+namespace {
+
+// ---- the C entry points, bound by binding.lib() when it loads the library
+typedef int (*move_t)(const void*, const void*, int64_t, void*, float*, void*);
+typedef int (*back_t)(const void*, const void*, const void*, int64_t, void*, void*);
+typedef int (*move_batched_t)(const void*, const void*, const void*, const void*, const void*, int, void*);
+typedef int (*scores_t)(const void*, const void*, int, const void*, const void*, int64_t, void*, void*, void*);
+typedef int (*attention_t)(const void*, const void*, const void*, int, const void*, const void*, const void*, const void*, int64_t, float, void*, void*, void*);
+typedef int (*absmax_t)(const void*, const void*, int64_t, void*, void*);
+typedef int (*append_t)(void*, const void*, int, void*);
+typedef int64_t (*bytes_plan_t)(const void*);
+typedef int64_t (*bytes_attention_t)(const void*, const void*, int, int64_t);
+typedef int (*plan_d_t)(const void*);
+struct {
+    move_t quantize;
+    back_t dequantize;
+    move_batched_t quantize_batched, dequantize_batched;
+    scores_t scores;
+    attention_t attention;
+    absmax_t absmax;
+    append_t append;
+    bytes_plan_t scores_bytes;
+    bytes_attention_t attention_bytes;
+    plan_d_t plan_d;
+    bool bound;
+} g;
+
+// ---- arguments
+bool handle_of(PyObject* o, const void** p) {                // a plan: the address as an int
+    if (!PyLong_CheckExact(o)) return false;
+    *p = PyLong_AsVoidPtr(o);
+    if (*p || !PyErr_Occurred()) return true;
+    PyErr_Clear();
+    return false;
+}
+// a plain contiguous tensor of this type on the device
+const at::Tensor* tensor_of(PyObject* o, at::ScalarType type) {
+    if (!THPVariable_CheckExact(o)) return nullptr;
+    const at::Tensor& t = THPVariable_Unpack(o);
+    return t.defined() && t.is_cuda() && t.scalar_type() == type && t.layout() == at::kStrided && t.unsafeGetTensorImpl()->has_storage() &&
+                   t.is_contiguous()
+               ? &t
+               : nullptr;
+}
+bool address_of(PyObject* o, void** p) {                     // of a ctypes array
+    Py_buffer b;
+    if (!PyObject_CheckBuffer(o) || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
+        PyErr_Clear();
+        return false;
+    }
+    *p = b.buf;
+    PyBuffer_Release(&b);
+    return true;
+}
+void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+
+// Runs `body` (true: the call was made, its status in *rc), turning what it throws into "not made".
+template <class F>
+PyObject* made(F body) {
+    int rc = 0;
+    bool done = false;
+    try {
+        done = g.bound && body(&rc);
+    } catch (...) {
+    }
+    if (done) return PyLong_FromLong(rc);
+    Py_RETURN_NONE;
+}
+template <class F>
+int without_gil(F call) {
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = call();
+    Py_END_ALLOW_THREADS
+    return rc;
+}
+int64_t bytes_of(const at::Tensor& t) { return t.numel() * (int64_t)t.element_size(); }
+
+// quantize(plan, x, codes, scales)
+PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return made([&](int* rc) {
+        const void* plan;
+        if (n != 4 || !handle_of(a[0], &plan)) return false;
+        const at::Tensor *x = tensor_of(a[1], at::kHalf), *c = tensor_of(a[2], at::kByte), *s = tensor_of(a[3], at::kFloat);
+        if (!x || !c || !s || x->dim() < 1) return false;
+        void *const xp = x->data_ptr(), *const cp = c->data_ptr(), *const sp = s->data_ptr(), *const st = current_stream();
+        const int64_t count = x->size(0);
+        *rc = without_gil([&] { return g.quantize(plan, xp, count, cp, (float*)sp, st); });
+        return true;
+    });
+}
+// dequantize(plan, codes, scales, out)
+PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return made([&](int* rc) {
+        const void* plan;
+        if (n != 4 || !handle_of(a[0], &plan)) return false;
+        const at::Tensor *c = tensor_of(a[1], at::kByte), *s = tensor_of(a[2], at::kFloat), *o = tensor_of(a[3], at::kHalf);
+        if (!c || !s || !o || c->dim() < 1) return false;
+        void *const cp = c->data_ptr(), *const sp = s->data_ptr(), *const op = o->data_ptr(), *const st = current_stream();
+        const int64_t count = c->size(0);
+        *rc = without_gil([&] { return g.dequantize(plan, cp, sp, count, op, st); });
+        return true;
+    });
+}
+// the arrays of a BatchTable
+PyObject *s_plans, *s_big, *s_codes, *s_scales, *s_n_vec, *s_count;
+PyObject* batched(PyObject* table, bool write) {
+    PyObject* held[6] = {};                                  // (the arrays stay for the call, whatever happens to the table meanwhile)
+    PyObject* const r = made([&](int* rc) {
+        PyObject* const names[6] = {s_plans, s_big, s_codes, s_scales, s_n_vec, s_count};
+        void* p[5];
+        for (int i = 0; i < 6; ++i)
+            if (!(held[i] = PyObject_GetAttr(table, names[i])) || (i < 5 && !address_of(held[i], &p[i]))) {
+                PyErr_Clear();
+                return false;
+            }
+        int overflow;
+        const long count = PyLong_CheckExact(held[5]) ? PyLong_AsLongAndOverflow(held[5], &overflow) : -1;
+        if (count < 0 || count > INT32_MAX) return false;
+        void* const st = current_stream();
+        *rc = without_gil([&] {
+            return write ? g.quantize_batched(p[0], p[1], p[4], p[2], p[3], (int)count, st)
+                         : g.dequantize_batched(p[0], p[2], p[3], p[4], p[1], (int)count, st);
+        });
+        return true;
+    });
+    for (PyObject* o : held) Py_XDECREF(o);
+    return r;
+}
+PyObject* quantize_batched(PyObject*, PyObject* table) { return batched(table, true); }
+PyObject* dequantize_batched(PyObject*, PyObject* table) { return batched(table, false); }
+
+// scores(plan, q, codes, scales, scores, workspace)
+PyObject* scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return made([&](int* rc) {
+        const void* plan;
+        if (n != 6 || !handle_of(a[0], &plan) || !plan || !THPVariable_CheckExact(a[5])) return false;
+        const at::Tensor *q = tensor_of(a[1], at::kHalf), *c = tensor_of(a[2], at::kByte), *s = tensor_of(a[3], at::kFloat),
+                         *o = tensor_of(a[4], at::kFloat), *w = tensor_of(a[5], THPVariable_Unpack(a[5]).scalar_type());
+        if (!q || !c || !s || !o || !w || q->dim() < 1 || c->dim() < 1 || o->dim() != 2 || o->size(0) != q->size(0) || o->size(1) != c->size(0) ||
+            bytes_of(*w) < g.scores_bytes(plan))
+            return false;
+        const int64_t n_q = q->size(0), keys = c->size(0);
+        void *const qp = q->data_ptr(), *const cp = c->data_ptr(), *const sp = s->data_ptr(), *const op = o->data_ptr(), *const wp = w->data_ptr(),
+             *const st = current_stream();
+        if (n_q > INT32_MAX) return false;
+        *rc = without_gil([&] { return g.scores(plan, qp, (int)n_q, cp, sp, keys, op, wp, st); });
+        return true;
+    });
+}
+// attention(plan_k, plan_v, q, k_codes, k_scales, v_codes, v_scales, softmax_scale, out, workspace)
+PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return made([&](int* rc) {
+        const void *pk, *pv;
+        if (n != 10 || !handle_of(a[0], &pk) || !handle_of(a[1], &pv) || !pk || !pv || !PyFloat_CheckExact(a[7]) || !THPVariable_CheckExact(a[9])) return false;
+        const at::Tensor *q = tensor_of(a[2], at::kHalf), *kc = tensor_of(a[3], at::kByte), *ks = tensor_of(a[4], at::kFloat), *vc = tensor_of(a[5], at::kByte),
+                         *vs = tensor_of(a[6], at::kFloat), *o = tensor_of(a[8], at::kFloat), *w = tensor_of(a[9], THPVariable_Unpack(a[9]).scalar_type());
+        if (!q || !kc || !ks || !vc || !vs || !o || !w || q->dim() < 1 || kc->dim() < 1 || vc->dim() < 1 || vc->size(0) != kc->size(0)) return false;
+        const int64_t n_q = q->size(0), keys = kc->size(0);
+        if (n_q > INT32_MAX || bytes_of(*w) < g.attention_bytes(pk, pv, (int)n_q, keys)) return false;
+        const float scale = (float)PyFloat_AS_DOUBLE(a[7]);
+        void *const qp = q->data_ptr(), *const kcp = kc->data_ptr(), *const ksp = ks->data_ptr(), *const vcp = vc->data_ptr(), *const vsp = vs->data_ptr(),
+             *const op = o->data_ptr(), *const wp = w->data_ptr(), *const st = current_stream();
+        *rc = without_gil([&] { return g.attention(pk, pv, qp, (int)n_q, kcp, ksp, vcp, vsp, keys, scale, op, wp, st); });
+        return true;
+    });
+}
+// absmax(plan, x, amax)
+PyObject* absmax(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return made([&](int* rc) {
+        const void* plan;
+        if (n != 3 || !handle_of(a[0], &plan) || !plan) return false;
+        const at::Tensor *x = tensor_of(a[1], at::kHalf), *m = tensor_of(a[2], at::kFloat);
+        if (!x || !m || x->dim() < 1 || m->numel() != g.plan_d(plan)) return false;
+        const int64_t count = x->size(0);
+        void *const xp = x->data_ptr(), *const mp = m->data_ptr(), *const st = current_stream();
+        *rc = without_gil([&] { return g.absmax(plan, xp, count, mp, st); });
+        return true;
+    });
+}
+
+// ---- lib().srft_cache_append: called like the ctypes function that it stands in front of, which takes the calls whose arguments
+// are anything else than None, ints, c_void_p and arrays of them, and answers for its attributes
+struct Append {
+    PyObject_HEAD
+    vectorcallfunc call;
+    PyObject *function, *pointer, *array;                    // the ctypes function; ctypes.c_void_p and ctypes.Array
+};
+bool pointer_of(const Append* self, PyObject* o, void** p) {
+    if (o == Py_None) {
+        *p = nullptr;
+        return true;
+    }
+    const void* v;
+    if (handle_of(o, &v)) {
+        *p = const_cast<void*>(v);
+        return true;
+    }
+    const bool cell = (PyObject*)Py_TYPE(o) == self->pointer;
+    if (!cell && !PyObject_TypeCheck(o, (PyTypeObject*)self->array)) return false;
+    void* at;
+    if (!address_of(o, &at)) return false;
+    if (cell) std::memcpy(p, at, sizeof(*p));
+    else *p = at;
+    return true;
+}
+PyObject* append_call(PyObject* o, PyObject* const* a, size_t nf, PyObject* names) {
+    const Append* self = (const Append*)o;
+    void *cache, *fresh, *st;
+    if (PyVectorcall_NARGS(nf) == 4 && !names && g.bound && pointer_of(self, a[0], &cache) && pointer_of(self, a[1], &fresh) &&
+        PyLong_CheckExact(a[2]) && pointer_of(self, a[3], &st)) {
+        int overflow;
+        const long t = PyLong_AsLongAndOverflow(a[2], &overflow);
+        if (!overflow && t == (int)t) return PyLong_FromLong(without_gil([&] { return g.append(cache, fresh, (int)t, st); }));
+    }
+    return PyObject_Vectorcall(self->function, a, nf, names);
+}
+PyObject* append_getattr(PyObject* o, PyObject* name) { return PyObject_GetAttr(((Append*)o)->function, name); }
+int append_setattr(PyObject* o, PyObject* name, PyObject* v) { return PyObject_SetAttr(((Append*)o)->function, name, v); }
+void append_free(PyObject* o) {
+    Append* self = (Append*)o;
+    Py_XDECREF(self->function);
+    Py_XDECREF(self->pointer);
+    Py_XDECREF(self->array);
+    Py_TYPE(o)->tp_free(o);
+}
+PyTypeObject append_type = [] {
+    PyTypeObject t = {PyVarObject_HEAD_INIT(nullptr, 0)};
+    t.tp_name = "_marshal.Append";
+    t.tp_basicsize = sizeof(Append);
+    t.tp_dealloc = append_free;
+    t.tp_vectorcall_offset = offsetof(Append, call);
+    t.tp_call = PyVectorcall_Call;
+    t.tp_getattro = append_getattr;
+    t.tp_setattro = append_setattr;
+    t.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL;
+    return t;
+}();
+// append(function, c_void_p, Array) -> the callable
+PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (n != 3 || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
+        PyErr_SetString(PyExc_TypeError, "append(function, c_void_p, Array)");
+        return nullptr;
+    }
+    Append* self = PyObject_New(Append, &append_type);
+    if (!self) return nullptr;
+    self->call = append_call;
+    self->function = Py_NewRef(a[0]);
+    self->pointer = Py_NewRef(a[1]);
+    self->array = Py_NewRef(a[2]);
+    return (PyObject*)self;
+}
+
+// bind(addresses): of the entry points, in the order of the struct above
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    constexpr int kCount = 11;
+    void* p[kCount];
+    if (n != kCount) {
+        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of 11 entry points");
+        return nullptr;
+    }
+    for (int i = 0; i < kCount; ++i) {
+        p[i] = PyLong_AsVoidPtr(a[i]);
+        if (!p[i]) {
+            if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no entry point");
+            return nullptr;
+        }
+    }
+    std::memcpy(&g, p, sizeof(p));
+    g.bound = true;
+    Py_RETURN_NONE;
+}
+static_assert(offsetof(decltype(g), bound) == 11 * sizeof(void*), "bind fills the pointers in order");
+
+#define FAST(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {FAST(quantize), FAST(dequantize), FAST(scores), FAST(attention), FAST(absmax), FAST(append), FAST(bind),
+                         {"quantize_batched", quantize_batched, METH_O, nullptr},
+                         {"dequantize_batched", dequantize_batched, METH_O, nullptr},
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__marshal(void) {
+    if (PyType_Ready(&append_type) < 0) return nullptr;
+    struct { PyObject** at; const char* name; } const names[] = {{&s_plans, "plans"}, {&s_big, "big"}, {&s_codes, "codes"}, {&s_scales, "scales"}, {&s_n_vec, "n_vec"}, {&s_count, "count"}};
+    for (const auto& e : names)
+        if (!(*e.at = PyUnicode_InternFromString(e.name))) return nullptr;
+    return PyModule_Create(&module);
+}

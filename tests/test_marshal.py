@@ -1,0 +1,100 @@
+"""The native marshalling (csrc/host/marshal.cpp) against the calls through ctypes that it stands in front of."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_05699_amd import binding as B
+
+FAST = ("quantize", "dequantize", "scores", "attention", "absmax", "quantize_batched", "dequantize_batched")
+
+
+def test_it_is_built():
+    assert B._marshal is not None
+
+
+def test_append_takes_what_ctypes_takes():
+    native, plain = B.lib().srft_cache_append, C.CDLL(B.LIB_PATH).srft_cache_append
+    plain.argtypes, plain.restype = native.argtypes, C.c_int
+    arr, cell = (C.c_void_p * 3)(), C.c_void_p()
+    for args in ((None, None, 1, None), (cell, arr, 1, 5), (0, 0, 0, 0), (None, arr, -1, cell), (None, C.byref(cell), 1, None), (None, arr, 2 ** 32 + 1, None),
+                 (C.c_void_p(None), arr, True, None), (None, None, np.int32(1), None), (None, "x", 1, None), (None, arr, 1.5, None), (None, arr, 1),
+                 (2 ** 70, arr, 1, None), (None, arr, None, None)):
+        got = []
+        for f in (native, plain):
+            try:
+                got.append(f(*args))
+            except Exception as e:
+                got.append(type(e))
+        assert got[0] == got[1], (args, got)
+    assert native.restype is C.c_int and native.argtypes == plain.argtypes
+
+
+@pytest.mark.parametrize("args", [("quantize", 4), ("dequantize", 4), ("scores", 6), ("attention", 10), ("absmax", 3)])
+def test_what_is_not_on_the_device_is_left_to_the_binding(args):
+    name, n = args
+    B.lib()
+    x = torch.zeros(4, 128, dtype=torch.float16)
+    f = getattr(B._marshal, name)
+    for a in (x, None, 0, "x", torch.nn.Parameter(x), torch.zeros(2, 2).to_sparse()):
+        assert f(1, *([a] * (n - 1))) is None
+    assert f() is None and f(*[x] * (n + 1)) is None
+    assert B._marshal.quantize_batched(x) is None and B._marshal.dequantize_batched(None) is None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("side", [False, True])
+def test_results_and_refusals_are_those_of_the_calls_through_ctypes(monkeypatch, side):
+    d, n = 128, 77
+    p, gen = B.Plan(d, 32, 3), torch.Generator("cuda").manual_seed(1)
+    x = torch.randn(n, d, device="cuda", generator=gen).half()
+    q = torch.randn(4, d, device="cuda", generator=gen).half()
+    ws = torch.empty(B.lib().srft_decode_attention_workspace_bytes(p.handle, p.handle, 4, n), dtype=torch.uint8, device="cuda")
+
+    def empty(*shape, dtype=torch.float32):
+        return torch.zeros(*shape, dtype=dtype, device="cuda")
+
+    def calls():
+        c, s, back = empty(n, d // 2, dtype=torch.uint8), empty(n, d // 32), empty(n, d, dtype=torch.float16)
+        out, sc, m = empty(4, d), empty(4, n), empty(d)
+        c2, s2, b2 = torch.zeros_like(c), torch.zeros_like(s), torch.zeros_like(back)
+        B.srft_kv_quantize(p.handle, x, c, s)
+        B.srft_kv_dequantize(p.handle, c, s, back)
+        B.srft_kv_scores(p.handle, q, c, s, sc, ws)
+        B.srft_kv_decode_attention(p.handle, p.handle, q, c, s, c, s, 0.1, out, ws)
+        B.srft_kv_channel_absmax(p.handle, x, m)
+        table = B.BatchTable([p.handle] * 2, [x[:40], x[40:]], [c2[:40], c2[40:]], [s2[:40], s2[40:]])
+        B.srft_kv_quantize_batched(table)
+        B.srft_kv_dequantize_batched(B.BatchTable([p.handle] * 2, [b2[:40], b2[40:]], [c2[:40], c2[40:]], [s2[:40], s2[40:]]))
+        refused = []
+        for f, a in ((B.srft_kv_quantize, (p.handle, x.float(), c, s)), (B.srft_kv_quantize, (p.handle, x.t(), c, s)), (B.srft_kv_quantize, (None, x, c, s)),
+                     (B.srft_kv_quantize, (p.handle, x.cpu(), c, s)), (B.srft_kv_quantize, (p.handle, x.view(-1)[1:9], c, s)), (B.srft_kv_dequantize, (p.handle, c, s, None)),
+                     (B.srft_kv_scores, (p.handle, q, c, s, sc[:, 1:], ws)), (B.srft_kv_scores, (p.handle, q, c, s, sc, ws[:16])),
+                     (B.srft_kv_scores, (p.handle, torch.cat([q] * 9), c, s, empty(36, n), ws)),
+                     (B.srft_kv_decode_attention, (p.handle, p.handle, q, c, s, c[1:], s, 0.1, out, ws)),
+                     (B.srft_kv_decode_attention, (p.handle, p.handle, q, c, s, c, s, float("inf"), out, ws)),
+                     (B.srft_kv_decode_attention, (p.handle, p.handle, q, c, s, c, s, 0.1, out, ws[:64])),
+                     (B.srft_kv_channel_absmax, (p.handle, x, m[1:])), (B.srft_kv_quantize_batched, (None,))):
+            with pytest.raises(Exception) as e:
+                f(*a)
+            refused.append((e.type, str(e.value)))
+        torch.cuda.synchronize()
+        return [c, s, back, out, sc, m, c2, s2, b2], refused
+
+    def under():
+        if not side:
+            return calls()
+        with torch.cuda.stream(torch.cuda.Stream()):
+            return calls()
+
+    torch.cuda.synchronize()
+    got, refused = under()
+    for name in FAST:
+        assert getattr(B, "_fast_" + name) is getattr(B._marshal, name)
+        monkeypatch.setattr(B, "_fast_" + name, lambda *a: None)
+    want, also = under()
+    assert refused == also
+    for a, b in zip(got, want):
+        assert torch.equal(a, b) and bool(a.any())
+    p.close()
