@@ -144,36 +144,35 @@ __device__ __forceinline__ srft_work srft_work_of_block(const srft_batch<N>& a) 
 // read path
 // ------------------------------------------------------------------------------------------
 // One dword of eight nibbles -> eight exact fp16 codes, as four packed pairs (n_m, n_{m+4}).
-// 0x6400 | u is the fp16 number 1024 + u; with u = q + 8 a packed fp16 subtract of 1032 leaves q.
-// A nibble one position higher (bits 4..7 of the 16-bit half) gives 1024 + 16 u instead; times 1/16 minus 72
-// is q again (exact), which saves the shift: ten vector-ALU operations per dword.
-__device__ __forceinline__ uint32_t and_or(uint32_t v, uint32_t mask, uint32_t bits) {
-    uint32_t r;                                  // one instruction; `bits` is kept in a vector register
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(mask), "v"(bits));
+// 0x6400 | u is the fp16 number 1024 + u; with u = q + 8, a nibble with its top bit flipped, a packed fp16 subtract of 1032 leaves
+// q.  A nibble one position higher (bits 4..7 of the 16-bit half) gives 1024 + 16 u instead; times 1/16 minus 72 is q again
+// (exact), which saves the shift.  Selecting the nibble, flipping its bit and setting the exponent is one v_bitop3: nine
+// vector-ALU operations per dword (ten with the flip in front).
+__device__ __forceinline__ uint32_t and_xor(uint32_t v, uint32_t mask, uint32_t bits) {
+    uint32_t r;                                  // (v & mask) ^ bits as one instruction; `bits` is kept in a vector register
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x6a" : "=v"(r) : "v"(v), "s"(mask), "v"(bits));
     return r;
 }
 __device__ __forceinline__ uint4 decode8(uint32_t v) {
-    v ^= 0x88888888u;
     const half2v bias = {(_Float16)1032.0f, (_Float16)1032.0f};
     const half2v sixteenth = {(_Float16)0.0625f, (_Float16)0.0625f}, bias16 = {(_Float16)72.0f, (_Float16)72.0f};
-    const uint32_t one_k = 0x64006400u, w = v >> 8;
+    const uint32_t low = 0x64086408u, high = 0x64806480u, w = v >> 8;
     uint4 o;
-    o.x = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_or(v, 0x000F000Fu, one_k)) - bias);
-    o.y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_or(v, 0x00F000F0u, one_k)) * sixteenth - bias16);
-    o.z = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_or(w, 0x000F000Fu, one_k)) - bias);
-    o.w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_or(w, 0x00F000F0u, one_k)) * sixteenth - bias16);
+    o.x = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_xor(v, 0x000F000Fu, low)) - bias);
+    o.y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_xor(v, 0x00F000F0u, high)) * sixteenth - bias16);
+    o.z = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_xor(w, 0x000F000Fu, low)) - bias);
+    o.w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_xor(w, 0x00F000F0u, high)) * sixteenth - bias16);
     return o;
 }
 
 // One dword of four two's-complement bytes -> four exact fp16 codes as the packed pairs (b0, b2) and (b1, b3):
 // flipping bit 7 gives u = q + 128 in 0..255, 0x6400 | u is 1024 + u, minus 1152 is q.
 __device__ __forceinline__ uint2 decode4_bytes(uint32_t v) {
-    v ^= 0x80808080u;
     const half2v bias = {(_Float16)1152.0f, (_Float16)1152.0f};
-    const uint32_t one_k = 0x64006400u;
+    const uint32_t bits = 0x64806480u;
     uint2 o;
-    o.x = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_or(v, 0x00FF00FFu, one_k)) - bias);
-    o.y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_or(v >> 8, 0x00FF00FFu, one_k)) - bias);
+    o.x = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_xor(v, 0x00FF00FFu, bits)) - bias);
+    o.y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, and_xor(v >> 8, 0x00FF00FFu, bits)) - bias);
     return o;
 }
 
