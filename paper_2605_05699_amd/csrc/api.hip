@@ -2,6 +2,7 @@
 // (all before the first HIP call), grid sizing, launches.
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 
 #include "common.h"
 #include "launch_shape.h"
@@ -23,7 +24,7 @@ int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* cod
                     int out, hipStream_t st) {
     const long long n_tiles = (n + kTileVecs - 1) / kTileVecs;
     const int teams = out == kOutAmax ? srft_plan_amax_teams(p, n_tiles) : 1;
-    long long grid = p->max_wgs > 0 ? p->max_wgs : out == kOutAmax ? amax_grid(p, n_tiles, teams) : p->grid_q;
+    long long grid = p->max_wgs > 0 ? p->max_wgs : out == kOutAmax ? amax_grid(p, n_tiles, teams) : out == kOutCodes ? srft_plan_write_grid(p, n_tiles) : p->grid_q;
     grid = std::min(grid, (n_tiles + teams - 1) / teams);    // no workgroup without a tile
     int threads = 0;
     const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads, n_tiles);
@@ -60,7 +61,7 @@ srft_segment segment_part(const srft_plan* p, bool write_path, const srft_segmen
 }
 
 // The kernels of a plan's batched launches, and their block size.
-batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, int* threads) {
+batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long tiles, int* threads) {
     if (write_path && p->fold4_q) {
         *threads = 256;
         return srft_pick_quantize_fold4_batched(p->bits, p->gm);
@@ -71,8 +72,8 @@ batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, int* thre
     }
     if (write_path) {
         *threads = 2 * p->d / p->slabs_q;
-        return p->bits == 8 ? srft_pick_quantize_plain_batched_b8(p->d, p->slabs_q, p->gm)
-                            : srft_pick_quantize_plain_batched_b4(p->d, p->slabs_q, p->gm);
+        const bool staged = srft_plan_staged(p, tiles);
+        return p->bits == 8 ? srft_pick_quantize_plain_batched_b8(p->d, p->gm, staged) : srft_pick_quantize_plain_batched_b4(p->d, p->gm, staged);
     }
     if (p->fold4_dq) {
         *threads = p->d;
@@ -89,7 +90,8 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
     for (int i = 0; i < count; ++i) tiles[i] = (whole.seg[i].n_vec + kTileVecs - 1) / kTileVecs;
     srft_share shares[kMaxBatch];
     int next = 0;
-    const int n = srft_share_out(tiles, count, p->max_wgs > 0 ? p->max_wgs : write_path ? p->grid_q : p->grid_dq, shares,
+    const long long all = std::accumulate(tiles, tiles + count, 0LL);
+    const int n = srft_share_out(tiles, count, write_path ? srft_plan_write_grid(p, all) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq, shares,
                                  kMaxBatch, &next);
     srft_batch_many cut;
     if (n > count)
@@ -101,7 +103,7 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
     }
     for (int i = n; i < kMaxBatch; ++i) a.first_block[i] = INT32_MAX;
     int threads = 0;
-    const batched_kernels_t kernel = batched_kernels(p, write_path, &threads);
+    const batched_kernels_t kernel = batched_kernels(p, write_path, all, &threads);
     if (!kernel.many) return SRFT_ERR_BAD_D;
     if (n <= kFewBatch) {
         srft_batch_few few;
@@ -126,7 +128,7 @@ bool even_batch(const srft_plan_t* const* plans, const void* const* in, void* co
         !srft_even_step(scales, count, &a->scales_step))
         return false;
     const srft_plan* p = plans[0];
-    const long long tiles = (n_vec[0] + kTileVecs - 1) / kTileVecs, budget = p->max_wgs > 0 ? p->max_wgs : write_path ? p->grid_q : p->grid_dq;
+    const long long tiles = (n_vec[0] + kTileVecs - 1) / kTileVecs, budget = write_path ? srft_plan_write_grid(p, tiles * count) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
     const int blocks = srft_even_blocks(tiles, count, budget);
     if (blocks == 0) return false;
     a->shape = srft_even_spread(tiles, count, write_path ? (long long)blocks * count : budget, blocks);
@@ -160,7 +162,8 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
     srft_batch_even even;
     if (even_batch(plans, in0, out0, write_path ? (const void* const*)out1 : in1, n_vec, count, write_path, &even)) {
         int threads = 0;
-        const batched_kernels_t kernel = batched_kernels(plans[0], write_path, &threads);
+        const long long tiles = (even.n_vec + kTileVecs - 1) / kTileVecs * count;
+        const batched_kernels_t kernel = batched_kernels(plans[0], write_path, tiles, &threads);
         if (!kernel.even) return SRFT_ERR_BAD_D;
         return srft_launch(kernel.even, dim3((unsigned)srft_even_grid(even.shape, count)), threads, st, even, plans[0]->gw);
     }

@@ -126,7 +126,7 @@ static bool cache_flush(const srft_cache* c, const void* const* fresh, int t, in
     const flush_kernels_t kernels = srft_plan_flush_kernels(p, &threads);
     const long long tiles = (n_vec + kTileVecs - 1) / kTileVecs;
     const bool whole = kernels.whole && tiles * np <= (long long)srft_flush_whole_tiles(p->d, p->g) * p->grid_flush;
-    const long long budget = p->max_wgs > 0 ? p->max_wgs : whole ? p->grid_flush : p->grid_q;
+    const long long budget = p->max_wgs > 0 ? p->max_wgs : whole ? p->grid_flush : p->grid_staged;
     if (np > budget) return false;
     const long long blocks = std::min(tiles, budget / np);
     if (blocks * np * blocks >= (1LL << 31)) return false;

@@ -24,11 +24,11 @@
 #include "quantize_tiles.h"
 
 // The two halves of a plan's forms, for workgroups of one size.
-template <int D, int S, int GM, int BITS>
+template <int D, int S, int GM, int BITS, bool STAGED>
 struct srft_flush_write_plain {
     static __device__ __forceinline__ void run(const uint4* frag, float unscale, const srft_flush& a, uint2* codes, float* scales,
                                                const srft_rows_paged& rows, int place, int blocks) {
-        srft_quantize_tiles<D, S, kOutCodes, GM, BITS>(frag, nullptr, a.n_vec, codes, scales, nullptr, unscale,
+        srft_quantize_tiles<D, S, kOutCodes, GM, BITS, STAGED>(frag, nullptr, a.n_vec, codes, scales, nullptr, unscale,
                                                        unscale / (BITS == 8 ? 127.0f : 7.0f), a.gw, place, blocks, rows);
     }
 };
@@ -68,7 +68,7 @@ struct srft_flush_read_fold4 {
 struct srft_flush_read_later {};             // (a launch of its own)
 
 template <int D, int NT, class WRITE, class READ>
-__global__ void __launch_bounds__(NT, NT == D ? 2 : 1)
+__global__ void __launch_bounds__(NT, NT == D && D >= 128 ? 2 : 1)
 srft_cache_flush_kernel(const srft_flush a) {
     constexpr int U = D / 8;
     const int block = srft_block_by_die();

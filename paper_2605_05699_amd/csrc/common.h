@@ -192,6 +192,7 @@ struct srft_plan {
     float unscale_r = 1.0f;
     float unscale_r4 = 1.0f;    // 2^-e of the twice-folded read table
     int grid_q = 0, grid_dq = 0;    // default persistent grid sizes
+    int grid_staged = 0;            // ... of the write path's plain form with the record through LDS (elsewhere grid_q)
     int grid_flush = 0;             // ... of a cache's flush with both paths in one launch (0: there is no such kernel)
     int slabs_q = 1, slabs_dq = 1;  // slabs of the matrix per wavefront in the write / read kernel
     int gm = 1, gw = 1;             // group mode (kGroup16 / kGroup32 / kGroupWide) and slabs per group
@@ -209,11 +210,29 @@ struct srft_cache {
 };
 
 // ---- kernel instances, one function per translation unit under kernels/ (nullptr: no such instance) ----
-// write path, plain form, codes out: d, slabs per wavefront (1 or 2), group mode; 4- and 8-bit codes
-quantize_kernel_t srft_pick_quantize_plain_b4(int d, int slabs, int gm);
-quantize_kernel_t srft_pick_quantize_plain_b8(int d, int slabs, int gm);
-batched_kernels_t srft_pick_quantize_plain_batched_b4(int d, int slabs, int gm);
-batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int slabs, int gm);
+// write path, plain form, codes out: d, group mode, way of the record; 4- and 8-bit codes.
+// Whether the record goes through LDS and is written through to memory (device_util.h), or is stored from the lanes, in pieces of 8
+// bytes that the L2 puts together, by the tiles of a launch and its workgroups.  us, from the lanes -> through LDS, over three sets of
+// buffers:
+//   up to one tile for each of 768 workgroups the way through LDS is only longer: d = 96, 240 vectors 2.33 -> 2.40, 17,027 3.15 -> 3.26;
+//     64 x 512 (1024 tiles) 4.56 -> 4.48
+//   up to 11 tiles a workgroup nothing is left to write back: d = 96 40,000 vectors 4.47 -> 3.99, 30 MB 9.2 -> 8.0, 110 MB 28.6 -> 26.4;
+//     d = 64 20 MB 5.65 -> 5.05, 107 MB 24.5 -> 21.4; d = 128, g = 16 10 MB 4.9 -> 3.8, 101 MB 29.1 -> 26.2
+//   from there to 200 MB the memory-side cache takes the record better from the L2, where the rows are short: d = 96 151 MB 34 -> 38.7, 180
+//     MB 38.6 -> 46; d = 64 122 MB 26.5 -> 27.5, 176 MB 37 -> 40
+//   beyond whole rows help again, except the shortest: d = 96 330 MB 66.4 -> 63.6, 505 MB 100 -> 92.8; d = 64 322 MB 62 -> 65.6, g = 16 563
+//     MB 112.3 -> 114.4; d = 32 350 MB 67.6 -> 68.0
+//   d >= 128 is never slower: d = 128, g = 16 115 MB 34.4 -> 30.3, 210 MB 52 -> 50; d = 192 (the matrix cores' rate) 200 MB 66.7 -> 62.6,
+//     300 MB 98 -> 95
+constexpr bool srft_write_staged(int d, long long tiles, long long workgroups) {
+    if (tiles <= 768) return false;
+    if (d >= 128 || tiles <= 11 * workgroups) return true;
+    return d >= 96 && tiles >= 22 * workgroups;
+}
+quantize_kernel_t srft_pick_quantize_plain_b4(int d, int gm, bool staged);
+quantize_kernel_t srft_pick_quantize_plain_b8(int d, int gm, bool staged);
+batched_kernels_t srft_pick_quantize_plain_batched_b4(int d, int gm, bool staged);
+batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int gm, bool staged);
 // write path, plain form, other outputs (kOutRaw, kOutAmax)
 quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out, int teams);
 // write path, folded form (d = 128, 256)
@@ -322,6 +341,13 @@ dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads
 // the tables and the matrix scaling the kernels of a plan take
 inline int srft_plan_amax_teams(const srft_plan* p, long long n_tiles) {
     return srft_amax_teams(p->d, p->wfold4 ? 2 : p->fold_q ? 1 : 0, n_tiles);
+}
+// the way of the record of a launch of the write path over this many tiles, and the most workgroups of that launch
+inline bool srft_plan_staged(const srft_plan* p, long long tiles) {
+    return srft_write_staged(p->d, tiles, p->max_wgs > 0 ? p->max_wgs : p->grid_q);
+}
+inline long long srft_plan_write_grid(const srft_plan* p, long long tiles) {
+    return p->max_wgs > 0 ? p->max_wgs : srft_plan_staged(p, tiles) ? p->grid_staged : p->grid_q;
 }
 inline const uint4* srft_plan_write_table(const srft_plan* p) { return p->fold4_q ? p->wfold4 : p->fold_q ? p->wfold : p->wfrag; }
 inline const uint4* srft_plan_read_table(const srft_plan* p) { return p->fold4_dq ? p->rfold4 : p->fold_dq ? p->rfold : p->rfrag; }

@@ -271,7 +271,7 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int u = tid + i * NT, r = u / U, c = u % U;
-            stream_store(&tile_base[(unsigned)(min(r, lim) * U + c)], stg[r * ROW + c]);   // rows past the end alias to the last row
+            stream_store(tile_base, (unsigned)(min(r, lim) * U + c), stg[r * ROW + c]);   // rows past the end alias to the last row
         }
     };
 

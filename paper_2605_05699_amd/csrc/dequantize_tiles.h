@@ -204,7 +204,7 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
             // (Rows past the end alias to the last row.  24 bits: where U is no power of two, a 32-bit product becomes a 64-bit
             // multiply-add, whose unused upper half may be any register, the target of a prefetch among them, with a wait for
             // it in front: 9 plans x 66,666 vectors of differing counts at d = 192, 8-bit codes, 82 us, with that wait 89.)
-            stream_store(&tile_base[__umul24(min(r, lim), U) + c], stg[b][r * ROW + c]);
+            stream_store(tile_base, __umul24(min(r, lim), U) + c, stg[b][r * ROW + c]);
         }
     };
     // all groups of the tile in dec[b] (scales in scl[b]); `prev`: first fold in the last group of the

@@ -5,11 +5,11 @@ namespace {
 template <int D, int S, int GM, int BITS>
 flush_kernels_t kernels() {
     constexpr int NT = 2 * D / S, KS = GM == kGroup16 ? 1 : 2;
-    using write = srft_flush_write_plain<D, S, GM, BITS>;
+    const auto alone = srft_cache_flush_kernel<D, NT, srft_flush_write_plain<D, S, GM, BITS, true>, srft_flush_read_later>;
     if constexpr (D <= 128)
-        return {srft_cache_flush_kernel<D, NT, write, srft_flush_read_later>, srft_cache_flush_kernel<D, NT, write, srft_flush_read_plain<D, S, KS, BITS>>};
+        return {alone, srft_cache_flush_kernel<D, NT, srft_flush_write_plain<D, S, GM, BITS, false>, srft_flush_read_plain<D, S, KS, BITS>>};
     else
-        return {srft_cache_flush_kernel<D, NT, write, srft_flush_read_later>, nullptr};
+        return {alone, nullptr};
 }
 template <int D>
 flush_kernels_t pick(int bits, int gm) {

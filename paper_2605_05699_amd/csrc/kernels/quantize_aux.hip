@@ -5,11 +5,11 @@
 namespace {
 template <int D, int S>
 quantize_kernel_t by_output(int out, int teams) {
-    if (out == kOutRaw) return srft_quantize_kernel<D, S, kOutRaw, kGroup32, 4>;
+    if (out == kOutRaw) return srft_quantize_kernel<D, S, kOutRaw, kGroup32, 4, false>;
     if (out != kOutAmax) return nullptr;
     constexpr int MANY = D == 32 ? 8 : D == 64 || D == 96 ? 4 : D == 128 ? 2 : 1;
-    return teams == 1      ? srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, 1>
-           : teams == MANY ? srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, MANY>
+    return teams == 1      ? srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, false, 1>
+           : teams == MANY ? srft_quantize_kernel<D, S, kOutAmax, kGroup32, 4, false, MANY>
                            : nullptr;
 }
 template <int D>

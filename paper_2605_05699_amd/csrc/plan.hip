@@ -325,7 +325,13 @@ int occupancy_grids(srft_plan* p, int cus) {
     const quantize_kernel_t qk = srft_plan_quantize_kernel(p, kOutCodes, &threads);
     int rc = resident_blocks((const void*)qk, threads, &blocks);
     if (rc != SRFT_OK) return rc;
-    p->grid_q = cus * blocks;
+    p->grid_q = p->grid_staged = cus * blocks;
+    const quantize_kernel_t staged = srft_plan_quantize_kernel(p, kOutCodes, &threads, 769);     // (the plain form's other instance)
+    if (staged != qk) {
+        rc = resident_blocks((const void*)staged, threads, &blocks);
+        if (rc != SRFT_OK) return rc;
+        p->grid_staged = cus * blocks;
+    }
     const dequantize_kernel_t dk = srft_plan_dequantize_kernel(p, &threads);
     rc = resident_blocks((const void*)dk, threads, &blocks);
     if (rc != SRFT_OK) return rc;
@@ -364,8 +370,8 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
         return srft_pick_quantize_fold(p->d, p->bits, p->gm == kGroupWide);
     }
     *threads = 2 * p->d / p->slabs_q;
-    return p->bits == 8 ? srft_pick_quantize_plain_b8(p->d, p->slabs_q, p->gm)
-                        : srft_pick_quantize_plain_b4(p->d, p->slabs_q, p->gm);
+    const bool staged = srft_plan_staged(p, n_tiles);
+    return p->bits == 8 ? srft_pick_quantize_plain_b8(p->d, p->gm, staged) : srft_pick_quantize_plain_b4(p->d, p->gm, staged);
 }
 
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads) {

@@ -307,19 +307,22 @@ srft_quantize_fold4_tiles(const uint4* __restrict__ wf4, const uint4* __restrict
             uint4* cbase = reinterpret_cast<uint4*>(codes) + row0 * PIECES;
             const int r = tid / PIECES, pc = tid % PIECES;
             const uint2 lo = cstage[b][r * CROW + 2 * pc], hi = cstage[b][r * CROW + 2 * pc + 1];
-            cbase[(unsigned)(min(r, lim) * PIECES + pc)] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            stream_store(cbase, (unsigned)(min(r, lim) * PIECES + pc), make_uint4(lo.x, lo.y, hi.x, hi.y));
         }
         if constexpr (AMAX) {
         } else if constexpr (GM == kGroupWide) {
             float scale, inv;
             if (tid < kTileVecs) {
                 scale_of(row_max(&sstage[b][tid * SR]), scale, inv);
-                (scales + row0)[(unsigned)min(tid, lim)] = scale;
+                if constexpr (STAGE) stream_store<kStoreThrough>(scales + row0, (unsigned)min(tid, lim), scale);
+                else (scales + row0)[(unsigned)min(tid, lim)] = scale;
             }
         } else if (tid < kTileVecs * SR / 4) {           // uniform per wavefront
             const int r = tid / (SR / 4), q = tid % (SR / 4);
             const floatx4 v = *reinterpret_cast<const floatx4*>(&sstage[b][r * SR + 4 * q]);
-            reinterpret_cast<floatx4u*>(scales + row0 * SR)[(unsigned)(min(r, lim) * (SR / 4) + q)] = v;
+            const unsigned at = min(r, lim) * (SR / 4) + q;
+            if constexpr (STAGE) stream_store<kStoreThrough>(reinterpret_cast<floatx4*>(scales + row0 * SR), at, __builtin_bit_cast(uint4, v));
+            else reinterpret_cast<floatx4u*>(scales + row0 * SR)[at] = v;
         }
     };
     // AMAX: lanes of one half hold the same 32 indices for 32 different vectors: they meet in LDS (the tile buffers,

@@ -13,9 +13,6 @@
 #ifndef SRFT_QF_STAGE_OUT
 #define SRFT_QF_STAGE_OUT 1          // the record goes through LDS and is stored as whole rows one stage later
 #endif
-#ifndef SRFT_QF_NT_STORE
-#define SRFT_QF_NT_STORE 1           // non-temporal stores of the staged rows (+2.5 % at d = 128; nothing at d = 256)
-#endif
 #ifndef SRFT_QF_WG_PER_CU_256
 #define SRFT_QF_WG_PER_CU_256 2
 #endif
@@ -318,17 +315,11 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
             for (int i = 0; i < kTileVecs * PIECES / NT; ++i) {
                 const int u = tid + i * NT, r = u / PIECES, pc = u % PIECES;
                 const uint2 lo = cstage[b][r * CROW + 2 * pc], hi = cstage[b][r * CROW + 2 * pc + 1];
-                
-#if SRFT_QF_NT_STORE
-            stream_store(&cbase[(unsigned)(min(r, lim) * PIECES + pc)], make_uint4(lo.x, lo.y, hi.x, hi.y));
-#else
-            cbase[(unsigned)(min(r, lim) * PIECES + pc)] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-#endif
-
+                stream_store<kStoreThroughOnce>(cbase, (unsigned)(min(r, lim) * PIECES + pc), make_uint4(lo.x, lo.y, hi.x, hi.y));
             }
             const int ns = WIDE ? G / gw : G;            // 32 ns floats, next to each other in memory
             if (tid < kTileVecs * ns)
-                (scales + row0 * ns)[(unsigned)(min(tid / ns, lim) * ns + tid % ns)] = sstage[b][tid];
+                stream_store<kStoreThrough>(scales + row0 * ns, (unsigned)(min(tid / ns, lim) * ns + tid % ns), sstage[b][tid]);
         }
     };
 

@@ -20,8 +20,9 @@
 //         two more barriers per tile.
 // The work of one workgroup: tiles t0, t0 + stride, ... of one plan's n_vec vectors (t0 < number of tiles).
 // BITS  : 4 (two nibbles per byte) or 8 (one byte per value, scale = abs-max / 127; Sec. 3.2 steps 3-4)
+// STAGED: the record goes through LDS and is written through to memory (srft_write_staged).
 // SUB   : teams of G / S wavefronts per workgroup (kOutAmax), as in srft_quantize_fold_tiles
-template <int D, int S, int OUT, int GM, int BITS, int SUB = 1, class ROWS = srft_rows_dense>
+template <int D, int S, int OUT, int GM, int BITS, bool STAGED, int SUB = 1, class ROWS = srft_rows_dense>
 __device__ __forceinline__ void
 srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x, long long n_vec,
                     uint2* __restrict__ codes, float* __restrict__ scales, float4* __restrict__ wout,
@@ -37,6 +38,12 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
     static_assert(G % S == 0, "slabs per wavefront must divide the number of groups");
     __shared__ uint4 lds_of[SUB][2][kTileVecs * ROW];
     __shared__ float gmax[GM == kGroupWide ? kTileVecs * G : 1];     // per (vector, slab) abs-max
+    // the record of a finished tile, stored one stage later as whole rows (STAGED)
+    constexpr bool STAGE = OUT == kOutCodes && STAGED;
+    constexpr int CU8 = D * BITS / 64, CROW = CU8 + 1;       // 8-byte units per code row; padded
+    constexpr int SMAX = GM == kGroup16 ? 2 * G : G;         // most scales of a vector
+    __shared__ uint2 cstage[STAGE ? 2 : 1][STAGE ? kTileVecs * CROW : 1];
+    __shared__ float sstage[STAGE ? 2 : 1][STAGE ? kTileVecs * SMAX : 1];
 
     const int team = SUB > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0, t0 = first_tile + team;
     auto& lds = lds_of[team];
@@ -95,8 +102,9 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
                 }
         }
     };
-    // vector-ALU tail of one tile: per-group abs-max, scale, int4 codes, stores
-    auto finish = [&](Acc& accs, int tile) __attribute__((always_inline)) {
+    [[maybe_unused]] const int ns = GM == kGroupWide ? G / gw : SMAX;
+    // vector-ALU tail of one tile: per-group abs-max, scale, int4 codes, into staging buffer b or to memory
+    auto finish = [&](Acc& accs, int tile, [[maybe_unused]] const int b) __attribute__((always_inline)) {
         const long long row0 = (long long)tile * kTileVecs;
         const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;     // uniform
         const int c = min(col, lim);                                      // alias rows past the end
@@ -142,21 +150,59 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
                 float scale = mm[s] * scale_mul;             // scale_mul = fl(2^-e / 7): abs-max / 7
                 float inv = unscale * __builtin_amdgcn_rcpf(scale);
                 if (!(scale >= kMinScale)) { scale = 0.0f; inv = 0.0f; }
-                if constexpr (BITS == 8) {       // 16 bytes per lane; a row is D / 16 such units
-                    const uint4 packed = make_uint4(pack4_bytes(acc, 0, inv), pack4_bytes(acc, 4, inv),
-                                                    pack4_bytes(acc, 8, inv), pack4_bytes(acc, 12, inv));
-                    (reinterpret_cast<uint4*>(codes) + row0 * (D / 16))[(unsigned)(c * (D / 16) + 2 * slab + half)] = packed;
-                } else {
-                    uint2 packed;
-                    packed.x = pack8(acc, 0, inv);
-                    packed.y = pack8(acc, 8, inv);
-                    (codes + row0 * (D / 16))[(unsigned)(c * (D / 16) + 2 * slab + half)] = packed;
+                if constexpr (!STAGE) {
+                    if constexpr (BITS == 8) {   // 16 bytes per lane; a row is D / 16 such units
+                        const uint4 packed = make_uint4(pack4_bytes(acc, 0, inv), pack4_bytes(acc, 4, inv),
+                                                        pack4_bytes(acc, 8, inv), pack4_bytes(acc, 12, inv));
+                        (reinterpret_cast<uint4*>(codes) + row0 * (D / 16))[(unsigned)(c * (D / 16) + 2 * slab + half)] = packed;
+                    } else {
+                        uint2 packed;
+                        packed.x = pack8(acc, 0, inv);
+                        packed.y = pack8(acc, 8, inv);
+                        (codes + row0 * (D / 16))[(unsigned)(c * (D / 16) + 2 * slab + half)] = packed;
+                    }
+                    // lanes that hold the same group store the same value to the same place
+                    if constexpr (GM == kGroup16) (scales + row0 * (2 * G))[(unsigned)(c * (2 * G) + 2 * slab + half)] = scale;
+                    else if constexpr (GM == kGroup32) (scales + row0 * G)[(unsigned)(c * G + slab)] = scale;
+                    else (scales + row0 * (G / gw))[(unsigned)(c * (G / gw) + slab / gw)] = scale;
+                    return;
                 }
-                // lanes that hold the same group store the same value to the same place
-                if constexpr (GM == kGroup16) (scales + row0 * (2 * G))[(unsigned)(c * (2 * G) + 2 * slab + half)] = scale;
-                else if constexpr (GM == kGroup32) (scales + row0 * G)[(unsigned)(c * G + slab)] = scale;
-                else (scales + row0 * (G / gw))[(unsigned)(c * (G / gw) + slab / gw)] = scale;
+                uint2* const crow = &cstage[b][col * CROW + (2 * slab + half) * (BITS / 4)];
+                if constexpr (BITS == 8) {
+                    crow[0] = make_uint2(pack4_bytes(acc, 0, inv), pack4_bytes(acc, 4, inv));
+                    crow[1] = make_uint2(pack4_bytes(acc, 8, inv), pack4_bytes(acc, 12, inv));
+                } else {
+                    crow[0] = make_uint2(pack8(acc, 0, inv), pack8(acc, 8, inv));
+                }
+                sstage[b][col * ns + (GM == kGroup16 ? 2 * slab + half : GM == kGroup32 ? slab : slab / gw)] = scale;
             });
+        }
+    };
+
+    // staged record of `tile` -> global memory, whole rows next to each other (rows past the end alias to the last row; lanes
+    // without a scale store behind the end of the buffer, that is nowhere)
+    auto flush = [&](int b, int tile) __attribute__((always_inline)) {
+        if constexpr (STAGE) {
+            const long long row0 = (long long)tile * kTileVecs;
+            const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;
+            constexpr int WIDTH = BITS * S >= 8 ? 2 : 1, ROWS_OF = CU8 / WIDTH, PIECES = kTileVecs * ROWS_OF;    // 8-byte units a piece
+            static_assert(PIECES % NT == 0, "as many pieces for every thread");
+            uint2* const cbase = codes + row0 * CU8;
+#pragma unroll
+            for (int i = 0; i < PIECES / NT; ++i) {
+                const int u = tid + i * NT, r = u / ROWS_OF, p = u % ROWS_OF;
+                const uint2* const from = &cstage[b][r * CROW + WIDTH * p];
+                const unsigned at = __umul24(min(r, lim), CU8) + WIDTH * p;
+                if constexpr (WIDTH == 2) stream_store<kStoreThroughOnce>(cbase, at, make_uint4(from[0].x, from[0].y, from[1].x, from[1].y));
+                else stream_store<kStoreThroughOnce>(cbase, at, from[0]);
+            }
+#pragma unroll
+            for (int i = 0; i < (kTileVecs * SMAX + NT - 1) / NT; ++i) {
+                const int e = tid + i * NT;
+                const int r = GM == kGroupWide ? e / ns : e / SMAX, j = GM == kGroupWide ? e % ns : e % SMAX;
+                const bool mine = e < kTileVecs * ns;
+                stream_store<kStoreThrough>(scales + row0 * ns, (unsigned)(min(r, lim) * ns + j), sstage[b][mine ? e : 0], mine);
+            }
         }
     };
 
@@ -189,25 +235,41 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
         const int tk = t0 + k * stride;
         __syncthreads();                         // stage k (odd)
         rotate_priority(k + team);
+        if constexpr (STAGE)
+            if (k >= 2) flush(1, tk - 2 * stride);
         contract(1, acc_b);
-        finish(acc_a, tk - stride);
+        finish(acc_a, tk - stride, 0);
         to_lds(0, pa0, pa1, pa2, pa3);
         fetch(pa0, pa1, pa2, pa3, tk + 3 * stride);
         __syncthreads();                         // stage k + 1 (even)
         rotate_priority(k + 1 + team);
+        flush(0, tk - stride);
         contract(0, acc_a);
-        finish(acc_b, tk);
+        finish(acc_b, tk, 1);
         to_lds(1, pb0, pb1, pb2, pb3);
         fetch(pb0, pb1, pb2, pb3, tk + 4 * stride);
     }
     if (k < m) {                                 // one more odd stage
         const int tk = t0 + k * stride;
         __syncthreads();
+        if constexpr (STAGE)
+            if (k >= 2) flush(1, tk - 2 * stride);
         contract(1, acc_b);
-        finish(acc_a, tk - stride);
-        finish(acc_b, tk);
+        finish(acc_a, tk - stride, 0);
+        if constexpr (STAGE) __syncthreads();    // (staging buffer 1 has been read, buffer 0 is full)
+        flush(0, tk - stride);
+        finish(acc_b, tk, 1);
+        if constexpr (STAGE) __syncthreads();
+        flush(1, tk);
     } else {
-        finish(acc_a, t0 + (k - 1) * stride);
+        const int tl = t0 + (k - 1) * stride;
+        if constexpr (STAGE) {
+            __syncthreads();
+            if (k >= 2) flush(1, tl - stride);
+        }
+        finish(acc_a, tl, 0);
+        if constexpr (STAGE) __syncthreads();
+        flush(0, tl);
     }
     if constexpr (OUT == kOutAmax) {
         // lanes of one half hold the same 16 channels for 32 different vectors: they meet in LDS (the tile buffers, which
@@ -223,21 +285,25 @@ srft_quantize_tiles(const uint4* __restrict__ wfrag, const uint4* __restrict__ x
     }
 }
 
-template <int D, int S, int OUT, int GM, int BITS, int SUB = 1>
-__global__ void __launch_bounds__(2 * D / S * SUB)
+// Wavefronts per SIMD that the registers are to leave room for.  With the record's way through LDS the compiler takes 10 to 15
+// registers more: at d = 128 3 past the step to one wavefront less, which it finds again when asked (at d = 96 9 past it: asked, it
+// spills 6 to 20).
+template <int D, bool STAGED> constexpr int kQuantizeWaves = STAGED && D == 128 ? 3 : 1;
+template <int D, int S, int OUT, int GM, int BITS, bool STAGED, int SUB = 1>
+__global__ void __launch_bounds__(2 * D / S * SUB, (kQuantizeWaves<D, STAGED>))
 srft_quantize_kernel(const uint4* __restrict__ wfrag, const uint4* __restrict__ x, long long n_vec,
                      uint2* __restrict__ codes, float* __restrict__ scales, float4* __restrict__ wout,
                      float unscale, float scale_mul, int gw) {
-    srft_quantize_tiles<D, S, OUT, GM, BITS, SUB>(wfrag, x, n_vec, codes, scales, wout, unscale, scale_mul, gw, blockIdx.x * SUB,
+    srft_quantize_tiles<D, S, OUT, GM, BITS, STAGED, SUB>(wfrag, x, n_vec, codes, scales, wout, unscale, scale_mul, gw, blockIdx.x * SUB,
                                        gridDim.x * SUB);     // no workgroup without a tile
 }
 
 // Several plans in one launch (see srft_batch).
-template <int D, int S, int GM, int BITS, int N>
-__global__ void __launch_bounds__(2 * D / S)
+template <int D, int S, int GM, int BITS, bool STAGED, int N>
+__global__ void __launch_bounds__(2 * D / S, (kQuantizeWaves<D, STAGED>))
 srft_quantize_batched_kernel(const srft_batch<N> a, int gw) {
     const srft_work s = srft_work_of_block<true>(a);
-    srft_quantize_tiles<D, S, kOutCodes, GM, BITS>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
+    srft_quantize_tiles<D, S, kOutCodes, GM, BITS, STAGED>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
                                          nullptr, s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, s.place, s.blocks);
 }
 

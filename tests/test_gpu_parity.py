@@ -547,3 +547,38 @@ def test_scales_aligned_to_four_bytes_only(B, d, g, bits, off):
     assert bool((room[:off] == -1.0).all()) and bool((room[off + scales.numel():] == -1.0).all())
     assert torch.equal(plan.dequantize(codes, shifted), plan.dequantize(codes, scales))
     plan.close()
+
+
+# Ways of the record to memory.  Plain form: from the lanes (up to 768 tiles; more than 8 tiles for each of the workgroups, which the
+# cap sets), through LDS otherwise; the folded forms through LDS (one and several tiles a workgroup).  A vector's record is the same whichever
+# way it went: the launches of one size each are compared with each other, bit for bit, and nothing behind the last vector is written.
+@pytest.mark.parametrize("d,g,bits,transform", [
+    (32, 32, 4, "dft"), (32, 16, 8, "dft"), (64, 32, 4, "dft"), (64, 64, 8, "dft"), (64, 16, 4, "dft"), (96, 32, 4, "dft"), (96, 96, 4, "dft"), (96, 16, 8, "dft"),
+    (128, 16, 4, "dft"), (128, 128, 4, "hadamard"), (160, 32, 8, "dft"), (192, 192, 4, "dft"), (224, 16, 4, "dft"), (256, 32, 4, "hadamard"),
+    (128, 32, 4, "dft"), (128, 128, 8, "dft"), (256, 32, 4, "dft"), (256, 16, 4, "dft"), (256, 256, 4, "dft"), (256, 64, 4, "dft")])
+@pytest.mark.parametrize("n", [24_577, 24_608 + 31])
+def test_a_record_is_the_same_whichever_way_it_is_stored(B, d, g, bits, transform, n):
+    plan = B.Plan(d, g, 77, W.lognormal_lambda(d, seed=d), bits=bits, transform=transform)
+    x = (torch.randn(n, d, device="cuda", generator=torch.Generator("cuda").manual_seed(d)) * 2).to(torch.float16)
+    records, views = [], []
+    for cap in (0, 70, 69, 30):                              # workgroups: as many as fit, then 11, 12 and 26 tiles for each
+        B.srft_plan_set_max_workgroups(plan.handle, cap)
+        c = torch.full((n + 8, d * bits // 8), 99, dtype=torch.uint8, device="cuda")
+        s = torch.full((n + 8, d // g), 99.0, device="cuda")
+        B.srft_kv_quantize(plan.handle, x, c[:n], s[:n])
+        assert bool((c[n:] == 99).all()) and bool((s[n:] == 99).all())
+        records.append((c[:n], s[:n]))
+        back = torch.full((n + 8, d), 9.0, dtype=torch.float16, device="cuda")
+        B.srft_kv_dequantize(plan.handle, c[:n], s[:n], back[:n])
+        assert bool((back[n:] == 9).all())
+        views.append(back[:n])
+    B.srft_plan_set_max_workgroups(plan.handle, 0)
+    for i in range(0, n, 8_000):                             # short launches: from the lanes, and the oracle's ground in the other tests
+        k = min(8_000, n - i)
+        c, s = plan.quantize(x[i:i + k])
+        for rc, rs in records:
+            assert torch.equal(rc[i:i + k], c) and torch.equal(rs[i:i + k].view(torch.int32), s.view(torch.int32))
+        assert torch.equal(plan.dequantize(c, s).view(torch.int16), views[0][i:i + k].view(torch.int16))
+    for v in views[1:]:
+        assert torch.equal(v.view(torch.int16), views[0].view(torch.int16))
+    plan.close()
