@@ -77,7 +77,7 @@ batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long
     }
     if (p->fold4_dq) {
         *threads = p->d;
-        return srft_pick_dequantize_fold4_batched(p->d, p->bits);
+        return srft_pick_dequantize_fold4_batched(p->d, p->bits, p->gm == kGroup16);
     }
     *threads = 2 * p->d / p->slabs_dq;
     return p->bits == 8 ? srft_pick_dequantize_batched_b8(p->d, p->slabs_dq, p->gm, p->fold_dq)

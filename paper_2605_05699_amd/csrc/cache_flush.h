@@ -56,11 +56,11 @@ struct srft_flush_read_plain {
                                                      (a.n_vec + kTileVecs - 1) / kTileVecs);
     }
 };
-template <int D, int BITS>
+template <int D, int BITS, bool FINE = false>
 struct srft_flush_read_fold4 {
     static __device__ __forceinline__ void run(const uint4* frag, float unscale, const srft_flush& a, const uint2* codes,
                                                const float* scales, uint4* view, int place, int blocks) {
-        srft_dequantize_fold4_tiles<D, BITS>(frag, codes, scales, a.n_vec, view, unscale, a.gw, place, blocks,
+        srft_dequantize_fold4_tiles<D, BITS, FINE>(frag, codes, scales, a.n_vec, view, unscale, a.gw, place, blocks,
                                              (a.n_vec + kTileVecs - 1) / kTileVecs);
     }
 };

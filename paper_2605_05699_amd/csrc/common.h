@@ -276,8 +276,8 @@ dequantize_kernel_t srft_pick_dequantize_b8(int d, int slabs, int gm, bool fold)
 batched_kernels_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm, bool fold);
 batched_kernels_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm, bool fold);
 // read path, folded twice (d = 128 and 256, g >= 32); the size of its table in 16-byte units
-dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits);
-batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits);
+dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits, bool fine);
+batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits, bool fine);
 int srft_rfold4_table_units(int d);
 // a cache's flush (cache_flush.h)
 flush_kernels_t srft_pick_cache_flush_plain(int d, int bits, int gm);

@@ -1,5 +1,5 @@
 // dequantize_fold4_tiles.h -- read path at d = 128 and 256, folded twice: a quarter of the dense matrix work, half the
-// scale fold of the once-folded form.
+// scale fold of the once-folded form.  FINE: groups of 16, at d = 256.
 //
 // With h = d/2 the inverse of Eq. 1-2 is  u_n = C_n + S_n,  C_n the sum over the packed indices p <= h (DC, the cosine
 // rows, Nyquist) and S_n the sum over p > h (the sine rows) of Q[p][n] z_p.  C is even and S is odd under n -> d - n,
@@ -34,7 +34,14 @@
 // buffers.  (Decoding T_{k+1} after the second barrier instead would let the decoded tile be a single buffer too, and
 // at d = 128 a fifth workgroup fit a compute unit: measured 2 - 3.5 % slower at both sizes.)
 //
-// Table (16-byte units), NW = d/64 wavefronts: [NW][E, O][d/64 groups][hi, lo][64 lanes] A-operand fragments;
+// FINE: a group of 16 holds 8 even and 8 odd codes, half the K of an MFMA.  Both halves of a coefficient share one: lanes 0 .. 31
+// carry the high and lanes 32 .. 63 the low halves of the same 8 codes, and all lanes read those codes.  So there are as many MFMAs
+// as at g = 32 and twice the multiply-adds (every group is folded in by itself), which stay below the time of memory.  us, plain
+// form -> this one, 4 bits: 40 vectors 5.3 -> 3.95, 20,000 12.4 -> 6.8, 2 plans x 210,000 (295 MB) 132 -> 73.5 (4.0 TB/s); 8 bits,
+// 300,000 99.2 -> 56.9.  At d = 128 the plain form is at 4.6 TB/s (420,000 vectors, 37.4 us).
+//
+// Table (16-byte units), NW = d/64 wavefronts: [NW][E, O][d/64 groups][hi, lo][64 lanes] A-operand fragments
+// (FINE: [first, second group of 16][64 lanes, hi below lo]);
 // [NW][2 lane halves][6]: sign masks (8 dwords ascending run, 8 dwords descending run) and the 8 fp32 coefficients of
 // row m = d/4 for the even codes of group w a lane of that half reads (the 32 lanes of a half share them: the kernel
 // keeps them in LDS and reads them as broadcasts); [NW] per-wavefront constants (.x = Nyquist factor).
@@ -67,20 +74,21 @@ __device__ __forceinline__ uint4 decode8_flip_first(uint32_t v) {
     return o;
 }
 
-template <int D, int BITS>
+template <int D, int BITS, bool FINE>
 __device__ __forceinline__ void
 srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restrict__ codes_raw,
                             const float* __restrict__ scales, long long n_vec, uint4* __restrict__ out,
                             float unscale, int gw, const int t0, const int stride, const int t_end) {
     static_assert(D == 128 || D == 256, "one or two blocks of 32 values of m per class");
     constexpr int NB = D / 128, NW = 2 * NB, GH = D / 64;      // m blocks per class, wavefronts, groups per half of the record
-    constexpr int LG = D == 256 ? 3 : 2;                        // log2 of the groups per vector at g = 32
-    constexpr int U = D / 8, ROW = U + 1, C = D / 16, NT = 64 * NW, SROW = D / 32 + 1;
+    constexpr int LG = (D == 256 ? 3 : 2) + FINE;               // log2 of the groups per vector at g = 32 (FINE: 16)
+    constexpr int U = D / 8, ROW = U + 1, C = D / 16, NT = 64 * NW, SROW = (FINE ? D / 16 : D / 32) + 1;
     constexpr int kFragUnits = srft_rfold4_frag_units(D), kHalfUnits = srft_rfold4_half_units(D);
     using CodeUnit = std::conditional_t<BITS == 8, uint4, uint2>;
+    using Scale = std::conditional_t<FINE, float2, float>;
     const CodeUnit* __restrict__ codes = reinterpret_cast<const CodeUnit*>(codes_raw);
-    const int sh = __builtin_ctz((unsigned)gw);  // g = 32 gw, gw a power of two: group j uses scale j >> sh
-    const int ns = (D / 32) >> sh;               // scales per vector
+    const int sh = FINE ? 0 : __builtin_ctz((unsigned)gw);       // g = 32 gw, gw a power of two: group j uses scale j >> sh
+    const int ns = FINE ? D / 16 : (D / 32) >> sh;               // scales per vector
     __shared__ uint4 dec[2][kTileVecs * ROW];    // decoded codes of T_k in dec[k % 2]: per code unit [even p][odd p]
     __shared__ uint4 stg[kTileVecs * ROW];       // finished fp16 rows of the tile staged last
     __shared__ uint4 xch[2 * NB * 4 * 64];       // [sent by: cosine, sine][m block][quarter][lane]: `send`, fp32
@@ -110,15 +118,20 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
         const int u = tid + i * NT, r = u / C, c = u % C;
         v = stream_load(&tile_base[(unsigned)(min(r, lim) * C + c)]);
     };
-    auto fetch = [&](CodeUnit& c0, CodeUnit& c1, float& s0, int tile) __attribute__((always_inline)) {
+    auto fetch = [&](CodeUnit& c0, CodeUnit& c1, Scale& s0, int tile) __attribute__((always_inline)) {
         if (tile > n_tiles - 1) tile = n_tiles - 1;
         const long long row0 = (long long)tile * kTileVecs;
         const int lim = (tile == n_tiles - 1) ? last_lim : kTileVecs - 1;
         fetch1(c0, 0, codes + row0 * C, lim);
         fetch1(c1, 1, codes + row0 * C, lim);
-        int e = tid;
-        if (e > 32 * ns - 1) e = 32 * ns - 1;
-        s0 = (scales + row0 * ns)[(unsigned)(min(e >> (LG - sh), lim) * ns + (e & (ns - 1)))];
+        if constexpr (FINE) {                    // two scales per thread
+            s0.x = (scales + row0 * ns)[(unsigned)(min(tid >> LG, lim) * ns + (tid & (ns - 1)))];
+            s0.y = (scales + row0 * ns)[(unsigned)(min((tid + NT) >> LG, lim) * ns + (tid & (ns - 1)))];
+        } else {
+            int e = tid;
+            if (e > 32 * ns - 1) e = 32 * ns - 1;
+            s0 = (scales + row0 * ns)[(unsigned)(min(e >> (LG - sh), lim) * ns + (e & (ns - 1)))];
+        }
     };
     auto put1 = [&](int b, const CodeUnit& v, int i) __attribute__((always_inline)) {
         const int u = tid + i * NT, r = u / C, c = u % C;
@@ -132,61 +145,101 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
             dec[b][r * ROW + 2 * c + 1] = make_uint4(lo.y, lo.w, hi.y, hi.w);
         }
     };
-    auto to_lds = [&](int b, const CodeUnit& c0, const CodeUnit& c1, float s0) __attribute__((always_inline)) {
+    auto to_lds = [&](int b, const CodeUnit& c0, const CodeUnit& c1, Scale s0) __attribute__((always_inline)) {
         put1(b, c0, 0);
         put1(b, c1, 1);
-        float* dst = tid < 32 * ns ? &scl[b][(tid >> (LG - sh)) * SROW + (tid & (ns - 1))] : &s_dump[tid];
-        *dst = s0 * unscale;
+        if constexpr (FINE) {
+            float* dst = &scl[b][(tid >> LG) * SROW + (tid & (ns - 1))];
+            dst[0] = s0.x * unscale;
+            dst[(NT >> LG) * SROW] = s0.y * unscale;
+        } else {
+            float* dst = tid < 32 * ns ? &scl[b][(tid >> (LG - sh)) * SROW + (tid & (ns - 1))] : &s_dump[tid];
+            *dst = s0 * unscale;
+        }
     };
 
     floatx16 oE, oO, accE, accO, own;
     const int jb = GH * sine;                    // first group of this wavefront's half of the record
     // ---- contraction of the tile in dec[b], and what leaves this wavefront through LDS ----
     auto contract = [&](int b) __attribute__((always_inline)) {
-        const uint4* rowp = &dec[b][col * ROW + 2 * half + 4 * jb];     // + 4 jj (+ 1): even / odd codes of group jb + jj
+        const uint4* rowp = &dec[b][col * ROW + (FINE ? 0 : 2 * half) + 4 * jb];     // + 4 jj (+ 1): even / odd codes of group jb + jj
         const float* srow = &scl[b][col * SROW];
         const float code_n = (float)reinterpret_cast<const _Float16*>(&dec[b][col * ROW + D / 16])[0];
-        const float t_n = code_n * srow[GH >> sh] * c_nyq;
-        float sc = srow[jb >> sh], sc_next = sc;
-        half8 fa_next = __builtin_bit_cast(half8, rowp[0]), fb = __builtin_bit_cast(half8, rowp[1]), fb_next = fb;
-        accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rhi[0][0], fa_next, floatx16{0}, 0, 0, 0);
-        accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rlo[0][0], fa_next, accE, 0, 0, 0);
-        // One accumulator per class, pipelined at half-group granularity with the order pinned: MFMA, eight
-        // multiply-adds, MFMA, eight multiply-adds (a wavefront issues in order; the vector ALU has work exactly
-        // while the matrix pipe is taken).
-        auto pin_half_step = [&]() __attribute__((always_inline)) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-        };
+        const float t_n = code_n * srow[FINE ? 2 * GH : GH >> sh] * c_nyq;
+        if constexpr (FINE) {
+            // A group's 8 even (odd) codes against the two halves of their coefficients in one MFMA; every group is folded in by
+            // itself, 16 multiply-adds beside the next MFMA.
+            const float* const sg = srow + 2 * jb;
+            float sc = sg[0];
+            half8 fa = __builtin_bit_cast(half8, rowp[0]), fb = __builtin_bit_cast(half8, rowp[1]);
+            accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rhi[0][0], fa, floatx16{0}, 0, 0, 0);
+            auto pin_step = [&]() __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
+            };
 #pragma unroll
-        for (int jj = 0; jj < GH; ++jj) {
-            // O_jj on the matrix pipe, E_jj folded in
-            __builtin_amdgcn_sched_barrier(0);
-            if (jj + 1 < GH) fa_next = __builtin_bit_cast(half8, rowp[4 * (jj + 1)]);
-            accO = __builtin_amdgcn_mfma_f32_32x32x16_f16(rhi[1][jj], fb, floatx16{0}, 0, 0, 0);
+            for (int i = 0; i < 2 * GH; ++i) {
+                const int jj = i / 2, jn = (i + 1) / 2;
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 1 < 2 * GH) fa = __builtin_bit_cast(half8, rowp[2 * (i + 1)]);
+                accO = __builtin_amdgcn_mfma_f32_32x32x16_f16(i % 2 ? rlo[1][jj] : rhi[1][jj], fb, floatx16{0}, 0, 0, 0);
 #pragma unroll
-            for (int v = 0; v < 8; ++v) oE[v] = fmaf(accE[v], sc, jj == 0 ? ((v & 1) ? -t_n : t_n) : oE[v]);
-            accO = __builtin_amdgcn_mfma_f32_32x32x16_f16(rlo[1][jj], fb, accO, 0, 0, 0);
+                for (int v = 0; v < 16; ++v) oE[v] = fmaf(accE[v], sc, i == 0 ? ((v & 1) ? -t_n : t_n) : oE[v]);
+                pin_step();
+                __builtin_amdgcn_sched_barrier(0);
+                float sc_next = sc;
+                if (i + 1 < 2 * GH) {
+                    fb = __builtin_bit_cast(half8, rowp[2 * (i + 1) + 1]);
+                    sc_next = sg[i + 1];
+                    accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(i % 2 ? rhi[0][jn] : rlo[0][jn], fa, floatx16{0}, 0, 0, 0);
+                }
 #pragma unroll
-            for (int v = 8; v < 16; ++v) oE[v] = fmaf(accE[v], sc, jj == 0 ? ((v & 1) ? -t_n : t_n) : oE[v]);
-            pin_half_step();
-            // E_{jj+1} on the matrix pipe, O_jj folded in
-            __builtin_amdgcn_sched_barrier(0);
-            if (jj + 1 < GH) {
-                fb_next = __builtin_bit_cast(half8, rowp[4 * (jj + 1) + 1]);
-                sc_next = srow[(jb + jj + 1) >> sh];
-                accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rhi[0][jj + 1], fa_next, floatx16{0}, 0, 0, 0);
+                for (int v = 0; v < 16; ++v) oO[v] = i == 0 ? accO[v] * sc : fmaf(accO[v], sc, oO[v]);
+                if (i + 1 < 2 * GH) pin_step();
+                sc = sc_next;
             }
-#pragma unroll
-            for (int v = 0; v < 8; ++v) oO[v] = jj == 0 ? accO[v] * sc : fmaf(accO[v], sc, oO[v]);
-            if (jj + 1 < GH) accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rlo[0][jj + 1], fa_next, accE, 0, 0, 0);
-#pragma unroll
-            for (int v = 8; v < 16; ++v) oO[v] = jj == 0 ? accO[v] * sc : fmaf(accO[v], sc, oO[v]);
-            if (jj + 1 < GH) pin_half_step();
-            sc = sc_next;
-            fb = fb_next;
+        } else {
+            float sc = srow[jb >> sh], sc_next = sc;
+            half8 fa_next = __builtin_bit_cast(half8, rowp[0]), fb = __builtin_bit_cast(half8, rowp[1]), fb_next = fb;
+            accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rhi[0][0], fa_next, floatx16{0}, 0, 0, 0);
+            accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rlo[0][0], fa_next, accE, 0, 0, 0);
+            // One accumulator per class, pipelined at half-group granularity with the order pinned: MFMA, eight
+            // multiply-adds, MFMA, eight multiply-adds (a wavefront issues in order; the vector ALU has work exactly
+            // while the matrix pipe is taken).
+            auto pin_half_step = [&]() __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+            };
+    #pragma unroll
+            for (int jj = 0; jj < GH; ++jj) {
+                // O_jj on the matrix pipe, E_jj folded in
+                __builtin_amdgcn_sched_barrier(0);
+                if (jj + 1 < GH) fa_next = __builtin_bit_cast(half8, rowp[4 * (jj + 1)]);
+                accO = __builtin_amdgcn_mfma_f32_32x32x16_f16(rhi[1][jj], fb, floatx16{0}, 0, 0, 0);
+    #pragma unroll
+                for (int v = 0; v < 8; ++v) oE[v] = fmaf(accE[v], sc, jj == 0 ? ((v & 1) ? -t_n : t_n) : oE[v]);
+                accO = __builtin_amdgcn_mfma_f32_32x32x16_f16(rlo[1][jj], fb, accO, 0, 0, 0);
+    #pragma unroll
+                for (int v = 8; v < 16; ++v) oE[v] = fmaf(accE[v], sc, jj == 0 ? ((v & 1) ? -t_n : t_n) : oE[v]);
+                pin_half_step();
+                // E_{jj+1} on the matrix pipe, O_jj folded in
+                __builtin_amdgcn_sched_barrier(0);
+                if (jj + 1 < GH) {
+                    fb_next = __builtin_bit_cast(half8, rowp[4 * (jj + 1) + 1]);
+                    sc_next = srow[(jb + jj + 1) >> sh];
+                    accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rhi[0][jj + 1], fa_next, floatx16{0}, 0, 0, 0);
+                }
+    #pragma unroll
+                for (int v = 0; v < 8; ++v) oO[v] = jj == 0 ? accO[v] * sc : fmaf(accO[v], sc, oO[v]);
+                if (jj + 1 < GH) accE = __builtin_amdgcn_mfma_f32_32x32x16_f16(rlo[0][jj + 1], fa_next, accE, 0, 0, 0);
+    #pragma unroll
+                for (int v = 8; v < 16; ++v) oO[v] = jj == 0 ? accO[v] * sc : fmaf(accO[v], sc, oO[v]);
+                if (jj + 1 < GH) pin_half_step();
+                sc = sc_next;
+                fb = fb_next;
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
         // Ce at m = d/4: this wavefront's share is cosine group `wave`; a lane holds 8 of its 16 even codes
@@ -201,7 +254,7 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
                 dot0 = fmaf((float)fx[e], cf[e], dot0);
                 dot1 = fmaf((float)fx[e + 1], cf[e + 1], dot1);
             }
-            float part = (dot0 + dot1) * srow[wave >> sh];
+            float part = (dot0 + dot1) * srow[FINE ? 2 * wave + half : wave >> sh];
             part += (wave == 0 && half == 0) ? t_n : 0.0f;
             const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(part), __float_as_uint(part), false, false);
             *(half == 0 ? &s_c64[wave][col] : &s_dump[tid]) = __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -277,7 +330,7 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
 
     const int m = (t_end - 1 - t0) / stride + 1;            // tiles of this workgroup: t0, t0 + stride, ... < t_end
     CodeUnit pa0, pa1, pb0, pb1;
-    float pas, pbs;
+    Scale pas, pbs;
     fetch(pa0, pa1, pas, t0);
     // The first tile is asked for ahead of the matrix (it comes from farther away, and does not wait for the plan's entry), the
     // second one behind it: the first tile goes to LDS while the matrix is on its way.
@@ -340,21 +393,21 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
     }
 }
 
-template <int D, int BITS>
+template <int D, int BITS, bool FINE>
 __global__ void __launch_bounds__(D / 64 * 64, 2)
 srft_dequantize_fold4_kernel(const uint4* __restrict__ tab, const uint2* __restrict__ codes,
                              const float* __restrict__ scales, long long n_vec, uint4* __restrict__ out,
                              float unscale, int gw) {
     int t0, stride, t_end;
     if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
-    srft_dequantize_fold4_tiles<D, BITS>(tab, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
+    srft_dequantize_fold4_tiles<D, BITS, FINE>(tab, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
 }
 
-template <int D, int BITS, int N>
+template <int D, int BITS, bool FINE, int N>
 __global__ void __launch_bounds__(D / 64 * 64, 2)
 srft_dequantize_fold4_batched_kernel(const srft_batch<N> a, int gw) {
     const srft_work s = srft_work_of_block<false>(a);
-    srft_dequantize_fold4_tiles<D, BITS>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
+    srft_dequantize_fold4_tiles<D, BITS, FINE>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
                                          s.unscale, gw, s.place, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 

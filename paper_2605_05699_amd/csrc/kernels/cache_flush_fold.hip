@@ -2,9 +2,9 @@
 #include "../cache_flush.h"
 
 namespace {
-template <int D, int BITS, class WRITE>
+template <int D, int BITS, class WRITE, bool FINE = false>
 flush_kernels_t kernels() {
-    return {srft_cache_flush_kernel<D, D, WRITE, srft_flush_read_later>, srft_cache_flush_kernel<D, D, WRITE, srft_flush_read_fold4<D, BITS>>};
+    return {srft_cache_flush_kernel<D, D, WRITE, srft_flush_read_later>, srft_cache_flush_kernel<D, D, WRITE, srft_flush_read_fold4<D, BITS, FINE>>};
 }
 template <int BITS>
 flush_kernels_t pick(int d, int gm, bool fold4_q) {
@@ -12,7 +12,7 @@ flush_kernels_t pick(int d, int gm, bool fold4_q) {
         return gm == kGroupWide ? kernels<128, BITS, srft_flush_write_fold<128, BITS, true>>() : kernels<128, BITS, srft_flush_write_fold<128, BITS, false>>();
     if (d != 256) return nullptr;
     if (!fold4_q) return kernels<256, BITS, srft_flush_write_fold<256, BITS, true>>();
-    if (gm == kGroup16) return {srft_cache_flush_kernel<256, 256, srft_flush_write_fold4<BITS, kGroup16>, srft_flush_read_later>, nullptr};
+    if (gm == kGroup16) return kernels<256, BITS, srft_flush_write_fold4<BITS, kGroup16>, true>();
     return gm == kGroupWide ? kernels<256, BITS, srft_flush_write_fold4<BITS, kGroupWide>>() : kernels<256, BITS, srft_flush_write_fold4<BITS, kGroup32>>();
 }
 }  // namespace

@@ -175,7 +175,7 @@ void build_fold4_table(const dft_matrix& Q, const std::vector<int8_t>& signs, co
 // are Q[p][m] / max(lambda_p, 1e-6), without the sign diagonal, which the kernel applies through the masks.
 // Returns the exponent e of the fp16 scaling.
 int build_rfold4_table(const dft_matrix& Q, const std::vector<int8_t>& signs, const std::vector<double>& lam, int bits,
-                       std::vector<uint32_t>& out) {
+                       bool fine, std::vector<uint32_t>& out) {
     const int d = Q.d, h = d / 2, NB = d / 128, NW = 2 * NB, GH = d / 64;
     static const int off4[8] = {0, 4, 2, 6, 8, 12, 10, 14}, off8[8] = {0, 2, 4, 6, 8, 10, 12, 14};
     const int* off = bits == 8 ? off8 : off4;
@@ -206,9 +206,13 @@ int build_rfold4_table(const dft_matrix& Q, const std::vector<int8_t>& signs, co
                 for (int l = 0; l < 64; ++l) {
                     const int r = slab_output_of_row(l % 32), kh = l / 32;
                     for (int el = 0; el < 8; ++el) {
-                        const int i = (16 * kh + off[el]) / 2;          // even (or odd) code 2 i (+ 1) of the group
-                        const size_t src = ((((size_t)w * 2 + c) * 32 + r) * GH + jj) * 16 + i;
+                        const size_t row = ((((size_t)w * 2 + c) * 32 + r) * GH + jj) * 16;
                         const size_t dst = ((((size_t)(w * 2 + c) * GH + jj) * 2) * 64);
+                        if (fine) {      // both groups of 16, each with its high halves in lanes 0..31 and its low ones in 32..63
+                            for (int s = 0; s < 2; ++s) frag[((dst + 64 * s) + l) * 8 + el] = (kh ? lo : hi)[row + (16 * s + off[el]) / 2];
+                            continue;
+                        }
+                        const size_t src = row + (16 * kh + off[el]) / 2;      // even (or odd) code 2 i (+ 1) of the group
                         frag[((dst + 0) + l) * 8 + el] = hi[src];
                         frag[((dst + 64) + l) * 8 + el] = lo[src];
                     }
@@ -377,7 +381,7 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads) {
     if (p->fold4_dq) {
         *threads = p->d;
-        return srft_pick_dequantize_fold4(p->d, p->bits);
+        return srft_pick_dequantize_fold4(p->d, p->bits, p->gm == kGroup16);
     }
     *threads = 2 * p->d / p->slabs_dq;
     return p->bits == 8 ? srft_pick_dequantize_b8(p->d, p->slabs_dq, p->gm, p->fold_dq)
@@ -572,10 +576,11 @@ static int plan_create(srft_plan_t** out, int d, int group_size, int bits, int t
     }
     std::vector<uint32_t> wfold4;
     if (has_fold4) build_fold4_table(Q, p->signs, lam, wfold4);
-    // Twice-folded read path at d = 128 and 256 (any g >= 32); it replaces the once-folded form there.
-    p->fold4_dq = (d == 128 || d == 256) && p->gm != kGroup16 && transform == SRFT_TRANSFORM_DFT;
+    // Twice-folded read path at d = 128 and 256 (any g >= 32; at d = 256 also g = 16, where the plain form is
+    // bound by the matrix cores: 295 MB 132 us, folded 73.5); it replaces the once-folded form there.
+    p->fold4_dq = (d == 256 || (d == 128 && p->gm != kGroup16)) && transform == SRFT_TRANSFORM_DFT;
     std::vector<uint32_t> rfold4;
-    if (p->fold4_dq) p->unscale_r4 = (float)std::ldexp(1.0, -build_rfold4_table(Q, p->signs, lam, bits, rfold4));
+    if (p->fold4_dq) p->unscale_r4 = (float)std::ldexp(1.0, -build_rfold4_table(Q, p->signs, lam, bits, p->gm == kGroup16, rfold4));
     // Butterfly form of the write path (comparison kernel): per packed index lambda times the packing constant of
     // Eq. 2 -- 1/sqrt d for DC and Nyquist, sqrt(2/d) elsewhere, halved where the unpack leaves a factor 2 (every
     // bin except 0, d/4 and d/2) -- then the sign diagonal as sign-bit masks of the packed fp16 pairs.

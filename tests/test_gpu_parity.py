@@ -136,7 +136,7 @@ def test_every_nibble_value_at_every_position_is_decoded(B, d):
     plan.close()
 
 
-@pytest.mark.parametrize("d,g", [(128, 32), (128, 64), (128, 128), (256, 32), (256, 128), (256, 256)])
+@pytest.mark.parametrize("d,g", [(128, 32), (128, 64), (128, 128), (256, 16), (256, 32), (256, 128), (256, 256)])
 def test_codes_the_twice_folded_read_form_treats_apart(B, d, g):
     # The read kernel at d = 128 / 256 contracts cosine and sine rows, even and odd packed indices, in four separate
     # classes, brings Nyquist (p = d/2) in as an addend and takes the outputs n = d/4, 3d/4 from a row of its own.
