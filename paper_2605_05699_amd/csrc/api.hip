@@ -80,8 +80,7 @@ batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long
         return srft_pick_dequantize_fold4_batched(p->d, p->bits, p->gm == kGroup16);
     }
     *threads = 2 * p->d / p->slabs_dq;
-    return p->bits == 8 ? srft_pick_dequantize_batched_b8(p->d, p->slabs_dq, p->gm, p->fold_dq)
-                        : srft_pick_dequantize_batched_b4(p->d, p->slabs_dq, p->gm, p->fold_dq);
+    return p->bits == 8 ? srft_pick_dequantize_batched_b8(p->d, p->slabs_dq, p->gm) : srft_pick_dequantize_batched_b4(p->d, p->slabs_dq, p->gm);
 }
 
 // One batched launch over the first `count` segments of the table, which is complete except for the workgroups.

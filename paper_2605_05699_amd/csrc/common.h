@@ -271,11 +271,11 @@ quantize_kernel_t srft_pick_quantize_fold4_amax(int teams);
 batched_kernels_t srft_pick_quantize_fold4_batched(int bits, int gm);
 int srft_fold4_table_units(void);
 // read path
-dequantize_kernel_t srft_pick_dequantize_b4(int d, int slabs, int gm, bool fold);
-dequantize_kernel_t srft_pick_dequantize_b8(int d, int slabs, int gm, bool fold);
-batched_kernels_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm, bool fold);
-batched_kernels_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm, bool fold);
-// read path, folded twice (d = 128 and 256, g >= 32); the size of its table in 16-byte units
+dequantize_kernel_t srft_pick_dequantize_b4(int d, int slabs, int gm);
+dequantize_kernel_t srft_pick_dequantize_b8(int d, int slabs, int gm);
+batched_kernels_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm);
+batched_kernels_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm);
+// read path, folded twice (d = 128 at g >= 32, d = 256; fine: g = 16); the size of its table in 16-byte units
 dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits, bool fine);
 batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits, bool fine);
 int srft_rfold4_table_units(int d);

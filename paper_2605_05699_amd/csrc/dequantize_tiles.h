@@ -23,8 +23,8 @@
 // S : output slabs per wavefront (the workgroup has D / (32 S) wavefronts), as on the write path.
 // KS: MFMA k-steps (of 16 codes) contracted under one scale: 2 for g >= 32 (g = 32 * gw, gw slabs of codes
 //     share a scale), 1 for g = 16.  "Group" below means one such run of 16 * KS codes.
-// FOLD: half the matrix work, for d a multiple of 64 and g >= 32 (run at d = 128 and 192; d = 256 has a kernel of its
-//     own, dequantize_fold4_tiles.h, that folds twice).  Every row of Q satisfies
+// FOLD: half the matrix work, for d a multiple of 64 (run at d = 192; d = 128 and 256 have a kernel of their own,
+//     dequantize_fold4_tiles.h, that folds twice).  Every row of Q satisfies
 //     Q[p][n + d/2] = (-1)^p Q[p][n]   (DC and Nyquist rows: +1; cos and sin rows of bin k: (-1)^k, and the
 //     packed index p has the parity of k), so with  A_n = sum over even p,  B_n = sum over odd p  of
 //     Q[p][n] z_p  the outputs are  x_n = s_n (A_n + B_n)  and  x_{n+d/2} = s_{n+d/2} (A_n - B_n),  n < d/2.
@@ -32,7 +32,8 @@
 //     the high nibbles.  Wavefront w owns n = 32w .. 32w+31: slab 0 is A, slab 1 is B (S = 2, KS = 1: per
 //     group of 32 codes one k-step of 16 even and one of 16 odd codes), rows scaled by s_n on the host;
 //     the relative sign s_n s_{n+d/2} is applied to the packed fp16 bits.  There is room for one accumulator per slab;
-//     the loop is pipelined at half-group granularity (see lean_body).  rfrag is then
+//     the loop is pipelined at half-group granularity (see lean_body).  With KS = 2 a run of 32 codes has two scales (g = 16).
+//     rfrag is then
 //     [D/64 waves][A, B][D/32 groups][hi, lo][64 lanes], followed by [D/64 waves][64 lanes][2] sign masks.
 // BITS: 4, or 8 (one two's-complement byte per code).  A "code unit" is 16 codes: 8 bytes at 4 bits, 16 at 8.
 //     At 8 bits a dword gives the pairs (b0, b2) and (b1, b3): again even and odd p apart, so FOLD applies as is.
@@ -44,8 +45,9 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     constexpr int G = FOLD ? D / 32 : D / 32 * (2 / KS);  // groups per vector as contracted
     constexpr int NSMAX = D / 16;         // most scales a vector can have (g = 16)
     constexpr bool kPerStep = (KS == 1 && !FOLD);         // g = 16: a scale per k-step of the full matrix
-    const int ns = kPerStep ? D / 16 : D / 32 / gw;       // scales per vector
-    static_assert(!FOLD || (S == 2 && KS == 1 && D % 64 == 0), "the folded form pairs an A and a B slab");
+    constexpr bool FINE = FOLD && KS == 2;                // g = 16: two scales per contracted group
+    const int ns = kPerStep || FINE ? D / 16 : D / 32 / gw;       // scales per vector
+    static_assert(!FOLD || (S == 2 && D % 64 == 0), "the folded form pairs an A and a B slab");
     constexpr int U = D / 8;             // 16-byte units per decoded row (D fp16)
     constexpr int ROW = U + 1;
     constexpr int C = D / 16;            // code units (16 codes) per row
@@ -59,7 +61,7 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     // soon as it is done, the tile staged in the stage that computes it.  That is the folded form, g = 16 (two accumulator
     // sets, and the compiler reads the many groups' operands ahead: 192 to 256 registers and up to 400 of them in scratch
     // against 110 to 190) and d >= 224.  Measured, us over 400 MB of record and result at 4 bits, alternating -> one set:
-    // g = 16: d = 96 110 -> 82, 128 108 -> 96, 160 282 -> 166, 192 682 -> 173, 224 1061 -> 181; d = 224, g = 32: 195 -> 155.
+    // g = 16: d = 96 110 -> 82, 128 108 -> 96, 160 282 -> 166, 224 1061 -> 181; d = 224, g = 32: 195 -> 155.
     // At d = 160, g = 32, the two are equal.  (d = 32 and 64 fit.)
     constexpr bool LEAN = FOLD || (S == 1 && D >= (kPerStep ? 96 : 224));
     __shared__ uint4 dec[2][kTileVecs * ROW];    // decoded codes of T_k in dec[k % 2]
@@ -72,7 +74,7 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     const int n_tiles = (int)((n_vec + kTileVecs - 1) / kTileVecs);
     const int last_lim = (int)(n_vec - 1 - (long long)(n_tiles - 1) * kTileVecs);   // last valid row of the last tile
 
-    half8 rhi[S * G][KS], rlo[S * G][KS];        // [s * G + group][k-step within the group]
+    half8 rhi[S * G][FOLD ? 1 : KS], rlo[S * G][FOLD ? 1 : KS];  // [s * G + group][k-step within the group]
     uint4 flip0 = {}, flip1 = {};                // sign-bit masks of this lane's 16 outputs n + d/2 (FOLD)
 
     // each thread decodes S 8-byte units of the 32 x D/2 code tile (32 * C = S * NT units) and carries up to
@@ -133,7 +135,7 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
         if constexpr (PS > 1) put_scale(b, s1, 1);
     };
     // scale of contracted group j: its own at g = 16 and g = 32, shared by gw groups at g = 32 * gw
-    auto scale_of = [&](int b, int j) __attribute__((always_inline)) { return scl[b][col * SROW + (kPerStep ? j : j / gw)]; };
+    auto scale_of = [&](int b, int j) __attribute__((always_inline)) { return scl[b][col * SROW + (kPerStep || FINE ? j : j / gw)]; };
     // The last group of a tile is folded in one stage later, under group 0 of the next tile (which uses
     // acc0); with an even number of groups it can live in acc1, otherwise it needs a register set of its own.
     floatx16 o[S], acc0[S], acc1[S], acc_odd[S];
@@ -234,7 +236,41 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     };
 
     auto lean_body = [&](int b) __attribute__((always_inline)) {
-        if constexpr (FOLD && SRFT_DQ_HALF_PIPE) {
+        if constexpr (FINE) {
+            // A group's 8 even (odd) codes against both halves of their coefficients in one MFMA (lanes 0 .. 31 carry the high, lanes
+            // 32 .. 63 the low halves, all lanes the same codes); every group is folded in by itself, 16 multiply-adds beside the
+            // next MFMA.  us, the whole matrix -> folded, 4 bits: 40 vectors 4.1 -> 3.7, 20,000 11.1 -> 6.35, 270,000 (142 MB) 64 -> 45
+            // (g = 32: 35.4); 8 bits, 270,000 68.4 -> 47.2.
+            const uint4* rowp = &dec[b][col * ROW];                 // units 2i (+ 1): even / odd codes of group i
+            float sc = scale_of(b, 0), sc_next = sc;
+            half8 fa = __builtin_bit_cast(half8, rowp[0]), fb = __builtin_bit_cast(half8, rowp[1]);
+            auto frag = [&](int i) -> const half8& { return i % 2 ? rlo[i / 2][0] : rhi[i / 2][0]; };
+            auto pin_step = [&]() __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);     // sixteen vector-ALU instructions
+            };
+            acc0[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(frag(0), fa, floatx16{0}, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 2 * G; ++i) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 1 < 2 * G) fa = __builtin_bit_cast(half8, rowp[2 * (i + 1)]);
+                acc0[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(frag(2 * G + i), fb, floatx16{0}, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[0][v] = i == 0 ? acc0[0][v] * sc : fmaf(acc0[0][v], sc, o[0][v]);
+                pin_step();
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 1 < 2 * G) {
+                    fb = __builtin_bit_cast(half8, rowp[2 * (i + 1) + 1]);
+                    sc_next = scale_of(b, i + 1);
+                    acc0[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(frag(i + 1), fa, floatx16{0}, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[1][v] = i == 0 ? acc0[1][v] * sc : fmaf(acc0[1][v], sc, o[1][v]);
+                if (i + 1 < 2 * G) pin_step();
+                sc = sc_next;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        } else if constexpr (FOLD && SRFT_DQ_HALF_PIPE) {
             // One accumulator per slab, software-pipelined at half-group granularity.  The MFMA pairs go A_0, B_0, A_1,
             // B_1, ...; each result is folded in (16 multiply-adds) one half-step after its pair, under the other
             // slab's pair.  A wavefront issues in order, and a second MFMA cannot issue while the first occupies the
@@ -307,7 +343,7 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
 #pragma unroll
         for (int j = 0; j < G; ++j)
 #pragma unroll
-            for (int t = 0; t < KS; ++t) {
+            for (int t = 0; t < (FOLD ? 1 : KS); ++t) {
                 const int slab = wave * S + s, kstep = j * KS + t;
                 const int f = FOLD ? slab * G + j : slab * (D / 16) + kstep;
                 rhi[s * G + j][t] = __builtin_bit_cast(half8, rfrag[(f * 2 + 0) * 64 + lane]);

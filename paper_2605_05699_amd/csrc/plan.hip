@@ -384,8 +384,7 @@ dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads
         return srft_pick_dequantize_fold4(p->d, p->bits, p->gm == kGroup16);
     }
     *threads = 2 * p->d / p->slabs_dq;
-    return p->bits == 8 ? srft_pick_dequantize_b8(p->d, p->slabs_dq, p->gm, p->fold_dq)
-                        : srft_pick_dequantize_b4(p->d, p->slabs_dq, p->gm, p->fold_dq);
+    return p->bits == 8 ? srft_pick_dequantize_b8(p->d, p->slabs_dq, p->gm) : srft_pick_dequantize_b4(p->d, p->slabs_dq, p->gm);
 }
 
 flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads) {
@@ -496,8 +495,8 @@ static int plan_create(srft_plan_t** out, int d, int group_size, int bits, int t
     // (At d = 256 two slabs leave one wavefront per SIMD: read at g = 16, 600,961 vectors, 220 us against 188 with one slab.)
     p->slabs_q = (d == 64) ? 2 : 1;
     p->slabs_dq = (d == 64) ? 2 : 1;
-    // Folded read path where it applies and pays (d = 192; g >= 32); d = 128 and 256 have the twice-folded form below.
-    p->fold_dq = (d % 64 == 0) && d >= 128 && d != 128 && d != 256 && p->gm != kGroup16 &&    // at d = 64 it gains nothing
+    // Folded read path where it applies and pays (d = 192); d = 128 and 256 have the twice-folded form below.
+    p->fold_dq = (d % 64 == 0) && d >= 128 && d != 128 && d != 256 &&                         // at d = 64 it gains nothing
                  transform == SRFT_TRANSFORM_DFT;                      // (the symmetries are the DFT's)
     std::vector<uint16_t> rfold;
     if (p->fold_dq) {
@@ -517,8 +516,13 @@ static int plan_create(srft_plan_t** out, int d, int group_size, int bits, int t
                 for (int ab = 0; ab < 2; ++ab)
                     for (int j = 0; j < G; ++j)
                         for (int e = 0; e < 8; ++e) {
-                            const size_t src = (size_t)n * d + (32 * j + 16 * kh + off[e] + ab);
                             const size_t dst = (((size_t)(w * 2 + ab) * G + j) * 2) * 64;
+                            if (p->gm == kGroup16) {     // both groups of 16: high halves in lanes 0..31, low ones in 32..63
+                                for (int s = 0; s < 2; ++s)
+                                    rfold[((dst + 64 * s) + l) * 8 + e] = (kh ? rlo : rhi)[(size_t)n * d + (32 * j + 16 * s + off[e] + ab)];
+                                continue;
+                            }
+                            const size_t src = (size_t)n * d + (32 * j + 16 * kh + off[e] + ab);
                             rfold[((dst + 0) + l) * 8 + e] = rhi[src];
                             rfold[((dst + 64) + l) * 8 + e] = rlo[src];
                         }
