@@ -27,7 +27,7 @@ template <int D, int RB> constexpr int kTileKeys = D * RB > 256 || D == 256 ? 32
 // 16 queries, 1,000,000 keys 27.0 -> 21.5; d = 128, 32 queries 49 -> 45.  With half-empty blocks it is slower at 300,000 keys
 // (8 queries, d = 64 7.4 -> 7.6) and with one query everywhere (1,000,000 keys 10.4 -> 11.0).
 // codes [n_keys][D / 2] bytes, scales [n_keys][D / 32 / gw], out [n_q][n_keys]
-template <int D, int RB, bool WIDE, bool STAGE>
+template <int D, int RB, bool WIDE, bool STAGE, bool THROUGH>
 __global__ void __launch_bounds__(64 * kWaves, 2)
 srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict__ q_table, int hadamard,
                    const uint8_t* __restrict__ codes, const float* __restrict__ scales, int gw,
@@ -44,9 +44,6 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
     float* const ks = reinterpret_cast<float*>(lds) + wave * G * KEYS;      // this wavefront's scales, [group][key]
     const long long n_tiles = (n_keys + KEYS - 1) / KEYS, stride = (long long)gridDim.x * W;
     const long long first = (long long)wave * gridDim.x + blockIdx.x;
-    // Rows of whole 64-byte pieces are written through (device_util.h): 8 queries, 100,000 keys at d = 128 4.75 -> 4.45 us, 1,000,000
-    // 23.7 -> 19.3, 32 queries, 100,000 7.8 -> 6.15.  Pieces that straddle lines are not (334,146 keys 16.5 -> 24.7).
-    const bool through = n_keys % 16 == 0 && (reinterpret_cast<uintptr_t>(out) & 63) == 0;
 
     uint4 pk[BK][QUADS ? QUADS : 1];
     static_assert(REST == 0 || REST == 2, "d is a multiple of 64");
@@ -150,7 +147,7 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
                     const floatx4 v = *reinterpret_cast<const floatx4*>(&st[mine * SROW + c]);
                     if (16 * rb + mine < n_q) {
                         float* const p = out + (16 * rb + mine) * n_keys + t0 + c;
-                        if (through) stream_store_at(p, v);
+                        if constexpr (THROUGH) stream_store_at(p, v);
                         else *reinterpret_cast<floatx4u*>(p) = v;
                     }
                 }
@@ -159,7 +156,7 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
                 if (t0 + KEYS <= n_keys) {                  // uniform
 #pragma unroll
                     for (int b = 0; b < BK; ++b) {
-                        if (through) stream_store_at(row + 16 * b, w[rb][b]);
+                        if constexpr (THROUGH) stream_store_at(row + 16 * b, w[rb][b]);
                         else *reinterpret_cast<floatx4u*>(row + 16 * b) = w[rb][b];
                     }
                 } else {
@@ -174,6 +171,14 @@ srft_scores_kernel(const uint4* __restrict__ q, int n_q, const uint4* __restrict
     }
 }
 
+// n_q <= 8 / 16 / 32
+template <int D, bool WIDE, bool THROUGH>
+auto kernel_of(int n_q) {
+    return n_q <= 8    ? srft_scores_kernel<D, 1, WIDE, false, THROUGH>
+           : n_q <= 16 ? srft_scores_kernel<D, 1, WIDE, true, THROUGH>
+                       : srft_scores_kernel<D, 2, WIDE, true, THROUGH>;
+}
+
 template <int D>
 int launch(const srft_plan* p, const void* q, int n_q, const uint8_t* codes, const float* scales, long long n_keys, float* out,
            hipStream_t st) {
@@ -185,9 +190,12 @@ int launch(const srft_plan* p, const void* q, int n_q, const uint8_t* codes, con
     long long grid = p->max_wgs > 0 ? p->max_wgs : (D == 64 && n_q <= 16 ? 2 : 1) * p->compute_units;
     if (grid > n_tiles) grid = n_tiles;
     const bool wide = p->gw > 1;
-    auto kernel = n_q <= 8    ? (wide ? srft_scores_kernel<D, 1, true, false> : srft_scores_kernel<D, 1, false, false>)
-                  : n_q <= 16 ? (wide ? srft_scores_kernel<D, 1, true, true> : srft_scores_kernel<D, 1, false, true>)
-                              : (wide ? srft_scores_kernel<D, 2, true, true> : srft_scores_kernel<D, 2, false, true>);
+    // Rows of whole 64-byte pieces are written through (device_util.h): 8 queries, 100,000 keys at d = 128 4.75 -> 4.45 us, 1,000,000
+    // 23.7 -> 19.3, 32 queries, 100,000 7.8 -> 6.15.  Pieces that straddle lines are not (334,146 keys 16.5 -> 24.7), nor a single row,
+    // which is next to nothing to write back (1,000,000 keys at d = 128 17.0 -> 17.3).
+    const bool through = n_q > 1 && n_keys % 16 == 0 && (reinterpret_cast<uintptr_t>(out) & 63) == 0;
+    const auto kernel = through ? (wide ? kernel_of<D, true, true>(n_q) : kernel_of<D, false, true>(n_q))
+                                : (wide ? kernel_of<D, true, false>(n_q) : kernel_of<D, false, false>(n_q));
     return srft_launch(kernel, dim3((unsigned)grid), 64 * kWaves, st, (const uint4*)q, n_q, (const uint4*)p->q_table,
                        (int)(p->transform == SRFT_TRANSFORM_HADAMARD), codes, scales, p->gw, n_keys, out);
 }
