@@ -221,11 +221,14 @@ struct srft_cache {
 //   from there to 200 MB the memory-side cache takes the record better from the L2, where the rows are short: d = 96 151 MB 34 -> 38.7, 180
 //     MB 38.6 -> 46; d = 64 122 MB 26.5 -> 27.5, 176 MB 37 -> 40
 //   beyond whole rows help again, except the shortest: d = 96 330 MB 66.4 -> 63.6, 505 MB 100 -> 92.8; d = 64 322 MB 62 -> 65.6, g = 16 563
-//     MB 112.3 -> 114.4; d = 32 350 MB 67.6 -> 68.0
+//     MB 112.3 -> 114.4
+//   d = 32, with a vector in half a line, gains between 1 and 4 tiles for each of 4096 workgroups: 190,000 vectors 4.2 -> 3.9, 400,000 7.0
+//     -> 6.7; 36 plans x 1494 2.75 -> 3.1, 1,000,000 13.9 -> 14.4
 //   d >= 128 is never slower: d = 128, g = 16 115 MB 34.4 -> 30.3, 210 MB 52 -> 50; d = 192 (the matrix cores' rate) 200 MB 66.7 -> 62.6,
 //     300 MB 98 -> 95
 constexpr bool srft_write_staged(int d, long long tiles, long long workgroups) {
     if (tiles <= 768) return false;
+    if (d == 32) return tiles > workgroups && tiles <= 4 * workgroups;
     if (d >= 128 || tiles <= 11 * workgroups) return true;
     return d >= 96 && tiles >= 22 * workgroups;
 }

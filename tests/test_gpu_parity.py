@@ -549,7 +549,7 @@ def test_scales_aligned_to_four_bytes_only(B, d, g, bits, off):
     plan.close()
 
 
-# Ways of the record to memory.  Plain form: from the lanes (up to 768 tiles; more than 8 tiles for each of the workgroups, which the
+# Ways of the record to memory.  Plain form: from the lanes (up to 768 tiles; by the tiles for each of the workgroups, which the
 # cap sets), through LDS otherwise; the folded forms through LDS (one and several tiles a workgroup).  A vector's record is the same whichever
 # way it went: the launches of one size each are compared with each other, bit for bit, and nothing behind the last vector is written.
 @pytest.mark.parametrize("d,g,bits,transform", [
@@ -561,7 +561,7 @@ def test_a_record_is_the_same_whichever_way_it_is_stored(B, d, g, bits, transfor
     plan = B.Plan(d, g, 77, W.lognormal_lambda(d, seed=d), bits=bits, transform=transform)
     x = (torch.randn(n, d, device="cuda", generator=torch.Generator("cuda").manual_seed(d)) * 2).to(torch.float16)
     records, views = [], []
-    for cap in (0, 70, 69, 30):                              # workgroups: as many as fit, then 11, 12 and 26 tiles for each
+    for cap in (0, 200, 70, 69, 30):                         # workgroups: as many as fit, then 4, 11, 12 and 26 tiles for each
         B.srft_plan_set_max_workgroups(plan.handle, cap)
         c = torch.full((n + 8, d * bits // 8), 99, dtype=torch.uint8, device="cuda")
         s = torch.full((n + 8, d // g), 99.0, device="cuda")
