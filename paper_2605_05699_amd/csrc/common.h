@@ -222,15 +222,15 @@ struct srft_cache {
 //     MB 38.6 -> 46; d = 64 122 MB 26.5 -> 27.5, 176 MB 37 -> 40
 //   beyond whole rows help again, except the shortest: d = 96 330 MB 66.4 -> 63.6, 505 MB 100 -> 92.8; d = 64 322 MB 62 -> 65.6, g = 16 563
 //     MB 112.3 -> 114.4
-//   d = 32, with a vector in half a line, gains between 1 and 4 tiles for each of 4096 workgroups: 190,000 vectors 4.2 -> 3.9, 400,000 7.0
-//     -> 6.7; 36 plans x 1494 2.75 -> 3.1, 1,000,000 13.9 -> 14.4
-//   d >= 128 is never slower: d = 128, g = 16 115 MB 34.4 -> 30.3, 210 MB 52 -> 50; d = 192 (the matrix cores' rate) 200 MB 66.7 -> 62.6,
-//     300 MB 98 -> 95
+//   d = 128 (g = 16, Walsh-Hadamard) is never slower: g = 16 115 MB 34.4 -> 30.3, 10 plans x 67,517 57.5 -> 54
+//   d >= 160 is at the matrix cores' rate beyond 16 tiles a workgroup, and no way is the faster one there (10 plans x 67,517 d = 160 89.5 ->
+//     91.5, d = 224 132 -> 135, d = 192 111 -> 112); before, d = 192 10 plans x 20,000 34.9 -> 33.2
+//   d = 32, with a vector in an eighth of a line, gains on single plans and loses on several: 400,000 vectors 7.0 -> 6.65, 7 plans x 51,556
+//     6.8 -> 7.9, 36 x 1494 2.75 -> 3.1, 1,000,000 13.9 -> 14.4: never
 constexpr bool srft_write_staged(int d, long long tiles, long long workgroups) {
-    if (tiles <= 768) return false;
-    if (d == 32) return tiles > workgroups && tiles <= 4 * workgroups;
-    if (d >= 128 || tiles <= 11 * workgroups) return true;
-    return d >= 96 && tiles >= 22 * workgroups;
+    if (d == 32 || tiles <= 768) return false;
+    if (d == 128 || tiles <= (d >= 160 ? 16 : 11) * workgroups) return true;
+    return d == 96 && tiles >= 22 * workgroups;
 }
 quantize_kernel_t srft_pick_quantize_plain_b4(int d, int gm, bool staged);
 quantize_kernel_t srft_pick_quantize_plain_b8(int d, int gm, bool staged);

@@ -5,7 +5,7 @@ namespace {
 template <int D, int S, int GM, int BITS>
 flush_kernels_t kernels() {
     constexpr int NT = 2 * D / S, KS = GM == kGroup16 ? 1 : 2;
-    const auto alone = srft_cache_flush_kernel<D, NT, srft_flush_write_plain<D, S, GM, BITS, true>, srft_flush_read_later>;
+    const auto alone = srft_cache_flush_kernel<D, NT, srft_flush_write_plain<D, S, GM, BITS, D != 32>, srft_flush_read_later>;
     if constexpr (D <= 128)
         return {alone, srft_cache_flush_kernel<D, NT, srft_flush_write_plain<D, S, GM, BITS, false>, srft_flush_read_plain<D, S, KS, BITS>>};
     else

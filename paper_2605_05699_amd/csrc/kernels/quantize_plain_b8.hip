@@ -13,7 +13,7 @@ quantize_kernel_t by_group_mode(int gm) {
 template <int D>
 quantize_kernel_t pick(int gm, bool staged) {
     constexpr int S = D == 64 ? 2 : 1;
-    return staged ? by_group_mode<D, S, true>(gm) : by_group_mode<D, S, false>(gm);
+    return staged ? by_group_mode<D, S, D != 32>(gm) : by_group_mode<D, S, false>(gm);      // (d = 32: srft_write_staged)
 }
 template <int D, int S, bool STAGED>
 batched_kernels_t batched_by_group_mode(int gm) {
@@ -24,7 +24,7 @@ batched_kernels_t batched_by_group_mode(int gm) {
 template <int D>
 batched_kernels_t pick_batched(int gm, bool staged) {
     constexpr int S = D == 64 ? 2 : 1;
-    return staged ? batched_by_group_mode<D, S, true>(gm) : batched_by_group_mode<D, S, false>(gm);
+    return staged ? batched_by_group_mode<D, S, D != 32>(gm) : batched_by_group_mode<D, S, false>(gm);      // (d = 32: srft_write_staged)
 }
 }  // namespace
 
