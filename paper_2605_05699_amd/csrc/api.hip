@@ -24,7 +24,10 @@ int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* cod
                     int out, hipStream_t st) {
     const long long n_tiles = (n + kTileVecs - 1) / kTileVecs;
     const int teams = out == kOutAmax ? srft_plan_amax_teams(p, n_tiles) : 1;
-    long long grid = p->max_wgs > 0 ? p->max_wgs : out == kOutAmax ? amax_grid(p, n_tiles, teams) : out == kOutCodes ? srft_plan_write_grid(p, n_tiles) : p->grid_q;
+    long long grid = out == kOutCodes ? srft_plan_write_grid(p, n_tiles)
+                     : p->max_wgs > 0 ? p->max_wgs
+                     : out == kOutAmax ? amax_grid(p, n_tiles, teams)
+                                       : p->grid_q;
     grid = std::min(grid, (n_tiles + teams - 1) / teams);    // no workgroup without a tile
     int threads = 0;
     const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads, n_tiles);
@@ -90,8 +93,8 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
     srft_share shares[kMaxBatch];
     int next = 0;
     const long long all = std::accumulate(tiles, tiles + count, 0LL);
-    const int n = srft_share_out(tiles, count, write_path ? srft_plan_write_grid(p, all) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq, shares,
-                                 kMaxBatch, &next);
+    const long long budget = write_path ? srft_plan_write_grid(p, all) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
+    const int n = srft_share_out(tiles, count, budget, shares, kMaxBatch, &next);
     srft_batch_many cut;
     if (n > count)
         for (int i = 0; i < n; ++i) cut.seg[i] = segment_part(p, write_path, whole.seg[shares[i].segment], shares[i]);
@@ -127,7 +130,8 @@ bool even_batch(const srft_plan_t* const* plans, const void* const* in, void* co
         !srft_even_step(scales, count, &a->scales_step))
         return false;
     const srft_plan* p = plans[0];
-    const long long tiles = (n_vec[0] + kTileVecs - 1) / kTileVecs, budget = write_path ? srft_plan_write_grid(p, tiles * count) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
+    const long long tiles = (n_vec[0] + kTileVecs - 1) / kTileVecs;
+    const long long budget = write_path ? srft_plan_write_grid(p, tiles * count) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
     const int blocks = srft_even_blocks(tiles, count, budget);
     if (blocks == 0) return false;
     a->shape = srft_even_spread(tiles, count, write_path ? (long long)blocks * count : budget, blocks);

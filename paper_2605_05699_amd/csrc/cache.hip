@@ -13,7 +13,8 @@ namespace {
 // (slot0 + j) % R.  One thread per unit, blockIdx.y the plan, blockIdx.z the first sequence.  A decode step moves a few
 // kilobytes, so the launch is all there is: 32-bit index arithmetic (one token of 2 sequences x 56 plans: 2.9 -> 2.3 us on the
 // device) and no table of addresses where they lie a constant step apart (72 bytes of arguments against 1 KB: 3.0 against 4.2 us
-// of the host; a prompt of 1000 tokens and 24 steps over 56 plans, with the conversions' launches, 151 -> 135 us).  A prompt is a
+// of the host; a prompt of 1000 tokens and 24 steps over 56 plans, with the conversions' launches, 151 -> 135 us; 85 to
+// 97 with a flush of its own, see cache_flush.h).  A prompt is a
 // copy at 4.7 TB/s.
 struct scatter_args {
     const uint4* in[kMaxBatch];
@@ -203,8 +204,8 @@ int srft_cache_append(srft_cache_t* cache, const void* const* new_f16_dev, int t
             if (rc != SRFT_OK) return rc;
         }
     cache->tokens += t;
-    // 2. (buffers that do not lie a constant step apart) every window that is now full is quantized into the store and replaced, in the view, by what the store
-    //    decodes to (the window is "re-quantized when full"; the dequantized prefix is refreshed only here)
+    // 2. (where cache_flush does not apply) every window that is now full is quantized into the store and replaced, in the view, by
+    //    what the store decodes to (the window is "re-quantized when full"; the dequantized prefix is refreshed only here)
     if (full > cache->quantized) {
         const int rc = srft_no_throw([&] { return cache_convert(cache, cache->quantized, full - cache->quantized, true, st); });
         if (rc != SRFT_OK) return rc;
