@@ -37,9 +37,11 @@ template <int POLICY = kStoreThroughOnce>
 __device__ __forceinline__ void stream_store(float* base, unsigned at, float v, bool there = true) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), stream_rows(base), there ? (int)(at * 4) : (int)0x80000000, 0, POLICY);
 }
-// ... at any address of four-byte alignment.  (The compiler does not count this store: its waits for loads then include it.)
+// ... at any address of four-byte alignment.  The data registers of a store of more than 8 bytes must not be written again by a
+// vector instruction within two wait states.  The compiler keeps to that behind its own stores and does not see into this one, so the
+// wait states stand with it.  (Nor does it count the store: its waits for loads then include it.)
 __device__ __forceinline__ void stream_store_at(float* p, floatx4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 // Non-temporal loads help where one load instruction covers whole cache lines (the read path's code units) and cost up to 20 %
 // where several loads of a lane share a line (the folded write paths, whose lanes read 32 or 64 contiguous bytes), so those loads
