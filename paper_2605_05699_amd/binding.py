@@ -46,6 +46,23 @@ class SrftError(RuntimeError):
         super().__init__(f"{where}: {msg} (status {status})")
 
 
+def _native_append(L: C.CDLL) -> None:
+    """L.srft_cache_append stays a ctypes function, with calls that are marshalled in native code as long as nothing is set on it."""
+    plain = L.srft_cache_append
+
+    class Function(L._FuncPtr):
+        _flags_, _restype_ = L._FuncPtr._flags_, L._FuncPtr._restype_
+
+        def __setattr__(self, name, value):            # argtypes, restype, errcheck: from here on ctypes makes the calls
+            Function.__call__ = L._FuncPtr.__call__
+            L._FuncPtr.__setattr__(self, name, value)
+
+    native = Function((plain.__name__, L))
+    native.argtypes, native.restype, native.__name__ = plain.argtypes, plain.restype, plain.__name__
+    Function.__call__ = _marshal.append(L._FuncPtr.__call__.__get__(native), C.c_void_p, C.Array)
+    L.srft_cache_append = native
+
+
 def lib() -> C.CDLL:
     """Load the library (once).  Raises if it has not been built."""
     global _lib
@@ -104,7 +121,7 @@ def lib() -> C.CDLL:
             "srft_kv_quantize", "srft_kv_dequantize", "srft_kv_quantize_batched", "srft_kv_dequantize_batched", "srft_kv_scores",
             "srft_kv_decode_attention", "srft_kv_channel_absmax", "srft_cache_append", "srft_scores_workspace_bytes",
             "srft_decode_attention_workspace_bytes", "srft_plan_d")])
-        L.srft_cache_append = _marshal.append(L.srft_cache_append, vp, C.Array)
+        _native_append(L)
     _lib = L
     return L
 

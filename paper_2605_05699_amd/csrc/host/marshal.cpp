@@ -198,14 +198,9 @@ PyObject* absmax(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// ---- lib().srft_cache_append: called like the ctypes function that it stands in front of, which takes the calls whose arguments
-// are anything else than None, ints, c_void_p and arrays of them, and answers for its attributes
-struct Append {
-    PyObject_HEAD
-    vectorcallfunc call;
-    PyObject *function, *pointer, *array;                    // the ctypes function; ctypes.c_void_p and ctypes.Array
-};
-bool pointer_of(const Append* self, PyObject* o, void** p) {
+// ---- lib().srft_cache_append, a ctypes function whose calls come here first: those with other arguments than None, ints, c_void_p and
+// arrays of them go on to ctypes
+bool pointer_of(PyObject* o, PyObject* cell_type, PyObject* array_type, void** p) {
     if (o == Py_None) {
         *p = nullptr;
         return true;
@@ -215,59 +210,37 @@ bool pointer_of(const Append* self, PyObject* o, void** p) {
         *p = const_cast<void*>(v);
         return true;
     }
-    const bool cell = (PyObject*)Py_TYPE(o) == self->pointer;
-    if (!cell && !PyObject_TypeCheck(o, (PyTypeObject*)self->array)) return false;
+    const bool cell = (PyObject*)Py_TYPE(o) == cell_type;
+    if (!cell && !PyObject_TypeCheck(o, (PyTypeObject*)array_type)) return false;
     void* at;
     if (!address_of(o, &at)) return false;
     if (cell) std::memcpy(p, at, sizeof(*p));
     else *p = at;
     return true;
 }
-PyObject* append_call(PyObject* o, PyObject* const* a, size_t nf, PyObject* names) {
-    const Append* self = (const Append*)o;
+PyObject* append_call(PyObject* self, PyObject* const* a, Py_ssize_t n, PyObject* names) {
+    PyObject *const ctypes_call = PyTuple_GET_ITEM(self, 0), *const cell = PyTuple_GET_ITEM(self, 1), *const array = PyTuple_GET_ITEM(self, 2);
     void *cache, *fresh, *st;
-    if (PyVectorcall_NARGS(nf) == 4 && !names && g.bound && pointer_of(self, a[0], &cache) && pointer_of(self, a[1], &fresh) &&
-        PyLong_CheckExact(a[2]) && pointer_of(self, a[3], &st)) {
+    if (n == 4 && !names && g.bound && pointer_of(a[0], cell, array, &cache) && pointer_of(a[1], cell, array, &fresh) && PyLong_CheckExact(a[2]) &&
+        pointer_of(a[3], cell, array, &st)) {
         int overflow;
         const long t = PyLong_AsLongAndOverflow(a[2], &overflow);
         if (!overflow && t == (int)t) return PyLong_FromLong(without_gil([&] { return g.append(cache, fresh, (int)t, st); }));
     }
-    return PyObject_Vectorcall(self->function, a, nf, names);
+    return PyObject_Vectorcall(ctypes_call, a, n, names);
 }
-PyObject* append_getattr(PyObject* o, PyObject* name) { return PyObject_GetAttr(((Append*)o)->function, name); }
-int append_setattr(PyObject* o, PyObject* name, PyObject* v) { return PyObject_SetAttr(((Append*)o)->function, name, v); }
-void append_free(PyObject* o) {
-    Append* self = (Append*)o;
-    Py_XDECREF(self->function);
-    Py_XDECREF(self->pointer);
-    Py_XDECREF(self->array);
-    Py_TYPE(o)->tp_free(o);
-}
-PyTypeObject append_type = [] {
-    PyTypeObject t = {PyVarObject_HEAD_INIT(nullptr, 0)};
-    t.tp_name = "_marshal.Append";
-    t.tp_basicsize = sizeof(Append);
-    t.tp_dealloc = append_free;
-    t.tp_vectorcall_offset = offsetof(Append, call);
-    t.tp_call = PyVectorcall_Call;
-    t.tp_getattro = append_getattr;
-    t.tp_setattro = append_setattr;
-    t.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL;
-    return t;
-}();
-// append(function, c_void_p, Array) -> the callable
+PyMethodDef append_method = {"srft_cache_append", (PyCFunction)(void (*)(void))append_call, METH_FASTCALL | METH_KEYWORDS, nullptr};
+// append(the call by way of ctypes, c_void_p, Array) -> the callable
 PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 3 || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
-        PyErr_SetString(PyExc_TypeError, "append(function, c_void_p, Array)");
+        PyErr_SetString(PyExc_TypeError, "append(call, c_void_p, Array)");
         return nullptr;
     }
-    Append* self = PyObject_New(Append, &append_type);
+    PyObject* const self = PyTuple_Pack(3, a[0], a[1], a[2]);
     if (!self) return nullptr;
-    self->call = append_call;
-    self->function = Py_NewRef(a[0]);
-    self->pointer = Py_NewRef(a[1]);
-    self->array = Py_NewRef(a[2]);
-    return (PyObject*)self;
+    PyObject* const r = PyCFunction_New(&append_method, self);
+    Py_DECREF(self);
+    return r;
 }
 
 // bind(addresses): of the entry points, in the order of the struct above
@@ -301,7 +274,6 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 }  // namespace
 
 PyMODINIT_FUNC PyInit__marshal(void) {
-    if (PyType_Ready(&append_type) < 0) return nullptr;
     struct { PyObject** at; const char* name; } const names[] = {{&s_plans, "plans"}, {&s_big, "big"}, {&s_codes, "codes"}, {&s_scales, "scales"}, {&s_n_vec, "n_vec"}, {&s_count, "count"}};
     for (const auto& e : names)
         if (!(*e.at = PyUnicode_InternFromString(e.name))) return nullptr;

@@ -1,5 +1,6 @@
 """The native marshalling (csrc/host/marshal.cpp) against the calls through ctypes that it stands in front of."""
 import ctypes as C
+import importlib.util
 
 import numpy as np
 import pytest
@@ -29,6 +30,28 @@ def test_append_takes_what_ctypes_takes():
                 got.append(type(e))
         assert got[0] == got[1], (args, got)
     assert native.restype is C.c_int and native.argtypes == plain.argtypes
+
+
+def test_append_is_a_ctypes_function():
+    native, plain = B.lib().srft_cache_append, C.CDLL(B.LIB_PATH).srft_cache_append
+    assert C.cast(native, C.c_void_p).value == C.cast(plain, C.c_void_p).value
+    assert isinstance(native, C._CFuncPtr) and C.sizeof(native) == C.sizeof(plain) and C.addressof(native) and bool(native)
+    assert C.c_void_p.from_param(native) is not None and C.byref(native) is not None
+
+
+def test_what_is_set_on_append_holds_for_its_calls():
+    spec = importlib.util.spec_from_file_location(B.__package__ + ".binding_of_its_own", B.__file__)
+    own = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(own)
+    f = own.lib().srft_cache_append
+    assert f(None, None, 1, None) == -1
+    f.errcheck = lambda rc, function, args: (rc, function is f, args[2])
+    assert f(None, None, 1, None) == (-1, True, 1)
+    f.argtypes = [C.c_void_p, C.c_void_p, C.c_double, C.c_void_p]
+    assert f(None, None, 1.5, None)[2] == 1.5
+    del f.errcheck
+    assert f(None, None, 1.5, None) == -1
+    assert B.lib().srft_cache_append(None, None, 1, None) == -1                       # (another library object's is as it was)
 
 
 @pytest.mark.parametrize("args", [("quantize", 4), ("dequantize", 4), ("scores", 6), ("attention", 10), ("absmax", 3)])
