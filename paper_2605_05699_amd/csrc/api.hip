@@ -30,7 +30,7 @@ int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* cod
                                        : p->grid_q;
     grid = std::min(grid, (n_tiles + teams - 1) / teams);    // no workgroup without a tile
     int threads = 0;
-    const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads, n_tiles);
+    const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads, n_tiles, srft_aligned(codes, 64));
     if (!kernel) return SRFT_ERR_BAD_D;
     const bool fold4 = out == kOutCodes ? p->fold4_q : out == kOutAmax && p->wfold4;
     const bool fold = p->fold_q && (out == kOutCodes || out == kOutAmax);
@@ -63,15 +63,16 @@ srft_segment segment_part(const srft_plan* p, bool write_path, const srft_segmen
     return s;
 }
 
-// The kernels of a plan's batched launches, and their block size.
-batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long tiles, int* threads) {
+// The kernels of a plan's batched launches, and their block size.  tiles: of the launch; lines: its results start at multiples of 64
+// bytes.
+batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long tiles, bool lines, int* threads) {
     if (write_path && p->fold4_q) {
         *threads = 256;
         return srft_pick_quantize_fold4_batched(p->bits, p->gm);
     }
     if (write_path && p->fold_q) {
         *threads = p->d;
-        return srft_pick_quantize_fold_batched(p->d, p->bits, p->gm == kGroupWide);
+        return srft_pick_quantize_fold_batched(p->d, p->bits, p->gm == kGroupWide, srft_plan_fold_through(p, tiles, lines));
     }
     if (write_path) {
         *threads = 2 * p->d / p->slabs_q;
@@ -87,7 +88,7 @@ batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long
 }
 
 // One batched launch over the first `count` segments of the table, which is complete except for the workgroups.
-int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool write_path, hipStream_t st) {
+int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool write_path, bool lines, hipStream_t st) {
     long long tiles[kMaxBatch];
     for (int i = 0; i < count; ++i) tiles[i] = (whole.seg[i].n_vec + kTileVecs - 1) / kTileVecs;
     srft_share shares[kMaxBatch];
@@ -105,7 +106,7 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
     }
     for (int i = n; i < kMaxBatch; ++i) a.first_block[i] = INT32_MAX;
     int threads = 0;
-    const batched_kernels_t kernel = batched_kernels(p, write_path, all, &threads);
+    const batched_kernels_t kernel = batched_kernels(p, write_path, all, lines, &threads);
     if (!kernel.many) return SRFT_ERR_BAD_D;
     if (n <= kFewBatch) {
         srft_batch_few few;
@@ -152,6 +153,7 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
     if (count < 0) return SRFT_ERR_BAD_N;
     if (count == 0) return SRFT_OK;
     if (!plans || !in0 || !out0 || !n_vec || (write_path ? !out1 : !in1)) return SRFT_ERR_NULL;
+    bool lines = true;
     // validate everything before the first launch: a bad segment must not leave half a batch enqueued
     for (int i = 0; i < count; ++i) {
         if (!plans[i]) return SRFT_ERR_NULL;
@@ -161,12 +163,13 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
         const void* small = write_path ? (const void*)out1[i] : in1[i];       // the scales
         if (!in0[i] || !out0[i] || !small) return SRFT_ERR_NULL;
         if (!srft_aligned(in0[i], 16) || !srft_aligned(out0[i], 16) || !srft_aligned(small, 4)) return SRFT_ERR_ALIGN;
+        lines &= srft_aligned(out0[i], 64);
     }
     srft_batch_even even;
     if (even_batch(plans, in0, out0, write_path ? (const void* const*)out1 : in1, n_vec, count, write_path, &even)) {
         int threads = 0;
         const long long tiles = (even.n_vec + kTileVecs - 1) / kTileVecs * count;
-        const batched_kernels_t kernel = batched_kernels(plans[0], write_path, tiles, &threads);
+        const batched_kernels_t kernel = batched_kernels(plans[0], write_path, tiles, lines, &threads);
         if (!kernel.even) return SRFT_ERR_BAD_D;
         return srft_launch(kernel.even, dim3((unsigned)srft_even_grid(even.shape, count)), threads, st, even, plans[0]->gw);
     }
@@ -183,7 +186,7 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
             s.unscale = write_path ? plans[i]->unscale_w : srft_plan_read_unscale(plans[i]);
         }
         if (k == kMaxBatch || (i == count && k > 0)) {
-            const int rc = launch_batched(plans[0], a, k, write_path, st);
+            const int rc = launch_batched(plans[0], a, k, write_path, lines, st);
             if (rc != SRFT_OK) return rc;
             k = 0;
         }

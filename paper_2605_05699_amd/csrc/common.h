@@ -239,7 +239,7 @@ batched_kernels_t srft_pick_quantize_plain_batched_b8(int d, int gm, bool staged
 // write path, plain form, other outputs (kOutRaw, kOutAmax)
 quantize_kernel_t srft_pick_quantize_aux(int d, int slabs, int out, int teams);
 // write path, folded form (d = 128, 256)
-quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide);
+quantize_kernel_t srft_pick_quantize_fold(int d, int bits, bool wide, bool through);
 // Teams of wavefronts per workgroup of the abs-max statistic, by head dimension, form of the write path (0 plain, 1 once, 2
 // twice folded) and tiles.  Teams leave fewer workgroups, up to one per compute unit, that update the statistic's cache lines one
 // after the other; but they start later (each with its matrix), share their barriers, and a call of few tiles wants them on
@@ -267,7 +267,7 @@ constexpr int srft_amax_teams(int d, int form, long long tiles) {
     return 1;
 }
 quantize_kernel_t srft_pick_quantize_fold_amax(int teams);  // the abs-max statistic through the once-folded contraction (d = 128)
-batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide);
+batched_kernels_t srft_pick_quantize_fold_batched(int d, int bits, bool wide, bool through);
 // write path, folded twice (d = 256; g = 16, 32 and 256); the abs-max statistic; the size of its table in 16-byte units
 quantize_kernel_t srft_pick_quantize_fold4(int bits, int gm);
 quantize_kernel_t srft_pick_quantize_fold4_amax(int teams);
@@ -339,11 +339,19 @@ int srft_launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t st, co
 }
 
 // the kernels a plan launches, and their block sizes
-quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles = 0);
+// (tiles: of the launch; lines: its codes start at multiples of 64 bytes)
+quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles = 0, bool lines = true);
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads);
 // the tables and the matrix scaling the kernels of a plan take
 inline int srft_plan_amax_teams(const srft_plan* p, long long n_tiles) {
     return srft_amax_teams(p->d, p->wfold4 ? 2 : p->fold_q ? 1 : 0, n_tiles);
+}
+// the bytes of this many tiles, fp16 vectors and record
+inline long long srft_plan_bytes(const srft_plan* p, long long tiles) {
+    return tiles * kTileVecs * (2LL * p->d + p->d * p->bits / 8 + 4 * (p->d / p->g));
+}
+inline bool srft_plan_fold_through(const srft_plan* p, long long tiles, bool lines) {
+    return srft_fold_through(p->d, p->bits, lines, srft_plan_bytes(p, tiles));
 }
 // the way of the record of a launch of the write path over this many tiles, and the most workgroups of that launch
 inline bool srft_plan_staged(const srft_plan* p, long long tiles) {

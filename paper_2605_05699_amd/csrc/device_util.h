@@ -37,6 +37,12 @@ template <int POLICY = kStoreThroughOnce>
 __device__ __forceinline__ void stream_store(float* base, unsigned at, float v, bool there = true) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), stream_rows(base), there ? (int)(at * 4) : (int)0x80000000, 0, POLICY);
 }
+// A row's piece written through, or left to the L2 (nt alone).
+template <bool THROUGH, class T>
+__device__ __forceinline__ void store_row(T* base, unsigned at, uint4 v) {
+    if constexpr (THROUGH) stream_store(base, at, v);
+    else __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(base + at));
+}
 // ... at any address of four-byte alignment.  The data registers of a store of more than 8 bytes must not be written again by a
 // vector instruction within two wait states.  The compiler keeps to that behind its own stores and does not see into this one, so the
 // wait states stand with it.  (Nor does it count the store: its waits for loads then include it.)

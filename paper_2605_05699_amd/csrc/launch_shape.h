@@ -114,6 +114,20 @@ constexpr bool srft_flush_fits(long long n_vec, long long page_rows, long long n
 // (d = 256, g = 16, 52 plans: two launches -> one, a page of 8 sequences and a step 12.3 -> 11.1 us.)
 constexpr int srft_flush_whole_tiles(int d, int g) { return d == 128 && g == 16 ? 1 : d == 256 || d == 32 ? 4 : 8; }
 
+// Whether the once-folded write path (d = 128; d = 256 with g = 64 and 128) writes its record through to memory or leaves it to the
+// L2 (device_util.h), by the bytes of a launch, in and out.  Written through, nothing is left to write back at the end, which is what a
+// short launch takes longest over; a long one loses a little by it.  Left to the L2 -> written through, in turn over one / three / six
+// sets of buffers (the memory-side cache holds 256 MB):
+//   d = 128   11 MB 0.91 / 0.94 / 0.96   30 MB 0.95 / 0.96 / 0.96   50 MB 0.95 / 0.98 / 0.97   60 MB 0.98 / 1.00 / 0.98   80 MB 0.98 /
+//     1.02 / 1.01   154 MB 1.00 / 1.01 / 1.02   300 MB 0.99 / 1.03 / 1.02   1 GB 1.01; 56 x 8192 (154 MB) 39.7 -> 40.5 us
+//   d = 256   20 MB 0.98 / 0.98 / 0.98   100 MB 0.99 / 0.99 / 1.00   160 MB 0.97 / 0.98 / 0.98   250 MB 1.02 / 1.00 / 1.02   350 MB 1.02 /
+//     1.01 / 1.02
+// lines: the record starts at a multiple of 64 bytes.  Where it does not, 8-bit rows at d = 128 reach memory as partial lines (16 bytes
+// into a line, 33 MB 1.04, 88 MB 1.05, 300 MB 1.05); 4-bit rows and d = 256 do not mind (d = 128, 33 MB 0.96; d = 256, 8 bits, 20 MB 0.97).
+constexpr bool srft_fold_through(int d, int bits, bool lines, long long bytes) {
+    return (lines || bits == 4 || d == 256) && bytes <= (d == 128 ? 60000000 : 200000000);
+}
+
 // True when count addresses lie a constant step apart; *step is that step in bytes (0 for one).
 inline bool srft_even_step(const void* const* p, int count, long long* step) {
     *step = count > 1 ? (long long)((uintptr_t)p[1] - (uintptr_t)p[0]) : 0;

@@ -355,7 +355,7 @@ int srft_hip_fail(hipError_t e) {
     return SRFT_ERR_HIP;
 }
 
-quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles) {
+quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles, bool lines) {
     const int teams = out == kOutAmax ? srft_plan_amax_teams(p, n_tiles) : 1;
     if (out == kOutAmax && (p->wfold4 || p->fold_q)) {   // the statistic does not depend on the groups: folded wherever a table exists
         *threads = p->d * teams;
@@ -371,7 +371,7 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
     }
     if (p->fold_q) {
         *threads = p->d;
-        return srft_pick_quantize_fold(p->d, p->bits, p->gm == kGroupWide);
+        return srft_pick_quantize_fold(p->d, p->bits, p->gm == kGroupWide, srft_plan_fold_through(p, n_tiles, lines));
     }
     *threads = 2 * p->d / p->slabs_q;
     const bool staged = srft_plan_staged(p, n_tiles);

@@ -53,7 +53,8 @@
 // SUB: teams of M wavefronts per workgroup, each with tiles of its own (t0 + team, and stride counts tiles of all teams);
 //       they share the barriers and, at the end, one update of the statistic (AMAX).  All of them walk as many tiles as the
 //       first: past the end a team sees the last tile again, which a maximum does not mind.
-template <int D, int BITS, bool WIDE, bool AMAX = false, int SUB = 1, class ROWS = srft_rows_dense>
+// THROUGH: the record is written through to memory (srft_fold_through).
+template <int D, int BITS, bool WIDE, bool AMAX = false, int SUB = 1, class ROWS = srft_rows_dense, bool THROUGH = true>
 __device__ __forceinline__ void
 srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restrict__ x, long long n_vec,
                          uint2* __restrict__ codes, float* __restrict__ scales, float unscale, float scale_mul,
@@ -315,11 +316,14 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
             for (int i = 0; i < kTileVecs * PIECES / NT; ++i) {
                 const int u = tid + i * NT, r = u / PIECES, pc = u % PIECES;
                 const uint2 lo = cstage[b][r * CROW + 2 * pc], hi = cstage[b][r * CROW + 2 * pc + 1];
-                stream_store<kStoreThroughOnce>(cbase, (unsigned)(min(r, lim) * PIECES + pc), make_uint4(lo.x, lo.y, hi.x, hi.y));
+                store_row<THROUGH>(cbase, (unsigned)(min(r, lim) * PIECES + pc), make_uint4(lo.x, lo.y, hi.x, hi.y));
             }
             const int ns = WIDE ? G / gw : G;            // 32 ns floats, next to each other in memory
-            if (tid < kTileVecs * ns)
-                stream_store<kStoreThrough>(scales + row0 * ns, (unsigned)(min(tid / ns, lim) * ns + tid % ns), sstage[b][tid]);
+            if (tid < kTileVecs * ns) {
+                const unsigned at = min(tid / ns, lim) * ns + tid % ns;
+                if constexpr (THROUGH) stream_store<kStoreThrough>(scales + row0 * ns, at, sstage[b][tid]);
+                else (scales + row0 * ns)[at] = sstage[b][tid];
+            }
         }
     };
 
@@ -474,14 +478,15 @@ srft_quantize_fold_tiles(const uint4* __restrict__ wfold, const uint4* __restric
 }
 
 // two wavefronts per SIMD (8 per compute unit): the register allocator is told to stay within 256 VGPRs
-template <int D, int BITS, bool WIDE>
+template <int D, int BITS, bool WIDE, bool THROUGH>
 __global__ void __launch_bounds__(D, (D >= 256 ? SRFT_QF_WG_PER_CU_256 : 2))
 srft_quantize_fold_kernel(const uint4* __restrict__ wfold, const uint4* __restrict__ x, long long n_vec,
                           uint2* __restrict__ codes, float* __restrict__ scales, float4* __restrict__,
                           float unscale, float scale_mul, int gw) {
     int t0, stride, t_end;
     if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
-    srft_quantize_fold_tiles<D, BITS, WIDE>(wfold, x, n_vec, codes, scales, unscale, scale_mul, gw, t0, stride, t_end);
+    srft_quantize_fold_tiles<D, BITS, WIDE, false, 1, srft_rows_dense, THROUGH>(wfold, x, n_vec, codes, scales, unscale, scale_mul, gw, t0,
+                                                                                stride, t_end);
 }
 
 // the abs-max statistic through the folded contraction: amax is float[d] read as unsigned, updated with atomic maxima
@@ -496,13 +501,13 @@ srft_quantize_fold_amax_kernel(const uint4* __restrict__ wfold, const uint4* __r
                                                      gridDim.x * SUB, n_tiles, reinterpret_cast<unsigned int*>(amax));
 }
 
-template <int D, int BITS, bool WIDE, int N>
+template <int D, int BITS, bool WIDE, bool THROUGH, int N>
 __global__ void __launch_bounds__(D, (D >= 256 ? SRFT_QF_WG_PER_CU_256 : 2))
 srft_quantize_fold_batched_kernel(const srft_batch<N> a, int gw) {
     const srft_work s = srft_work_of_block<true>(a);
-    srft_quantize_fold_tiles<D, BITS, WIDE>(s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales,
-                                            s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, s.place, s.blocks,
-                                            (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
+    srft_quantize_fold_tiles<D, BITS, WIDE, false, 1, srft_rows_dense, THROUGH>(
+        s.frag, (const uint4*)s.in, s.n_vec, (uint2*)s.out, s.scales, s.unscale, s.unscale / (BITS == 8 ? 127.0f : 7.0f), gw, s.place, s.blocks,
+        (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 
 #endif  // SRFT_QUANTIZE_FOLD_TILES_H

@@ -582,3 +582,53 @@ def test_a_record_is_the_same_whichever_way_it_is_stored(B, d, g, bits, transfor
     for v in views[1:]:
         assert torch.equal(v.view(torch.int16), views[0].view(torch.int16))
     plan.close()
+
+
+# ... and by a launch's size and the place its results start at (16, 48 and 64 bytes into a line), alone, as plans a constant step
+# apart and as a table of ragged parts: `many` lies beyond the last size that is written through.  Compared with short launches into
+# buffers of their own.
+WAYS = [(128, 32, 4, "dft", 180_000), (128, 32, 8, "dft", 152_000), (128, 128, 4, "dft", 186_000), (256, 64, 4, "dft", 306_000), (256, 128, 8, "dft", 252_000)]
+
+
+@pytest.mark.parametrize("d,g,bits,transform,many", WAYS)
+@pytest.mark.parametrize("few", [False, True])
+def test_results_are_the_same_whatever_their_size_and_place(B, d, g, bits, transform, many, few):
+    n, step = (26_001 if few else many) + 7, 16_000
+    plan = B.Plan(d, g, 78, W.lognormal_lambda(d, seed=d), bits=bits, transform=transform)
+    x = (torch.randn(n, d, device="cuda", generator=torch.Generator("cuda").manual_seed(d)) * 2).to(torch.float16)
+    row, ns = d * bits // 8, d // g
+    want = [torch.empty(n, row, dtype=torch.uint8, device="cuda"), torch.empty(n, ns, device="cuda"), torch.empty(n, d, dtype=torch.float16, device="cuda")]
+    for i in range(0, n, step):
+        c, s = plan.quantize(x[i:i + step])
+        want[0][i:i + step], want[1][i:i + step], want[2][i:i + step] = c, s, plan.dequantize(c, s)
+
+    def room(rows, width, dtype, lead):
+        """rows x width values that start `lead` bytes into a line, and all of the buffer around them."""
+        size = torch.empty((), dtype=dtype).element_size()
+        flat = torch.full(((rows * width * size + 256) // size,), 9, dtype=dtype, device="cuda")
+        return flat[lead // size:lead // size + rows * width].view(rows, width), flat
+
+    def check(got, expected, flat, lead):
+        k, bits_of = lead // flat.element_size(), torch.uint8 if flat.dtype == torch.uint8 else torch.int16 if flat.dtype == torch.float16 else torch.int32
+        assert torch.equal(got.view(bits_of), expected.view(bits_of))
+        assert bool((flat[:k] == 9).all()) and bool((flat[k + got.numel():] == 9).all())
+
+    for lead in (0, 16, 48, 64):
+        c, cf = room(n, row, torch.uint8, lead)
+        s, sf = room(n, ns, torch.float32, 4 * (lead // 16))
+        v, vf = room(n, d, torch.float16, lead)
+        for parts in ([n], [n // 3] * 3, [n // 2, 0, n // 5, 1, n - n // 2 - n // 5 - 1]):
+            k = sum(parts)
+            for t in (cf, sf, vf):
+                t.fill_(9)
+            cut = [list(torch.split(t[:k], parts)) for t in (x, c, s, v)]
+            if len(parts) == 1:
+                B.srft_kv_quantize(plan.handle, cut[0][0], cut[1][0], cut[2][0])
+                B.srft_kv_dequantize(plan.handle, cut[1][0], cut[2][0], cut[3][0])
+            else:
+                B.srft_kv_quantize_batched(B.BatchTable([plan.handle] * len(parts), cut[0], cut[1], cut[2]))
+                B.srft_kv_dequantize_batched(B.BatchTable([plan.handle] * len(parts), cut[3], cut[1], cut[2]))
+            check(c[:k], want[0][:k], cf, lead)
+            check(s[:k], want[1][:k], sf, 4 * (lead // 16))
+            check(v[:k], want[2][:k], vf, lead)
+    plan.close()

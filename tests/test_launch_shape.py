@@ -30,6 +30,7 @@ extern "C" int even_step(const void* const* p, int count, long long* step) { ret
 extern "C" int flush_fits(long long n_vec, long long page_rows, long long n_seq, long long t, long long units) {
     return srft_flush_fits(n_vec, page_rows, n_seq, t, units);
 }
+extern "C" int fold_through(int d, int bits, int lines, long long bytes) { return srft_fold_through(d, bits, lines, bytes); }
 extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
 extern "C" long long copy_first(int i) { return srft_copy_first(i); }
 extern "C" unsigned copy_tokens(int i, int t) { return srft_copy_tokens(i, t); }
@@ -214,3 +215,13 @@ def test_leftover_workgroups_are_spread(lib, count, tiles, budget, each):
         seen[segment[b]] = seen.get(segment[b], 0) + 1
     assert sorted(seen) == list(range(count))
     assert all(blocks[b] == seen[segment[b]] and seen[segment[b]] in (each, each + 1) and blocks[b] <= tiles for b in range(grid))
+
+
+@pytest.mark.parametrize("d,last", [(128, 60_000_000), (256, 200_000_000)])
+def test_a_folded_record_is_written_through_where_that_is_faster(lib, d, last):
+    """Short launches; of 8-bit records at d = 128 only those that start at a multiple of 64 bytes."""
+    ll = C.c_longlong
+    for n in (80, 30_000_000, last):
+        assert [lib.fold_through(d, bits, lines, ll(n)) for bits, lines in ((4, 1), (4, 0), (8, 1), (8, 0))] == [1, 1, 1, d == 256]
+    for n in (last + 1, 56 * 8192 * 336, 1_409_286_144) if d == 128 else (last + 1, 1_409_286_144):
+        assert not any(lib.fold_through(d, bits, lines, ll(n)) for bits, lines in ((4, 1), (4, 0), (8, 1), (8, 0)))
