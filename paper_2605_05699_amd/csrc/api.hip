@@ -24,13 +24,14 @@ int launch_quantize(const srft_plan* p, const void* x, long long n, uint8_t* cod
                     int out, hipStream_t st) {
     const long long n_tiles = (n + kTileVecs - 1) / kTileVecs;
     const int teams = out == kOutAmax ? srft_plan_amax_teams(p, n_tiles) : 1;
-    long long grid = out == kOutCodes ? srft_plan_write_grid(p, n_tiles)
+    const bool lines = srft_aligned(codes, 64);
+    long long grid = out == kOutCodes ? srft_plan_write_grid(p, n_tiles, lines)
                      : p->max_wgs > 0 ? p->max_wgs
                      : out == kOutAmax ? amax_grid(p, n_tiles, teams)
                                        : p->grid_q;
     grid = std::min(grid, (n_tiles + teams - 1) / teams);    // no workgroup without a tile
     int threads = 0;
-    const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads, n_tiles, srft_aligned(codes, 64));
+    const quantize_kernel_t kernel = srft_plan_quantize_kernel(p, out, &threads, n_tiles, lines);
     if (!kernel) return SRFT_ERR_BAD_D;
     const bool fold4 = out == kOutCodes ? p->fold4_q : out == kOutAmax && p->wfold4;
     const bool fold = p->fold_q && (out == kOutCodes || out == kOutAmax);
@@ -63,7 +64,7 @@ srft_segment segment_part(const srft_plan* p, bool write_path, const srft_segmen
     return s;
 }
 
-// The kernels of a plan's batched launches, and their block size.  tiles: of the launch; lines: its results start at multiples of 64
+// The kernels of a plan's batched launches, and their block size.  tiles: of the launch; lines: results of it start at a multiple of 64
 // bytes.
 batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long tiles, bool lines, int* threads) {
     if (write_path && p->fold4_q) {
@@ -76,7 +77,7 @@ batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long
     }
     if (write_path) {
         *threads = 2 * p->d / p->slabs_q;
-        const bool staged = srft_plan_staged(p, tiles);
+        const bool staged = srft_plan_staged(p, tiles, lines);
         return p->bits == 8 ? srft_pick_quantize_plain_batched_b8(p->d, p->gm, staged) : srft_pick_quantize_plain_batched_b4(p->d, p->gm, staged);
     }
     if (p->fold4_dq) {
@@ -94,7 +95,7 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
     srft_share shares[kMaxBatch];
     int next = 0;
     const long long all = std::accumulate(tiles, tiles + count, 0LL);
-    const long long budget = write_path ? srft_plan_write_grid(p, all) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
+    const long long budget = write_path ? srft_plan_write_grid(p, all, lines) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
     const int n = srft_share_out(tiles, count, budget, shares, kMaxBatch, &next);
     srft_batch_many cut;
     if (n > count)
@@ -120,7 +121,7 @@ int launch_batched(const srft_plan* p, srft_batch_many& whole, int count, bool w
 // The whole batch as one launch without a table, where its counts are equal and its addresses and plan entries a constant step
 // apart (srft_batch_even).  False: not such a batch.
 bool even_batch(const srft_plan_t* const* plans, const void* const* in, void* const* out, const void* const* scales,
-                const int64_t* n_vec, int count, bool write_path, srft_batch_even* a) {
+                const int64_t* n_vec, int count, bool write_path, bool lines, srft_batch_even* a) {
     for (int i = 1; i < count; ++i)
         if (n_vec[i] != n_vec[0]) return false;
     if (n_vec[0] == 0 || !plans[0]->entry) return false;
@@ -132,7 +133,7 @@ bool even_batch(const srft_plan_t* const* plans, const void* const* in, void* co
         return false;
     const srft_plan* p = plans[0];
     const long long tiles = (n_vec[0] + kTileVecs - 1) / kTileVecs;
-    const long long budget = write_path ? srft_plan_write_grid(p, tiles * count) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
+    const long long budget = write_path ? srft_plan_write_grid(p, tiles * count, lines) : p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
     const int blocks = srft_even_blocks(tiles, count, budget);
     if (blocks == 0) return false;
     a->shape = srft_even_spread(tiles, count, write_path ? (long long)blocks * count : budget, blocks);
@@ -153,7 +154,7 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
     if (count < 0) return SRFT_ERR_BAD_N;
     if (count == 0) return SRFT_OK;
     if (!plans || !in0 || !out0 || !n_vec || (write_path ? !out1 : !in1)) return SRFT_ERR_NULL;
-    bool lines = true;
+    bool lines = false;
     // validate everything before the first launch: a bad segment must not leave half a batch enqueued
     for (int i = 0; i < count; ++i) {
         if (!plans[i]) return SRFT_ERR_NULL;
@@ -163,10 +164,10 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
         const void* small = write_path ? (const void*)out1[i] : in1[i];       // the scales
         if (!in0[i] || !out0[i] || !small) return SRFT_ERR_NULL;
         if (!srft_aligned(in0[i], 16) || !srft_aligned(out0[i], 16) || !srft_aligned(small, 4)) return SRFT_ERR_ALIGN;
-        lines &= srft_aligned(out0[i], 64);
+        lines |= srft_aligned(out0[i], 64);
     }
     srft_batch_even even;
-    if (even_batch(plans, in0, out0, write_path ? (const void* const*)out1 : in1, n_vec, count, write_path, &even)) {
+    if (even_batch(plans, in0, out0, write_path ? (const void* const*)out1 : in1, n_vec, count, write_path, lines, &even)) {
         int threads = 0;
         const long long tiles = (even.n_vec + kTileVecs - 1) / kTileVecs * count;
         const batched_kernels_t kernel = batched_kernels(plans[0], write_path, tiles, lines, &threads);

@@ -210,28 +210,7 @@ struct srft_cache {
 };
 
 // ---- kernel instances, one function per translation unit under kernels/ (nullptr: no such instance) ----
-// write path, plain form, codes out: d, group mode, way of the record; 4- and 8-bit codes.
-// Whether the record goes through LDS and is written through to memory (device_util.h), or is stored from the lanes, in pieces of 8
-// bytes that the L2 puts together, by the tiles of a launch and its workgroups.  us, from the lanes -> through LDS, over three sets of
-// buffers:
-//   up to one tile for each of 768 workgroups the way through LDS is only longer: d = 96, 240 vectors 2.33 -> 2.40, 17,027 3.15 -> 3.26;
-//     64 x 512 (1024 tiles) 4.56 -> 4.48
-//   up to 11 tiles a workgroup nothing is left to write back: d = 96 40,000 vectors 4.47 -> 3.99, 30 MB 9.2 -> 8.0, 110 MB 28.6 -> 26.4;
-//     d = 64 20 MB 5.65 -> 5.05, 107 MB 24.5 -> 21.4; d = 128, g = 16 10 MB 4.9 -> 3.8, 101 MB 29.1 -> 26.2
-//   from there to 200 MB the memory-side cache takes the record better from the L2, where the rows are short: d = 96 151 MB 34 -> 38.7, 180
-//     MB 38.6 -> 46; d = 64 122 MB 26.5 -> 27.5, 176 MB 37 -> 40
-//   beyond whole rows help again, except the shortest: d = 96 330 MB 66.4 -> 63.6, 505 MB 100 -> 92.8; d = 64 322 MB 62 -> 65.6, g = 16 563
-//     MB 112.3 -> 114.4
-//   d = 128 (g = 16, Walsh-Hadamard) is never slower: g = 16 115 MB 34.4 -> 30.3, 10 plans x 67,517 57.5 -> 54
-//   d >= 160 is at the matrix cores' rate beyond 16 tiles a workgroup, and no way is the faster one there (10 plans x 67,517 d = 160 89.5 ->
-//     91.5, d = 224 132 -> 135, d = 192 111 -> 112); before, d = 192 10 plans x 20,000 34.9 -> 33.2
-//   d = 32, with a vector in an eighth of a line, gains on single plans and loses on several: 400,000 vectors 7.0 -> 6.65, 7 plans x 51,556
-//     6.8 -> 7.9, 36 x 1494 2.75 -> 3.1, 1,000,000 13.9 -> 14.4: never
-constexpr bool srft_write_staged(int d, long long tiles, long long workgroups) {
-    if (d == 32 || tiles <= 768) return false;
-    if (d == 128 || tiles <= (d >= 160 ? 16 : 11) * workgroups) return true;
-    return d == 96 && tiles >= 22 * workgroups;
-}
+// write path, plain form, codes out: d, group mode, way of the record (srft_write_staged); 4- and 8-bit codes.
 quantize_kernel_t srft_pick_quantize_plain_b4(int d, int gm, bool staged);
 quantize_kernel_t srft_pick_quantize_plain_b8(int d, int gm, bool staged);
 batched_kernels_t srft_pick_quantize_plain_batched_b4(int d, int gm, bool staged);
@@ -339,7 +318,7 @@ int srft_launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t st, co
 }
 
 // the kernels a plan launches, and their block sizes
-// (tiles: of the launch; lines: its codes start at multiples of 64 bytes)
+// (tiles: of the launch; lines: its codes start at a multiple of 64 bytes)
 quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles = 0, bool lines = true);
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads);
 // the tables and the matrix scaling the kernels of a plan take
@@ -353,12 +332,12 @@ inline long long srft_plan_bytes(const srft_plan* p, long long tiles) {
 inline bool srft_plan_fold_through(const srft_plan* p, long long tiles, bool lines) {
     return srft_fold_through(p->d, p->bits, lines, srft_plan_bytes(p, tiles));
 }
-// the way of the record of a launch of the write path over this many tiles, and the most workgroups of that launch
-inline bool srft_plan_staged(const srft_plan* p, long long tiles) {
-    return srft_write_staged(p->d, tiles, p->max_wgs > 0 ? p->max_wgs : p->grid_q);
+// the way of the record of a launch of the write path's plain form over this many tiles, and the most workgroups of a launch
+inline bool srft_plan_staged(const srft_plan* p, long long tiles, bool lines) {
+    return !p->fold_q && !p->fold4_q && srft_write_staged(p->d, p->g, p->bits, lines, tiles, p->max_wgs > 0 ? p->max_wgs : p->grid_q, p->compute_units);
 }
-inline long long srft_plan_write_grid(const srft_plan* p, long long tiles) {
-    return p->max_wgs > 0 ? p->max_wgs : srft_plan_staged(p, tiles) ? p->grid_staged : p->grid_q;
+inline long long srft_plan_write_grid(const srft_plan* p, long long tiles, bool lines) {
+    return p->max_wgs > 0 ? p->max_wgs : srft_plan_staged(p, tiles, lines) ? p->grid_staged : p->grid_q;
 }
 inline const uint4* srft_plan_write_table(const srft_plan* p) { return p->fold4_q ? p->wfold4 : p->fold_q ? p->wfold : p->wfrag; }
 inline const uint4* srft_plan_read_table(const srft_plan* p) { return p->fold4_dq ? p->rfold4 : p->fold_dq ? p->rfold : p->rfrag; }

@@ -114,6 +114,40 @@ constexpr bool srft_flush_fits(long long n_vec, long long page_rows, long long n
 // (d = 256, g = 16, 52 plans: two launches -> one, a page of 8 sequences and a step 12.3 -> 11.1 us.)
 constexpr int srft_flush_whole_tiles(int d, int g) { return d == 128 && g == 16 ? 1 : d == 256 || d == 32 ? 4 : 8; }
 
+// Whether a record of the write path's plain form goes through LDS and is written through to memory (device_util.h), or is stored from
+// the lanes, in pieces of 8 bytes that the L2 puts together; by the tiles of a launch, its workgroups and the compute units.  Time
+// through LDS over time from the lanes, over one / three / six sets of buffers in turn (the memory-side cache holds 256 MB).  From some
+// 60 MB on where the buffers lie moves the ratio by up to 10 %, from one card and run to the next: two figures for a set are two cards.
+//   up to three tiles a compute unit the way through LDS is only longer: d = 96, 240 vectors 2.33 -> 2.40 us, 17,027 3.15 -> 3.26; 64 x
+//     512 (1024 tiles) 4.56 -> 4.48.  d = 192 up to four and a half (15 MB 1.03 / 1.02 / 1.02, 8 plans 1.05 / 1.04 / 1.03; 20 MB 0.97 / 0.98 /
+//     0.97), d = 224 three and a half (15 MB 1.02 / 1.03 / 1.02, 20 MB 0.97 / 0.98 / 0.97)
+//   up to some tiles a workgroup nothing is left to write back; from there on the memory-side cache takes the record better from the L2,
+//     where the rows are short:
+//     d = 64    10 MB 0.96 / 0.94 / 0.94   30 MB 0.91 / 0.93 / 0.92   50 MB 0.95 / 0.92 / 0.77   85 MB 1.00 1.00 / 0.99 0.95 / 1.02 0.98   105 MB
+//       0.99 1.00 / 0.85 0.96 / 1.07 0.99   118 MB 0.99 1.01 / 1.16 0.92 / 1.13 1.00; 8 bits 55 MB 0.75 / 0.99 / 0.83, 110 MB 1.00 / 0.85 / 1.05;
+//       56 plans 15 MB 0.94 / 0.94 / 0.95, 90 MB 0.99 / 0.91 / 0.99
+//     d = 96    10 MB 0.90 / 0.90 / 0.93   40 MB 0.91 / 0.96 / 0.98   60 MB 0.96 0.93 / 1.00 0.92 / 0.93 0.94   90 MB 1.05 0.97 / 0.98 0.91 / 1.05 1.04
+//       130 MB 1.05 / 1.08 / 1.12   180 MB 1.02 / 1.06 / 1.00   260 MB 0.97 / 0.95 / 0.96; 8 bits 90 MB 1.11 0.93 / 1.03 0.83 / 1.05 1.05, 150 MB
+//       1.04 / 1.05 / 1.08, 300 MB 0.86 / 0.97 / 0.93; 56 plans 90 MB 1.04 0.91 / 0.93 0.80 / 0.93 0.91
+//     d = 128   plain at g = 16 and with Walsh-Hadamard.  g = 16 10 MB 0.88 / 0.90 / 0.91   60 MB 0.95 / 1.01 / 0.91   200 MB 1.03 / 0.99 / 1.00
+//       400 MB 0.97 / 0.97 / 0.98; 8 bits 40 MB 0.82 / 0.90 / 0.90, 160 MB 1.12 / 1.02 / 0.99, 300 MB 0.77 / 0.85 / 0.88: always.  4 bits, g =
+//       32: 90 MB 0.99 / 0.93 / 0.99, 115 MB 1.04 / 0.90 / 0.98, 160 MB 1.03 / 1.07 / 1.04, 200 MB 1.04 / 1.04 / 1.09, 400 MB 1.06 / 1.05 / 1.06
+//     d >= 160  at the matrix cores' rate beyond 16 tiles a workgroup, and no way is the faster one there; before, 30 MB d = 160 0.88 /
+//       0.87 / 0.87, d = 192 0.96, d = 224 0.96 / 0.98 / 0.98, d = 256 0.96
+//   d = 32, with a vector in an eighth of a line, gains on single plans and loses on several: 400,000 vectors 7.0 -> 6.65 us, 7 plans x
+//     51,556 6.8 -> 7.9, 36 x 1494 2.75 -> 3.1, 1,000,000 13.9 -> 14.4: never
+// lines: a record of the launch starts at a multiple of 64 bytes.  16 bytes into a line: d = 64 11 MB 1.11 / 1.04 / 1.02, 33 MB 0.93 / 0.94 /
+// 0.94; d = 96 11 MB 1.03 / 1.03 / 1.02, 33 MB 0.94 / 0.95 / 0.95, 300 MB 0.93 / 1.01 / 1.01; d = 128, g = 16 11 MB 1.01 / 1.02 / 1.07, 300 MB 0.90 /
+// 1.01 / 1.03; d = 160 11 MB 0.88; d = 192 15 MB 1.03 / 1.02 / 1.02, 33 MB 0.97 / 0.97 / 0.98.  (Some records of a batch inside a line do not
+// matter: 14 plans at d = 96, 14 MB 0.89 / 0.87 / 0.88.)
+constexpr bool srft_write_staged(int d, int g, int bits, bool lines, long long tiles, long long workgroups, long long compute_units) {
+    if (d == 32 || 2 * tiles <= (d == 192 ? 9 : d == 224 ? 7 : 6) * compute_units) return false;
+    if (!lines && (d == 128 || tiles <= (d < 128 ? 8 : d == 160 ? 0 : 5) * compute_units)) return false;
+    if (d == 128 && (g != 32 || bits == 8)) return true;
+    if (d == 96 && lines && tiles >= 22 * workgroups) return true;
+    return tiles <= (d == 64 ? 9 : d == 96 ? 11 : d == 128 ? 14 : 16) * workgroups;
+}
+
 // Whether the once-folded write path (d = 128; d = 256 with g = 64 and 128) writes its record through to memory or leaves it to the
 // L2 (device_util.h), by the bytes of a launch, in and out.  Written through, nothing is left to write back at the end, which is what a
 // short launch takes longest over; a long one loses a little by it.  Left to the L2 -> written through, in turn over one / three / six

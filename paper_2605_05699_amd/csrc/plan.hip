@@ -324,14 +324,17 @@ int resident_blocks(const void* kernel, int threads, int* blocks) {
     return SRFT_OK;
 }
 
+quantize_kernel_t plain_quantize_kernel(const srft_plan* p, bool staged) {
+    return p->bits == 8 ? srft_pick_quantize_plain_b8(p->d, p->gm, staged) : srft_pick_quantize_plain_b4(p->d, p->gm, staged);
+}
+
 int occupancy_grids(srft_plan* p, int cus) {
     int threads = 0, blocks = 0;
     const quantize_kernel_t qk = srft_plan_quantize_kernel(p, kOutCodes, &threads);
     int rc = resident_blocks((const void*)qk, threads, &blocks);
     if (rc != SRFT_OK) return rc;
     p->grid_q = p->grid_staged = cus * blocks;
-    const quantize_kernel_t staged = srft_plan_quantize_kernel(p, kOutCodes, &threads, 769);     // (the plain form's other instance)
-    if (staged != qk) {
+    if (const quantize_kernel_t staged = p->fold_q || p->fold4_q ? nullptr : plain_quantize_kernel(p, true)) {       // the plain form's other instance
         rc = resident_blocks((const void*)staged, threads, &blocks);
         if (rc != SRFT_OK) return rc;
         p->grid_staged = cus * blocks;
@@ -374,8 +377,7 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
         return srft_pick_quantize_fold(p->d, p->bits, p->gm == kGroupWide, srft_plan_fold_through(p, n_tiles, lines));
     }
     *threads = 2 * p->d / p->slabs_q;
-    const bool staged = srft_plan_staged(p, n_tiles);
-    return p->bits == 8 ? srft_pick_quantize_plain_b8(p->d, p->gm, staged) : srft_pick_quantize_plain_b4(p->d, p->gm, staged);
+    return plain_quantize_kernel(p, srft_plan_staged(p, n_tiles, lines));
 }
 
 dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads) {

@@ -30,6 +30,9 @@ extern "C" int even_step(const void* const* p, int count, long long* step) { ret
 extern "C" int flush_fits(long long n_vec, long long page_rows, long long n_seq, long long t, long long units) {
     return srft_flush_fits(n_vec, page_rows, n_seq, t, units);
 }
+extern "C" int write_staged(int d, int g, int bits, int lines, long long tiles, long long workgroups, long long units) {
+    return srft_write_staged(d, g, bits, lines, tiles, workgroups, units);
+}
 extern "C" int fold_through(int d, int bits, int lines, long long bytes) { return srft_fold_through(d, bits, lines, bytes); }
 extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
 extern "C" long long copy_first(int i) { return srft_copy_first(i); }
@@ -225,3 +228,30 @@ def test_a_folded_record_is_written_through_where_that_is_faster(lib, d, last):
         assert [lib.fold_through(d, bits, lines, ll(n)) for bits, lines in ((4, 1), (4, 0), (8, 1), (8, 0))] == [1, 1, 1, d == 256]
     for n in (last + 1, 56 * 8192 * 336, 1_409_286_144) if d == 128 else (last + 1, 1_409_286_144):
         assert not any(lib.fold_through(d, bits, lines, ll(n)) for bits, lines in ((4, 1), (4, 0), (8, 1), (8, 0)))
+
+
+# d, g, bits, workgroups that fit, most tiles through LDS, fewest of the sizes beyond that go through LDS again; the last size below
+@pytest.mark.parametrize("d,g,bits,wgs,last,again,low", [
+    (64, 32, 4, 2048, 9 * 2048, None, 768), (64, 64, 8, 2048, 9 * 2048, None, 768), (96, 32, 4, 1280, 11 * 1280, 22 * 1280, 768), (96, 96, 8, 1024, 11 * 1024, 22 * 1024, 768),
+    (128, 16, 4, 768, None, None, 768), (128, 32, 8, 768, None, None, 768), (128, 128, 4, 768, None, None, 768), (128, 32, 4, 768, 14 * 768, None, 768),
+    (160, 32, 4, 512, 16 * 512, None, 768), (192, 32, 4, 256, 16 * 256, None, 1152), (224, 16, 8, 256, 16 * 256, None, 896), (256, 32, 4, 256, 16 * 256, None, 768)])
+def test_a_plain_record_goes_through_lds_where_that_is_faster(lib, d, g, bits, wgs, last, again, low):
+    def staged(tiles, lines=1, units=256):
+        return lib.write_staged(d, g, bits, lines, C.c_longlong(tiles), C.c_longlong(wgs), C.c_longlong(units))
+
+    assert not staged(1) and not staged(low) and staged(low + 1)
+    assert not staged(low // 4, units=64) and staged(low // 4 + 1, units=64)          # (the least goes with the compute units)
+    far = 2 ** 27
+    if last is None:
+        assert staged(far)
+    else:
+        assert staged(last) and not staged(last + 1) and staged(far) == (again is not None)
+        if again:
+            assert not staged(again - 1) and staged(again)
+    # 16 bytes into a line: from the lanes up to some tiles a compute unit, at d = 128 always
+    at = max(low, {64: 2048, 96: 2048, 160: 0}.get(d, 1280))
+    assert not staged(at, lines=0) and staged(at + 1, lines=0) == (d != 128) and not staged(far, lines=0)
+
+
+def test_a_record_of_d_32_is_always_stored_from_the_lanes(lib):
+    assert not any(lib.write_staged(32, 32, 4, 1, C.c_longlong(t), C.c_longlong(2048), C.c_longlong(256)) for t in (1, 769, 5000, 20000, 10 ** 6))
