@@ -47,7 +47,7 @@ int launch_dequantize(const srft_plan* p, const uint8_t* codes, const float* sca
     long long grid = p->max_wgs > 0 ? p->max_wgs : p->grid_dq;
     if (grid > n_tiles) grid = n_tiles;
     int threads = 0;
-    const dequantize_kernel_t kernel = srft_plan_dequantize_kernel(p, &threads);
+    const dequantize_kernel_t kernel = srft_plan_dequantize_kernel(p, &threads, n_tiles, srft_aligned(out, 64));
     if (!kernel) return SRFT_ERR_BAD_D;
     return srft_launch(kernel, dim3((unsigned)grid), threads, st, srft_plan_read_table(p), (const uint2*)codes, scales, n,
                        (uint4*)out, srft_plan_read_unscale(p), p->gw);
@@ -80,12 +80,14 @@ batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long
         const bool staged = srft_plan_staged(p, tiles, lines);
         return p->bits == 8 ? srft_pick_quantize_plain_batched_b8(p->d, p->gm, staged) : srft_pick_quantize_plain_batched_b4(p->d, p->gm, staged);
     }
+    const bool through = srft_plan_read_through(p, tiles, lines);
     if (p->fold4_dq) {
         *threads = p->d;
-        return srft_pick_dequantize_fold4_batched(p->d, p->bits, p->gm == kGroup16);
+        return srft_pick_dequantize_fold4_batched(p->d, p->bits, p->gm == kGroup16, through);
     }
     *threads = 2 * p->d / p->slabs_dq;
-    return p->bits == 8 ? srft_pick_dequantize_batched_b8(p->d, p->slabs_dq, p->gm) : srft_pick_dequantize_batched_b4(p->d, p->slabs_dq, p->gm);
+    return p->bits == 8 ? srft_pick_dequantize_batched_b8(p->d, p->slabs_dq, p->gm, through)
+                        : srft_pick_dequantize_batched_b4(p->d, p->slabs_dq, p->gm, through);
 }
 
 // One batched launch over the first `count` segments of the table, which is complete except for the workgroups.

@@ -252,14 +252,14 @@ quantize_kernel_t srft_pick_quantize_fold4(int bits, int gm);
 quantize_kernel_t srft_pick_quantize_fold4_amax(int teams);
 batched_kernels_t srft_pick_quantize_fold4_batched(int bits, int gm);
 int srft_fold4_table_units(void);
-// read path
-dequantize_kernel_t srft_pick_dequantize_b4(int d, int slabs, int gm);
-dequantize_kernel_t srft_pick_dequantize_b8(int d, int slabs, int gm);
-batched_kernels_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm);
-batched_kernels_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm);
+// read path (through: the rows are written through to memory, srft_read_through)
+dequantize_kernel_t srft_pick_dequantize_b4(int d, int slabs, int gm, bool through);
+dequantize_kernel_t srft_pick_dequantize_b8(int d, int slabs, int gm, bool through);
+batched_kernels_t srft_pick_dequantize_batched_b4(int d, int slabs, int gm, bool through);
+batched_kernels_t srft_pick_dequantize_batched_b8(int d, int slabs, int gm, bool through);
 // read path, folded twice (d = 128 at g >= 32, d = 256; fine: g = 16); the size of its table in 16-byte units
-dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits, bool fine);
-batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits, bool fine);
+dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits, bool fine, bool through);
+batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits, bool fine, bool through);
 int srft_rfold4_table_units(int d);
 // a cache's flush (cache_flush.h)
 flush_kernels_t srft_pick_cache_flush_plain(int d, int bits, int gm);
@@ -318,9 +318,9 @@ int srft_launch(void (*kernel)(P...), dim3 grid, int threads, hipStream_t st, co
 }
 
 // the kernels a plan launches, and their block sizes
-// (tiles: of the launch; lines: its codes start at a multiple of 64 bytes)
+// (tiles: of the launch; lines: its results start at a multiple of 64 bytes)
 quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* threads, long long n_tiles = 0, bool lines = true);
-dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads);
+dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads, long long n_tiles = 0, bool lines = true);
 // the tables and the matrix scaling the kernels of a plan take
 inline int srft_plan_amax_teams(const srft_plan* p, long long n_tiles) {
     return srft_amax_teams(p->d, p->wfold4 ? 2 : p->fold_q ? 1 : 0, n_tiles);
@@ -331,6 +331,9 @@ inline long long srft_plan_bytes(const srft_plan* p, long long tiles) {
 }
 inline bool srft_plan_fold_through(const srft_plan* p, long long tiles, bool lines) {
     return srft_fold_through(p->d, p->bits, lines, srft_plan_bytes(p, tiles));
+}
+inline bool srft_plan_read_through(const srft_plan* p, long long tiles, bool lines) {
+    return srft_read_through(p->d, lines, srft_plan_bytes(p, tiles));
 }
 // the way of the record of a launch of the write path's plain form over this many tiles, and the most workgroups of a launch
 inline bool srft_plan_staged(const srft_plan* p, long long tiles, bool lines) {

@@ -74,7 +74,8 @@ __device__ __forceinline__ uint4 decode8_flip_first(uint32_t v) {
     return o;
 }
 
-template <int D, int BITS, bool FINE>
+// THROUGH: the rows are written through to memory (srft_read_through).
+template <int D, int BITS, bool FINE, bool THROUGH = true>
 __device__ __forceinline__ void
 srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restrict__ codes_raw,
                             const float* __restrict__ scales, long long n_vec, uint4* __restrict__ out,
@@ -324,7 +325,7 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int u = tid + i * NT, r = u / U, c = u % U;
-            stream_store(tile_base, (unsigned)(min(r, lim) * U + c), stg[r * ROW + c]);   // rows past the end alias to the last row
+            store_row<THROUGH>(tile_base, (unsigned)(min(r, lim) * U + c), stg[r * ROW + c]);   // rows past the end alias to the last row
         }
     };
 
@@ -393,21 +394,21 @@ srft_dequantize_fold4_tiles(const uint4* __restrict__ tab, const uint2* __restri
     }
 }
 
-template <int D, int BITS, bool FINE>
+template <int D, int BITS, bool FINE, bool THROUGH>
 __global__ void __launch_bounds__(D / 64 * 64, 2)
 srft_dequantize_fold4_kernel(const uint4* __restrict__ tab, const uint2* __restrict__ codes,
                              const float* __restrict__ scales, long long n_vec, uint4* __restrict__ out,
                              float unscale, int gw) {
     int t0, stride, t_end;
     if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
-    srft_dequantize_fold4_tiles<D, BITS, FINE>(tab, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
+    srft_dequantize_fold4_tiles<D, BITS, FINE, THROUGH>(tab, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
 }
 
-template <int D, int BITS, bool FINE, int N>
+template <int D, int BITS, bool FINE, bool THROUGH, int N>
 __global__ void __launch_bounds__(D / 64 * 64, 2)
 srft_dequantize_fold4_batched_kernel(const srft_batch<N> a, int gw) {
     const srft_work s = srft_work_of_block<false>(a);
-    srft_dequantize_fold4_tiles<D, BITS, FINE>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
+    srft_dequantize_fold4_tiles<D, BITS, FINE, THROUGH>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
                                          s.unscale, gw, s.place, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 

@@ -37,7 +37,8 @@
 //     [D/64 waves][A, B][D/32 groups][hi, lo][64 lanes], followed by [D/64 waves][64 lanes][2] sign masks.
 // BITS: 4, or 8 (one two's-complement byte per code).  A "code unit" is 16 codes: 8 bytes at 4 bits, 16 at 8.
 //     At 8 bits a dword gives the pairs (b0, b2) and (b1, b3): again even and odd p apart, so FOLD applies as is.
-template <int D, int S, int KS, bool FOLD, int BITS>
+// THROUGH: the rows are written through to memory (srft_read_through).
+template <int D, int S, int KS, bool FOLD, int BITS, bool THROUGH = true>
 __device__ __forceinline__ void
 srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__ codes_raw,
                       const float* __restrict__ scales, long long n_vec, uint4* __restrict__ out,
@@ -206,7 +207,7 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
             // (Rows past the end alias to the last row.  24 bits: where U is no power of two, a 32-bit product becomes a 64-bit
             // multiply-add, whose unused upper half may be any register, the target of a prefetch among them, with a wait for
             // it in front: 9 plans x 66,666 vectors of differing counts at d = 192, 8-bit codes, 82 us, with that wait 89.)
-            stream_store(tile_base, __umul24(min(r, lim), U) + c, stg[b][r * ROW + c]);
+            store_row<THROUGH>(tile_base, __umul24(min(r, lim), U) + c, stg[b][r * ROW + c]);
         }
     };
     // all groups of the tile in dec[b] (scales in scl[b]); `prev`: first fold in the last group of the
@@ -460,21 +461,21 @@ srft_dequantize_tiles(const uint4* __restrict__ rfrag, const uint2* __restrict__
     }
 }
 
-template <int D, int S, int KS, bool FOLD, int BITS>
+template <int D, int S, int KS, bool FOLD, int BITS, bool THROUGH>
 __global__ void __launch_bounds__(2 * D / S, 1)
 srft_dequantize_kernel(const uint4* __restrict__ rfrag, const uint2* __restrict__ codes,
                        const float* __restrict__ scales, long long n_vec, uint4* __restrict__ out,
                        float unscale, int gw) {
     int t0, stride, t_end;
     if (!srft_tile_range(n_vec, t0, stride, t_end)) return;
-    srft_dequantize_tiles<D, S, KS, FOLD, BITS>(rfrag, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
+    srft_dequantize_tiles<D, S, KS, FOLD, BITS, THROUGH>(rfrag, codes, scales, n_vec, out, unscale, gw, t0, stride, t_end);
 }
 
-template <int D, int S, int KS, bool FOLD, int BITS, int N>
+template <int D, int S, int KS, bool FOLD, int BITS, bool THROUGH, int N>
 __global__ void __launch_bounds__(2 * D / S, 1)
 srft_dequantize_batched_kernel(const srft_batch<N> a, int gw) {
     const srft_work s = srft_work_of_block<false>(a);
-    srft_dequantize_tiles<D, S, KS, FOLD, BITS>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
+    srft_dequantize_tiles<D, S, KS, FOLD, BITS, THROUGH>(s.frag, (const uint2*)s.in, s.scales, s.n_vec, (uint4*)s.out,
                                     s.unscale, gw, s.place, s.blocks, (int)((s.n_vec + kTileVecs - 1) / kTileVecs));
 }
 

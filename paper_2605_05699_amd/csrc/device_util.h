@@ -10,16 +10,18 @@
 // Stores of results, which go through to memory (sc1) instead of staying in the L2 of a die.  What bounds a launch of up to some
 // 100 MB is not the rate of its loop alone but the write-back of the L2s at its end: each die's is searched and written back before
 // the next launch, and beyond some 16 MB of results lines are also evicted one by one while the kernel reads.  Written through,
-// nothing is left to write back.  Only for stores that cover whole cache lines: a partial line goes to memory as a partial write
-// (8-bit records at d = 256, 16 bytes of a row at a time: 62 -> 130 us over 300 MB).  us by bytes moved, non-temporal stores -> sc1
+// nothing is left to write back.  Only for stores that cover whole lines, or halves of 64 bytes: a part of one goes to memory as a partial
+// write (8-bit records at d = 256, 16 bytes of a row at a time: 62 -> 130 us over 300 MB).  By sizes and alignment each path has a rule
+// where it pays (srft_write_staged, srft_fold_through, srft_read_through in launch_shape.h; scores.hip).  us by bytes moved, non-temporal stores -> sc1
 // nt:
 //   read, d = 128   11 MB 5.4 -> 4.3   22 6.1 -> 5.4   33 9.7 -> 7.8   44 13.4 -> 11.6   88 21.5 -> 21.8   352 65.8 -> 64.7
 //   read, d = 256   11 MB 6.2 -> 5.3   33 11.3 -> 9.8  44 15.4 -> 12.6 88 24.2 -> 24.0   176 41.8 -> 40.6
 //   read, d = 96    10 MB 6.0 -> 4.5   31 10.1 -> 8.2  83 22.0 -> 21.5 330 65.5 -> 63.9
 //   write, d = 256  11 MB 5.8 -> 5.3   33 10.7 -> 9.7  88 22.0 -> 19.0 176 37.8 -> 36.3   352 70.2 -> 68.5
-//   write, d = 128  11 MB 5.3 -> 5.0   30 9.15 -> 8.8  88 17.7 -> 17.6 1409 262.2 -> 263.0
-// nt on top of sc1 keeps the lines out of the memory-side cache: better from 100 MB on (reads 67.0 -> 65.0 at 352 MB, writes at d =
-// 128 271 -> 263 at 1.4 GB), worse between 40 and 90 MB (reads 19.7 -> 21.9 at 88 MB).  Stored without it: all scales (a tile has
+//   write, d = 128  11 MB 5.3 -> 5.0   30 9.15 -> 8.8  (beyond 60 MB left to the L2)
+// nt on top of sc1 keeps the lines out of the memory-side cache: better from 100 MB on (reads 67.0 -> 65.0 at 352 MB) and for d = 64 and
+// 96 wherever memory is cold (130 MB at d = 64 33.3 -> 28.9), worse where the sets in turn just fill that cache (three of 88 MB at d = 128
+// 20.5 -> 21.8).  Stored without it: all scales (a tile has
 // 512 bytes of them at d = 128; with it 14 plans x 50 vectors 3.3 -> 3.5).
 // The buffer form of the store takes the policy as an operand; base is uniform, offsets in bytes stay below 2^31.
 constexpr int kStoreThrough = 16, kStoreThroughOnce = 18;                // cache policy: sc1; sc1 nt

@@ -148,6 +148,28 @@ constexpr bool srft_write_staged(int d, int g, int bits, bool lines, long long t
     return tiles <= (d == 64 ? 9 : d == 96 ? 11 : d == 128 ? 14 : 16) * workgroups;
 }
 
+// Whether the read path writes its rows through to memory or leaves them to the L2 (device_util.h), by the bytes of a launch, in and
+// out.  Left to the L2 -> written through, over one / three / six sets of buffers in turn (the memory-side cache holds 256 MB):
+//   d = 32    20 MB 0.99 / 0.95 / 0.94   40 MB 0.97 / 0.84 / 1.03   60 MB 0.90 / 0.98 / 1.04   90 MB 0.83 / 1.04 / 1.00   130 MB 0.83 / 1.02 / 1.01   160 MB
+//     1.01 / 1.02 / 1.02   300 MB 1.04 / 1.04 / 1.04 (there it is the form of the store that costs: 1.05 without sc1)
+//   d = 64    45 MB 0.91 / 0.89 / 0.90   90 MB 0.89 / 1.02 / 0.99   130 MB 0.90 / 0.99 / 0.99   300 MB 0.98; 56 plans 40 MB 0.88 / 0.85 / 0.84, 80 MB 0.76 /
+//     0.95 / 0.93
+//   d = 96    60 MB 0.87 / 0.93 / 0.98   88 MB 0.87 / 0.99 / 0.97   160 MB 0.95 / 0.98 / 0.97
+//   d = 128   40 MB 0.90 / 0.89 / 0.96   80 MB 0.80 / 1.04 / 0.99   90 MB 0.82 / 1.05 / 1.00   110 MB 0.73 / 1.01 / 1.00   300 MB 0.99; 56 plans 40 MB 0.84 / 0.83 /
+//     0.83, 80 MB 0.80 / 0.95 / 0.95; 14 ragged ones 84 MB 0.82 / 0.97 / 0.98; 8 bits 85 MB 0.91 / 0.98 / 0.97
+//   d = 256   60 MB 0.91 / 0.93 / 0.96   90 MB 0.88 / 1.02 / 1.00   160 MB 0.98 / 0.99 / 0.98; d = 160, 192 and 224 0.93 - 0.99 at all sizes
+// (One plan of 64 to 128 channels, its sets just filling the memory-side cache, is 2 to 5 % slower at 75 to 100 MB; with fewer sets the
+// same launches are 20 % faster, with more the same, several plans 5 % faster, so they have no way of their own.  sc1 without
+// nt is faster there and slower cold: d = 64 1.10 - 1.16, d = 96 1.06 - 1.09, d = 128 1.02.)
+// lines: rows of the launch start at a multiple of 64 bytes (half a line does: 64 bytes into a line 0.88 as at its start).  16 bytes into
+// a line every piece that a wavefront stores ends in a partial line: d = 32 11 MB 1.04, 33 MB 1.14, 300 MB 1.18; d = 64 and 96 the same; d =
+// 128 11 MB 1.01, 33 MB 1.11, 300 MB 1.20; d = 192 33 MB 1.04, 300 MB 1.02; d = 256 33 MB 1.01, 88 MB 1.04, 300 MB 1.05.  d = 160 and 224, which
+// the matrix cores bound, gain still (11 MB 0.92, 33 MB 0.96, 88 MB 0.98).
+constexpr bool srft_read_through(int d, bool lines, long long bytes) {
+    if (!lines) return d == 160 || d == 224;
+    return d != 32 || bytes <= 140000000;
+}
+
 // Whether the once-folded write path (d = 128; d = 256 with g = 64 and 128) writes its record through to memory or leaves it to the
 // L2 (device_util.h), by the bytes of a launch, in and out.  Written through, nothing is left to write back at the end, which is what a
 // short launch takes longest over; a long one loses a little by it.  Left to the L2 -> written through, in turn over one / three / six

@@ -380,13 +380,14 @@ quantize_kernel_t srft_plan_quantize_kernel(const srft_plan* p, int out, int* th
     return plain_quantize_kernel(p, srft_plan_staged(p, n_tiles, lines));
 }
 
-dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads) {
+dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads, long long n_tiles, bool lines) {
+    const bool through = srft_plan_read_through(p, n_tiles, lines);
     if (p->fold4_dq) {
         *threads = p->d;
-        return srft_pick_dequantize_fold4(p->d, p->bits, p->gm == kGroup16);
+        return srft_pick_dequantize_fold4(p->d, p->bits, p->gm == kGroup16, through);
     }
     *threads = 2 * p->d / p->slabs_dq;
-    return p->bits == 8 ? srft_pick_dequantize_b8(p->d, p->slabs_dq, p->gm) : srft_pick_dequantize_b4(p->d, p->slabs_dq, p->gm);
+    return p->bits == 8 ? srft_pick_dequantize_b8(p->d, p->slabs_dq, p->gm, through) : srft_pick_dequantize_b4(p->d, p->slabs_dq, p->gm, through);
 }
 
 flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads) {

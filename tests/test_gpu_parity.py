@@ -590,7 +590,8 @@ def test_a_record_is_the_same_whichever_way_it_is_stored(B, d, g, bits, transfor
 WAYS = [(128, 32, 4, "dft", 180_000), (128, 32, 8, "dft", 152_000), (128, 128, 4, "dft", 186_000), (256, 64, 4, "dft", 306_000), (256, 128, 8, "dft", 252_000),
         (64, 32, 4, "dft", 590_000), (64, 64, 8, "dft", 100_000), (96, 32, 4, "dft", 451_000), (96, 96, 8, "dft", 100_000), (96, 16, 4, "dft", 902_000),
         (128, 32, 4, "hadamard", 345_000), (128, 16, 8, "dft", 100_000), (160, 32, 4, "dft", 100_000), (192, 16, 8, "dft", 135_000), (224, 224, 4, "dft", 100_000),
-        (256, 32, 4, "hadamard", 135_000), (32, 32, 4, "dft", 100_000)]
+        (256, 32, 4, "hadamard", 135_000), (32, 32, 4, "dft", 100_000), (32, 16, 8, "dft", 1_350_000),
+        (64, 16, 4, "dft", 560_000), (128, 16, 4, "dft", 250_000), (128, 64, 8, "dft", 200_000), (256, 16, 4, "dft", 100_000), (256, 128, 8, "hadamard", 100_000)]
 
 
 @pytest.mark.parametrize("d,g,bits,transform,many", WAYS)

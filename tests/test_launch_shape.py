@@ -33,6 +33,7 @@ extern "C" int flush_fits(long long n_vec, long long page_rows, long long n_seq,
 extern "C" int write_staged(int d, int g, int bits, int lines, long long tiles, long long workgroups, long long units) {
     return srft_write_staged(d, g, bits, lines, tiles, workgroups, units);
 }
+extern "C" int read_through(int d, int lines, long long bytes) { return srft_read_through(d, lines, bytes); }
 extern "C" int fold_through(int d, int bits, int lines, long long bytes) { return srft_fold_through(d, bits, lines, bytes); }
 extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
 extern "C" long long copy_first(int i) { return srft_copy_first(i); }
@@ -255,3 +256,14 @@ def test_a_plain_record_goes_through_lds_where_that_is_faster(lib, d, g, bits, w
 
 def test_a_record_of_d_32_is_always_stored_from_the_lanes(lib):
     assert not any(lib.write_staged(32, 32, 4, 1, C.c_longlong(t), C.c_longlong(2048), C.c_longlong(256)) for t in (1, 769, 5000, 20000, 10 ** 6))
+
+
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 160, 192, 224, 256])
+def test_rows_are_written_through_where_that_is_faster(lib, d):
+    def through(n, lines=1):
+        return bool(lib.read_through(d, lines, C.c_longlong(n)))
+
+    most = 140_000_000
+    assert all(through(n) == (d != 32 or n <= most) for n in (1, 10 ** 6, 8 * 10 ** 7, most, most + 1, 10 ** 10))
+    # 16 bytes into a line: only what the matrix cores bound
+    assert all(through(n, lines=0) == (d in (160, 224)) for n in (1, 10 ** 6, 10 ** 8, 10 ** 10))
