@@ -66,7 +66,7 @@ __device__ __forceinline__ float wave_sum(float x) {
     return quarters_sum(x);
 }
 
-// D: head dimension.  KEYS: keys per tile, 64 or 32 (then ONE).  WIDE: groups of gw > 1 runs of 32 channels share a scale.
+// D: head dimension.  KEYS: keys per tile, 64 or 32 (then ONE, but at D = 192).  WIDE: groups of gw > 1 runs of 32 channels share a scale.
 // blockIdx.y: block of 16 queries.  (Both blocks of 32 queries in one wavefront -- the codes decoded once -- needs more
 // registers than two wavefronts per SIMD leave: 250 spilled at d = 128.)
 // ONE: no wavefront has more than one tile (up to 131,072 keys and 16 queries on a whole chip): nothing is asked for behind
@@ -102,7 +102,7 @@ srft_attention_scan_kernel(const uint4* __restrict__ q, int n_q, const uint4* __
     constexpr int LDS_BYTES = TEAM == 1 ? TILE_BYTES : std::max(TILE_BYTES, std::max(MEET_BYTES, QUERY_BYTES));
     static_assert(D % 64 == 0 && VTILE % 16 == 0 && (KEYS == 32 || KEYS == 64), "layout");
     static_assert(TEAM == 1 || (ONE && KEYS == 32 && (G == 2 || G == 4) && G * TEAM == ALL), "a team has one tile, two or four groups a wavefront");
-    static_assert(KEYS == 64 || ONE, "tiles of 32 keys are for short prefixes");
+    static_assert(KEYS == 64 || ONE || D == 192, "tiles of 32 keys are for short prefixes");
     __shared__ __align__(16) unsigned char lds[LDS_BYTES];
     __shared__ uint4 qs[ALL * 2 * 64];
     __shared__ float meet[2][W][16];
@@ -581,8 +581,9 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
            const uint8_t* v_codes, const float* v_scales, long long n_keys, float softmax_scale, float* out, void* workspace,
            hipStream_t st) {
     // Tiles of 64 keys, or of 32 where that still leaves every wavefront of the chip at most one (and then wavefronts in teams, while
-    // every team has at most one): the chain of one tile is then half as long.  Workgroups: one per tile, up to one per compute unit (its eight wavefronts fill the register file); with
-    // two blocks of queries half of that each, so that both read a tile at about the same time.
+    // every team has at most one): the chain of one tile is then half as long.  Workgroups: one per tile, up to one per compute unit
+    // (its eight wavefronts fill the register file); with two blocks of queries half of that each, so that both read a tile at about
+    // the same time.
     const int blocks = n_q <= 16 ? 1 : 2;
     long long most = pv->compute_units;
     if (pk->max_wgs > 0) most = pk->max_wgs;
@@ -596,8 +597,12 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
                 if (n > one_pass && n <= one_pass + one_pass / 63) return one_pass;
         return n;
     };
-    grid = in_one_pass(grid);
-    const bool narrow = n_keys <= 32 * kWaves * grid;
+    // What 252 of 256 leave over of the short tiles, 64,513 to 65,536 keys at D = 192, goes to a few wavefronts as a second one (65,000
+    // keys, 1 / 8 / 16 queries 14.6 / 15.8 / 17.5 us; 64-key tiles 16.6 / 16.9 / 17.5, 256 workgroups and a finish of two passes 15.7 / 17.0 /
+    // 18.9); with two blocks of queries 64-key tiles are the faster (32,768 keys, 17 queries 15.9, so 16.2).
+    const long long cut = in_one_pass(grid);
+    const bool narrow = n_keys <= 32 * kWaves * (blocks == 1 ? grid : cut);
+    grid = cut;
     const long long n_tiles = narrow ? (n_keys + 31) / 32 : (n_keys + 63) / 64;
     grid = in_one_pass(std::min(grid, n_tiles));
     static_assert((size_t)kScanGridMax * 32 * (2 + D) <= srft_attend_workspace_floats(D), "fits what callers are told to bring");
@@ -611,7 +616,8 @@ int launch(const srft_plan* pk, const srft_plan* pv, const void* q, int n_q, con
     const auto kernel =
         narrow && n_tiles <= kWaves / TWO * grid    ? pick(srft_attention_scan_kernel<D, 32, true, true, TWO>, srft_attention_scan_kernel<D, 32, false, true, TWO>)
         : narrow && n_tiles <= kWaves / FOUR * grid ? pick(srft_attention_scan_kernel<D, 32, true, true, FOUR>, srft_attention_scan_kernel<D, 32, false, true, FOUR>)
-        : narrow                                    ? pick(srft_attention_scan_kernel<D, 32, true, true>, srft_attention_scan_kernel<D, 32, false, true>)
+        : narrow && n_tiles <= kWaves * grid        ? pick(srft_attention_scan_kernel<D, 32, true, true>, srft_attention_scan_kernel<D, 32, false, true>)
+        : narrow                                    ? pick(srft_attention_scan_kernel<D, 32, true, D != 192>, srft_attention_scan_kernel<D, 32, false, D != 192>)
         : n_tiles <= kWaves * grid                  ? pick(srft_attention_scan_kernel<D, 64, true, true>, srft_attention_scan_kernel<D, 64, false, true>)
                                                     : pick(srft_attention_scan_kernel<D, 64, true, false>, srft_attention_scan_kernel<D, 64, false, false>);
     const int rc = srft_launch(kernel, dim3((unsigned)grid, blocks), 64 * kWaves, st, (const uint4*)q, n_q, (const uint4*)pk->q_table,

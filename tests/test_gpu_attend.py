@@ -440,3 +440,11 @@ def test_decode_attention_of_hadamard_plans(B, transforms, d, g, n_q, n_keys, ca
     (128, 32, 32, 3), (128, 128, 384, 3), (128, 32, 385, 3), (128, 32, 768, 3), (128, 128, 769, 3), (64, 32, 768, 3), (64, 64, 769, 3)])
 def test_decode_attention_at_the_edges_of_its_teams(B, d, g, n_q, n_keys, cap):
     test_decode_attention_at_the_edges_of_its_tiles_and_grid(B, d, g, n_q, n_keys, cap, 0.1)
+
+
+# d = 192: 63 of 64 workgroups scan (252 of 256), and what is left over of the tiles of 32 keys is a second one for a few wavefronts.
+# The last size that does not need it, the first and the last that do, and the first of the 64-key tiles.
+@pytest.mark.parametrize("n_q", [1, 16, 17])
+@pytest.mark.parametrize("g,n_keys,cap", [(32, 16128, 64), (32, 16129, 64), (192, 16384, 64), (32, 16385, 64), (192, 8065, 64), (32, 8192, 64), (32, 32257, 128), (192, 32768, 128)])
+def test_decode_attention_of_192_channels_beside_its_whole_grid(B, g, n_q, n_keys, cap):
+    test_decode_attention_at_the_edges_of_its_tiles_and_grid(B, 192, g, n_q, n_keys, cap, 0.1)
