@@ -64,7 +64,7 @@ srft_segment segment_part(const srft_plan* p, bool write_path, const srft_segmen
     return s;
 }
 
-// The kernels of a plan's batched launches, and their block size.  tiles: of the launch; lines: results of it start at a multiple of 64
+// The kernels of a plan's batched launches, and their block size.  tiles: of the launch; lines: its results start at multiples of 64
 // bytes.
 batched_kernels_t batched_kernels(const srft_plan* p, bool write_path, long long tiles, bool lines, int* threads) {
     if (write_path && p->fold4_q) {
@@ -156,7 +156,7 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
     if (count < 0) return SRFT_ERR_BAD_N;
     if (count == 0) return SRFT_OK;
     if (!plans || !in0 || !out0 || !n_vec || (write_path ? !out1 : !in1)) return SRFT_ERR_NULL;
-    bool lines = false;
+    bool lines = true;
     // validate everything before the first launch: a bad segment must not leave half a batch enqueued
     for (int i = 0; i < count; ++i) {
         if (!plans[i]) return SRFT_ERR_NULL;
@@ -166,7 +166,7 @@ int srft_run_batched(const srft_plan_t* const* plans, const void* const* in0, co
         const void* small = write_path ? (const void*)out1[i] : in1[i];       // the scales
         if (!in0[i] || !out0[i] || !small) return SRFT_ERR_NULL;
         if (!srft_aligned(in0[i], 16) || !srft_aligned(out0[i], 16) || !srft_aligned(small, 4)) return SRFT_ERR_ALIGN;
-        lines |= srft_aligned(out0[i], 64);
+        lines &= srft_aligned(out0[i], 64);
     }
     srft_batch_even even;
     if (even_batch(plans, in0, out0, write_path ? (const void* const*)out1 : in1, n_vec, count, write_path, lines, &even)) {

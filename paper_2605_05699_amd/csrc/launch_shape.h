@@ -118,55 +118,62 @@ constexpr int srft_flush_whole_tiles(int d, int g) { return d == 128 && g == 16 
 // the lanes, in pieces of 8 bytes that the L2 puts together; by the tiles of a launch, its workgroups and the compute units.  Time
 // through LDS over time from the lanes, over one / three / six sets of buffers in turn (the memory-side cache holds 256 MB).  From some
 // 60 MB on where the buffers lie moves the ratio by up to 10 %, from one card and run to the next: two figures for a set are two cards.
-//   up to three tiles a compute unit the way through LDS is only longer: d = 96, 240 vectors 2.33 -> 2.40 us, 17,027 3.15 -> 3.26; 64 x
-//     512 (1024 tiles) 4.56 -> 4.48.  d = 192 up to four and a half (15 MB 1.03 / 1.02 / 1.02, 8 plans 1.05 / 1.04 / 1.03; 20 MB 0.97 / 0.98 /
-//     0.97), d = 224 three and a half (15 MB 1.02 / 1.03 / 1.02, 20 MB 0.97 / 0.98 / 0.97)
-//   up to some tiles a workgroup nothing is left to write back; from there on the memory-side cache takes the record better from the L2,
-//     where the rows are short:
-//     d = 64    10 MB 0.96 / 0.94 / 0.94   30 MB 0.91 / 0.93 / 0.92   50 MB 0.95 / 0.92 / 0.77   85 MB 1.00 1.00 / 0.99 0.95 / 1.02 0.98   105 MB
-//       0.99 1.00 / 0.85 0.96 / 1.07 0.99   118 MB 0.99 1.01 / 1.16 0.92 / 1.13 1.00; 8 bits 55 MB 0.75 / 0.99 / 0.83, 110 MB 1.00 / 0.85 / 1.05;
-//       56 plans 15 MB 0.94 / 0.94 / 0.95, 90 MB 0.99 / 0.91 / 0.99
-//     d = 96    10 MB 0.90 / 0.90 / 0.93   40 MB 0.91 / 0.96 / 0.98   60 MB 0.96 0.93 / 1.00 0.92 / 0.93 0.94   90 MB 1.05 0.97 / 0.98 0.91 / 1.05 1.04
-//       130 MB 1.05 / 1.08 / 1.12   180 MB 1.02 / 1.06 / 1.00   260 MB 0.97 / 0.95 / 0.96; 8 bits 90 MB 1.11 0.93 / 1.03 0.83 / 1.05 1.05, 150 MB
-//       1.04 / 1.05 / 1.08, 300 MB 0.86 / 0.97 / 0.93; 56 plans 90 MB 1.04 0.91 / 0.93 0.80 / 0.93 0.91
-//     d = 128   plain at g = 16 and with Walsh-Hadamard.  g = 16 10 MB 0.88 / 0.90 / 0.91   60 MB 0.95 / 1.01 / 0.91   200 MB 1.03 / 0.99 / 1.00
-//       400 MB 0.97 / 0.97 / 0.98; 8 bits 40 MB 0.82 / 0.90 / 0.90, 160 MB 1.12 / 1.02 / 0.99, 300 MB 0.77 / 0.85 / 0.88: always.  4 bits, g =
-//       32: 90 MB 0.99 / 0.93 / 0.99, 115 MB 1.04 / 0.90 / 0.98, 160 MB 1.03 / 1.07 / 1.04, 200 MB 1.04 / 1.04 / 1.09, 400 MB 1.06 / 1.05 / 1.06
-//     d >= 160  at the matrix cores' rate beyond 16 tiles a workgroup, and no way is the faster one there; before, 30 MB d = 160 0.88 /
-//       0.87 / 0.87, d = 192 0.96, d = 224 0.96 / 0.98 / 0.98, d = 256 0.96
+//   Up to three tiles a compute unit the way through LDS is only longer: d = 96, 240 vectors 2.33 -> 2.40 us, 17,027 3.15 -> 3.26;
+//     64 x 512 (1024 tiles) 4.56 -> 4.48.  d = 192 up to four and a half (15 MB 1.03 / 1.02 / 1.02, 8 plans 1.05 / 1.04 / 1.03; 20 MB
+//     0.97 / 0.98 / 0.97), d = 224 three and a half (15 MB 1.02 / 1.03 / 1.02; 20 MB 0.97 / 0.98 / 0.97).
+//   Up to some tiles a workgroup nothing is left to write back; from there on the memory-side cache takes the record better from the
+//     L2, where the rows are short.
+//   d = 64   10 MB 0.96 / 0.94 / 0.94   30 MB 0.91 / 0.93 / 0.92   50 MB 0.95 / 0.92 / 0.77   85 MB 1.00 1.00 / 0.99 0.95 / 1.02 0.98
+//     105 MB 0.99 1.00 / 0.85 0.96 / 1.07 0.99   118 MB 0.99 1.01 / 1.16 0.92 / 1.13 1.00   8 bits: 55 MB 0.75 / 0.99 / 0.83,
+//     110 MB 1.00 / 0.85 / 1.05   56 plans: 15 MB 0.94 / 0.94 / 0.95, 90 MB 0.99 / 0.91 / 0.99
+//   d = 96   10 MB 0.90 / 0.90 / 0.93   40 MB 0.91 / 0.96 / 0.98   60 MB 0.96 0.93 / 1.00 0.92 / 0.93 0.94   90 MB 1.05 0.97 /
+//     0.98 0.91 / 1.05 1.04   130 MB 1.05 / 1.08 / 1.12   180 MB 1.02 / 1.06 / 1.00   260 MB 0.97 / 0.95 / 0.96   8 bits: 90 MB
+//     1.11 0.93 / 1.03 0.83 / 1.05 1.05, 150 MB 1.04 / 1.05 / 1.08, 300 MB 0.86 / 0.97 / 0.93   56 plans: 90 MB 1.04 0.91 / 0.93 0.80 /
+//     0.93 0.91
+//   d = 128 (plain at g = 16 and with Walsh-Hadamard)   g = 16: 10 MB 0.88 / 0.90 / 0.91, 60 MB 0.95 / 1.01 / 0.91, 200 MB 1.03 / 0.99 /
+//     1.00, 400 MB 0.97 / 0.97 / 0.98; 8 bits 40 MB 0.82 / 0.90 / 0.90, 160 MB 1.12 / 1.02 / 0.99, 300 MB 0.77 / 0.85 / 0.88: always.
+//     4 bits, g = 32: 90 MB 0.99 / 0.93 / 0.99, 115 MB 1.04 / 0.90 / 0.98, 160 MB 1.03 / 1.07 / 1.04, 200 MB 1.04 / 1.04 / 1.09, 400 MB
+//     1.06 / 1.05 / 1.06
+//   d >= 160 is at the matrix cores' rate beyond 16 tiles a workgroup, and no way is the faster one there; before, 30 MB d = 160 0.88 /
+//     0.87 / 0.87, d = 192 0.96, d = 224 0.96 / 0.98 / 0.98, d = 256 0.96
 //   d = 32, with a vector in an eighth of a line, gains on single plans and loses on several: 400,000 vectors 7.0 -> 6.65 us, 7 plans x
 //     51,556 6.8 -> 7.9, 36 x 1494 2.75 -> 3.1, 1,000,000 13.9 -> 14.4: never
-// lines: a record of the launch starts at a multiple of 64 bytes.  16 bytes into a line: d = 64 11 MB 1.11 / 1.04 / 1.02, 33 MB 0.93 / 0.94 /
-// 0.94; d = 96 11 MB 1.03 / 1.03 / 1.02, 33 MB 0.94 / 0.95 / 0.95, 300 MB 0.93 / 1.01 / 1.01; d = 128, g = 16 11 MB 1.01 / 1.02 / 1.07, 300 MB 0.90 /
-// 1.01 / 1.03; d = 160 11 MB 0.88; d = 192 15 MB 1.03 / 1.02 / 1.02, 33 MB 0.97 / 0.97 / 0.98.  (Some records of a batch inside a line do not
-// matter: 14 plans at d = 96, 14 MB 0.89 / 0.87 / 0.88.)
+// lines: all records of the launch start at multiples of 64 bytes.  16 bytes into a line: d = 64 11 MB 1.11 / 1.04 / 1.02, 33 MB 0.93 /
+// 0.94 / 0.94; d = 96 11 MB 1.03 / 1.03 / 1.02, 33 MB 0.94 / 0.95 / 0.95, 300 MB 0.93 / 1.01 / 1.01; d = 128, g = 16 11 MB 1.01 / 1.02 /
+// 1.07, 300 MB 0.90 / 1.01 / 1.03; d = 160 11 MB 0.88; d = 192 15 MB 1.03 / 1.02 / 1.02, 33 MB 0.97 / 0.97 / 0.98.  14 ragged plans, whose
+// records start anywhere, over three sets: d = 64 5 MB 1.07, 8 MB 1.04, 14 MB 0.98; d = 96 7 MB 1.12, g = 16 9 MB 1.08, 11 MB 0.89, 14 MB
+// 0.87; d = 192 22 MB 1.04.
 constexpr bool srft_write_staged(int d, int g, int bits, bool lines, long long tiles, long long workgroups, long long compute_units) {
     if (d == 32 || 2 * tiles <= (d == 192 ? 9 : d == 224 ? 7 : 6) * compute_units) return false;
-    if (!lines && (d == 128 || tiles <= (d < 128 ? 8 : d == 160 ? 0 : 5) * compute_units)) return false;
+    if (!lines && (d == 128 || tiles <= (d == 64 ? 8 : d == 96 ? 5 : d == 160 ? 0 : 6) * compute_units)) return false;
     if (d == 128 && (g != 32 || bits == 8)) return true;
-    if (d == 96 && lines && tiles >= 22 * workgroups) return true;
+    if (d == 96 && tiles >= 22 * workgroups) return true;
     return tiles <= (d == 64 ? 9 : d == 96 ? 11 : d == 128 ? 14 : 16) * workgroups;
 }
 
 // Whether the read path writes its rows through to memory or leaves them to the L2 (device_util.h), by the bytes of a launch, in and
 // out.  Left to the L2 -> written through, over one / three / six sets of buffers in turn (the memory-side cache holds 256 MB):
-//   d = 32    20 MB 0.99 / 0.95 / 0.94   40 MB 0.97 / 0.84 / 1.03   60 MB 0.90 / 0.98 / 1.04   90 MB 0.83 / 1.04 / 1.00   130 MB 0.83 / 1.02 / 1.01   160 MB
-//     1.01 / 1.02 / 1.02   300 MB 1.04 / 1.04 / 1.04 (there it is the form of the store that costs: 1.05 without sc1)
-//   d = 64    45 MB 0.91 / 0.89 / 0.90   90 MB 0.89 / 1.02 / 0.99   130 MB 0.90 / 0.99 / 0.99   300 MB 0.98; 56 plans 40 MB 0.88 / 0.85 / 0.84, 80 MB 0.76 /
-//     0.95 / 0.93
+//   d = 32   20 MB 0.99 / 0.95 / 0.94   40 MB 0.97 / 0.84 / 1.03   60 MB 0.90 / 0.98 / 1.04   90 MB 0.83 / 1.04 / 1.00   130 MB
+//     0.83 / 1.02 / 1.01   160 MB 1.01 / 1.02 / 1.02   300 MB 1.04 / 1.04 / 1.04 (there it is the form of the store that costs:
+//     1.05 without sc1)
+//   d = 64   45 MB 0.91 / 0.89 / 0.90   90 MB 0.89 / 1.02 / 0.99   130 MB 0.90 / 0.99 / 0.99   300 MB 0.98; 56 plans 40 MB 0.88 /
+//     0.85 / 0.84, 80 MB 0.76 / 0.95 / 0.93
 //   d = 96    60 MB 0.87 / 0.93 / 0.98   88 MB 0.87 / 0.99 / 0.97   160 MB 0.95 / 0.98 / 0.97
-//   d = 128   40 MB 0.90 / 0.89 / 0.96   80 MB 0.80 / 1.04 / 0.99   90 MB 0.82 / 1.05 / 1.00   110 MB 0.73 / 1.01 / 1.00   300 MB 0.99; 56 plans 40 MB 0.84 / 0.83 /
-//     0.83, 80 MB 0.80 / 0.95 / 0.95; 14 ragged ones 84 MB 0.82 / 0.97 / 0.98; 8 bits 85 MB 0.91 / 0.98 / 0.97
-//   d = 256   60 MB 0.91 / 0.93 / 0.96   90 MB 0.88 / 1.02 / 1.00   160 MB 0.98 / 0.99 / 0.98; d = 160, 192 and 224 0.93 - 0.99 at all sizes
+//   d = 128   40 MB 0.90 / 0.89 / 0.96   80 MB 0.80 / 1.04 / 0.99   90 MB 0.82 / 1.05 / 1.00   110 MB 0.73 / 1.01 / 1.00   300 MB
+//     0.99; 56 plans 40 MB 0.84 / 0.83 / 0.83, 80 MB 0.80 / 0.95 / 0.95; 14 ragged ones 84 MB 0.82 / 0.97 / 0.98; 8 bits 85 MB 0.91
+//     / 0.98 / 0.97
+//   d = 256   60 MB 0.91 / 0.93 / 0.96   90 MB 0.88 / 1.02 / 1.00   160 MB 0.98 / 0.99 / 0.98; d = 160, 192 and 224 0.93 - 0.99 at
+//     all sizes
 // (One plan of 64 to 128 channels, its sets just filling the memory-side cache, is 2 to 5 % slower at 75 to 100 MB; with fewer sets the
 // same launches are 20 % faster, with more the same, several plans 5 % faster, so they have no way of their own.  sc1 without
 // nt is faster there and slower cold: d = 64 1.10 - 1.16, d = 96 1.06 - 1.09, d = 128 1.02.)
-// lines: rows of the launch start at a multiple of 64 bytes (half a line does: 64 bytes into a line 0.88 as at its start).  16 bytes into
-// a line every piece that a wavefront stores ends in a partial line: d = 32 11 MB 1.04, 33 MB 1.14, 300 MB 1.18; d = 64 and 96 the same; d =
-// 128 11 MB 1.01, 33 MB 1.11, 300 MB 1.20; d = 192 33 MB 1.04, 300 MB 1.02; d = 256 33 MB 1.01, 88 MB 1.04, 300 MB 1.05.  d = 160 and 224, which
-// the matrix cores bound, gain still (11 MB 0.92, 33 MB 0.96, 88 MB 0.98).
+// lines: all rows of the launch start at multiples of 64 bytes (half a line does: 64 bytes into a line 0.88 as at its start).  16
+// bytes into a line every piece that a wavefront stores ends in a partial line: d = 32 11 MB 1.04, 33 MB 1.14, 300 MB 1.18; d = 64
+// and 96 the same; d = 128 11 MB 1.01, 33 MB 1.11, 300 MB 1.20; d = 192 33 MB 1.04, 300 MB 1.02; d = 256 33 MB 1.01, 88 MB 1.04,
+// 300 MB 1.05.  d = 160 and 224, which the matrix cores bound, gain still (3000 vectors 0.97, 11 MB 0.92, 33 MB 0.96, 88 MB 0.98)
+// but for the shortest launches (300 vectors 1.06 and 1.12).
 constexpr bool srft_read_through(int d, bool lines, long long bytes) {
-    if (!lines) return d == 160 || d == 224;
+    if (!lines) return (d == 160 || d == 224) && bytes > 1000000;
     return d != 32 || bytes <= 140000000;
 }
 
@@ -176,10 +183,11 @@ constexpr bool srft_read_through(int d, bool lines, long long bytes) {
 // sets of buffers (the memory-side cache holds 256 MB):
 //   d = 128   11 MB 0.91 / 0.94 / 0.96   30 MB 0.95 / 0.96 / 0.96   50 MB 0.95 / 0.98 / 0.97   60 MB 0.98 / 1.00 / 0.98   80 MB 0.98 /
 //     1.02 / 1.01   154 MB 1.00 / 1.01 / 1.02   300 MB 0.99 / 1.03 / 1.02   1 GB 1.01; 56 x 8192 (154 MB) 39.7 -> 40.5 us
-//   d = 256   20 MB 0.98 / 0.98 / 0.98   100 MB 0.99 / 0.99 / 1.00   160 MB 0.97 / 0.98 / 0.98   250 MB 1.02 / 1.00 / 1.02   350 MB 1.02 /
-//     1.01 / 1.02
+//   d = 256   20 MB 0.98 / 0.98 / 0.98   100 MB 0.99 / 0.99 / 1.00   160 MB 0.97 / 0.98 / 0.98   250 MB 1.02 / 1.00 / 1.02   350 MB
+//     1.02 / 1.01 / 1.02
 // lines: the record starts at a multiple of 64 bytes.  Where it does not, 8-bit rows at d = 128 reach memory as partial lines (16 bytes
-// into a line, 33 MB 1.04, 88 MB 1.05, 300 MB 1.05); 4-bit rows and d = 256 do not mind (d = 128, 33 MB 0.96; d = 256, 8 bits, 20 MB 0.97).
+// into a line, 33 MB 1.04, 88 MB 1.05, 300 MB 1.05); 4-bit rows and d = 256 do not mind (d = 128, 33 MB 0.96; d = 256, 8 bits, 20
+// MB 0.97).
 constexpr bool srft_fold_through(int d, int bits, bool lines, long long bytes) {
     return (lines || bits == 4 || d == 256) && bytes <= (d == 128 ? 60000000 : 200000000);
 }

@@ -250,8 +250,8 @@ def test_a_plain_record_goes_through_lds_where_that_is_faster(lib, d, g, bits, w
         if again:
             assert not staged(again - 1) and staged(again)
     # 16 bytes into a line: from the lanes up to some tiles a compute unit, at d = 128 always
-    at = max(low, {64: 2048, 96: 2048, 160: 0}.get(d, 1280))
-    assert not staged(at, lines=0) and staged(at + 1, lines=0) == (d != 128) and not staged(far, lines=0)
+    at = max(low, {64: 2048, 96: 1280, 160: 0}.get(d, 1536))
+    assert not staged(at, lines=0) and staged(at + 1, lines=0) == (d != 128) and staged(far, lines=0) == (again is not None)
 
 
 def test_a_record_of_d_32_is_always_stored_from_the_lanes(lib):
@@ -265,5 +265,5 @@ def test_rows_are_written_through_where_that_is_faster(lib, d):
 
     most = 140_000_000
     assert all(through(n) == (d != 32 or n <= most) for n in (1, 10 ** 6, 8 * 10 ** 7, most, most + 1, 10 ** 10))
-    # 16 bytes into a line: only what the matrix cores bound
-    assert all(through(n, lines=0) == (d in (160, 224)) for n in (1, 10 ** 6, 10 ** 8, 10 ** 10))
+    # 16 bytes into a line: only what the matrix cores bound, and not the shortest
+    assert all(through(n, lines=0) == (d in (160, 224) and n > 10 ** 6) for n in (1, 10 ** 6, 10 ** 6 + 1, 10 ** 8, 10 ** 10))
