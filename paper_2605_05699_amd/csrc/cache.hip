@@ -124,10 +124,11 @@ static bool cache_flush(const srft_cache* c, const void* const* fresh, int t, in
     for (int i = 1; i < np; ++i)
         if (!c->plans[i]->entry || (uintptr_t)c->plans[i]->entry - (uintptr_t)c->plans[i - 1]->entry != (uintptr_t)a.plan_step) return false;
     int threads = 0;
-    const flush_kernels_t kernels = srft_plan_flush_kernels(p, &threads);
     const long long tiles = (n_vec + kTileVecs - 1) / kTileVecs;
+    const bool staged = !p->fold_q && !p->fold4_q && srft_flush_staged(p->d, tiles * np);
+    const flush_kernels_t kernels = srft_plan_flush_kernels(p, &threads, staged);
     const bool whole = kernels.whole && tiles * np <= (long long)srft_flush_whole_tiles(p->d, p->g) * p->grid_flush;
-    const long long budget = p->max_wgs > 0 ? p->max_wgs : whole ? p->grid_flush : p->grid_staged;
+    const long long budget = p->max_wgs > 0 ? p->max_wgs : whole ? p->grid_flush : staged ? p->grid_staged : p->grid_q;
     if (np > budget) return false;
     const long long blocks = std::min(tiles, budget / np);
     if (blocks * np * blocks >= (1LL << 31)) return false;

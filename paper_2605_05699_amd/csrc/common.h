@@ -262,9 +262,9 @@ dequantize_kernel_t srft_pick_dequantize_fold4(int d, int bits, bool fine, bool 
 batched_kernels_t srft_pick_dequantize_fold4_batched(int d, int bits, bool fine, bool through);
 int srft_rfold4_table_units(int d);
 // a cache's flush (cache_flush.h)
-flush_kernels_t srft_pick_cache_flush_plain(int d, int bits, int gm);
+flush_kernels_t srft_pick_cache_flush_plain(int d, int bits, int gm, bool staged);
 flush_kernels_t srft_pick_cache_flush_fold(int d, int bits, int gm, bool fold4_q);
-flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads);
+flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads, bool staged = false);
 // write path with the transform as FFT butterflies on the vector ALU (d = 128 or 256, g = 32, 4-bit; the comparison form)
 int srft_launch_quantize_butterfly(int d, const float* table_dev, const void* x, long long n_vec, uint8_t* codes,
                                    float* scales, int max_workgroups, hipStream_t st);

@@ -192,6 +192,20 @@ constexpr bool srft_fold_through(int d, int bits, bool lines, long long bytes) {
     return (lines || bits == 4 || d == 256) && bytes <= (d == 128 ? 60000000 : 200000000);
 }
 
+// Whether the record of a flush's write half, where that is a launch of its own, goes through LDS (plain form; srft_write_staged), by
+// head dimension and the tiles of all plans.  The rows are gathered here, and what follows is the read path's launch, so the line lies
+// elsewhere than for a write alone.  us of one append, record from the lanes -> through LDS:
+//   d = 64    56 plans 8 x 1000 tokens 30.4 -> 33.0
+//   d = 96    56 plans 8 x 1000 55.7 -> 50.4 (shorter ones are one launch)
+//   d = 128   (g = 16) 80 plans 2 x 320 16.3 -> 18.4, 56 plans 2 x 1000 25.3 -> 28.1, 8 x 1000 75.9 -> 80.4
+//   d = 160   2 plans 1 x 16 7.5 -> 8.1, 56 plans 2 x 16 8.05 -> 8.8, 8 x 16 8.7 -> 9.1, 2 x 100 12.3 -> 11.1, 80 plans 2 x 320 24.2 -> 22.4
+//   d = 192   2 plans 1 x 16 7.7 -> 8.4, 56 plans 2 x 16 8.9 -> 9.2, 2 x 100 11.75 -> 12.4, 2 x 1000 38.9 -> 40.2, 8 x 1000 129.8 -> 130.2
+//   d = 224   2 plans 1 x 16 9.2 -> 9.9, 56 plans 2 x 100 14.5 -> 14.9, 80 plans 2 x 320 30.5 -> 29.7, 56 plans 2 x 1000 55.5 -> 55.0
+//   d = 256   (Walsh-Hadamard) 2 plans 1 x 16 10.4 -> 10.7, 56 plans 2 x 100 16.7 -> 17.1, 80 plans 2 x 320 35.5 -> 34.9
+constexpr bool srft_flush_staged(int d, long long tiles) {
+    return d == 96 || (d == 160 && tiles > 256) || ((d == 224 || d == 256) && tiles > 1024);
+}
+
 // True when count addresses lie a constant step apart; *step is that step in bytes (0 for one).
 inline bool srft_even_step(const void* const* p, int count, long long* step) {
     *step = count > 1 ? (long long)((uintptr_t)p[1] - (uintptr_t)p[0]) : 0;

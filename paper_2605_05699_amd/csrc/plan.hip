@@ -390,13 +390,13 @@ dequantize_kernel_t srft_plan_dequantize_kernel(const srft_plan* p, int* threads
     return p->bits == 8 ? srft_pick_dequantize_b8(p->d, p->slabs_dq, p->gm, through) : srft_pick_dequantize_b4(p->d, p->slabs_dq, p->gm, through);
 }
 
-flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads) {
+flush_kernels_t srft_plan_flush_kernels(const srft_plan* p, int* threads, bool staged) {
     if (p->fold4_q || p->fold_q) {
         *threads = p->d;
         return srft_pick_cache_flush_fold(p->d, p->bits, p->gm, p->fold4_q);
     }
     *threads = 2 * p->d / p->slabs_q;
-    flush_kernels_t k = srft_pick_cache_flush_plain(p->d, p->bits, p->gm);
+    flush_kernels_t k = srft_pick_cache_flush_plain(p->d, p->bits, p->gm, staged);
     if (p->fold_dq || p->fold4_dq) k.whole = nullptr;        // (the read path that goes with it there is the plain one)
     return k;
 }

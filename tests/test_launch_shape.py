@@ -34,6 +34,7 @@ extern "C" int write_staged(int d, int g, int bits, int lines, long long tiles, 
     return srft_write_staged(d, g, bits, lines, tiles, workgroups, units);
 }
 extern "C" int read_through(int d, int lines, long long bytes) { return srft_read_through(d, lines, bytes); }
+extern "C" int flush_staged(int d, long long tiles) { return srft_flush_staged(d, tiles); }
 extern "C" int fold_through(int d, int bits, int lines, long long bytes) { return srft_fold_through(d, bits, lines, bytes); }
 extern "C" int copy_launches(int t) { return srft_copy_launches(t); }
 extern "C" long long copy_first(int i) { return srft_copy_first(i); }
@@ -267,3 +268,9 @@ def test_rows_are_written_through_where_that_is_faster(lib, d):
     assert all(through(n) == (d != 32 or n <= most) for n in (1, 10 ** 6, 8 * 10 ** 7, most, most + 1, 10 ** 10))
     # 16 bytes into a line: only what the matrix cores bound, and not the shortest
     assert all(through(n, lines=0) == (d in (160, 224) and n > 10 ** 6) for n in (1, 10 ** 6, 10 ** 6 + 1, 10 ** 8, 10 ** 10))
+
+
+@pytest.mark.parametrize("d,last", [(32, None), (64, None), (96, 0), (128, None), (160, 256), (192, None), (224, 1024), (256, 1024)])
+def test_a_flush_sends_its_record_through_lds_where_that_is_faster(lib, d, last):
+    staged = [bool(lib.flush_staged(d, C.c_longlong(t))) for t in (1, 56, 256, 257, 1024, 1025, 10 ** 6)]
+    assert staged == [last is not None and t > last for t in (1, 56, 256, 257, 1024, 1025, 10 ** 6)]
