@@ -178,9 +178,10 @@ def test_new_tokens_are_copied_to_their_place(B, d, n_plans, n_seq, R, schedule)
         assert bool((view[:, T:] == 3.0).all())
 
 
-# One launch, two, and three.  Flushes of one tile and less; of many tiles, where the read path is a launch of its own from
-# 1, 4 or 8 tiles per resident workgroup on (d = 128 with g = 16, d = 256, d = 128 and 64); forms whose two paths' workgroups
-# differ (d = 192, d = 256 with g = 16); windows that held tokens before; and buffers that lie a constant step apart or not.
+# One launch, two, and three.  Flushes of one tile and less; of many tiles, where the read path is a launch of its own: more than 1, 4 or 8
+# tiles for each workgroup that the chip holds (d = 128 with g = 16; d = 256 and 32; d = 128, 96 and 64, with 5000 tokens and more here);
+# forms without a launch for both paths (d = 160, 192, 224, Walsh-Hadamard at d = 256), the record from the lanes and through LDS;
+# windows that held tokens before; and buffers that lie a constant step apart or not.
 @pytest.mark.parametrize("even", [True, False])
 @pytest.mark.parametrize("d,g,bits,transform,R,n_seq,schedule", [
     (128, 32, 4, "dft", 16, 2, [5, 11, 1, 70]), (128, 32, 8, "dft", 16, 3, [100, 1]), (128, 128, 4, "dft", 5, 2, [3, 3, 31]),
@@ -190,6 +191,10 @@ def test_new_tokens_are_copied_to_their_place(B, d, n_plans, n_seq, R, schedule)
     (64, 32, 4, "dft", 16, 1, [20, 12]), (64, 16, 8, "dft", 3, 5, [8, 2]), (64, 64, 4, "dft", 16, 2, [47]), (96, 32, 4, "dft", 16, 6, [1, 100]),
     (96, 96, 8, "dft", 1, 2, [1, 2]), (32, 32, 4, "dft", 16, 2, [18]), (192, 32, 4, "dft", 16, 2, [17, 40]), (160, 16, 8, "dft", 16, 2, [35]),
     (224, 224, 4, "dft", 16, 1, [33]),
+    (64, 32, 4, "dft", 16, 32, [7, 6000]), (64, 16, 8, "dft", 16, 32, [6001]), (64, 64, 4, "dft", 16, 32, [15, 6001]), (96, 32, 4, "dft", 16, 32, [3, 6000]),
+    (96, 16, 4, "dft", 16, 32, [6001]), (96, 96, 8, "dft", 16, 32, [6001]), (32, 32, 4, "dft", 16, 16, [5, 6000]), (32, 16, 8, "dft", 16, 16, [6001]),
+    (128, 16, 8, "dft", 16, 8, [11, 1100]), (160, 32, 4, "dft", 16, 8, [9, 500]), (160, 160, 8, "dft", 16, 8, [500]), (192, 16, 4, "dft", 16, 16, [9, 800]),
+    (224, 16, 8, "dft", 16, 16, [9, 800]), (224, 32, 4, "dft", 16, 16, [800]), (256, 32, 4, "hadamard", 16, 16, [9, 800]), (256, 256, 8, "hadamard", 16, 16, [800]),
 ])
 def test_a_flush_stores_and_shows_what_the_plans_own_paths_give(B, d, g, bits, transform, R, n_seq, schedule, even):
     n_plans, T = 3, sum(schedule)
