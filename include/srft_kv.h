@@ -237,9 +237,12 @@ int srft_kv_scores_static(const srft_plan_t* plan, const void* q_f16_dev, int n_
  * srft_cache_append   new_f16_dev: host array of n_plans device pointers, each [n_seq, t, d] fp16 (16-byte
  *                     aligned): t new tokens per sequence.  Enqueues a copy of the tokens into the view or, if one or
  *                     more pages became full, their quantization over all plans, out of the new tokens and of what the
- *                     window holds, and their decoding into the view, in one launch or two (three where the plans'
- *                     buffers do not lie a constant step apart).  Exceeding the capacity is SRFT_ERR_BAD_N
- *                     (nothing is enqueued).  The result does not depend on how the tokens are split into calls.
+ *                     window holds, and their decoding into the view, in one launch or two.  That takes addresses of
+ *                     the plans' buffers and of the plans' device constants that lie a constant step apart, no more
+ *                     plans than workgroups (srft_plan_set_max_workgroups), and pages and calls whose rows and 16-byte
+ *                     units 32-bit numbers count; else it is a copy, a quantization and a decoding, each one launch
+ *                     for every 64 plans.  Exceeding the capacity is SRFT_ERR_BAD_N (nothing is enqueued).  The result
+ *                     does not depend on how the tokens are split into calls.
  * srft_cache_rebuild_view  dequantizes the whole store into the view again (for a caller that dropped or
  *                     overwrote the view); O(prefix).  The window part of the view is not touched.
  * Calls on one cache must be made from one thread at a time and enqueued on one stream (or ordered by the caller).

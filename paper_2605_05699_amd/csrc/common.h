@@ -151,7 +151,7 @@ struct srft_flush {
 };
 struct flush_kernels_t {
     typedef void (*kernel)(const srft_flush);
-    kernel write, whole;                    // without and with the read path (null where the two paths' workgroups differ in size)
+    kernel write, whole;                    // without and with the read path (null at d = 160, 192, 224 and plain d = 256: not built)
     flush_kernels_t(std::nullptr_t = nullptr) : write(nullptr), whole(nullptr) {}
     flush_kernels_t(kernel w, kernel all) : write(w), whole(all) {}
 };

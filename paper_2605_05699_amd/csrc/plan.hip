@@ -495,7 +495,8 @@ static int plan_create(srft_plan_t** out, int d, int group_size, int bits, int t
         }
 
     // Slabs of the matrix per wavefront.  Two at d = 64, where a workgroup of one wavefront per slab has too little to do.
-    // (At d = 256 two slabs leave one wavefront per SIMD: read at g = 16, 600,961 vectors, 220 us against 188 with one slab.)
+    // (At d = 256, where only Walsh-Hadamard runs the plain read form, two slabs leave one wavefront per SIMD: with the DFT's dense matrix
+    // at g = 16, 600,961 vectors, 220 us against 188 with one slab.)
     p->slabs_q = (d == 64) ? 2 : 1;
     p->slabs_dq = (d == 64) ? 2 : 1;
     // Folded read path where it applies and pays (d = 192); d = 128 and 256 have the twice-folded form below.
