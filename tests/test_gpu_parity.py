@@ -585,7 +585,7 @@ def test_a_record_is_the_same_whichever_way_it_is_stored(B, d, g, bits, transfor
 
 
 # ... and by a launch's size and the place its results start at (16, 48 and 64 bytes into a line), alone, as plans a constant step
-# apart and as a table of ragged parts: `many` lies beyond the last size that is written through.  Compared with short launches into
+# apart and as a short and a long table of ragged parts: `many` lies beyond the last size that is written through.  Compared with short launches into
 # buffers of their own.
 WAYS = [(128, 32, 4, "dft", 180_000), (128, 32, 8, "dft", 152_000), (128, 128, 4, "dft", 186_000), (256, 64, 4, "dft", 306_000), (256, 128, 8, "dft", 252_000),
         (64, 32, 4, "dft", 590_000), (64, 64, 8, "dft", 100_000), (96, 32, 4, "dft", 451_000), (96, 96, 8, "dft", 100_000), (96, 16, 4, "dft", 902_000),
@@ -621,7 +621,7 @@ def test_results_are_the_same_whatever_their_size_and_place(B, d, g, bits, trans
         c, cf = room(n, row, torch.uint8, lead)
         s, sf = room(n, ns, torch.float32, 4 * (lead // 16))
         v, vf = room(n, d, torch.float16, lead)
-        for parts in ([n], [n // 3] * 3, [n // 2, 0, n // 5, 1, n - n // 2 - n // 5 - 1]):
+        for parts in ([n], [n // 3] * 3, [n // 2, 0, n // 5, 1, n - n // 2 - n // 5 - 1], [n // 13 + 5 * k for k in range(12)]):
             k = sum(parts)
             for t in (cf, sf, vf):
                 t.fill_(9)
