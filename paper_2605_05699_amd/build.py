@@ -58,19 +58,23 @@ def _object(src: str, force: bool, verbose: bool, extra: list[str]) -> str:
     return obj
 
 
-def _marshal(force: bool, verbose: bool) -> None:
-    """The CPython extension that binding.py calls: torch's headers, no HIP code."""
-    if not force and os.path.exists(LIB_MARSHAL) and os.path.getmtime(LIB_MARSHAL) > max(os.path.getmtime(f) for f in (SRC_MARSHAL, os.path.abspath(__file__))):
-        return
+def _marshal_command(include: str = os.path.join(ROOT, "include")) -> list[str]:
     import sysconfig
     import torch
     at = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
-    _run([shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", sysconfig.get_paths()["include"],
-          "-isystem", os.path.join(at, "include"), "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
-          "-isystem", os.path.join(rocm, "include"), SRC_MARSHAL, "-o", LIB_MARSHAL, "-L", os.path.join(at, "lib"),
-          "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], verbose)
+    return [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", sysconfig.get_paths()["include"],
+            "-isystem", os.path.join(at, "include"), "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
+            "-isystem", os.path.join(rocm, "include"), "-I", include, SRC_MARSHAL, "-L", os.path.join(at, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
+def _marshal(force: bool, verbose: bool) -> None:
+    """The CPython extension that binding.py calls: torch's headers, no HIP code."""
+    newest = max(os.path.getmtime(f) for f in (SRC_MARSHAL, *HEADERS, os.path.abspath(__file__)))
+    if force or not os.path.exists(LIB_MARSHAL) or os.path.getmtime(LIB_MARSHAL) < newest:
+        _run([*_marshal_command(), "-shared", "-o", LIB_MARSHAL], verbose)
 
 
 def build(verbose: bool = False, extra: list[str] | None = None, force: bool = True, jobs: int | None = None) -> str:

@@ -17,37 +17,31 @@
 #include <cstdint>
 #include <cstring>
 
+#include "srft_kv.h"
+
 namespace {
 
-// ---- the C entry points, bound by binding.lib() when it loads the library
-typedef int (*move_t)(const void*, const void*, int64_t, void*, float*, void*);
-typedef int (*back_t)(const void*, const void*, const void*, int64_t, void*, void*);
-typedef int (*move_batched_t)(const void*, const void*, const void*, const void*, const void*, int, void*);
-typedef int (*scores_t)(const void*, const void*, int, const void*, const void*, int64_t, void*, void*, void*);
-typedef int (*attention_t)(const void*, const void*, const void*, int, const void*, const void*, const void*, const void*, int64_t, float, void*, void*, void*);
-typedef int (*absmax_t)(const void*, const void*, int64_t, void*, void*);
-typedef int (*append_t)(void*, const void*, int, void*);
-typedef int64_t (*bytes_plan_t)(const void*);
-typedef int64_t (*bytes_attention_t)(const void*, const void*, int, int64_t);
-typedef int (*plan_d_t)(const void*);
+// ---- the C entry points, bound by binding.lib() when it loads the library; their types are the header's
 struct {
-    move_t quantize;
-    back_t dequantize;
-    move_batched_t quantize_batched, dequantize_batched;
-    scores_t scores;
-    attention_t attention;
-    absmax_t absmax;
-    append_t append;
-    bytes_plan_t scores_bytes;
-    bytes_attention_t attention_bytes;
-    plan_d_t plan_d;
+    decltype(&srft_kv_quantize) quantize;
+    decltype(&srft_kv_dequantize) dequantize;
+    decltype(&srft_kv_quantize_batched) quantize_batched;
+    decltype(&srft_kv_dequantize_batched) dequantize_batched;
+    decltype(&srft_kv_scores) scores;
+    decltype(&srft_kv_decode_attention) attention;
+    decltype(&srft_kv_channel_absmax) absmax;
+    decltype(&srft_cache_append) append;
+    decltype(&srft_scores_workspace_bytes) scores_bytes;
+    decltype(&srft_decode_attention_workspace_bytes) attention_bytes;
+    decltype(&srft_plan_d) plan_d;
     bool bound;
 } g;
 
 // ---- arguments
-bool handle_of(PyObject* o, const void** p) {                // a plan: the address as an int
+template <class T>
+bool handle_of(PyObject* o, T** p) {                         // a plan: the address as an int
     if (!PyLong_CheckExact(o)) return false;
-    *p = PyLong_AsVoidPtr(o);
+    *p = (T*)PyLong_AsVoidPtr(o);
     if (*p || !PyErr_Occurred()) return true;
     PyErr_Clear();
     return false;
@@ -71,6 +65,8 @@ bool address_of(PyObject* o, void** p) {                     // of a ctypes arra
     PyBuffer_Release(&b);
     return true;
 }
+uint8_t* codes_of(const at::Tensor* t) { return static_cast<uint8_t*>(t->data_ptr()); }
+float* floats_of(const at::Tensor* t) { return static_cast<float*>(t->data_ptr()); }
 void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 // Runs `body` (true: the call was made, its status in *rc), turning what it throws into "not made".
@@ -98,24 +94,28 @@ int64_t bytes_of(const at::Tensor& t) { return t.numel() * (int64_t)t.element_si
 // quantize(plan, x, codes, scales)
 PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return made([&](int* rc) {
-        const void* plan;
+        const srft_plan_t* plan;
         if (n != 4 || !handle_of(a[0], &plan)) return false;
         const at::Tensor *x = tensor_of(a[1], at::kHalf), *c = tensor_of(a[2], at::kByte), *s = tensor_of(a[3], at::kFloat);
         if (!x || !c || !s || x->dim() < 1) return false;
-        void *const xp = x->data_ptr(), *const cp = c->data_ptr(), *const sp = s->data_ptr(), *const st = current_stream();
+        void *const xp = x->data_ptr(), *const st = current_stream();
+        uint8_t* const cp = codes_of(c);
+        float* const sp = floats_of(s);
         const int64_t count = x->size(0);
-        *rc = without_gil([&] { return g.quantize(plan, xp, count, cp, (float*)sp, st); });
+        *rc = without_gil([&] { return g.quantize(plan, xp, count, cp, sp, st); });
         return true;
     });
 }
 // dequantize(plan, codes, scales, out)
 PyObject* dequantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return made([&](int* rc) {
-        const void* plan;
+        const srft_plan_t* plan;
         if (n != 4 || !handle_of(a[0], &plan)) return false;
         const at::Tensor *c = tensor_of(a[1], at::kByte), *s = tensor_of(a[2], at::kFloat), *o = tensor_of(a[3], at::kHalf);
         if (!c || !s || !o || c->dim() < 1) return false;
-        void *const cp = c->data_ptr(), *const sp = s->data_ptr(), *const op = o->data_ptr(), *const st = current_stream();
+        const uint8_t* const cp = codes_of(c);
+        const float* const sp = floats_of(s);
+        void *const op = o->data_ptr(), *const st = current_stream();
         const int64_t count = c->size(0);
         *rc = without_gil([&] { return g.dequantize(plan, cp, sp, count, op, st); });
         return true;
@@ -138,8 +138,10 @@ PyObject* batched(PyObject* table, bool write) {
         if (count < 0 || count > INT32_MAX) return false;
         void* const st = current_stream();
         *rc = without_gil([&] {
-            return write ? g.quantize_batched(p[0], p[1], p[4], p[2], p[3], (int)count, st)
-                         : g.dequantize_batched(p[0], p[2], p[3], p[4], p[1], (int)count, st);
+            const auto plans = (const srft_plan_t* const*)p[0];
+            const auto n_vec = (const int64_t*)p[4];
+            return write ? g.quantize_batched(plans, (const void* const*)p[1], n_vec, (uint8_t* const*)p[2], (float* const*)p[3], (int)count, st)
+                         : g.dequantize_batched(plans, (const uint8_t* const*)p[2], (const float* const*)p[3], n_vec, (void* const*)p[1], (int)count, st);
         });
         return true;
     });
@@ -152,7 +154,7 @@ PyObject* dequantize_batched(PyObject*, PyObject* table) { return batched(table,
 // scores(plan, q, codes, scales, scores, workspace)
 PyObject* scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return made([&](int* rc) {
-        const void* plan;
+        const srft_plan_t* plan;
         if (n != 6 || !handle_of(a[0], &plan) || !plan || !THPVariable_CheckExact(a[5])) return false;
         const at::Tensor *q = tensor_of(a[1], at::kHalf), *c = tensor_of(a[2], at::kByte), *s = tensor_of(a[3], at::kFloat),
                          *o = tensor_of(a[4], at::kFloat), *w = tensor_of(a[5], THPVariable_Unpack(a[5]).scalar_type());
@@ -160,8 +162,10 @@ PyObject* scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
             bytes_of(*w) < g.scores_bytes(plan))
             return false;
         const int64_t n_q = q->size(0), keys = c->size(0);
-        void *const qp = q->data_ptr(), *const cp = c->data_ptr(), *const sp = s->data_ptr(), *const op = o->data_ptr(), *const wp = w->data_ptr(),
-             *const st = current_stream();
+        const uint8_t* const cp = codes_of(c);
+        const float* const sp = floats_of(s);
+        float* const op = floats_of(o);
+        void *const qp = q->data_ptr(), *const wp = w->data_ptr(), *const st = current_stream();
         if (n_q > INT32_MAX) return false;
         *rc = without_gil([&] { return g.scores(plan, qp, (int)n_q, cp, sp, keys, op, wp, st); });
         return true;
@@ -170,7 +174,7 @@ PyObject* scores(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // attention(plan_k, plan_v, q, k_codes, k_scales, v_codes, v_scales, softmax_scale, out, workspace)
 PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return made([&](int* rc) {
-        const void *pk, *pv;
+        const srft_plan_t *pk, *pv;
         if (n != 10 || !handle_of(a[0], &pk) || !handle_of(a[1], &pv) || !pk || !pv || !PyFloat_CheckExact(a[7]) || !THPVariable_CheckExact(a[9])) return false;
         const at::Tensor *q = tensor_of(a[2], at::kHalf), *kc = tensor_of(a[3], at::kByte), *ks = tensor_of(a[4], at::kFloat), *vc = tensor_of(a[5], at::kByte),
                          *vs = tensor_of(a[6], at::kFloat), *o = tensor_of(a[8], at::kFloat), *w = tensor_of(a[9], THPVariable_Unpack(a[9]).scalar_type());
@@ -178,8 +182,10 @@ PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t n_q = q->size(0), keys = kc->size(0);
         if (n_q > INT32_MAX || bytes_of(*w) < g.attention_bytes(pk, pv, (int)n_q, keys)) return false;
         const float scale = (float)PyFloat_AS_DOUBLE(a[7]);
-        void *const qp = q->data_ptr(), *const kcp = kc->data_ptr(), *const ksp = ks->data_ptr(), *const vcp = vc->data_ptr(), *const vsp = vs->data_ptr(),
-             *const op = o->data_ptr(), *const wp = w->data_ptr(), *const st = current_stream();
+        const uint8_t *const kcp = codes_of(kc), *const vcp = codes_of(vc);
+        const float *const ksp = floats_of(ks), *const vsp = floats_of(vs);
+        float* const op = floats_of(o);
+        void *const qp = q->data_ptr(), *const wp = w->data_ptr(), *const st = current_stream();
         *rc = without_gil([&] { return g.attention(pk, pv, qp, (int)n_q, kcp, ksp, vcp, vsp, keys, scale, op, wp, st); });
         return true;
     });
@@ -187,12 +193,13 @@ PyObject* attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // absmax(plan, x, amax)
 PyObject* absmax(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return made([&](int* rc) {
-        const void* plan;
+        const srft_plan_t* plan;
         if (n != 3 || !handle_of(a[0], &plan) || !plan) return false;
         const at::Tensor *x = tensor_of(a[1], at::kHalf), *m = tensor_of(a[2], at::kFloat);
         if (!x || !m || x->dim() < 1 || m->numel() != g.plan_d(plan)) return false;
         const int64_t count = x->size(0);
-        void *const xp = x->data_ptr(), *const mp = m->data_ptr(), *const st = current_stream();
+        void *const xp = x->data_ptr(), *const st = current_stream();
+        float* const mp = floats_of(m);
         *rc = without_gil([&] { return g.absmax(plan, xp, count, mp, st); });
         return true;
     });
@@ -225,7 +232,7 @@ PyObject* append_call(PyObject* self, PyObject* const* a, Py_ssize_t n, PyObject
         pointer_of(a[3], cell, array, &st)) {
         int overflow;
         const long t = PyLong_AsLongAndOverflow(a[2], &overflow);
-        if (!overflow && t == (int)t) return PyLong_FromLong(without_gil([&] { return g.append(cache, fresh, (int)t, st); }));
+        if (!overflow && t == (int)t) return PyLong_FromLong(without_gil([&] { return g.append((srft_cache_t*)cache, (const void* const*)fresh, (int)t, st); }));
     }
     return PyObject_Vectorcall(ctypes_call, a, n, names);
 }

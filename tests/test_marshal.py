@@ -1,12 +1,15 @@
 """The native marshalling (csrc/host/marshal.cpp) against the calls through ctypes that it stands in front of."""
 import ctypes as C
 import importlib.util
+import subprocess
+from pathlib import Path
 
 import numpy as np
 import pytest
 import torch
 
 from paper_2605_05699_amd import binding as B
+from paper_2605_05699_amd import build as build_module
 
 FAST = ("quantize", "dequantize", "scores", "attention", "absmax", "quantize_batched", "dequantize_batched")
 
@@ -52,6 +55,16 @@ def test_what_is_set_on_append_holds_for_its_calls():
     del f.errcheck
     assert f(None, None, 1.5, None) == -1
     assert B.lib().srft_cache_append(None, None, 1, None) == -1                       # (another library object's is as it was)
+
+
+def test_a_changed_entry_point_does_not_compile(tmp_path):
+    """The types of the entry points are the header's: a parameter more in one of them is an error of the compiler."""
+    text = (Path(build_module.ROOT) / "include" / "srft_kv.h").read_text()
+    changed = text.replace("int srft_kv_channel_absmax(const srft_plan_t* plan, ", "int srft_kv_channel_absmax(const srft_plan_t* plan, int flags, ")
+    assert changed != text
+    (tmp_path / "srft_kv.h").write_text(changed)
+    r = subprocess.run([*build_module._marshal_command(str(tmp_path)), "-fsyntax-only"], capture_output=True, text=True)
+    assert r.returncode != 0 and "absmax" in r.stderr and "too few arguments" in r.stderr
 
 
 @pytest.mark.parametrize("args", [("quantize", 4), ("dequantize", 4), ("scores", 6), ("attention", 10), ("absmax", 3)])
