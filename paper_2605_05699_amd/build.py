@@ -1,5 +1,5 @@
 """Build libsrft_kv.so (the product) and libsrft_measure.so (measurement aids) in-tree with hipcc, for gfx950, and the
-binding's native marshalling (_marshal.so, host code) with g++.
+binding's native marshalling (_marshal, a CPython extension, host code) with g++.
 
 Every translation unit under csrc/ is compiled to an object of its own (in parallel), then linked; objects whose
 source and headers are older than they are are reused unless ``force`` is set.
@@ -11,6 +11,7 @@ import glob
 import os
 import shutil
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -19,7 +20,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsrft_kv.so")
 LIB_MEASURE = os.path.join(PKG, "libsrft_measure.so")
 SRC_MARSHAL = os.path.join(CSRC, "host", "marshal.cpp")
-LIB_MARSHAL = os.path.join(PKG, "_marshal.so")
+LIB_MARSHAL = os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))      # (of this interpreter, and found by no other)
 SRC = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "kernels", "*.hip")))
 SRC_MEASURE = sorted(glob.glob(os.path.join(CSRC, "measure", "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(ROOT, "include", "*.h")))
@@ -59,7 +60,6 @@ def _object(src: str, force: bool, verbose: bool, extra: list[str]) -> str:
 
 
 def _marshal_command(include: str = os.path.join(ROOT, "include")) -> list[str]:
-    import sysconfig
     import torch
     at = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
@@ -73,6 +73,8 @@ def _marshal_command(include: str = os.path.join(ROOT, "include")) -> list[str]:
 def _marshal(force: bool, verbose: bool) -> None:
     """The CPython extension that binding.py calls: torch's headers, no HIP code."""
     newest = max(os.path.getmtime(f) for f in (SRC_MARSHAL, *HEADERS, os.path.abspath(__file__)))
+    if os.path.exists(untagged := os.path.join(PKG, "_marshal.so")):       # (from builds that named it so: any interpreter would load it)
+        os.remove(untagged)
     if force or not os.path.exists(LIB_MARSHAL) or os.path.getmtime(LIB_MARSHAL) < newest:
         _run([*_marshal_command(), "-shared", "-o", LIB_MARSHAL], verbose)
 

@@ -2,6 +2,7 @@
 import ctypes as C
 import importlib.util
 import subprocess
+import sysconfig
 from pathlib import Path
 
 import numpy as np
@@ -16,6 +17,11 @@ FAST = ("quantize", "dequantize", "scores", "attention", "absmax", "quantize_bat
 
 def test_it_is_built():
     assert B._marshal is not None
+
+
+def test_it_is_named_for_its_interpreter():
+    assert B._marshal.__file__ == build_module.LIB_MARSHAL and B._marshal.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert not (Path(build_module.PKG) / "_marshal.so").exists()
 
 
 def test_append_takes_what_ctypes_takes():
