@@ -70,8 +70,26 @@ def _marshal_command(include: str = os.path.join(ROOT, "include")) -> list[str]:
             "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
+def _marshal_lacks() -> str:
+    """What the extension needs and is not there ("": nothing)."""
+    try:
+        import torch
+    except ImportError:
+        return "torch"
+    headers = [os.path.join(sysconfig.get_paths()["include"], "Python.h"),
+               os.path.join(os.path.dirname(torch.__file__), "include", "torch", "csrc", "autograd", "python_variable.h")]
+    missing = [] if shutil.which("g++") or shutil.which("c++") else ["g++"]
+    return ", ".join(missing + [h for h in headers if not os.path.exists(h)])
+
+
 def _marshal(force: bool, verbose: bool) -> None:
-    """The CPython extension that binding.py calls: torch's headers, no HIP code."""
+    """The CPython extension that binding.py calls: torch's headers, no HIP code.  Where a compiler or headers for it are missing the
+    libraries are built all the same, and the binding makes every call through ctypes."""
+    if lacks := _marshal_lacks():
+        print(f"_marshal is not built, calls go through ctypes: no {lacks}", flush=True)
+        if os.path.exists(LIB_MARSHAL):
+            os.remove(LIB_MARSHAL)                             # (one of other sources)
+        return
     newest = max(os.path.getmtime(f) for f in (SRC_MARSHAL, *HEADERS, os.path.abspath(__file__)))
     if os.path.exists(untagged := os.path.join(PKG, "_marshal.so")):       # (from builds that named it so: any interpreter would load it)
         os.remove(untagged)

@@ -2,6 +2,7 @@
 import ctypes as C
 import importlib.util
 import subprocess
+import sys
 import sysconfig
 from pathlib import Path
 
@@ -71,6 +72,26 @@ def test_a_changed_entry_point_does_not_compile(tmp_path):
     (tmp_path / "srft_kv.h").write_text(changed)
     r = subprocess.run([*build_module._marshal_command(str(tmp_path)), "-fsyntax-only"], capture_output=True, text=True)
     assert r.returncode != 0 and "absmax" in r.stderr and "too few arguments" in r.stderr
+
+
+def test_the_libraries_are_built_without_a_compiler_for_it(monkeypatch, tmp_path, capsys):
+    stale = tmp_path / "_marshal.so"
+    stale.write_bytes(b"of other sources")
+    monkeypatch.setattr(build_module, "LIB_MARSHAL", str(stale))
+    monkeypatch.setattr(build_module.shutil, "which", lambda name: None)
+    build_module._marshal(True, False)
+    assert not stale.exists() and "g++" in capsys.readouterr().out
+
+
+def test_the_binding_works_without_it():
+    code = """
+import sys
+sys.modules["paper_2605_05699_amd._marshal"] = None
+from paper_2605_05699_amd import binding as B
+assert B._marshal is None and B._fast_quantize(1, 2, 3, 4) is None
+assert B.lib().srft_cache_append(None, None, 1, None) == -1
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=build_module.ROOT)
 
 
 @pytest.mark.parametrize("args", [("quantize", 4), ("dequantize", 4), ("scores", 6), ("attention", 10), ("absmax", 3)])
