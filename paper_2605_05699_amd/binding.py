@@ -54,12 +54,12 @@ def _native_append(L: C.CDLL) -> None:
         _flags_, _restype_ = L._FuncPtr._flags_, L._FuncPtr._restype_
 
         def __setattr__(self, name, value):            # argtypes, restype, errcheck: from here on ctypes makes the calls
-            Function.__call__ = L._FuncPtr.__call__
+            _marshal.append(Function)
             L._FuncPtr.__setattr__(self, name, value)
 
     native = Function((plain.__name__, L))
     native.argtypes, native.restype, native.__name__ = plain.argtypes, plain.restype, plain.__name__
-    Function.__call__ = _marshal.append(L._FuncPtr.__call__.__get__(native), C.c_void_p, C.Array)
+    _marshal.append(Function, C.c_void_p, C.Array)
     L.srft_cache_append = native
 
 

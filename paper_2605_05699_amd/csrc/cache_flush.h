@@ -9,12 +9,13 @@
 // one allocation, their LDS adds up (60 KB at d = 128, 148 KB at d = 256), so from a few tiles per workgroup on the read path,
 // which could have more workgroups, is a launch of its own (srft_flush_whole_tiles).  Device time of one append over 56 plans, us,
 // copy + quantizer + read path -> write half, read path apart / whole:
-//   d = 128   2 x 16 tokens 9.0 -> 6.9 / 5.4    2 x 256 16.5 -> 11.5 / 8.5   2 x 1000 32.7 -> 24.3 / 22.4   8 x 1000 99.7 -> 61.6 / 72.5
-//   d = 256   2 x 16 10.9 -> 8.4 / 6.9          2 x 320 28.0 -> 20.7 / 20.2  2 x 1000 59.4 -> 41.5 / 49.0   8 x 3000 641 -> 396 / 504
-//   d = 96    2 x 16 7.9 -> 6.0 / 4.4           2 x 400 18.3 -> 13.4 / 9.2   3 x 1000 40.1 -> 30.4 / 24.0   8 x 3000 254 -> 164 / 144
-//   d = 64    2 x 16 7.8 -> 6.1 / 4.6           3 x 1000 25.1 -> 19.1 / 17.1 8 x 3000 139 -> 87 / 91
-//   d = 128, g = 16   2 x 128 12.7 -> 8.9 / 7.1    2 x 256 17.5 -> 12.7 / 13.0    2 x 500 23.2 -> 17.5 / 19.4
-//   d = 32    2 x 16 6.8 -> 5.0 / 3.5           3 x 1000 15.6 -> 10.2 / 9.1  8 x 1000 26.7 -> 19.3 / 19.5   8 x 3000 70.9 -> 40.5 / 47.0
+//   d = 128   2 x 16 tokens 8.95 -> 7.2 / 6.0   2 x 256 16.6 -> 10.7 / 8.7    2 x 1000 33.5 -> 22.6 / 23.2   8 x 1000 103 -> 63 / 74
+//   d = 256   2 x 16 10.9 -> 8.7 / 7.4          2 x 320 27.7 -> 19.7 / 19.9   2 x 500 36.4 -> 24.9 / 29.2    8 x 3000 644 -> 389 / 509
+//     g = 16  2 x 128 20.0 -> 12.4 / 11.2       2 x 256 29.4 -> 16.8 / 17.8   2 x 1000 84.5 -> 43.3 / 56.0
+//   d = 96    2 x 16 8.2 -> 6.4 / 4.6           2 x 500 19.6 -> 13.3 / 12.0   3 x 1000 41.3 -> 26.0 / 24.2   8 x 3000 261 -> 145 / 147
+//   d = 64    2 x 16 7.9 -> 6.2 / 4.7           3 x 1000 26.9 -> 17.6 / 17.0  8 x 1000 56.2 -> 32.2 / 33.9   8 x 3000 143 -> 90 / 92
+//   d = 128, g = 16   2 x 128 12.8 -> 8.7 / 7.1    2 x 256 17.6 -> 12.2 / 12.9    2 x 500 24.7 -> 17.4 / 19.7
+//   d = 32    2 x 16 6.85 -> 5.0 / 3.6          3 x 1000 15.4 -> 10.1 / 9.2   8 x 1000 29.5 -> 17.9 / 19.7   8 x 3000 76.4 -> 40.3 / 47.9
 #ifndef SRFT_CACHE_FLUSH_H
 #define SRFT_CACHE_FLUSH_H
 #include "dequantize_fold4_tiles.h"

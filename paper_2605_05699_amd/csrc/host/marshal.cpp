@@ -205,49 +205,57 @@ PyObject* absmax(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// ---- lib().srft_cache_append, a ctypes function whose calls come here first: those with other arguments than None, ints, c_void_p and
-// arrays of them go on to ctypes
-bool pointer_of(PyObject* o, PyObject* cell_type, PyObject* array_type, void** p) {
+// ---- lib().srft_cache_append, a ctypes function of a type of its own whose calls come here first: those with other arguments than
+// None, ints, c_void_p and arrays of them go on to ctypes.  (As the type's slot: by way of a __call__ in Python's sight a call took 0.03 us
+// more.)
+PyTypeObject *cell_type, *array_type;                        // ctypes.c_void_p and ctypes.Array
+bool pointer_of(PyObject* o, void** p) {
     if (o == Py_None) {
         *p = nullptr;
         return true;
     }
-    const void* v;
-    if (handle_of(o, &v)) {
-        *p = const_cast<void*>(v);
-        return true;
-    }
-    const bool cell = (PyObject*)Py_TYPE(o) == cell_type;
-    if (!cell && !PyObject_TypeCheck(o, (PyTypeObject*)array_type)) return false;
+    if (handle_of(o, p)) return true;
+    const bool cell = Py_TYPE(o) == cell_type;
+    if (!cell && !PyObject_TypeCheck(o, array_type)) return false;
     void* at;
     if (!address_of(o, &at)) return false;
     if (cell) std::memcpy(p, at, sizeof(*p));
     else *p = at;
     return true;
 }
-PyObject* append_call(PyObject* self, PyObject* const* a, Py_ssize_t n, PyObject* names) {
-    PyObject *const ctypes_call = PyTuple_GET_ITEM(self, 0), *const cell = PyTuple_GET_ITEM(self, 1), *const array = PyTuple_GET_ITEM(self, 2);
+PyObject* append_call(PyObject* self, PyObject* args, PyObject* names) {
     void *cache, *fresh, *st;
-    if (n == 4 && !names && g.bound && pointer_of(a[0], cell, array, &cache) && pointer_of(a[1], cell, array, &fresh) && PyLong_CheckExact(a[2]) &&
-        pointer_of(a[3], cell, array, &st)) {
-        int overflow;
-        const long t = PyLong_AsLongAndOverflow(a[2], &overflow);
-        if (!overflow && t == (int)t) return PyLong_FromLong(without_gil([&] { return g.append((srft_cache_t*)cache, (const void* const*)fresh, (int)t, st); }));
+    if (PyTuple_GET_SIZE(args) == 4 && !names && g.bound) {
+        PyObject* const* a = &PyTuple_GET_ITEM(args, 0);
+        if (pointer_of(a[0], &cache) && pointer_of(a[1], &fresh) && PyLong_CheckExact(a[2]) && pointer_of(a[3], &st)) {
+            int overflow;
+            const long t = PyLong_AsLongAndOverflow(a[2], &overflow);
+            if (!overflow && t == (int)t)
+                return PyLong_FromLong(without_gil([&] { return g.append((srft_cache_t*)cache, (const void* const*)fresh, (int)t, st); }));
+        }
     }
-    return PyObject_Vectorcall(ctypes_call, a, n, names);
+    PyTypeObject* base = Py_TYPE(self);
+    while (base->tp_call == append_call) base = base->tp_base;
+    return base->tp_call(self, args, names);
 }
-PyMethodDef append_method = {"srft_cache_append", (PyCFunction)(void (*)(void))append_call, METH_FASTCALL | METH_KEYWORDS, nullptr};
-// append(the call by way of ctypes, c_void_p, Array) -> the callable
+// append(type, c_void_p, Array): calls of the type's objects come here; without the last two: they go to ctypes (again)
 PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (n != 3 || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
-        PyErr_SetString(PyExc_TypeError, "append(call, c_void_p, Array)");
+    if ((n != 1 && n != 3) || !PyType_Check(a[0]) || !(((PyTypeObject*)a[0])->tp_flags & Py_TPFLAGS_HEAPTYPE) || (n == 3 && (!PyType_Check(a[1]) || !PyType_Check(a[2])))) {
+        PyErr_SetString(PyExc_TypeError, "append(type[, c_void_p, Array])");
         return nullptr;
     }
-    PyObject* const self = PyTuple_Pack(3, a[0], a[1], a[2]);
-    if (!self) return nullptr;
-    PyObject* const r = PyCFunction_New(&append_method, self);
-    Py_DECREF(self);
-    return r;
+    PyTypeObject* const type = (PyTypeObject*)a[0];
+    if (n == 3) {
+        if (!cell_type) {
+            cell_type = (PyTypeObject*)Py_NewRef(a[1]);
+            array_type = (PyTypeObject*)Py_NewRef(a[2]);
+        }
+        type->tp_call = append_call;
+    } else {
+        type->tp_call = type->tp_base->tp_call;
+    }
+    PyType_Modified(type);
+    Py_RETURN_NONE;
 }
 
 // bind(addresses): of the entry points, in the order of the struct above

@@ -190,9 +190,11 @@ int launch(const srft_plan* p, const void* q, int n_q, const uint8_t* codes, con
     long long grid = p->max_wgs > 0 ? p->max_wgs : (D == 64 && n_q <= 16 ? 2 : 1) * p->compute_units;
     if (grid > n_tiles) grid = n_tiles;
     const bool wide = p->gw > 1;
-    // Rows of whole 64-byte pieces are written through (device_util.h): 8 queries, 100,000 keys at d = 128 4.75 -> 4.45 us, 1,000,000
-    // 23.7 -> 19.3, 32 queries, 100,000 7.8 -> 6.15.  Pieces that straddle lines are not (334,146 keys 16.5 -> 24.7), nor a single row,
-    // which is next to nothing to write back (1,000,000 keys at d = 128 17.0 -> 17.3).
+    // Rows of whole 64-byte pieces, halves of a line, are written through (device_util.h).  Over three / six sets of keys and scores in turn,
+    // left to the L2 -> written through: 8 queries at d = 128, 100,000 keys 4.85 -> 4.5 us, 400,000 10.3 -> 9.6 / 10.8 -> 9.7, 1,000,000 22.5 ->
+    // 22.5 / 23.9 -> 23.9; 16 queries, 1,000,000 29.3 -> 24.8 / 29.5 -> 31.3; 32 queries, 100,000 8.0 -> 6.3, 1,000,000 43.9 -> 38.1 / 43.7 -> 44.4; d =
+    // 64, 8 queries, 400,000 8.0 -> 6.6, 1,000,000 14.0 -> 13.4 / 17.9 -> 18.9.  Pieces that straddle lines are not (334,146 keys 16.5 -> 24.7), nor a
+    // single row, which is next to nothing to write back (1,000,000 keys at d = 128 17.0 -> 17.3).
     const bool through = n_q > 1 && n_keys % 16 == 0 && (reinterpret_cast<uintptr_t>(out) & 63) == 0;
     const auto kernel = through ? (wide ? kernel_of<D, true, true>(n_q) : kernel_of<D, false, true>(n_q))
                                 : (wide ? kernel_of<D, true, false>(n_q) : kernel_of<D, false, false>(n_q));
