@@ -54,12 +54,12 @@ def _native_append(L: C.CDLL) -> None:
         _flags_, _restype_ = L._FuncPtr._flags_, L._FuncPtr._restype_
 
         def __setattr__(self, name, value):            # argtypes, restype, errcheck: from here on ctypes makes the calls
-            _marshal.append(Function)
+            _marshal.append(Function, False)
             L._FuncPtr.__setattr__(self, name, value)
 
     native = Function((plain.__name__, L))
     native.argtypes, native.restype, native.__name__ = plain.argtypes, plain.restype, plain.__name__
-    _marshal.append(Function, C.c_void_p, C.Array)
+    _marshal.append(Function, True)
     L.srft_cache_append = native
 
 
@@ -120,7 +120,7 @@ def lib() -> C.CDLL:
         _marshal.bind(*[C.cast(getattr(L, name), vp).value for name in (
             "srft_kv_quantize", "srft_kv_dequantize", "srft_kv_quantize_batched", "srft_kv_dequantize_batched", "srft_kv_scores",
             "srft_kv_decode_attention", "srft_kv_channel_absmax", "srft_cache_append", "srft_scores_workspace_bytes",
-            "srft_decode_attention_workspace_bytes", "srft_plan_d")])
+            "srft_decode_attention_workspace_bytes", "srft_plan_d")], vp, C.Array)
         _native_append(L)
     _lib = L
     return L

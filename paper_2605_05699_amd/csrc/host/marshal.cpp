@@ -55,9 +55,10 @@ const at::Tensor* tensor_of(PyObject* o, at::ScalarType type) {
                ? &t
                : nullptr;
 }
-bool address_of(PyObject* o, void** p) {                     // of a ctypes array
+PyTypeObject *cell_type, *array_type;                        // ctypes.c_void_p and ctypes.Array, with the entry points
+bool address_of(PyObject* o, void** p) {                     // of a ctypes array or cell
     Py_buffer b;
-    if (!PyObject_CheckBuffer(o) || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
+    if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
         PyErr_Clear();
         return false;
     }
@@ -129,7 +130,7 @@ PyObject* batched(PyObject* table, bool write) {
         PyObject* const names[6] = {s_plans, s_big, s_codes, s_scales, s_n_vec, s_count};
         void* p[5];
         for (int i = 0; i < 6; ++i)
-            if (!(held[i] = PyObject_GetAttr(table, names[i])) || (i < 5 && !address_of(held[i], &p[i]))) {
+            if (!(held[i] = PyObject_GetAttr(table, names[i])) || (i < 5 && (!PyObject_TypeCheck(held[i], array_type) || !address_of(held[i], &p[i])))) {
                 PyErr_Clear();
                 return false;
             }
@@ -208,7 +209,6 @@ PyObject* absmax(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // ---- lib().srft_cache_append, a ctypes function of a type of its own whose calls come here first: those with other arguments than
 // None, ints, c_void_p and arrays of them go on to ctypes.  (As the type's slot: by way of a __call__ in Python's sight a call took 0.03 us
 // more.)
-PyTypeObject *cell_type, *array_type;                        // ctypes.c_void_p and ctypes.Array
 bool pointer_of(PyObject* o, void** p) {
     if (o == Py_None) {
         *p = nullptr;
@@ -238,32 +238,24 @@ PyObject* append_call(PyObject* self, PyObject* args, PyObject* names) {
     while (base->tp_call == append_call) base = base->tp_base;
     return base->tp_call(self, args, names);
 }
-// append(type, c_void_p, Array): calls of the type's objects come here; without the last two: they go to ctypes (again)
+// append(type, native): calls of the type's objects come here, or go to ctypes (again)
 PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if ((n != 1 && n != 3) || !PyType_Check(a[0]) || !(((PyTypeObject*)a[0])->tp_flags & Py_TPFLAGS_HEAPTYPE) || (n == 3 && (!PyType_Check(a[1]) || !PyType_Check(a[2])))) {
-        PyErr_SetString(PyExc_TypeError, "append(type[, c_void_p, Array])");
+    if (n != 2 || !PyType_Check(a[0]) || !(((PyTypeObject*)a[0])->tp_flags & Py_TPFLAGS_HEAPTYPE)) {
+        PyErr_SetString(PyExc_TypeError, "append(type, native)");
         return nullptr;
     }
     PyTypeObject* const type = (PyTypeObject*)a[0];
-    if (n == 3) {
-        if (!cell_type) {
-            cell_type = (PyTypeObject*)Py_NewRef(a[1]);
-            array_type = (PyTypeObject*)Py_NewRef(a[2]);
-        }
-        type->tp_call = append_call;
-    } else {
-        type->tp_call = type->tp_base->tp_call;
-    }
+    type->tp_call = a[1] == Py_True ? append_call : type->tp_base->tp_call;
     PyType_Modified(type);
     Py_RETURN_NONE;
 }
 
-// bind(addresses): of the entry points, in the order of the struct above
+// bind(addresses, c_void_p, Array): of the entry points, in the order of the struct above
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     constexpr int kCount = 11;
     void* p[kCount];
-    if (n != kCount) {
-        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of 11 entry points");
+    if (n != kCount + 2 || !PyType_Check(a[kCount]) || !PyType_Check(a[kCount + 1])) {
+        PyErr_SetString(PyExc_TypeError, "bind takes the addresses of 11 entry points, c_void_p and Array");
         return nullptr;
     }
     for (int i = 0; i < kCount; ++i) {
@@ -272,6 +264,10 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no entry point");
             return nullptr;
         }
+    }
+    if (!g.bound) {                                          // (kept: another library object brings the same types)
+        cell_type = (PyTypeObject*)Py_NewRef(a[kCount]);
+        array_type = (PyTypeObject*)Py_NewRef(a[kCount + 1]);
     }
     std::memcpy(&g, p, sizeof(p));
     g.bound = true;

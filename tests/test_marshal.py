@@ -1,4 +1,5 @@
 """The native marshalling (csrc/host/marshal.cpp) against the calls through ctypes that it stands in front of."""
+import array
 import ctypes as C
 import importlib.util
 import subprocess
@@ -104,6 +105,21 @@ def test_what_is_not_on_the_device_is_left_to_the_binding(args):
         assert f(1, *([a] * (n - 1))) is None
     assert f() is None and f(*[x] * (n + 1)) is None
     assert B._marshal.quantize_batched(x) is None and B._marshal.dequantize_batched(None) is None
+
+
+@pytest.mark.gpu
+def test_a_table_holds_ctypes_arrays_and_nothing_else():
+    """What ctypes refuses for a pointer (a numpy array, a memory view, an array of the standard library) stays refused."""
+    table = B.BatchTable([], [], [], [])
+    for name in ("plans", "big", "codes", "scales", "n_vec"):
+        for wrong in (np.zeros(4, dtype=np.int64), memoryview(bytearray(32)), array.array("q", [0])):
+            kept = getattr(table, name)
+            setattr(table, name, wrong)
+            for f in (B.srft_kv_quantize_batched, B.srft_kv_dequantize_batched):
+                with pytest.raises(C.ArgumentError):
+                    f(table)
+            setattr(table, name, kept)
+    B.srft_kv_quantize_batched(table)
 
 
 @pytest.mark.gpu
