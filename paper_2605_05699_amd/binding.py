@@ -117,11 +117,12 @@ def lib() -> C.CDLL:
     L.srft_cache_tokens.restype = i64
     L.srft_cache_quantized_tokens.restype = i64
     if _marshal is not None:
-        _marshal.bind(*[C.cast(getattr(L, name), vp).value for name in (
-            "srft_kv_quantize", "srft_kv_dequantize", "srft_kv_quantize_batched", "srft_kv_dequantize_batched", "srft_kv_scores",
-            "srft_kv_decode_attention", "srft_kv_channel_absmax", "srft_cache_append", "srft_scores_workspace_bytes",
-            "srft_decode_attention_workspace_bytes", "srft_plan_d")], vp, C.Array)
-        _native_append(L)
+        entries = ("srft_kv_quantize", "srft_kv_dequantize", "srft_kv_quantize_batched", "srft_kv_dequantize_batched", "srft_kv_scores",
+                   "srft_kv_decode_attention", "srft_kv_channel_absmax", "srft_cache_append", "srft_scores_workspace_bytes",
+                   "srft_decode_attention_workspace_bytes", "srft_plan_d")
+        if _marshal.bind(*[C.cast(getattr(L, name), vp).value for name in entries], vp, C.Array):
+            _native_append(L)
+            _native_calls()
     _lib = L
     return L
 
@@ -131,13 +132,16 @@ def _check(status: int, where: str) -> None:
         raise SrftError(status, where)
 
 
-def _fast(name: str):
-    """The native form of a call on the current stream: its status, or None where it was not made (see csrc/host/marshal.cpp)."""
-    return getattr(_marshal, name, lambda *a: None)
+def _not_made(*args):
+    """A call in native code on the current stream: its status, or None where it was not made (see csrc/host/marshal.cpp)."""
 
 
-_fast_quantize, _fast_dequantize, _fast_scores, _fast_attention, _fast_absmax = map(_fast, ("quantize", "dequantize", "scores", "attention", "absmax"))
-_fast_quantize_batched, _fast_dequantize_batched = map(_fast, ("quantize_batched", "dequantize_batched"))
+_fast_quantize = _fast_dequantize = _fast_scores = _fast_attention = _fast_absmax = _fast_quantize_batched = _fast_dequantize_batched = _not_made
+
+
+def _native_calls() -> None:
+    for name in ("quantize", "dequantize", "scores", "attention", "absmax", "quantize_batched", "dequantize_batched"):
+        globals()["_fast_" + name] = getattr(_marshal, name)
 
 
 # The handle of the current stream without building a torch.cuda.Stream object around it: 0.3 us against 2.8 us a call,

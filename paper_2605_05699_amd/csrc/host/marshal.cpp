@@ -250,7 +250,8 @@ PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
-// bind(addresses, c_void_p, Array): of the entry points, in the order of the struct above
+// bind(addresses, c_void_p, Array): of the entry points, in the order of the struct above.  True: they are the ones called here; False: those
+// of another library are, which came first.
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     constexpr int kCount = 11;
     void* p[kCount];
@@ -265,13 +266,12 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
             return nullptr;
         }
     }
-    if (!g.bound) {                                          // (kept: another library object brings the same types)
-        cell_type = (PyTypeObject*)Py_NewRef(a[kCount]);
-        array_type = (PyTypeObject*)Py_NewRef(a[kCount + 1]);
-    }
+    if (g.bound) return PyBool_FromLong(std::memcmp(&g, p, sizeof(p)) == 0);
+    cell_type = (PyTypeObject*)Py_NewRef(a[kCount]);
+    array_type = (PyTypeObject*)Py_NewRef(a[kCount + 1]);
     std::memcpy(&g, p, sizeof(p));
     g.bound = true;
-    Py_RETURN_NONE;
+    Py_RETURN_TRUE;
 }
 static_assert(offsetof(decltype(g), bound) == 11 * sizeof(void*), "bind fills the pointers in order");
 

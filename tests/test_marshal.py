@@ -2,6 +2,7 @@
 import array
 import ctypes as C
 import importlib.util
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -93,6 +94,20 @@ assert B._marshal is None and B._fast_quantize(1, 2, 3, 4) is None
 assert B.lib().srft_cache_append(None, None, 1, None) == -1
 """
     subprocess.run([sys.executable, "-c", code], check=True, cwd=build_module.ROOT)
+
+
+def test_a_second_library_in_the_process_is_called_through_ctypes(monkeypatch, tmp_path):
+    """The native code calls the library it was bound to first; another one's plans never get there."""
+    B.lib()
+    monkeypatch.setenv("SRFT_KV_LIB", str(shutil.copy(B.LIB_PATH, tmp_path / "other.so")))
+    spec = importlib.util.spec_from_file_location(B.__package__ + ".binding_of_another", B.__file__)
+    other = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(other)
+    address = [C.cast(b.lib().srft_kv_quantize, C.c_void_p).value for b in (B, other)]
+    assert address[0] != address[1]
+    assert type(other.lib().srft_cache_append) is other.lib()._FuncPtr and type(B.lib().srft_cache_append) is not B.lib()._FuncPtr
+    for name in FAST:
+        assert getattr(other, "_fast_" + name) is not getattr(other._marshal, name) and getattr(B, "_fast_" + name) is getattr(B._marshal, name)
 
 
 @pytest.mark.parametrize("args", [("quantize", 4), ("dequantize", 4), ("scores", 6), ("attention", 10), ("absmax", 3)])
